@@ -8,12 +8,17 @@
 // of a wave64), each lane keeps VPL packs of 8 scores in registers, so a row is
 // read from HBM once, both reductions run on DPP inside the wave, and nothing
 // goes through LDS.  Short rows put many rows in one wave (k_len 32 -> 16 rows per
-// wave) so lanes are never idle.  Rows of 2049..16384 keys take one workgroup
-// each (the reductions cross its four waves through LDS).  Rows whose length is
-// not a multiple of 8 (up to 2048) use the same scheme with element-granular lanes
-// working on LDS, which is filled and drained in aligned 128-bit packs (10-30 %
-// slower than a length that is a multiple of 8);
-// anything else falls to a three-pass kernel that re-reads the row from cache.
+// wave) so lanes are never idle.  Rows of 257..2048 packs take one workgroup
+// each (the reductions cross its four waves through LDS).  Both exist in a form for rows
+// of whole packs and in one for any other length (RAG), the common case of a batch
+// that is padded to its longest sentence; longer rows fall to a three-pass kernel that
+// re-reads the row from cache.
+//
+// The RAG form walks the aligned packs of the flat tensor that a row touches.  What it replaced staged a workgroup's
+// rows in LDS (up to 2048 keys: 2-byte LDS accesses and three barriers bound it) or walked them in 2-byte accesses
+// (beyond).  Forward + backward, fp16 unless stated, before -> now in us: 113 keys padded with dropout 64 x 16 x 113
+// 47 -> 37, 201 keys 73 -> 52, 301 keys 97 -> 61, 751 keys causal 277 -> 97, 2001 keys bf16 415 -> 228, 3001 keys 624 -> 162,
+// 7001 keys 78 -> 25; 17 keys 18 -> 15, 45 keys 30 -> 27, 127 keys 53 -> 50.
 //
 // Masks restrict the SET the softmax runs over: packs that lie wholly beyond the
 // row's limit (key padding, or the causal diagonal) are not even loaded, and
@@ -29,8 +34,6 @@ namespace lsq {
 // backward is 2-3 % faster as one-wave workgroups (106 against 109 us at 8 x 20 x 1024 x 1024 causal, 62.6 against 64 us
 // with key padding at 512 keys, 16.8 against 17.1 us at 256 keys), the forward 3-4 % slower at 256 keys and equal elsewhere.
 constexpr int kSmWgFwd = 256, kSmWgBwd = 64;
-
-constexpr bool kNT = true;    // nontemporal hint on the streamed tensors
 
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -76,17 +79,191 @@ __device__ __forceinline__ int row_limit(const SoftmaxGeom& g, const SoftmaxLens
     return limit;
 }
 
+// ---- where the packs of a row lie.  RAG = false: rows are whole packs (k_len % 8 == 0), pack idx of a row starts at
+// its element 8 * idx.  RAG = true: any k_len.  The packs are those of the FLAT tensor (aligned 128-bit accesses, and the
+// groups the dropout contract counts): a row that starts s elements into a pack touches (s + k_len + 7) / 8 of them, pack
+// idx starts at row position 8 * idx - s, and the first and the last may be shared with the neighbouring rows.  Loading a
+// neighbour's elements is harmless (they are masked in registers), storing is done element by element for the
+// part that belongs to the row.
+//
+// Positions are kept relative to the workgroup's first pack: what is 64 bits wide (the row index times k_len, the tensor's
+// size) is computed once in scalar registers, and a lane's addresses are a scalar base plus a 32-bit offset.
+template <bool RAG>
+struct RowPacks {
+    int first;            // the row's first pack, counted from the workgroup's first pack
+    int s, n;             // elements of that pack in front of the row; packs the row touches
+};
+
+// The rows of a workgroup: `row0` on, `rows` of them exist (capped at 2^30, which no workgroup reaches).
+template <bool RAG>
+struct BlockRows {
+    int64_t row0, pack0;  // first row; first pack of the flat tensor that it touches
+    int s, rows, elems;   // elements of that pack in front of the first row; existing rows; elements of the tensor from pack0 on (capped)
+    __device__ __forceinline__ BlockRows(const SoftmaxGeom& g, int64_t first_row)
+    {
+        constexpr int64_t kCap = 1 << 30;
+        row0 = first_row;
+        const int64_t e0 = first_row * g.k_len, total = g.nrows * g.k_len;
+        pack0 = static_cast<int64_t>(static_cast<uint64_t>(e0) / kPack);
+        s = RAG ? static_cast<int>(e0 & (kPack - 1)) : 0;
+        rows = static_cast<int>(min(g.nrows - first_row, kCap));
+        elems = static_cast<int>(min(total - pack0 * kPack, kCap));
+    }
+    __device__ __forceinline__ RowPacks<RAG> row(const SoftmaxGeom& g, int i) const
+    {
+        const unsigned e = static_cast<unsigned>(s + i * g.k_len);
+        RowPacks<RAG> p;
+        p.first = static_cast<int>(e / kPack);
+        p.s = RAG ? static_cast<int>(e % kPack) : 0;
+        p.n = (RAG ? p.s + g.k_len + kPack - 1 : g.k_len) / kPack;
+        return p;
+    }
+};
+
+// Nontemporal hints of the ragged form.  Rows that do not start on a 128-byte line share lines between a lane's packs and
+// with their neighbours, and a line that is fetched or written in two pieces should stay in L2 in between: the loads go
+// without the hint up to a wave per row (113 keys, dropout and padding: 21.3 / 20.5 us forward / backward against 28.3 / 21.8),
+// the stores where a store instruction covers 128 bytes of a row or a row takes three (19.3 / 17.6 us; 751 keys causal 43.0 / 53.7
+// against 43.9 / 61.9).  Longer pieces keep it (2001 keys: 101 against 129 us backward; 201: 27.0 against 31.3 us forward).
+template <int LPR, int VPL, bool RAG> constexpr bool sm_load_nt() { return !RAG || LPR > kWave; }
+template <int LPR, int VPL, bool RAG> constexpr bool sm_store_nt() { return !RAG || VPL == 1 || LPR >= kWave || (LPR > 8 && VPL == 2); }
+
+// pack `idx` of a row (`base`: the workgroup's first pack); the last pack of the tensor may be cut short
+template <typename T, int LPR, int VPL, bool RAG>
+__device__ __forceinline__ RawPack<T> load_row_pack(const T* base, const RowPacks<RAG>& p, int idx, int elems)
+{
+    const unsigned e = static_cast<unsigned>(p.first + idx) * kPack;
+    if constexpr (RAG) {
+        const int left = elems - static_cast<int>(e);
+        if (left < kPack) {
+            RawPack<T> r = zero_raw<T>();
+            T f[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = j < left ? base[e + j] : from_f32<T>(0.0f);
+            __builtin_memcpy(&r, f, sizeof(r));
+            return r;
+        }
+    }
+    return load_raw<T, sm_load_nt<LPR, VPL, RAG>()>(base + e);
+}
+
+// A pack as registers: 4 for fp16/bf16, 8 for fp32.
+template <typename T> struct PackWords { uint32_t w[sizeof(T) * 2]; };
+
+// elements [a, 8) (TAIL = false) or [0, b) (TAIL = true) of the pack at `at`, in at most three naturally aligned
+// stores of 4, 2 and 1 elements (one store per element cost 20 cycles of a compute unit each, 8 per pack)
+template <typename T, bool TAIL>
+__device__ __forceinline__ void store_part(T* at, const RawPack<T>& r, int edge)
+{
+    const PackWords<T> p = __builtin_bit_cast(PackWords<T>, r);
+    const int n = TAIL ? edge : kPack - edge;                         // elements stored (1..7)
+    const int o2 = TAIL ? (edge & 4) : (edge + (edge & 1));           // where the pieces of two and of one start
+    const int o1 = TAIL ? edge - 1 : edge;
+    if constexpr (sizeof(T) == 2) {
+        if (n & 4) *reinterpret_cast<uvec2*>(at + (TAIL ? 0 : 4)) = TAIL ? uvec2{p.w[0], p.w[1]} : uvec2{p.w[2], p.w[3]};
+        if (n & 2) {
+            const uint32_t v = o2 < 4 ? (o2 < 2 ? p.w[0] : p.w[1]) : (o2 < 6 ? p.w[2] : p.w[3]);
+            *reinterpret_cast<uint32_t*>(at + o2) = v;
+        }
+        if (n & 1) {
+            const uint32_t v = o1 < 4 ? (o1 < 2 ? p.w[0] : p.w[1]) : (o1 < 6 ? p.w[2] : p.w[3]);
+            *reinterpret_cast<uint16_t*>(at + o1) = static_cast<uint16_t>(v >> (16 * (o1 & 1)));
+        }
+    } else {
+        if (n & 4) *reinterpret_cast<uvec4*>(at + (TAIL ? 0 : 4)) = TAIL ? uvec4{p.w[0], p.w[1], p.w[2], p.w[3]} : uvec4{p.w[4], p.w[5], p.w[6], p.w[7]};
+        if (n & 2) {
+            const uvec2 v = o2 < 4 ? (o2 < 2 ? uvec2{p.w[0], p.w[1]} : uvec2{p.w[2], p.w[3]})
+                                   : (o2 < 6 ? uvec2{p.w[4], p.w[5]} : uvec2{p.w[6], p.w[7]});
+            *reinterpret_cast<uvec2*>(at + o2) = v;
+        }
+        if (n & 1) {
+            uint32_t v = p.w[0];
+#pragma unroll
+            for (int j = 1; j < 8; ++j) v = o1 == j ? p.w[j] : v;
+            *reinterpret_cast<uint32_t*>(at + o1) = v;
+        }
+    }
+}
+
+// Stores one result row, VPL packs per lane.  A pack that two rows of one wave share is stored once, whole: the lane
+// that holds the end of a row fetches the start of the next row's first pack from that row's lane 0.  What is left
+// in parts is the first pack of the wave's first row and the last pack of its last.  All lanes of the wave call it
+// (`rv`: the row exists); LPR = 256 means the row spans the workgroup.  Rows of at most a pack may share one with
+// several others and are stored element by element.
+template <typename T, int LPR, int VPL, bool RAG>
+__device__ __forceinline__ void store_row(T* base, const RowPacks<RAG>& p, int sub, bool rv, bool next_rv, int k_len,
+                                          const RawPack<T> (&pk)[VPL])
+{
+    T* at = base + static_cast<unsigned>(p.first + sub) * kPack;      // of pack k: at + k * LPR * kPack
+    if constexpr (!RAG) {
+#pragma unroll
+        for (int k = 0; k < VPL; ++k)
+            if (rv && sub + k * LPR < p.n) store_raw<T, sm_store_nt<LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
+    } else {
+        if (k_len <= kPack) {                                         // uniform
+#pragma unroll
+            for (int k = 0; k < VPL; ++k) {
+                float f[8];
+                unpack<T>(pk[k], f);
+                const int p0 = (sub + k * LPR) * kPack - p.s;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (rv && static_cast<unsigned>(p0 + j) < static_cast<unsigned>(k_len)) at[k * LPR * kPack + j] = from_f32<T>(f[j]);
+            }
+            return;
+        }
+        const int cut = (p.s + k_len) % kPack;                        // elements of the last pack that are this row's (0: all)
+        RawPack<T> tail = pk[0];
+#pragma unroll
+        for (int k = 0; k < VPL; ++k) {
+            const int idx = sub + k * LPR;
+            const bool head = k == 0 && sub == 0 && p.s > 0;
+            const bool last = idx == p.n - 1 && cut > 0;
+            if (last) tail = pk[k];
+            if (rv && idx < p.n && !head && !last) store_raw<T, sm_store_nt<LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
+        }
+        const int kt = (p.n - 1) / LPR;                               // the last pack is pack kt of lane (n - 1) % LPR
+        const bool mine = rv && cut > 0 && sub + kt * LPR == p.n - 1;
+        T* tail_at = at + kt * LPR * kPack;
+        bool whole = false;
+        if constexpr (LPR < kWave) {
+            const int lane = threadIdx.x % kWave;
+            const int from = (lane / LPR + 1) * LPR;                  // lane 0 of the next row
+            PackWords<T> t = __builtin_bit_cast(PackWords<T>, tail);
+            const PackWords<T> h = __builtin_bit_cast(PackWords<T>, pk[0]);
+            whole = mine && from < kWave && next_rv;
+#pragma unroll
+            for (int i = 0; i < static_cast<int>(sizeof(T)) * 2; ++i) {
+                const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(from * 4, static_cast<int>(h.w[i])));
+                if constexpr (sizeof(T) == 2)       // which of the word's two elements are this row's
+                    t.w[i] = cut >= 2 * i + 2 ? t.w[i] : cut == 2 * i + 1 ? (t.w[i] & 0xFFFFu) | (o & 0xFFFF0000u) : o;
+                else
+                    t.w[i] = cut > i ? t.w[i] : o;
+            }
+            if (whole) store_raw<T, sm_store_nt<LPR, VPL, RAG>()>(tail_at, __builtin_bit_cast(RawPack<T>, t));
+            if (rv && p.s > 0 && lane == 0) store_part<T, false>(at, pk[0], p.s);
+        } else {
+            if (rv && p.s > 0 && sub == 0) store_part<T, false>(at, pk[0], p.s);
+        }
+        if (mine && !whole) store_part<T, true>(tail_at, tail, cut);
+    }
+}
+
 // RPT rows per lane group: the loads of all RPT rows are issued before the first
 // reduction, so a wave has RPT*VPL packs per lane in flight and the two dependent
 // round trips (lengths, then scores) are paid once per RPT rows.
-template <typename T, int LPR, int VPL, int RPT, bool DROP>
+template <typename T, int LPR, int VPL, int RPT, bool DROP, bool RAG>
 __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restrict__ yd, const T* x,
                                                           SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     constexpr int RPB = kSmWgFwd / LPR;
     const int sub = threadIdx.x % LPR;
-    const int nv = g.k_len / kPack;
-    int64_t row[RPT];
+    const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
+    x += blk.pack0 * kPack;
+    y += blk.pack0 * kPack;
+    if constexpr (DROP) yd += blk.pack0 * kPack;
+    int row[RPT];             // counted from the workgroup's first
+    RowPacks<RAG> rp[RPT];
     int limit[RPT];
     // Loads first, arithmetic after.  The packs of a row's first 128 bytes are loaded before the
     // row's limit is known (unless the row is empty that line is needed whatever the limit, and
@@ -98,54 +275,61 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
     RawPack<T> raw[RPT][VPL];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        row[r] = (static_cast<int64_t>(blockIdx.x) * RPT + r) * RPB + threadIdx.x / LPR;
+        row[r] = r * RPB + threadIdx.x / LPR;
+        rp[r] = blk.row(g, row[r]);
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int j0 = (sub + k * LPR) * kPack;
+            const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
             if (j0 < kEarly) {
-                if (row[r] < g.nrows && j0 < g.k_len) raw[r][k] = load_raw<T, kNT>(x + row[r] * g.k_len + j0);
+                if (row[r] < blk.rows && j0 < g.k_len) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);
                 else raw[r][k] = zero_raw<T>();
             }
         }
     }
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) limit[r] = row[r] < g.nrows ? row_limit(g, len, row[r]) : 0;
+    for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
 #pragma unroll
     for (int r = 0; r < RPT; ++r)
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int j0 = (sub + k * LPR) * kPack;
+            const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
             if (j0 >= kEarly) {
-                if (j0 < limit[r]) raw[r][k] = load_raw<T, kNT>(x + row[r] * g.k_len + j0);   // implies a valid row and pack
+                if (j0 < limit[r]) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);   // implies a valid row and pack
                 else raw[r][k] = zero_raw<T>();
             }
         }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        const int64_t ro = row[r] * g.k_len;
         const int lim = limit[r];
         float v[VPL][8];
         bool live[VPL];       // wave-uniform: does any lane of the wave hold an allowed element of pack k?
         float mx = -INFINITY;
+        // A positive scale (every attention scale is) commutes with the maximum and folds into the exponent's fma: one
+        // multiplication per element less in a kernel that is bound by vector-ALU issue slots.  Any other scale is
+        // multiplied in first (a uniform branch).
+        const bool fold = g.scale > 0.0f;
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int j0 = (sub + k * LPR) * kPack;
+            const int j0 = (sub + k * LPR) * kPack - rp[r].s;
             live[k] = __ballot(j0 < lim) != 0;
             if (live[k]) {    // a pack that is masked for the whole wave costs no arithmetic
                 unpack<T>(raw[r][k], v[k]);
+                if (!fold) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[k][j] *= g.scale;
+                }
                 const int allowed = lim - j0;             // of this pack's 8 elements (<= 0: none, >= 8: all)
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    v[k][j] = (j < allowed) ? v[k][j] : -INFINITY;
+                    bool in = j < allowed;
+                    if constexpr (RAG) { if (k == 0) in = in && j + j0 >= 0; }      // only pack 0 can start before the row
+                    v[k][j] = in ? v[k][j] : -INFINITY;
                     mx = fmaxf(mx, v[k][j]);
                 }
             }
         }
-        // The scale is positive here (the dispatch sends other scales to the element kernels), so the maximum of the
-        // scaled scores is the scaled maximum and the scale folds into the exponent's fma: one multiplication per
-        // element less in a kernel that is bound by vector-ALU issue slots.
         mx = group_max<LPR>(mx);
-        const float c = g.scale * kLog2e;
+        const float c = fold ? g.scale * kLog2e : kLog2e;
         const float mxs = (lim > 0 ? mx : 0.0f) * c;
         float z = 0.0f;
 #pragma unroll
@@ -161,52 +345,62 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
         }
         z = group_sum<LPR>(z);
         const float inv = lim > 0 ? 1.0f / z : 0.0f;
+        const bool rv = row[r] < blk.rows, next_rv = row[r] + 1 < blk.rows;
+        RawPack<T> pk[VPL];
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int idx = sub + k * LPR;
-            if (row[r] < g.nrows && idx < nv) {
-                float o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (live[k]) {
+            pk[k] = zero_raw<T>();
+            if (live[k]) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) o[j] = v[k][j] * inv;
-                }
-                store8<T, kNT>(y + ro + idx * kPack, o);
-                if constexpr (DROP) {
-                    if (idx * kPack < lim) {    // packs beyond the mask are zeros whatever the draw
-                        float kf[8];
-                        dropout_factors8(d, static_cast<uint64_t>(row[r]) * nv + idx, kf);
+                for (int j = 0; j < 8; ++j) v[k][j] *= inv;
+                pk[k] = pack_raw<T>(v[k]);
+            }
+        }
+        store_row<T, LPR, VPL, RAG>(y, rp[r], sub, rv, next_rv, g.k_len, pk);
+        if constexpr (DROP) {
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) o[j] *= kf[j];
-                    }
-                    store8<T, kNT>(yd + ro + idx * kPack, o);
+            for (int k = 0; k < VPL; ++k) {
+                const int idx = sub + k * LPR;
+                if (live[k] && idx * kPack - rp[r].s < lim) {    // packs beyond the mask are zeros whatever the draw
+                    float kf[8];
+                    dropout_factors8(d, static_cast<uint64_t>(blk.pack0 + (rp[r].first + idx)), kf);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) kf[j] *= v[k][j];
+                    pk[k] = pack_raw<T>(kf);
                 }
             }
+            store_row<T, LPR, VPL, RAG>(yd, rp[r], sub, rv, next_rv, g.k_len, pk);
         }
     }
 }
 
-template <typename T, int LPR, int VPL, int RPT, bool DROP>
+template <typename T, int LPR, int VPL, int RPT, bool DROP, bool RAG>
 __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* dy, const T* __restrict__ y,
                                                           SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     constexpr int RPB = kSmWgBwd / LPR;
     const int sub = threadIdx.x % LPR;
-    const int nv = g.k_len / kPack;
-    int64_t row[RPT];
+    const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
+    y += blk.pack0 * kPack;
+    dy += blk.pack0 * kPack;
+    dx += blk.pack0 * kPack;
+    int row[RPT];             // counted from the workgroup's first
+    RowPacks<RAG> rp[RPT];
     int limit[RPT];
     // as in forward: the first 128 bytes of a row are loaded before its limit is known
     const int kEarly = (len.key || len.query) ? 128 / static_cast<int>(sizeof(T)) : 0;
     RawPack<T> ry[RPT][VPL], rg[RPT][VPL];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        row[r] = (static_cast<int64_t>(blockIdx.x) * RPT + r) * RPB + threadIdx.x / LPR;
+        row[r] = r * RPB + threadIdx.x / LPR;
+        rp[r] = blk.row(g, row[r]);
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int j0 = (sub + k * LPR) * kPack;
+            const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
             if (j0 < kEarly) {
-                if (row[r] < g.nrows && j0 < g.k_len) {
-                    ry[r][k] = load_raw<T, kNT>(y + row[r] * g.k_len + j0);
-                    rg[r][k] = load_raw<T, kNT>(dy + row[r] * g.k_len + j0);
+                if (row[r] < blk.rows && j0 < g.k_len) {
+                    ry[r][k] = load_row_pack<T, LPR, VPL, RAG>(y, rp[r], idx, blk.elems);
+                    rg[r][k] = load_row_pack<T, LPR, VPL, RAG>(dy, rp[r], idx, blk.elems);
                 } else {
                     ry[r][k] = zero_raw<T>();
                     rg[r][k] = zero_raw<T>();
@@ -215,16 +409,16 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
         }
     }
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) limit[r] = row[r] < g.nrows ? row_limit(g, len, row[r]) : 0;
+    for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
 #pragma unroll
     for (int r = 0; r < RPT; ++r)
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int j0 = (sub + k * LPR) * kPack;
+            const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
             if (j0 >= kEarly) {
                 if (j0 < limit[r]) {
-                    ry[r][k] = load_raw<T, kNT>(y + row[r] * g.k_len + j0);
-                    rg[r][k] = load_raw<T, kNT>(dy + row[r] * g.k_len + j0);
+                    ry[r][k] = load_row_pack<T, LPR, VPL, RAG>(y, rp[r], idx, blk.elems);
+                    rg[r][k] = load_row_pack<T, LPR, VPL, RAG>(dy, rp[r], idx, blk.elems);
                 } else {
                     ry[r][k] = zero_raw<T>();
                     rg[r][k] = zero_raw<T>();
@@ -233,20 +427,19 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
         }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        const int64_t ro = row[r] * g.k_len;
         const int lim = limit[r];
         float yv[VPL][8], gv[VPL][8];
         float dot = 0.0f;
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR;
-            const int j0 = idx * kPack;
+            const int j0 = idx * kPack - rp[r].s;
             unpack<T>(ry[r][k], yv[k]);
             unpack<T>(rg[r][k], gv[k]);
             if constexpr (DROP) {
                 if (j0 < lim) {
                     float kf[8];
-                    dropout_factors8(d, static_cast<uint64_t>(row[r]) * nv + idx, kf);
+                    dropout_factors8(d, static_cast<uint64_t>(blk.pack0 + (rp[r].first + idx)), kf);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) gv[k][j] *= kf[j];
                 }
@@ -254,52 +447,58 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
             const int allowed = lim - j0;                 // of this pack's 8 elements (<= 0: none, >= 8: all)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                if (j >= allowed) { yv[k][j] = 0.0f; gv[k][j] = 0.0f; }       // whatever sits beyond the mask never counts
+                bool out = j >= allowed;
+                if constexpr (RAG) { if (k == 0) out = out || j + j0 < 0; }
+                if (out) { yv[k][j] = 0.0f; gv[k][j] = 0.0f; }       // whatever sits beyond the mask never counts
                 dot = fmaf(gv[k][j], yv[k][j], dot);
             }
         }
         dot = group_sum<LPR>(dot);
+        RawPack<T> pk[VPL];
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int idx = sub + k * LPR;
-            if (row[r] < g.nrows && idx < nv) {
-                float o[8];
+            float o[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j)      // outside the allowed set y and dy are zero here: the sum with +0 turns the product's -0 into +0
-                    o[j] = g.scale * yv[k][j] * (gv[k][j] - dot) + 0.0f;
-                store8<T, kNT>(dx + ro + idx * kPack, o);
-            }
+            for (int j = 0; j < 8; ++j)      // outside the allowed set y and dy are zero here: the sum with +0 turns the product's -0 into +0
+                o[j] = g.scale * yv[k][j] * (gv[k][j] - dot) + 0.0f;
+            pk[k] = pack_raw<T>(o);
         }
+        store_row<T, LPR, VPL, RAG>(dx, rp[r], sub, row[r] < blk.rows, row[r] + 1 < blk.rows, g.k_len, pk);
     }
 }
 
-// ---- long rows (2048 < k_len <= 16384): one workgroup per row, VPL packs per thread in
+// ---- long rows (257..2048 packs: about 2048 < k_len <= 16384): one workgroup per row, VPL packs per thread in
 // registers, the two reductions cross the four waves through LDS.  Still one read of the row.
-template <typename T, int VPL, bool DROP>
+template <typename T, int VPL, bool DROP, bool RAG>
 __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd, const T* x,
                                                         SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     __shared__ float red[4];
     const int64_t row = blockIdx.x;
-    const int nv = g.k_len / kPack;
+    const BlockRows<RAG> blk(g, row);
+    const RowPacks<RAG> rp = blk.row(g, 0);
+    x += blk.pack0 * kPack;
+    y += blk.pack0 * kPack;
+    if constexpr (DROP) yd += blk.pack0 * kPack;
     const int limit = row_limit(g, len, row);
-    const int64_t ro = row * g.k_len;
     RawPack<T> raw[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int j0 = (threadIdx.x + k * 256) * kPack;
-        if (j0 < limit) raw[k] = load_raw<T, kNT>(x + ro + j0);
+        const int idx = threadIdx.x + k * 256;
+        if (idx * kPack - rp.s < limit) raw[k] = load_row_pack<T, 256, VPL, RAG>(x, rp, idx, blk.elems);
         else raw[k] = zero_raw<T>();
     }
     float v[VPL][8];
     float mx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int j0 = (threadIdx.x + k * 256) * kPack;
+        const int j0 = (threadIdx.x + k * 256) * kPack - rp.s;
         unpack<T>(raw[k], v[k]);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            v[k][j] = (j0 + j < limit) ? v[k][j] * g.scale : -INFINITY;
+            bool in = j0 + j < limit;
+            if constexpr (RAG) { if (k == 0) in = in && j0 + j >= 0; }
+            v[k][j] = in ? v[k][j] * g.scale : -INFINITY;
             mx = fmaxf(mx, v[k][j]);
         }
     }
@@ -316,43 +515,49 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
         }
     z = block_allreduce<4, OpSum>(z, red);
     const float inv = limit > 0 ? 1.0f / z : 0.0f;
+    RawPack<T> pk[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int idx = threadIdx.x + k * 256;
-        if (idx < nv) {
-            float o[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = v[k][j] * inv;
-            store8<T, kNT>(y + ro + idx * kPack, o);
-            if constexpr (DROP) {
-                if (idx * kPack < limit) {
-                    float kf[8];
-                    dropout_factors8(d, static_cast<uint64_t>(row) * nv + idx, kf);
+        for (int j = 0; j < 8; ++j) v[k][j] *= inv;
+        pk[k] = pack_raw<T>(v[k]);
+    }
+    store_row<T, 256, VPL, RAG>(y, rp, threadIdx.x, true, false, g.k_len, pk);
+    if constexpr (DROP) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) o[j] *= kf[j];
-                }
-                store8<T, kNT>(yd + ro + idx * kPack, o);
+        for (int k = 0; k < VPL; ++k) {
+            const int idx = threadIdx.x + k * 256;
+            if (idx * kPack - rp.s < limit) {
+                float kf[8];
+                dropout_factors8(d, static_cast<uint64_t>(blk.pack0 + (rp.first + idx)), kf);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) kf[j] *= v[k][j];
+                pk[k] = pack_raw<T>(kf);
             }
         }
+        store_row<T, 256, VPL, RAG>(yd, rp, threadIdx.x, true, false, g.k_len, pk);
     }
 }
 
-template <typename T, int VPL, bool DROP>
+template <typename T, int VPL, bool DROP, bool RAG>
 __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, const T* __restrict__ y,
                                                         SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     __shared__ float red[4];
     const int64_t row = blockIdx.x;
-    const int nv = g.k_len / kPack;
+    const BlockRows<RAG> blk(g, row);
+    const RowPacks<RAG> rp = blk.row(g, 0);
+    y += blk.pack0 * kPack;
+    dy += blk.pack0 * kPack;
+    dx += blk.pack0 * kPack;
     const int limit = row_limit(g, len, row);
-    const int64_t ro = row * g.k_len;
     RawPack<T> ry[VPL], rg[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int j0 = (threadIdx.x + k * 256) * kPack;
-        if (j0 < limit) {
-            ry[k] = load_raw<T, kNT>(y + ro + j0);
-            rg[k] = load_raw<T, kNT>(dy + ro + j0);
+        const int idx = threadIdx.x + k * 256;
+        if (idx * kPack - rp.s < limit) {
+            ry[k] = load_row_pack<T, 256, VPL, RAG>(y, rp, idx, blk.elems);
+            rg[k] = load_row_pack<T, 256, VPL, RAG>(dy, rp, idx, blk.elems);
         } else {
             ry[k] = zero_raw<T>();
             rg[k] = zero_raw<T>();
@@ -363,268 +568,58 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
         const int idx = threadIdx.x + k * 256;
-        const int j0 = idx * kPack;
+        const int j0 = idx * kPack - rp.s;
         unpack<T>(ry[k], yv[k]);
         unpack<T>(rg[k], gv[k]);
         if constexpr (DROP) {
             if (j0 < limit) {
                 float kf[8];
-                dropout_factors8(d, static_cast<uint64_t>(row) * nv + idx, kf);
+                dropout_factors8(d, static_cast<uint64_t>(blk.pack0 + (rp.first + idx)), kf);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) gv[k][j] *= kf[j];
             }
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            if (j0 + j >= limit) yv[k][j] = 0.0f;
+            bool out = j0 + j >= limit;
+            if constexpr (RAG) { if (k == 0) out = out || j0 + j < 0; }
+            if (out) { yv[k][j] = 0.0f; gv[k][j] = 0.0f; }       // a neighbour's or a masked element never counts, NaN or not
             dot = fmaf(gv[k][j], yv[k][j], dot);
         }
     }
     dot = block_allreduce<4, OpSum>(dot, red);
+    RawPack<T> pk[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int idx = threadIdx.x + k * 256;
-        if (idx < nv) {
-            float o[8];
+        float o[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                o[j] = (idx * kPack + j < limit) ? g.scale * yv[k][j] * (gv[k][j] - dot) : 0.0f;
-            store8<T, kNT>(dx + ro + idx * kPack, o);
-        }
+        for (int j = 0; j < 8; ++j)
+            o[j] = ((threadIdx.x + k * 256) * kPack - rp.s + j < limit) ? g.scale * yv[k][j] * (gv[k][j] - dot) : 0.0f;
+        pk[k] = pack_raw<T>(o);
     }
+    store_row<T, 256, VPL, RAG>(dx, rp, threadIdx.x, true, false, g.k_len, pk);
 }
 
-// ---- rows whose length is not a multiple of 8 (or whose tensors are not 16-byte aligned), up
-// to 2048 keys: the common case of a sequence-to-sequence batch.  Same register-resident,
-// read-once scheme with ELEMENT-granular lanes: lane `sub` of a row's group holds elements
-// sub, sub + LPR, ... (2-byte accesses, contiguous across the wave).  Dropout decisions are
-// still one Philox call per aligned pack of the flat tensor: the workgroup's rows cover one
-// contiguous element range, its threads compute the keep bits of the packs of that range
-// into LDS, and every element then picks its bit.
-template <int LPR>
-__device__ __forceinline__ float elem_max(float v, float* lds)
-{
-    if constexpr (LPR == 256) return block_allreduce<4, OpMax>(v, lds);
-    else return group_max<LPR>(v);
-}
-template <int LPR>
-__device__ __forceinline__ float elem_sum(float v, float* lds)
-{
-    if constexpr (LPR == 256) return block_allreduce<4, OpSum>(v, lds);
-    else return group_sum<LPR>(v);
-}
-
-// keep bits of the packs that the rows [row0, row0 + rpb) touch; returns the first pack's index
-template <int NBYTES>
-__device__ __forceinline__ int64_t elem_keep_mask(uint8_t (&keep)[NBYTES], const SoftmaxGeom& g, const DropoutParams& d,
-                                                  int64_t row0, int rpb)
-{
-    const int64_t e_begin = row0 * g.k_len;
-    const int64_t r_end = row0 + rpb < g.nrows ? row0 + rpb : g.nrows;
-    const int64_t p_begin = e_begin >> 3, p_end = (r_end * g.k_len + 7) >> 3;
-    for (int64_t pk = p_begin + threadIdx.x; pk < p_end; pk += 256)
-        keep[pk - p_begin] = static_cast<uint8_t>(dropout_keep_bits8(d, static_cast<uint64_t>(pk)));
-    __syncthreads();
-    return p_begin;
-}
-
-// The rows of a workgroup are one contiguous element range [e0, e1) of the tensor.  Global memory
-// is touched in aligned 128-bit packs only: the packs that cover the range are copied to LDS (and
-// results back from LDS), the lanes work on LDS with 2-byte accesses.  The first and the last pack
-// may be shared with the neighbouring workgroups: reading them is harmless, writing is done element
-// by element for the part that belongs here.  Element i of LDS = element (e0 & ~7) + i of the tensor.
-constexpr bool kSmStage = true;
-
+// ---- rows of more than 2048 packs (beyond about 16384 keys): one workgroup per row, element-strided, the row is
+// re-read from cache
 template <typename T>
-__device__ __forceinline__ void stage_in(T* buf, const T* src, int64_t e0, int64_t e1, int64_t total)
-{
-    const int64_t p0 = e0 >> 3, p1 = (e1 + 7) >> 3;
-    for (int64_t pk = p0 + threadIdx.x; pk < p1; pk += 256) {
-        T* dst = buf + (pk - p0) * kPack;
-        const int64_t base = pk * kPack;
-        if (base + kPack <= total) {
-            *reinterpret_cast<RawPack<T>*>(dst) = load_raw<T, kNT>(src + base);
-        } else {
-            for (int j = 0; j < kPack; ++j)
-                if (base + j < total) dst[j] = src[base + j];
-        }
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void stage_out(T* dstg, const T* buf, int64_t e0, int64_t e1)
-{
-    const int64_t p0 = e0 >> 3, p1 = (e1 + 7) >> 3;
-    for (int64_t pk = p0 + threadIdx.x; pk < p1; pk += 256) {
-        const T* from = buf + (pk - p0) * kPack;
-        const int64_t base = pk * kPack;
-        if (base >= e0 && base + kPack <= e1) {
-            store_raw<T, kNT>(dstg + base, *reinterpret_cast<const RawPack<T>*>(from));
-        } else {
-            for (int j = 0; j < kPack; ++j)
-                if (base + j >= e0 && base + j < e1) dstg[base + j] = from[j];
-        }
-    }
-}
-
-template <typename T, int LPR, int EPL, bool DROP>
-__global__ __launch_bounds__(256) void softmax_fwd_elem(T* y, T* __restrict__ yd, const T* x,
-                                                        SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
-{
-    constexpr int RPB = 256 / LPR;
-    constexpr int NBUF = kSmStage ? 256 * EPL + 16 : 8;      // elements per staged tensor
-    __shared__ float red[4];
-    __shared__ uint8_t keep[DROP ? 256 * EPL / 8 + 8 : 1];
-    __shared__ __align__(16) T xs[NBUF];
-    __shared__ __align__(16) T ys[NBUF];
-    __shared__ __align__(16) T yds[DROP ? NBUF : 8];
-    const int sub = threadIdx.x % LPR;
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * RPB;
-    const int64_t row = row0 + threadIdx.x / LPR;
-    const bool rv = row < g.nrows;
-    const int limit = rv ? row_limit(g, len, row) : 0;
-    const int64_t ro = row * g.k_len;
-    const int64_t e0 = row0 * g.k_len;
-    const int64_t e1 = (row0 + RPB < g.nrows ? row0 + RPB : g.nrows) * g.k_len;
-    const int lo = static_cast<int>(ro - (e0 & ~static_cast<int64_t>(7)));     // this row's first element in LDS
-    if constexpr (kSmStage) {
-        stage_in<T>(xs, x, e0, e1, g.nrows * g.k_len);
-        __syncthreads();
-    }
-    float v[EPL];
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        const int j = sub + m * LPR;
-        if constexpr (kSmStage) v[m] = j < limit ? to_f32<T>(xs[lo + j]) * g.scale : -INFINITY;
-        else v[m] = j < limit ? to_f32<T>(x[ro + j]) * g.scale : -INFINITY;
-    }
-    int64_t p_begin = 0;
-    if constexpr (DROP) p_begin = elem_keep_mask(keep, g, d, row0, RPB);
-    float mx = v[0];
-#pragma unroll
-    for (int m = 1; m < EPL; ++m) mx = fmaxf(mx, v[m]);
-    mx = elem_max<LPR>(mx, red);
-    const float mxs = (limit > 0 ? mx : 0.0f) * kLog2e;
-    float z = 0.0f;
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        v[m] = __builtin_amdgcn_exp2f(fmaf(v[m], kLog2e, -mxs));
-        z += v[m];
-    }
-    z = elem_sum<LPR>(z, red);
-    const float inv = limit > 0 ? 1.0f / z : 0.0f;
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        const int j = sub + m * LPR;
-        if (rv && j < g.k_len) {
-            const float o = v[m] * inv;           // 0 beyond the limit (exp2(-inf)), and on empty rows
-            if constexpr (kSmStage) ys[lo + j] = from_f32<T>(o);
-            else y[ro + j] = from_f32<T>(o);
-            if constexpr (DROP) {
-                const int64_t e = ro + j;
-                const bool kept = (keep[(e >> 3) - p_begin] >> (e & 7)) & 1;
-                if constexpr (kSmStage) yds[lo + j] = from_f32<T>(kept ? o * d.scale : 0.0f);
-                else yd[e] = from_f32<T>(kept ? o * d.scale : 0.0f);
-            }
-        }
-    }
-    if constexpr (kSmStage) {
-        __syncthreads();
-        stage_out<T>(y, ys, e0, e1);
-        if constexpr (DROP) stage_out<T>(yd, yds, e0, e1);
-    }
-}
-
-template <typename T, int LPR, int EPL, bool DROP>
-__global__ __launch_bounds__(256) void softmax_bwd_elem(T* dx, const T* dy, const T* __restrict__ y,
-                                                        SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
-{
-    constexpr int RPB = 256 / LPR;
-    constexpr int NBUF = kSmStage ? 256 * EPL + 16 : 8;
-    __shared__ float red[4];
-    __shared__ uint8_t keep[DROP ? 256 * EPL / 8 + 8 : 1];
-    __shared__ __align__(16) T ysh[NBUF];
-    __shared__ __align__(16) T gsh[NBUF];        // dy in, dx out
-    const int sub = threadIdx.x % LPR;
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * RPB;
-    const int64_t row = row0 + threadIdx.x / LPR;
-    const bool rv = row < g.nrows;
-    const int limit = rv ? row_limit(g, len, row) : 0;
-    const int64_t ro = row * g.k_len;
-    const int64_t e0 = row0 * g.k_len;
-    const int64_t e1 = (row0 + RPB < g.nrows ? row0 + RPB : g.nrows) * g.k_len;
-    const int lo = static_cast<int>(ro - (e0 & ~static_cast<int64_t>(7)));
-    if constexpr (kSmStage) {
-        stage_in<T>(ysh, y, e0, e1, g.nrows * g.k_len);
-        stage_in<T>(gsh, dy, e0, e1, g.nrows * g.k_len);
-        __syncthreads();
-    }
-    float yv[EPL], gv[EPL];
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        const int j = sub + m * LPR;
-        if constexpr (kSmStage) {
-            yv[m] = j < limit ? to_f32<T>(ysh[lo + j]) : 0.0f;
-            gv[m] = j < limit ? to_f32<T>(gsh[lo + j]) : 0.0f;
-        } else {
-            yv[m] = j < limit ? to_f32<T>(y[ro + j]) : 0.0f;
-            gv[m] = j < limit ? to_f32<T>(dy[ro + j]) : 0.0f;
-        }
-    }
-    if constexpr (DROP) {
-        const int64_t p_begin = elem_keep_mask(keep, g, d, row0, RPB);
-#pragma unroll
-        for (int m = 0; m < EPL; ++m) {
-            const int j = sub + m * LPR;
-            if (j < limit) {
-                const int64_t e = ro + j;
-                const bool kept = (keep[(e >> 3) - p_begin] >> (e & 7)) & 1;
-                gv[m] = kept ? gv[m] * d.scale : 0.0f;
-            }
-        }
-    }
-    float dot = 0.0f;
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) dot = fmaf(gv[m], yv[m], dot);
-    dot = elem_sum<LPR>(dot, red);
-#pragma unroll
-    for (int m = 0; m < EPL; ++m) {
-        const int j = sub + m * LPR;
-        if (rv && j < g.k_len) {
-            const T o = from_f32<T>(j < limit ? g.scale * yv[m] * (gv[m] - dot) : 0.0f);
-            if constexpr (kSmStage) gsh[lo + j] = o;      // every element is read and written by one lane only
-            else dx[ro + j] = o;
-        }
-    }
-    if constexpr (kSmStage) {
-        __syncthreads();
-        stage_out<T>(dx, gsh, e0, e1);
-    }
-}
-
-// ---- generic path: any k_len; TH = 64 (one wave per row) or 256 lanes (one workgroup per row), element-strided,
-// row re-read from cache
-template <typename T, int TH>
 __global__ __launch_bounds__(256) void softmax_fwd_generic(T* y, T* __restrict__ yd, const T* x,
                                                            SoftmaxLens key_len, SoftmaxGeom g,
                                                            DropoutParams d)
 {
     __shared__ float lds[4];
-    constexpr int R = 256 / TH;
-    const int lane = threadIdx.x % TH;
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * R + threadIdx.x / TH;
-    if (row >= g.nrows) return;               // whole waves (TH = 64) or the whole workgroup (TH = 256) leave together
+    constexpr int TH = 256;
+    const int lane = threadIdx.x;
+    const int64_t row = blockIdx.x;
     const int limit = row_limit(g, key_len, row);
     const int64_t ro = row * g.k_len;
     float mx = -INFINITY;
     for (int j = lane; j < limit; j += TH) mx = fmaxf(mx, to_f32<T>(x[ro + j]) * g.scale);
-    if constexpr (TH == 64) mx = group_max<64>(mx);
-    else mx = block_allreduce<4, OpMax>(mx, lds);
+    mx = block_allreduce<4, OpMax>(mx, lds);
     const float mxs = (limit > 0 ? mx : 0.0f) * kLog2e;
     float z = 0.0f;
     for (int j = lane; j < limit; j += TH) z += __builtin_amdgcn_exp2f(fmaf(to_f32<T>(x[ro + j]) * g.scale, kLog2e, -mxs));
-    if constexpr (TH == 64) z = group_sum<64>(z);
-    else z = block_allreduce<4, OpSum>(z, lds);
+    z = block_allreduce<4, OpSum>(z, lds);
     const float inv = limit > 0 ? 1.0f / z : 0.0f;
     for (int j = lane; j < g.k_len; j += TH) {
         float o = 0.0f;
@@ -634,16 +629,15 @@ __global__ __launch_bounds__(256) void softmax_fwd_generic(T* y, T* __restrict__
     }
 }
 
-template <typename T, int TH>
+template <typename T>
 __global__ __launch_bounds__(256) void softmax_bwd_generic(T* dx, const T* dy, const T* __restrict__ y,
                                                            SoftmaxLens key_len, SoftmaxGeom g,
                                                            DropoutParams d)
 {
     __shared__ float lds[4];
-    constexpr int R = 256 / TH;
-    const int lane = threadIdx.x % TH;
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * R + threadIdx.x / TH;
-    if (row >= g.nrows) return;
+    constexpr int TH = 256;
+    const int lane = threadIdx.x;
+    const int64_t row = blockIdx.x;
     const int limit = row_limit(g, key_len, row);
     const int64_t ro = row * g.k_len;
     float dot = 0.0f;
@@ -652,8 +646,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_generic(T* dx, const T* dy, c
         if (d.on) gg *= dropout_factor1(d, static_cast<uint64_t>(ro + j));
         dot = fmaf(gg, to_f32<T>(y[ro + j]), dot);
     }
-    if constexpr (TH == 64) dot = group_sum<64>(dot);
-    else dot = block_allreduce<4, OpSum>(dot, lds);
+    dot = block_allreduce<4, OpSum>(dot, lds);
     for (int j = lane; j < g.k_len; j += TH) {
         float o = 0.0f;
         if (j < limit) {
@@ -666,45 +659,8 @@ __global__ __launch_bounds__(256) void softmax_bwd_generic(T* dx, const T* dy, c
 }
 
 // ------------------------------------------------------------------ dispatch
-struct SmShape { int lpr, vpl; };
-
-inline SmShape softmax_shape(int k_len)
-{
-    if (k_len % kPack != 0) return {0, 0};
-    const int nv = k_len / kPack;
-    if (nv <= 1) return {1, 1};
-    if (nv <= 2) return {2, 1};
-    if (nv <= 4) return {4, 1};
-    if (nv <= 8) return {8, 1};
-    if (nv <= 16) return {16, 1};
-    if (nv <= 32) return {32, 1};
-    if (nv <= 64) return {64, 1};
-    if (nv <= 128) return {64, 2};
-    if (nv <= 192) return {64, 3};
-    if (nv <= 256) return {64, 4};
-    if (nv <= 512) return {256, 2};      // one workgroup per row from here on
-    if (nv <= 1024) return {256, 4};
-    if (nv <= 2048) return {256, 8};
-    return {0, 0};
-}
-
-// element-granular buckets: lanes per row, elements per lane.  Few lanes per row with up to 8
-// elements each (more rows per workgroup, more loads in flight per lane) measured 2x faster
-// than one element per lane on 64 lanes.
-inline SmShape softmax_elem_shape(int k_len)
-{
-    if (k_len <= 8) return {8, 1};
-    if (k_len <= 16) return {8, 2};
-    if (k_len <= 32) return {8, 4};
-    if (k_len <= 64) return {8, 8};
-    if (k_len <= 128) return {16, 8};
-    if (k_len <= 256) return {32, 8};
-    if (k_len <= 512) return {64, 8};
-    if (k_len <= 1024) return {256, 4};
-    if (k_len <= 2048) return {256, 8};
-    return {0, 0};
-}
-#define LSQ_SM_ELEM_CASES(X) X(8, 1) X(8, 2) X(8, 4) X(8, 8) X(16, 8) X(32, 8) X(64, 8) X(256, 4) X(256, 8)
+// packs per thread of the one-workgroup-per-row kernels for rows of np packs; 0: too long
+inline int softmax_wide_vpl(int np) { return np <= 512 ? 2 : np <= 1024 ? 4 : np <= 2048 ? 8 : 0; }
 
 // ---- launch shapes of the register path for rows of up to 2048 keys, and their choice at run time.
 // The paper copes with the spread of softmax shapes by keeping several templates and searching for
@@ -781,6 +737,36 @@ inline SmCand sm_choose(const SoftmaxLens& len, const SoftmaxGeom& g, bool drop,
     return c;
 }
 
+// ---- rows that are not whole packs (k_len % 8 != 0): the packs a row can touch at most, and the shape for them.  A row
+// starts at any multiple of gcd(k_len, 8) inside a pack.
+inline int sm_ragged_packs(int k_len)
+{
+    int step = 1;
+    while (step < kPack && k_len % (2 * step) == 0) step *= 2;
+    return (kPack - step + k_len + kPack - 1) / kPack;
+}
+// Shapes by packs touched (lanes per row, packs per lane), one row per lane group (two cost 2-8 % here).  Three packs
+// per lane fill the gaps between the powers of two, because a row needs a pack or two more than its elements fill.  The
+// backward of short rows has fewer lanes with two or three packs each: 4 x 2 against 8 x 1 at 45 keys 11.5 against 14.4 us
+// (dropout) and 10.3 against 12.5; the forward of those rows is faster the other way, 10.2 against 12.2 us.
+struct SmRagged { int lpr, vpl; };
+static const SmRagged kSmRaggedFwd[] = {{2, 1}, {4, 1}, {8, 1}, {4, 3}, {8, 2}, {8, 3}, {16, 2}, {16, 3}, {32, 2}, {32, 3}, {64, 2}, {64, 3}, {64, 4}};
+static const SmRagged kSmRaggedBwd[] = {{2, 1}, {2, 2}, {4, 2}, {4, 3}, {8, 2}, {8, 3}, {16, 2}, {16, 3}, {32, 2}, {32, 3}, {64, 2}, {64, 3}, {64, 4}};
+#define LSQ_SM_RAGGED_CASES(X)                                                                               \
+    X(4, 3, 1) X(8, 2, 1) X(8, 3, 1) X(16, 2, 1) X(16, 3, 1) X(32, 2, 1) X(32, 3, 1) X(64, 2, 1) X(64, 3, 1) X(64, 4, 1)
+#define LSQ_SM_RAGGED_FWD(X) X(2, 1, 1) X(4, 1, 1) X(8, 1, 1) LSQ_SM_RAGGED_CASES(X)
+#define LSQ_SM_RAGGED_BWD(X) X(2, 1, 1) X(2, 2, 1) X(4, 2, 1) LSQ_SM_RAGGED_CASES(X)
+template <int N>
+inline SmCand sm_ragged_choose(const SmRagged (&table)[N], int np)
+{
+    for (const SmRagged& c : table)
+        if (c.lpr * c.vpl >= np) return {c.lpr, c.vpl, 1};
+    return {0, 0, 0};                       // not reached: the tables end at 256 packs
+}
+
+// The paths by row length, with `np` the packs a row touches (base pointers are 16-byte aligned, checked at the entry):
+// up to 256 packs the lanes of a wave, up to 2048 a workgroup per row, beyond that the element-strided kernels; each in a
+// form for rows of whole packs and one for any other length.
 template <typename T>
 static lsq_status softmax_fwd_dispatch(void* y, void* yd, const void* x, SoftmaxLens key_len, const SoftmaxGeom& g,
                                        const DropoutParams& d, hipStream_t s, int forced = -1)
@@ -788,53 +774,38 @@ static lsq_status softmax_fwd_dispatch(void* y, void* yd, const void* x, Softmax
     T* yp = static_cast<T*>(y);
     T* ydp = static_cast<T*>(yd);
     const T* xp = static_cast<const T*>(x);
-    const bool packs_ok = g.k_len % kPack == 0 && aligned16(y) && aligned16(yd) && aligned16(x);
-    SmShape sh = packs_ok ? softmax_shape(g.k_len) : SmShape{0, 0};
-    // the packed kernel of rows up to 2048 keys folds the scale into its exponent and needs it positive;
-    // other scales (never an attention scale) take the element kernels, which multiply first
-    if (sh.lpr != 0 && sh.lpr <= 64 && !(g.scale > 0.0f)) sh = SmShape{0, 0};
+    const bool rag = g.k_len % kPack != 0;
+    const int np = rag ? sm_ragged_packs(g.k_len) : g.k_len / kPack;
     const bool drop = d.on != 0;
-    const SmShape es = softmax_elem_shape(g.k_len);
-    if (sh.lpr == 0 && es.lpr != 0) {
-        const dim3 egrid(static_cast<unsigned>(ceil_div(g.nrows, 256 / es.lpr)));
-#define X(L, E)                                                                                              \
-        if (es.lpr == L && es.vpl == E) {                                                                    \
-            if (drop) hipLaunchKernelGGL((softmax_fwd_elem<T, L, E, true>), egrid, dim3(256), 0, s, yp, ydp, xp, key_len, g, d); \
-            else hipLaunchKernelGGL((softmax_fwd_elem<T, L, E, false>), egrid, dim3(256), 0, s, yp, ydp, xp, key_len, g, d);    \
-        }
-        LSQ_SM_ELEM_CASES(X)
-#undef X
-        return launch_status();
-    }
-    if (sh.lpr == 0) {
-        // long rows: a whole workgroup per row (four times the lanes, and rows of this length come in small numbers)
-        if (g.k_len > 2048)
-            hipLaunchKernelGGL((softmax_fwd_generic<T, 256>), dim3(static_cast<unsigned>(g.nrows)), dim3(256), 0, s,
-                               yp, ydp, xp, key_len, g, d);
-        else
-            hipLaunchKernelGGL((softmax_fwd_generic<T, 64>), dim3(static_cast<unsigned>(ceil_div(g.nrows, 4))), dim3(256), 0, s,
-                               yp, ydp, xp, key_len, g, d);
-        return launch_status();
-    }
-    const dim3 block(256);
+    if (np > 256) {
+        const dim3 grid(static_cast<unsigned>(g.nrows)), block(256);
+        const int vpl = softmax_wide_vpl(np);
+        if (vpl == 0) hipLaunchKernelGGL((softmax_fwd_generic<T>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);
 #define W(V)                                                                                                 \
-    if (sh.lpr == 256 && sh.vpl == V) {                                                                      \
-        const dim3 grid(static_cast<unsigned>(g.nrows));                                                     \
-        if (drop) hipLaunchKernelGGL((softmax_fwd_wide<T, V, true>), grid, block, 0, s, yp, ydp, xp, key_len, g, d); \
-        else hipLaunchKernelGGL((softmax_fwd_wide<T, V, false>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);    \
-    }
-    W(2) W(4) W(8)
+        if (vpl == V) {                                                                                      \
+            if (rag && drop) hipLaunchKernelGGL((softmax_fwd_wide<T, V, true, true>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);   \
+            else if (rag) hipLaunchKernelGGL((softmax_fwd_wide<T, V, false, true>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);      \
+            else if (drop) hipLaunchKernelGGL((softmax_fwd_wide<T, V, true, false>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);     \
+            else hipLaunchKernelGGL((softmax_fwd_wide<T, V, false, false>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);              \
+        }
+        W(2) W(4) W(8)
 #undef W
-    if (sh.lpr == 256) return launch_status();
-    const SmCand c = sm_choose(key_len, g, drop, sizeof(T), 0, forced);
-    const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgFwd / c.lpr), c.rpt)));
-#define X(L, V, R)                                                                                           \
-    if (c.lpr == L && c.vpl == V && c.rpt == R) {                                                            \
-        if (drop) hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, true>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d); \
-        else hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, false>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d);    \
+        return launch_status();
     }
+    const SmCand c = rag ? sm_ragged_choose(kSmRaggedFwd, np) : sm_choose(key_len, g, drop, sizeof(T), 0, forced);
+    const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgFwd / c.lpr), c.rpt)));
+#define XR(L, V, R, RAG)                                                                                     \
+    if (rag == RAG && c.lpr == L && c.vpl == V && c.rpt == R) {                                              \
+        if (drop) hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, true, RAG>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d); \
+        else hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, false, RAG>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d);    \
+    }
+#define X(L, V, R) XR(L, V, R, false)
     LSQ_SM_CASES(X)
 #undef X
+#define X(L, V, R) XR(L, V, R, true)
+    LSQ_SM_RAGGED_FWD(X)
+#undef X
+#undef XR
     return launch_status();
 }
 
@@ -845,49 +816,38 @@ static lsq_status softmax_bwd_dispatch(void* dx, const void* dy, const void* y, 
     T* dxp = static_cast<T*>(dx);
     const T* dyp = static_cast<const T*>(dy);
     const T* yp = static_cast<const T*>(y);
-    const bool packs_ok = g.k_len % kPack == 0 && aligned16(dx) && aligned16(dy) && aligned16(y);
-    const SmShape sh = packs_ok ? softmax_shape(g.k_len) : SmShape{0, 0};
+    const bool rag = g.k_len % kPack != 0;
+    const int np = rag ? sm_ragged_packs(g.k_len) : g.k_len / kPack;
     const bool drop = d.on != 0;
-    const SmShape es = softmax_elem_shape(g.k_len);
-    if (sh.lpr == 0 && es.lpr != 0) {
-        const dim3 egrid(static_cast<unsigned>(ceil_div(g.nrows, 256 / es.lpr)));
-#define X(L, E)                                                                                              \
-        if (es.lpr == L && es.vpl == E) {                                                                    \
-            if (drop) hipLaunchKernelGGL((softmax_bwd_elem<T, L, E, true>), egrid, dim3(256), 0, s, dxp, dyp, yp, key_len, g, d); \
-            else hipLaunchKernelGGL((softmax_bwd_elem<T, L, E, false>), egrid, dim3(256), 0, s, dxp, dyp, yp, key_len, g, d);    \
-        }
-        LSQ_SM_ELEM_CASES(X)
-#undef X
-        return launch_status();
-    }
-    if (sh.lpr == 0) {
-        if (g.k_len > 2048)
-            hipLaunchKernelGGL((softmax_bwd_generic<T, 256>), dim3(static_cast<unsigned>(g.nrows)), dim3(256), 0, s,
-                               dxp, dyp, yp, key_len, g, d);
-        else
-            hipLaunchKernelGGL((softmax_bwd_generic<T, 64>), dim3(static_cast<unsigned>(ceil_div(g.nrows, 4))), dim3(256), 0, s,
-                               dxp, dyp, yp, key_len, g, d);
-        return launch_status();
-    }
-    const dim3 block(256);
+    if (np > 256) {
+        const dim3 grid(static_cast<unsigned>(g.nrows)), block(256);
+        const int vpl = softmax_wide_vpl(np);
+        if (vpl == 0) hipLaunchKernelGGL((softmax_bwd_generic<T>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);
 #define W(V)                                                                                                 \
-    if (sh.lpr == 256 && sh.vpl == V) {                                                                      \
-        const dim3 grid(static_cast<unsigned>(g.nrows));                                                     \
-        if (drop) hipLaunchKernelGGL((softmax_bwd_wide<T, V, true>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d); \
-        else hipLaunchKernelGGL((softmax_bwd_wide<T, V, false>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);    \
-    }
-    W(2) W(4) W(8)
+        if (vpl == V) {                                                                                      \
+            if (rag && drop) hipLaunchKernelGGL((softmax_bwd_wide<T, V, true, true>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);   \
+            else if (rag) hipLaunchKernelGGL((softmax_bwd_wide<T, V, false, true>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);      \
+            else if (drop) hipLaunchKernelGGL((softmax_bwd_wide<T, V, true, false>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);     \
+            else hipLaunchKernelGGL((softmax_bwd_wide<T, V, false, false>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);              \
+        }
+        W(2) W(4) W(8)
 #undef W
-    if (sh.lpr == 256) return launch_status();
-    const SmCand c = sm_choose(key_len, g, drop, sizeof(T), 1, forced);
-    const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgBwd / c.lpr), c.rpt)));
-#define X(L, V, R)                                                                                           \
-    if (c.lpr == L && c.vpl == V && c.rpt == R) {                                                            \
-        if (drop) hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, true>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d); \
-        else hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, false>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d);    \
+        return launch_status();
     }
+    const SmCand c = rag ? sm_ragged_choose(kSmRaggedBwd, np) : sm_choose(key_len, g, drop, sizeof(T), 1, forced);
+    const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgBwd / c.lpr), c.rpt)));
+#define XR(L, V, R, RAG)                                                                                     \
+    if (rag == RAG && c.lpr == L && c.vpl == V && c.rpt == R) {                                              \
+        if (drop) hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, true, RAG>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d); \
+        else hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, false, RAG>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d);    \
+    }
+#define X(L, V, R) XR(L, V, R, false)
     LSQ_SM_CASES(X)
 #undef X
+#define X(L, V, R) XR(L, V, R, true)
+    LSQ_SM_RAGGED_BWD(X)
+#undef X
+#undef XR
     return launch_status();
 }
 

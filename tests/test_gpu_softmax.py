@@ -149,3 +149,39 @@ def test_softmax_full_size_transformer_big_with_dropout():
     dx = L.lsq_softmax_bwd(dy, y, kl, True, 0.125, cfg.p_attn, cfg.philox_seed, 9)
     rdx = oracle.softmax_bwd(t["dy"], from_torch(y, dt), t["key_len"], True, 0.125, dt, cfg.p_attn, cfg.philox_seed, 9)
     assert_close_store(dx, rdx, dt, "dx")
+
+
+# rows that are not whole packs: both sides of every bucket edge (a row of k keys touches up to (k + 14) / 8 packs for odd
+# k, fewer for k = 2 or 4 mod 8), one row, and a tensor whose last pack is cut short
+RAGGED = [2, 9, 10, 25, 26, 57, 58, 121, 122, 124, 185, 187, 249, 251, 377, 379, 505, 507, 761, 763, 1017, 1019, 1529, 1531, 2041, 2043,
+          4089, 4091, 8185, 8187, 16377, 16379]
+
+
+@pytest.mark.parametrize("scale,p", [(0.125, 0.1), (-0.5, 0.0)])
+@pytest.mark.parametrize("dt", ["f16", "f32"])
+@pytest.mark.parametrize("Lk", RAGGED)
+def test_softmax_ragged_rows(Lk, dt, scale, p):
+    say(f"[softmax] ragged rows Lk={Lk} dt={dt} scale={scale} p={p}")
+    d = dev()
+    B, N, Lq = 3, 1, 3 if Lk > 1000 else 11
+    t = attention_tensors(CONFIGS[0], dt, batch=B, heads=N, q_len=Lq, k_len=Lk, stream=1200 + Lk)
+    key_len, query_len = np.array([Lk, max(1, Lk // 3), max(1, Lk - 1)], np.int32), np.array([Lq, 1, Lq - 1], np.int32)
+    x, dy = to_torch(t["x"], dt, d), to_torch(t["dy"], dt, d)
+    kl, ql = torch.from_numpy(key_len).to(d), torch.from_numpy(query_len).to(d)
+    ry, ryd = oracle.softmax_fwd(t["x"], key_len, False, scale, dt, p, 11, 3, query_len=query_len)
+    # what lies outside the mask never counts, whatever it holds
+    off = torch.arange(Lk, device=d)[None, None, None, :] >= kl[:, None, None, None]
+    off = off | (torch.arange(Lq, device=d)[None, None, :, None] >= ql[:, None, None, None])
+    x, dy = x.masked_fill(off, float("nan")), dy.masked_fill(off, float("nan"))
+    y, yd = L.lsq_softmax_varlen_fwd(x, kl, ql, False, scale, p, 11, 3)
+    assert_close_store(y, ry, dt, "y", f32_floor=1e-7)
+    assert not y[off].any()
+    if p > 0:
+        assert_close_store(yd, ryd, dt, "y_drop", f32_floor=1e-7)
+        assert np.array_equal(to_np64(yd, dt) == 0, ryd == 0)
+    dx = L.lsq_softmax_varlen_bwd(dy, y, kl, ql, False, scale, p, 11, 3)
+    rdx = oracle.softmax_bwd(t["dy"], from_torch(y, dt), key_len, False, scale, dt, p, 11, 3, query_len=query_len)
+    assert_close_store(dx, rdx, dt, "dx", f32_floor=1e-7)
+    # in place, forward and backward
+    assert torch.equal(L.lsq_softmax_varlen_fwd(x, kl, ql, False, scale, p, 11, 3, y=x)[0], y)
+    assert torch.equal(L.lsq_softmax_varlen_bwd(dy, y, kl, ql, False, scale, p, 11, 3, dx=dy), dx)

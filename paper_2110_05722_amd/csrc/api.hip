@@ -29,7 +29,7 @@ extern "C" size_t lsq_workspace_bytes(int32_t op, int64_t rows, int32_t cols)
             // one [cols] fp32 partial row (dbias) per row block
             return static_cast<size_t>(heads_bwd_row_blocks(rows, cols)) * static_cast<size_t>(cols) * sizeof(float);
         case LSQ_OP_EMBEDDING_BWD:
-            // sorted order, fp32 rows of the id segments that cross a window, rank counts
+            // sorted order, fp32 rows of the id segments that cross a window, the sort of many tokens
             return emb_bwd_plan(rows, cols).total();
         default:
             return 0;

@@ -5,13 +5,10 @@
 // The paper sums the gradient rows of a repeated token with atomicAdd.  Floating-point
 // atomics make the result depend on the arrival order; here the sum has a fixed order
 // instead, with no atomics at all:
-//   1. rank: every token's position in the order sorted by (token id, position) is
-//      COUNTED — tile against tile, 256 x 256 comparisons per workgroup out of LDS, one
-//      compare per pair — rather than sorted: counting is order-free, so the result is
-//      deterministic; beyond 16384 tokens (counting is quadratic) a stable radix sort of
-//      (position, id) by id produces the same order;
-//   2. scatter: order[rank[t]] = (t, id);
-//   3. accumulate: the sorted order is cut into windows of 8 entries; one wave per (window,
+//   1. order: the tokens of a call, equal ids together in ascending position.  Up to 16384 tokens a few
+//      workgroups sort them, each the ids of one residue class, in LDS (stable radix sort), while the other workgroups
+//      of the launch stream dy for dP; beyond that the sort runs over many workgroups, two launches per digit;
+//   2. accumulate: the sorted order is cut into windows of 8 entries; one wave per (window,
 //      64-pack column block) sums m (.) dy in ascending position in fp32, the eight rows and
 //      the destination rows in flight together.  An id whose rows lie inside one window is
 //      added to dE[w,:] at once; a more frequent one leaves one fp32 row per window that a
@@ -25,7 +22,6 @@ namespace lsq {
 
 constexpr bool kNT = true;
 constexpr int kEmbWaves = 4;
-constexpr int kTile = kEmbTile;
 
 __device__ __forceinline__ bool emb_is_pad(int w, int vocab, int pad_idx) { return w == pad_idx || w < 0 || w >= vocab; }
 
@@ -70,85 +66,185 @@ __device__ __forceinline__ unsigned emb_key(int w, int vocab, int pad_idx)
     return emb_is_pad(w, vocab, pad_idx) ? kPadKey : static_cast<unsigned>(w);
 }
 
-// Workgroup (it, js): for the 256 tokens i of tile `it`, how many tokens j of span `js` sort
-// before i by (key, position).  Every j of an earlier tile has j < i, so key_j <= key_i decides;
-// in a later tile key_j < key_i does; both are one unsigned compare against key_i + 1 or key_i.
-// Only the tile's own diagonal looks at the position.  Keys come out of LDS four at a time.
-__device__ __forceinline__ void emb_rank_body(int it, int js, int32_t* __restrict__ partial, const int32_t* __restrict__ tokens,
-                                              int64_t rows, int ntiles, int span_tiles, int vocab, int pad_idx)
-{
-    __shared__ __align__(16) unsigned keys[kTile];
-    const int me = threadIdx.x;
-    const int64_t i = static_cast<int64_t>(it) * kTile + me;
-    const unsigned ki = i < rows ? emb_key(tokens[i], vocab, pad_idx) : 0u;
-    const int jt0 = js * span_tiles;
-    const int jt1 = min(ntiles, jt0 + span_tiles);
-    const uint4* k4 = reinterpret_cast<const uint4*>(keys);
-    int count = 0;
-    for (int jt = jt0; jt < jt1; ++jt) {                   // uniform: every thread reaches both barriers
-        const int64_t j = static_cast<int64_t>(jt) * kTile + me;
-        __syncthreads();
-        keys[me] = j < rows ? emb_key(tokens[j], vocab, pad_idx) : kNoKey;   // kNoKey is below no bound
-        __syncthreads();
-        if (jt != it) {
-            const unsigned bound = ki + (jt < it ? 1u : 0u);
-#pragma unroll 8
-            for (int q = 0; q < kTile / 4; ++q) {
-                const uint4 k = k4[q];                     // LDS broadcast
-                count += (k.x < bound ? 1 : 0) + (k.y < bound ? 1 : 0) + (k.z < bound ? 1 : 0) + (k.w < bound ? 1 : 0);
-            }
-        } else {
-#pragma unroll 4
-            for (int q = 0; q < kTile / 4; ++q) {
-                const uint4 k = k4[q];
-                const int j4 = 4 * q;
-                count += (k.x < ki || (k.x == ki && j4 + 0 < me) ? 1 : 0) + (k.y < ki || (k.y == ki && j4 + 1 < me) ? 1 : 0)
-                       + (k.z < ki || (k.z == ki && j4 + 2 < me) ? 1 : 0) + (k.w < ki || (k.w == ki && j4 + 3 < me) ? 1 : 0);
-            }
-        }
-    }
-    if (i < rows) partial[static_cast<int64_t>(js) * rows + i] = count;
-}
+// The order of up to kEmbSortMax tokens, without a launch of its own: kSortParts workgroups, each for the ids of one residue
+// class.  What the accumulation needs is that equal ids stand together in ascending position; which id comes before
+// which is free, so a part can be any set of ids whose share does not follow from their frequency (frequent words have
+// small ids).  A workgroup looks at every token once, keeps the positions of its ids, in order, and counts those of the
+// parts before it, which is where its own begin; then it sorts its positions by the rest of the id: a stable least-
+// significant-digit radix sort, at most 6 bits per pass.  The lanes of a round of 64 entries that hold the same digit find
+// each other with ballots, the lowest takes as many places as they are from the wave's counter of that digit (waves
+// apart: nothing depends on timing).  An entry is 32 bits, the position and what the part leaves of the id, in LDS, or in
+// the workspace where a part is larger than kSortLds (one id everywhere).  Padding is not
+// sorted: what is left of `order` behind the live tokens is filled with it.
+// What bounds it is the latency of its steps, 13 us alone at 8192 tokens, most of it behind the dP stream that shares the
+// launch (together 15, bf16 hidden 1280; the quadratic rank count over 1024 workgroups with dP 15.7 and a scatter
+// launch of 4 before it).  One 1024-thread workgroup for all of 8192 tokens took 20 us; with the ids read again from the
+// tokens in every round instead of carried, the part of the most frequent word took 19.  The whole backward in us, before -> now:
+// 8 x 1024 tokens, hidden 1280 38.8 -> 34; 60 x 77, 1024 29 -> 20; 8 x 64, 512 20 -> 16; 300 x 50, 640 77 -> 33.
+constexpr int kSortPartBits = 6, kSortParts = 1 << kSortPartBits, kSortDigits = 64, kSortLds = 2048;
+constexpr int kSortPosBits = 14, kSortMaxIdBits = 32 - kSortPosBits + kSortPartBits;          // ids of up to 24 bits
+static_assert(kEmbSortMax <= 1 << kSortPosBits, "an entry holds the position");
+constexpr int kSortLdsBytes = 2 * kSortLds * 4 + 4 * kSortDigits * 4 + 16 * 4;
 
-__global__ __launch_bounds__(kTile) void emb_rank_partial(int32_t* __restrict__ partial, const int32_t* __restrict__ tokens,
-                                                          int64_t rows, int ntiles, int span_tiles, int vocab, int pad_idx)
+// src -> (passes) -> order; src and tmp hold n entries each
+__device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t* tmp, int n, int part, int2* __restrict__ order,
+                                              int passes, int pass_bits)
 {
-    emb_rank_body(blockIdx.x % ntiles, blockIdx.x / ntiles, partial, tokens, rows, ntiles, span_tiles, vocab, pad_idx);
-}
-
-// order[rank of t] = (t, key of t): the counts are a permutation of 0..rows-1.  Four lanes per
-// token add every fourth span each (integer sums: any order).
-__global__ __launch_bounds__(256) void emb_scatter(int2* __restrict__ order, const int32_t* __restrict__ partial,
-                                                   const int32_t* __restrict__ tokens, int64_t rows, int nspans,
-                                                   int vocab, int pad_idx)
-{
-    const int part = threadIdx.x >> 6;                                       // the wave: tokens stay coalesced
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
-    __shared__ int sm[3][64];
-    int rank = 0;
-    if (t < rows) {
-        int js = part;
-        for (; js + 12 < nspans; js += 16) {            // four loads in flight per trip
-            int a[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int rounds = (n + 255) / 256;
+    const int first = wave * rounds * kWave + lane;              // entry of round r: first + 64 r
+    const unsigned mask = (1u << pass_bits) - 1u;
+    // calls f(whether there is one, the entry, its digit's counter, the lanes of the round with that digit) round by round
+    auto walk = [&](int shift, auto&& f) {
+        for (int r = 0; r < rounds; ++r) {
+            const int i = first + r * kWave;
+            const bool valid = i < n;
+            const uint32_t e = valid ? src[i] : 0u;
+            const unsigned digit = (e >> shift) & mask;
+            uint64_t same = __ballot(valid);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) a[k] = partial[static_cast<int64_t>(js + 4 * k) * rows + t];
-            rank += a[0] + a[1] + a[2] + a[3];
+            for (int b = 0; b < 6; ++b) {
+                if (b < pass_bits) {
+                    const uint64_t has = __ballot((digit >> b) & 1);
+                    same &= ((digit >> b) & 1) ? has : ~has;
+                }
+            }
+            if (!valid) same = 1ull << lane;
+            f(valid, e, &cnt[wave * kSortDigits + digit], same);
         }
-        for (; js < nspans; js += 4) rank += partial[static_cast<int64_t>(js) * rows + t];
-    }
-    if (part > 0) sm[part - 1][threadIdx.x & 63] = rank;
-    __syncthreads();
-    if (part == 0 && t < rows) {
-        rank += sm[0][threadIdx.x] + sm[1][threadIdx.x] + sm[2][threadIdx.x];
-        order[rank] = make_int2(static_cast<int>(t), static_cast<int>(emb_key(tokens[t], vocab, pad_idx)));
+    };
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = kSortPosBits + pass_bits * pass;
+        cnt[threadIdx.x] = 0;                                    // 4 waves x 64 digits
+        __syncthreads();
+        walk(shift, [&](bool valid, uint32_t, int* c, uint64_t same) {
+            if (valid && lane == __builtin_ctzll(same)) *c += __popcll(same);
+        });
+        __syncthreads();
+        if (wave == 0) {                                         // lane = digit: starts in (digit, wave) order
+            int c[4], total = 0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) c[w] = cnt[w * kSortDigits + lane];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) total += c[w];
+            int incl = total;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(incl, o);
+                if (lane >= o) incl += v;
+            }
+            int at = incl - total;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) { cnt[w * kSortDigits + lane] = at; at += c[w]; }
+        }
+        __syncthreads();
+        const bool last = pass == passes - 1;
+        walk(shift, [&](bool valid, uint32_t e, int* c, uint64_t same) {
+            const int leader = __builtin_ctzll(same);
+            int to = 0;
+            if (valid && lane == leader) { to = *c; *c = to + __popcll(same); }
+            to = __shfl(to, leader) + __popcll(same & ((1ull << lane) - 1ull));
+            if (valid) {
+                if (last) order[to] = make_int2(static_cast<int>(e & ((1u << kSortPosBits) - 1u)),
+                                                static_cast<int>((e >> kSortPosBits) << kSortPartBits) | part);
+                else tmp[to] = e;
+            }
+        });
+        __syncthreads();
+        uint32_t* t = src; src = tmp; tmp = t;
     }
 }
 
-// ---- the same order for MANY tokens.  Counting pairs is quadratic in the tokens of a call (10 us at
-// 8192, 270 us at 65536); beyond 16384 tokens the (token, key) pairs go through a stable
-// least-significant-digit radix sort instead, 8 bits per pass over the bits an id can have (two
-// passes up to 65535 ids): a stable sort by key leaves equal ids in ascending position, which is the
-// order the accumulation wants.  A workgroup owns 2048 consecutive entries, striped over its 256
+__device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restrict__ order, uint32_t* __restrict__ spill,
+                                              const int32_t* __restrict__ tokens, int rows, int passes, int pass_bits,
+                                              int vocab, int pad_idx)
+{
+    __builtin_amdgcn_s_setprio(3);      // a chain of short steps: its instructions go before those of the dP waves on the same unit
+    uint32_t* in_lds = reinterpret_cast<uint32_t*>(lds);                                  // [2][kSortLds]
+    int* cnt = reinterpret_cast<int*>(lds + 2 * kSortLds * 4);                            // [4][kSortDigits]
+    int* sums = cnt + 4 * kSortDigits;                                                    // [3][4]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int rounds = (rows + 255) / 256;
+    const int first = wave * rounds * kWave + lane;              // token of round r: first + 64 r
+    constexpr int U = 32;                                        // rounds whose loads are in flight together (8192 tokens)
+    unsigned key[U];
+    auto load = [&](int r0) {
+        int w[U];
+#pragma unroll
+        for (int g = 0; g < U; g += 8) {
+            if (r0 + g < rounds) {                               // uniform; loads only, all in flight
+#pragma unroll
+                for (int u = g; u < g + 8; ++u) w[u] = tokens[min(first + (r0 + u) * kWave, rows - 1)];
+            } else {
+#pragma unroll
+                for (int u = g; u < g + 8; ++u) w[u] = pad_idx;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool there = r0 + u < rounds && first + (r0 + u) * kWave < rows;
+            key[u] = there ? emb_key(w[u], vocab, pad_idx) : kPadKey;
+        }
+    };
+    int mine = 0, below = 0, live = 0;                           // of the lane, then of the wave
+    for (int r0 = 0; r0 < rounds; r0 += U) {
+        load(r0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int cls = key[u] != kPadKey ? static_cast<int>(key[u] & (kSortParts - 1)) : kSortParts;
+            mine += cls == part ? 1 : 0;
+            below += cls < part ? 1 : 0;
+            live += cls < kSortParts ? 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        mine += __shfl_xor(mine, o);
+        below += __shfl_xor(below, o);
+        live += __shfl_xor(live, o);
+    }
+    if (lane == 0) { sums[wave] = mine; sums[4 + wave] = below; sums[8 + wave] = live; }
+    __syncthreads();
+    int to = 0, n = 0, base = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int c = sums[w];
+        to += w < wave ? c : 0;
+        n += c;
+        base += sums[4 + w];
+        all += sums[8 + w];
+    }
+    uint32_t* big0 = spill + base;                               // parts are disjoint: base + n <= live tokens <= rows
+    uint32_t* big1 = spill + rows + base;
+    const bool fits = n <= kSortLds;                             // uniform over the workgroup
+    for (int r0 = 0; r0 < rounds; r0 += U) {
+        if (rounds > U) load(r0);                                // up to U rounds they are still here
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u >= rounds) break;                         // uniform
+            const bool in = key[u] != kPadKey && static_cast<int>(key[u] & (kSortParts - 1)) == part;
+            const uint64_t m = __ballot(in);
+            if (m != 0) {
+                if (in) {
+                    const int at = to + __popcll(m & ((1ull << lane) - 1ull));
+                    const uint32_t e = (key[u] >> kSortPartBits) << kSortPosBits | static_cast<uint32_t>(first + (r0 + u) * kWave);
+                    if (fits) in_lds[at] = e;
+                    else big0[at] = e;
+                }
+                to += __popcll(m);
+            }
+        }
+    }
+    for (int i = all + part * 256 + static_cast<int>(threadIdx.x); i < rows; i += kSortParts * 256)
+        order[i] = make_int2(0, static_cast<int>(kPadKey));
+    __syncthreads();
+    if (fits) emb_sort_part(cnt, in_lds, in_lds + kSortLds, n, part, order + base, passes, pass_bits);
+    else emb_sort_part(cnt, big0, big1, n, part, order + base, passes, pass_bits);
+}
+
+// ---- the same order for MANY tokens: beyond kEmbSortMax the (token, key) pairs go through the same kind of
+// sort over many workgroups, 8 bits per pass over the bits an id can have (two
+// passes up to 65535 ids).  A workgroup owns 2048 consecutive entries, striped over its 256
 // threads (entry j*256 + i is item j of thread i), so that "round j, wave w, lane l" is ascending
 // position.  Per pass: digit histogram per workgroup (integer LDS atomics: the counts do not depend
 // on arrival order), exclusive scan of the [digit][workgroup] table (its own kernel only for very
@@ -450,27 +546,33 @@ __global__ __launch_bounds__(256) void emb_combine(T* __restrict__ demb, const f
     }
 }
 
-// dP[l,:] += sum over the batch.  A workgroup owns 64 packs of one position; its four
-// waves take every fourth sentence each (four loads in flight per wave) and their
-// partial sums are added in wave order, so the result does not depend on timing.
-template <typename T, bool DROP>
-__device__ __forceinline__ void emb_dpos_body(int cb, int l, T* __restrict__ dpos, const T* __restrict__ dy,
+// dP[l,:] += sum over the batch.  256 threads own W packs of one position; 256 / W groups of W lanes take every
+// (256 / W)-th sentence each (four loads in flight per lane) and their partial sums are added in group order, so the
+// result does not depend on timing.  W = 64 up to 16 sentences (one trip of 4 x 4 loads), and where there are many positions
+// to stream (fp32, 20 x 900, hidden 1600: 33 us, 59 as W = 16).  Otherwise 16 lanes per group, four times the sentences in
+// flight and four times the workgroups: with few positions and long batches the serial trips were the whole time
+// (250 sentences of 77, hidden 512: 48 us, now 20.6; 100 of 20, hidden 1024: 22 with the rank count, now 11.8).
+constexpr int kDposWideBatch = 16, kDposManyUnits = 1024;
+template <int W> constexpr int dpos_lds_floats() { return (256 / W - 1) * 8 * W; }
+constexpr int kEmbLds = dpos_lds_floats<16>() * 4 > kSortLdsBytes ? dpos_lds_floats<16>() * 4 : kSortLdsBytes;
+
+template <typename T, bool DROP, int W>
+__device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __restrict__ dpos, const T* __restrict__ dy,
                                               const int32_t* __restrict__ tokens, int batch, int len, int ppr,
                                               int vocab, int pad_idx, const DropoutParams& d)
 {
-    constexpr int U = 4;
-    __shared__ float sm[kEmbWaves - 1][8][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cp = cb * 64 + lane;
+    constexpr int U = 4, G = 256 / W;
+    const int lane = threadIdx.x % W, grp = threadIdx.x / W;
+    const int cp = cb * W + lane;
     const bool active = cp < ppr;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (active) {
-        for (int b0 = wave; b0 < batch; b0 += kEmbWaves * U) {
+        for (int b0 = grp; b0 < batch; b0 += G * U) {
             RawPack<T> raw[U];
             bool ok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int b = b0 + u * kEmbWaves;
+                const int b = b0 + u * G;
                 ok[u] = false;
                 if (b < batch) {
                     const int64_t t = static_cast<int64_t>(b) * len + l;
@@ -482,7 +584,7 @@ __device__ __forceinline__ void emb_dpos_body(int cb, int l, T* __restrict__ dpo
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (!ok[u]) continue;
-                const int64_t pack = (static_cast<int64_t>(b0 + u * kEmbWaves) * len + l) * ppr + cp;
+                const int64_t pack = (static_cast<int64_t>(b0 + u * G) * len + l) * ppr + cp;
                 float g[8];
                 unpack<T>(raw[u], g);
                 if constexpr (DROP) {
@@ -497,16 +599,16 @@ __device__ __forceinline__ void emb_dpos_body(int cb, int l, T* __restrict__ dpo
             }
         }
     }
-    if (wave > 0) {
+    if (grp > 0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sm[wave - 1][j][lane] = acc[j];
+        for (int j = 0; j < 8; ++j) sm[((grp - 1) * 8 + j) * W + lane] = acc[j];
     }
     __syncthreads();
-    if (wave == 0 && active) {
+    if (grp == 0 && active) {
 #pragma unroll
-        for (int w = 0; w < kEmbWaves - 1; ++w)
+        for (int w = 0; w < G - 1; ++w)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += sm[w][j][lane];
+            for (int j = 0; j < 8; ++j) acc[j] += sm[(w * 8 + j) * W + lane];
         T* dst = dpos + (static_cast<int64_t>(l) * ppr + cp) * kPack;
         float o[8];
         load8<T>(dst, o);
@@ -516,23 +618,36 @@ __device__ __forceinline__ void emb_dpos_body(int cb, int l, T* __restrict__ dpo
     }
 }
 
-// The rank count is arithmetic out of LDS, the position gradient a stream over dy; neither
-// needs the other.  One launch holds the workgroups of both (the rank ones first, so that they
-// all start at once and the streaming ones fill the remaining wave slots): the two overlap
-// instead of running back to back.
-template <typename T, bool DROP>
-__global__ __launch_bounds__(256) void emb_rank_dpos(int32_t* __restrict__ partial, const int32_t* __restrict__ tokens,
-                                                     int64_t rows, int ntiles, int span_tiles, int rank_blocks,
-                                                     T* __restrict__ dpos, const T* __restrict__ dy, int batch, int len,
+// The sort is a few workgroups' work, the position gradient a stream over dy; neither needs the other.  One launch holds
+// both, the sort first (workgroups 0 .. sorts - 1), so that they overlap instead of running back to back.  Without dP (units = 0) only
+// the sort runs, without the sort (many tokens) only dP.
+template <typename T, bool DROP, int W>
+__global__ __launch_bounds__(256) void emb_sort_dpos(int2* __restrict__ order, uint32_t* __restrict__ spill,
+                                                     const int32_t* __restrict__ tokens, int64_t rows, int sorts, int passes,
+                                                     int pass_bits, T* __restrict__ dpos, const T* __restrict__ dy, int batch, int len,
                                                      int ppr, int ncb, int vocab, int pad_idx, DropoutParams d)
 {
-    static_assert(kTile == 256, "one block size for both bodies");
-    if (static_cast<int>(blockIdx.x) < rank_blocks) {            // workgroup-uniform
-        emb_rank_body(blockIdx.x % ntiles, blockIdx.x / ntiles, partial, tokens, rows, ntiles, span_tiles, vocab, pad_idx);
-    } else {
-        const int b = static_cast<int>(blockIdx.x) - rank_blocks;
-        emb_dpos_body<T, DROP>(b % ncb, b / ncb, dpos, dy, tokens, batch, len, ppr, vocab, pad_idx, d);
-    }
+    __shared__ __align__(16) char lds[kEmbLds];
+    const int b = static_cast<int>(blockIdx.x) - sorts;
+    if (b < 0) emb_sort_body(lds, blockIdx.x, order, spill, tokens, static_cast<int>(rows), passes, pass_bits, vocab, pad_idx);
+    else emb_dpos_body<T, DROP, W>(reinterpret_cast<float*>(lds), b % ncb, b / ncb, dpos, dy, tokens, batch, len, ppr, vocab, pad_idx, d);
+}
+
+template <typename T>
+inline void launch_sort_dpos(int2* order, uint32_t* spill, const int32_t* tokens, int64_t rows, bool sort, int bits, T* dpos, const T* dy,
+                             int batch, int len, int ppr, int vocab, int pad_idx, const DropoutParams& d, hipStream_t s)
+{
+    const int w = batch <= kDposWideBatch || ceil_div(ppr, 64) * len >= kDposManyUnits ? 64 : 16;
+    const int ncb = static_cast<int>(ceil_div(ppr, w));
+    const int64_t units = dpos ? static_cast<int64_t>(ncb) * len : 0;
+    const int rest = bits > kSortPartBits ? bits - kSortPartBits : 1;           // bits of an id that the parts leave to sort by
+    const int passes = (rest + 5) / 6, pass_bits = (rest + passes - 1) / passes, sorts = sort ? kSortParts : 0;
+    const dim3 grid(static_cast<unsigned>(sorts + units)), block(256);
+    if (grid.x == 0) return;
+#define D(DROP, W) hipLaunchKernelGGL((emb_sort_dpos<T, DROP, W>), grid, block, 0, s, order, spill, tokens, rows, sorts, passes, pass_bits, dpos, dy, batch, len, ppr, ncb, vocab, pad_idx, d)
+    if (d.on) { if (w == 64) D(true, 64); else D(true, 16); }
+    else { if (w == 64) D(false, 64); else D(false, 16); }
+#undef D
 }
 
 // ---- generic paths (hidden not a multiple of 8): one element per thread
@@ -633,7 +748,6 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
     const EmbBwdPlan plan = emb_bwd_plan(rows, hidden);
     int2* order = reinterpret_cast<int2*>(ws);
     float* win_rows = reinterpret_cast<float*>(static_cast<char*>(ws) + plan.order_bytes);
-    int32_t* partial = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + plan.order_bytes + plan.win_bytes);
     T* de = static_cast<T*>(demb);
     T* dp = static_cast<T*>(dpos);
     const T* g = static_cast<const T*>(dy);
@@ -641,30 +755,16 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
     const bool packed = hidden % kPack == 0;
     const int ppr = hidden / kPack;
     const int ncb = static_cast<int>(ceil_div(ppr, 64));
-    if (rows <= kEmbCountMax) {
-        // few tokens: order[rank of t] = (t, key), the rank counted pair by pair
-        const unsigned rank_blocks = static_cast<unsigned>(plan.ntiles) * static_cast<unsigned>(plan.nspans);
-        if (packed && dp) {
-            // the position gradient rides along with the rank count
-            const dim3 rgrid(rank_blocks + static_cast<unsigned>(ncb) * static_cast<unsigned>(len));
-            if (d.on) hipLaunchKernelGGL((emb_rank_dpos<T, true>), rgrid, dim3(256), 0, s, partial, tokens, rows, plan.ntiles, plan.span_tiles,
-                                          static_cast<int>(rank_blocks), dp, g, batch, len, ppr, ncb, vocab, pad_idx, d);
-            else hipLaunchKernelGGL((emb_rank_dpos<T, false>), rgrid, dim3(256), 0, s, partial, tokens, rows, plan.ntiles, plan.span_tiles,
-                                    static_cast<int>(rank_blocks), dp, g, batch, len, ppr, ncb, vocab, pad_idx, d);
-        } else {
-            hipLaunchKernelGGL(emb_rank_partial, dim3(rank_blocks), dim3(kTile), 0, s, partial, tokens, rows, plan.ntiles,
-                               plan.span_tiles, vocab, pad_idx);
-        }
-        hipLaunchKernelGGL(emb_scatter, dim3(static_cast<unsigned>(ceil_div(rows, 64))), dim3(256), 0, s, order, partial,
-                           tokens, rows, plan.nspans, vocab, pad_idx);
-    } else {
-        // many tokens: stable radix sort of (t, key) by the bits an id can have; padding (all ones) comes last
-        int bits = 1;
-        while ((static_cast<int64_t>(1) << bits) <= vocab) ++bits;                 // 2^bits > vocab
-        const int passes = (bits + 7) / 8;
+    int bits = 1;
+    while ((static_cast<int64_t>(1) << bits) <= vocab) ++bits;                 // 2^bits > vocab: padding (all ones) comes last
+    const int passes = (bits + 7) / 8;
+    const bool few = rows <= kEmbSortMax && bits <= kSortMaxIdBits;
+    int32_t* hist = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + plan.order_bytes + plan.win_bytes);     // [256][radix blocks]
+    int2* tmp = reinterpret_cast<int2*>(reinterpret_cast<char*>(hist) + plan.radix_hist_bytes);                 // [rows]
+    // the position gradient rides along with the one-workgroup sort (rows of whole packs)
+    launch_sort_dpos<T>(order, reinterpret_cast<uint32_t*>(tmp), tokens, rows, few, bits, packed ? dp : nullptr, g, batch, len, ppr, vocab, pad_idx, d, s);
+    if (!few) {
         const int nblocks = plan.radix_blocks;
-        int32_t* hist = partial;                                                     // [256][nblocks]
-        int2* tmp = reinterpret_cast<int2*>(reinterpret_cast<char*>(partial) + plan.radix_hist_bytes);
         const int2* src = nullptr;
         for (int pass = 0; pass < passes; ++pass) {
             int2* dst = (passes - pass) % 2 == 1 ? order : tmp;                      // the last pass lands in `order`
@@ -676,11 +776,6 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
                 hipLaunchKernelGGL((emb_radix_scatter<true>), dim3(nblocks), dim3(256), 0, s, dst, hist, src, tokens, rows, nblocks, 8 * pass, vocab, pad_idx);
             }
             src = dst;
-        }
-        if (packed && dp) {            // the position gradient on its own (no rank workgroups in the launch)
-            const dim3 rgrid(static_cast<unsigned>(ncb) * static_cast<unsigned>(len));
-            if (d.on) hipLaunchKernelGGL((emb_rank_dpos<T, true>), rgrid, dim3(256), 0, s, partial, tokens, rows, 1, 1, 0, dp, g, batch, len, ppr, ncb, vocab, pad_idx, d);
-            else hipLaunchKernelGGL((emb_rank_dpos<T, false>), rgrid, dim3(256), 0, s, partial, tokens, rows, 1, 1, 0, dp, g, batch, len, ppr, ncb, vocab, pad_idx, d);
         }
     }
     if (packed) {
@@ -737,7 +832,7 @@ extern "C" lsq_status lsq_embedding_bwd(void* demb, void* dpos, const void* dy, 
     if (rows == 0) return LSQ_OK;
     LSQ_REQUIRE(rows <= 0x7FFFFFFF / 2);
     LSQ_REQUIRE(ceil_div(rows, kEmbWin) * ceil_div(hidden, 8 * 64) < 0x7FFFFFFF);   // one workgroup per (window, column block)
-    LSQ_REQUIRE(ceil_div(rows, kTile) * 64 + ceil_div(hidden, 8 * 64) * static_cast<int64_t>(len) < 0x7FFFFFFF);
+    LSQ_REQUIRE(ceil_div(rows, 256) * 64 + ceil_div(hidden, 8 * 64) * static_cast<int64_t>(len) < 0x7FFFFFFF);   // (position, column block) pairs
     LSQ_REQUIRE(demb && dy && tokens);
     LSQ_ALIGNED(demb); LSQ_ALIGNED(dpos); LSQ_ALIGNED(dy); LSQ_ALIGNED(workspace);
     const size_t need = lsq_workspace_bytes(LSQ_OP_EMBEDDING_BWD, rows, hidden);

@@ -354,33 +354,27 @@ inline int heads_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_ro
 //   order  [rows] (token position, sort key), 8 bytes each
 //   window rows [2 * windows][hidden rounded up to 8] fp32: the partial sums of id segments
 //          that cross a window of kEmbWin sorted entries (at most two per window)
-//   rank counts [spans][rows] int32: token i against the tokens of span js (a span is a run
-//          of 256-token tiles, at most 64 spans); beyond kEmbCountMax tokens the same region holds
-//          the radix sort's [256][workgroups] digit counts and its second (token, key) buffer
-constexpr int kEmbTile = 256;
-constexpr int64_t kEmbCountMax = 16384;
+//   the radix sort's [256][workgroups] digit counts and its second (token, key) buffer, which up to
+//          kEmbSortMax tokens holds the parts of the in-LDS sort that are too large for it
+constexpr int64_t kEmbSortMax = 16384;
 constexpr int kEmbWin = 8;
 struct EmbBwdPlan {
-    int ntiles, span_tiles, nspans, radix_blocks;
+    int radix_blocks;
     size_t radix_hist_bytes;
     int64_t nwin;
-    size_t order_bytes, win_bytes, rank_bytes;
-    size_t total() const { return order_bytes + win_bytes + rank_bytes; }
+    size_t order_bytes, win_bytes, sort_bytes;
+    size_t total() const { return order_bytes + win_bytes + sort_bytes; }
 };
 inline EmbBwdPlan emb_bwd_plan(int64_t rows, int32_t hidden)
 {
     EmbBwdPlan p;
-    p.ntiles = static_cast<int>(ceil_div(rows, kEmbTile));
-    p.span_tiles = static_cast<int>(ceil_div(p.ntiles, 64));
-    p.nspans = static_cast<int>(ceil_div(p.ntiles, p.span_tiles));
     p.nwin = ceil_div(rows, kEmbWin);
     const size_t colsp = (static_cast<size_t>(hidden) + 7u) / 8u * 8u;
     p.order_bytes = (static_cast<size_t>(rows) * 8u + 15u) / 16u * 16u;
     p.win_bytes = 2u * static_cast<size_t>(p.nwin) * colsp * sizeof(float);
-    p.rank_bytes = static_cast<size_t>(p.nspans) * static_cast<size_t>(rows) * sizeof(int32_t);
     p.radix_blocks = static_cast<int>(ceil_div(rows, 2048));
     p.radix_hist_bytes = (static_cast<size_t>(256) * static_cast<size_t>(p.radix_blocks) * sizeof(int32_t) + 15u) / 16u * 16u;
-    if (rows > kEmbCountMax) p.rank_bytes = p.radix_hist_bytes + static_cast<size_t>(rows) * 8u;
+    p.sort_bytes = p.radix_hist_bytes + static_cast<size_t>(rows) * 8u;
     return p;
 }
 

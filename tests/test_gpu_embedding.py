@@ -19,7 +19,7 @@ CASES = [(8, 64, 8000, 512, 0.1), (128, 32, 32768, 512, 0.1), (16, 128, 4096, 10
          (36, 512, 100, 16, 0.1), (9, 2048, 70001, 16, 0.1),      # one pass (ids below 256) and three (above 65535)
          (550, 2000, 3000, 8, 0.1),     # 1.1 M tokens: the radix passes with the stand-alone offset scan
          (1, 70000, 500, 8, 0.1),       # one sentence longer than 65535 positions
-         (4, 4096, 50257, 8, 0.0)]      # exactly 16384 tokens: the last size whose ranks are counted, 64 one-tile spans
+         (4, 4096, 50257, 8, 0.0)]      # exactly 16384 tokens: the largest one-workgroup sort
 
 
 def _tokens(B, Ln, V, rng):
@@ -98,3 +98,21 @@ def test_embedding_bwd_degenerate_batches(kind):
     assert_close_store(dpos, decode(p0, dt) + inc_p, dt, "dpos", f32_floor=1e-4)
     if kind == "all padding":
         assert np.array_equal(from_torch(demb, dt), d0) and np.array_equal(from_torch(dpos, dt), p0)
+
+
+# the one-workgroup sort: rounds of 1024 tokens (edges of one, of eight, of the largest), ids of one, two and three digits, the
+# hand-over to the sort over many workgroups; and the position gradient on both sides of 16 sentences
+@pytest.mark.parametrize("B,Ln,V", [(1, 63, 255), (1, 64, 256), (3, 341, 65535), (1, 1024, 65536), (25, 41, 300), (16, 512, 50257),
+                                    (17, 482, 70000), (17, 71, 9), (64, 255, 40), (4, 1500, 3), (1, 16384, 50257), (5, 3277, 50257)])
+def test_embedding_bwd_token_order(B, Ln, V):
+    say(f"[embedding] token order B={B} L={Ln} V={V}")
+    d, dt, H = dev(), "f16", 24
+    rng = np.random.default_rng(B + Ln + V)
+    tok = _tokens(B, Ln, V, rng)
+    dys = encode(rng.standard_normal((B * Ln, H), dtype=np.float32) * 0.05, dt)
+    d0, p0 = encode(np.zeros((V, H), np.float32), dt), encode(np.zeros((Ln, H), np.float32), dt)
+    demb, dpos = to_torch(d0, dt, d), to_torch(p0, dt, d)
+    L.lsq_embedding_bwd(demb, dpos, to_torch(dys, dt, d), torch.from_numpy(tok).to(d), PAD, 2.0, 0.1, 3, 7)
+    inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.1, 3, 7, dt)
+    assert_close_store(demb, inc_e, dt, "demb")
+    assert_close_store(dpos, inc_p, dt, "dpos")

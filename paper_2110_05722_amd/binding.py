@@ -127,13 +127,14 @@ def _check(code: int, name: str):
 
 
 def _ptr(t):
+    """Device address of a tensor (an int: ctypes converts it for a c_void_p argument as fast as a ready-made object)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise LsqError("tensors must live on the GPU (there is no CPU path)")
     if not t.is_contiguous():
         raise LsqError("tensors must be contiguous")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dt(t) -> int:
@@ -144,7 +145,11 @@ def _dt(t) -> int:
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream, as an int.  torch.cuda.current_stream() builds a Stream object for it, 2.75 us of
+    a 13 us call; the raw query takes 0.19.  It wants an initialised runtime, which the public call sees to."""
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _need(name: str, t, numel: int, dtype=None):

@@ -356,6 +356,122 @@ __device__ __forceinline__ void dropout_factors8(const DropoutParams& d, uint64_
     }
 }
 
+// The factors of the 8 elements from flat element `e` on, at any alignment: the two groups that they touch are drawn and the
+// sixteen 16-bit lanes shifted down by e % 8 (e is the same for all lanes of a row walk up to multiples of 8: the shifts'
+// conditions are uniform).
+__device__ __forceinline__ void dropout_factors8_any(const DropoutParams& d, uint64_t e, float (&k)[8])
+{
+    const uint64_t g = e >> 3;
+    uint32_t lo[4], hi[4];
+    philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), d.ctr2, d.ctr3, d.key0, d.key1, lo);
+    philox4x32_10(static_cast<uint32_t>(g + 1), static_cast<uint32_t>((g + 1) >> 32), d.ctr2, d.ctr3, d.key0, d.key1, hi);
+    const unsigned s = static_cast<unsigned>(e) & 7u;
+    // (scalars, not an array in a loop: selected by element address it would live in scratch memory)
+    const bool by4 = s & 4u, by2 = s & 2u, by1 = s & 1u;
+    const uint32_t a0 = by4 ? lo[2] : lo[0], a1 = by4 ? lo[3] : lo[1], a2 = by4 ? hi[0] : lo[2], a3 = by4 ? hi[1] : lo[3];
+    const uint32_t a4 = by4 ? hi[2] : hi[0], a5 = by4 ? hi[3] : hi[1];
+    const uint32_t b0 = by2 ? a1 : a0, b1 = by2 ? a2 : a1, b2 = by2 ? a3 : a2, b3 = by2 ? a4 : a3, b4 = by2 ? a5 : a4;
+    const uint32_t w[4] = {by1 ? (b0 >> 16) | (b1 << 16) : b0, by1 ? (b1 >> 16) | (b2 << 16) : b1,
+                           by1 ? (b2 >> 16) | (b3 << 16) : b2, by1 ? (b3 >> 16) | (b4 << 16) : b3};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        k[2 * j] = (w[j] & 0xFFFFu) >= d.t16 ? d.scale : 0.0f;
+        k[2 * j + 1] = (w[j] >> 16) >= d.t16 ? d.scale : 0.0f;
+    }
+}
+
+// a pack moved down by s elements (0..7), zeros from above
+__device__ __forceinline__ RawPack<float> shift_down(const RawPack<float>& r, int s)
+{
+    const bool by4 = s & 4, by2 = s & 2, by1 = s & 1;
+    const fvec4 z = {0.f, 0.f, 0.f, 0.f};
+    const fvec4 a = by4 ? r.b : r.a, b = by4 ? z : r.b;
+    const fvec4 c = by2 ? fvec4{a.z, a.w, b.x, b.y} : a, d = by2 ? fvec4{b.z, b.w, 0.f, 0.f} : b;
+    RawPack<float> o;
+    o.a = by1 ? fvec4{c.y, c.z, c.w, d.x} : c;
+    o.b = by1 ? fvec4{d.y, d.z, d.w, 0.f} : d;
+    return o;
+}
+template <typename T>
+__device__ __forceinline__ RawPack<T> shift_down(const RawPack<T>& r, int s)
+{
+    const bool by4 = s & 4, by2 = s & 2, by1 = s & 1;
+    const uvec4 a = by4 ? uvec4{r.u.z, r.u.w, 0u, 0u} : r.u;
+    const uvec4 b = by2 ? uvec4{a.y, a.z, a.w, 0u} : a;
+    RawPack<T> o;
+    o.u = by1 ? uvec4{(b.x >> 16) | (b.y << 16), (b.y >> 16) | (b.z << 16), (b.z >> 16) | (b.w << 16), b.w >> 16} : b;
+    return o;
+}
+
+// ------------------------------------------------------------------ rows of any length
+// A [rows, hidden] tensor walked in packs of 8 columns counted from each row's start.  RAG = false: hidden is a whole
+// number of packs, every access aligned.  RAG = true: any hidden.  Rows then start at any element, so a pack is a 128-bit access
+// that is aligned to the element only (the hardware takes it; it may touch two lines), the last pack of a row has
+// hidden % 8 elements and goes element by element, and a pack's dropout lanes come from two groups.
+typedef uint32_t any4 __attribute__((ext_vector_type(4), aligned(2)));
+template <typename T, bool RAG>
+struct RowPackIO {
+    int hidden, ppr;                                             // columns; packs per row, the cut one included
+    __host__ __device__ explicit RowPackIO(int h) : hidden(h), ppr(RAG ? (h + kPack - 1) / kPack : h / kPack) {}
+
+    __device__ __forceinline__ int64_t element(int64_t row, int cp) const { return row * hidden + cp * kPack; }
+    template <bool NT>
+    __device__ __forceinline__ RawPack<T> load(const T* __restrict__ base, int64_t row, int cp) const
+    {
+        const T* p = base + element(row, cp);
+        if constexpr (!RAG) return load_raw<T, NT>(p);
+        const int left = hidden - cp * kPack;
+        if (hidden < kPack) {                                    // uniform: rows shorter than a pack
+            float f[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = to_f32<T>(p[j < left ? j : 0]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = j < left ? f[j] : 0.0f;
+            return pack_raw<T>(f);                               // exact: the values come from T
+        }
+        // the cut pack: the row's last 8 elements, shifted down by those that belong to the pack before (no branch; one
+        // load per element behind branches took 0.8 us each, 14 of them in a row in the forward)
+        const int s = left < kPack ? kPack - left : 0;
+        RawPack<T> r;
+        if constexpr (sizeof(T) == 2) {
+            r.u = *reinterpret_cast<const any4*>(p - s);
+        } else {
+            r.a = __builtin_bit_cast(fvec4, static_cast<uvec4>(*reinterpret_cast<const any4*>(p - s)));
+            r.b = __builtin_bit_cast(fvec4, static_cast<uvec4>(*reinterpret_cast<const any4*>(p - s + 4)));
+        }
+        return shift_down(r, s);
+    }
+    template <bool NT>
+    __device__ __forceinline__ void store(T* base, int64_t row, int cp, const float (&f)[8]) const
+    {
+        T* p = base + element(row, cp);
+        if constexpr (!RAG) {
+            store8<T, NT>(p, f);
+        } else {
+            const int left = hidden - cp * kPack;
+            if (left >= kPack) {
+                const RawPack<T> r = pack_raw<T>(f);
+                if constexpr (sizeof(T) == 2) {
+                    *reinterpret_cast<any4*>(p) = r.u;
+                } else {
+                    *reinterpret_cast<any4*>(p) = __builtin_bit_cast(uvec4, r.a);
+                    *reinterpret_cast<any4*>(p + 4) = __builtin_bit_cast(uvec4, r.b);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 7; ++j)
+                    if (j < left) p[j] = from_f32<T>(f[j]);
+            }
+        }
+    }
+    __device__ __forceinline__ void factors(const DropoutParams& d, int64_t row, int cp, float (&k)[8]) const
+    {
+        const uint64_t e = static_cast<uint64_t>(element(row, cp));
+        if constexpr (RAG) dropout_factors8_any(d, e, k);
+        else dropout_factors8(d, e >> 3, k);
+    }
+};
+
 // The factor for one element (element-strided paths and the ragged last pack of a flat walk: one Philox call per element).
 __device__ __forceinline__ float dropout_factor1(const DropoutParams& d, uint64_t e)
 {

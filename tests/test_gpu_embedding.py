@@ -116,3 +116,36 @@ def test_embedding_bwd_token_order(B, Ln, V):
     inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.1, 3, 7, dt)
     assert_close_store(demb, inc_e, dt, "demb")
     assert_close_store(dpos, inc_p, dt, "dpos")
+
+
+# rows that are not whole packs: one column, less than a pack, a pack and a bit, both sides of a 64-pack column block; every
+# alignment of a row start (odd, 2 and 4 mod 8), segments that cross windows, and the last rows of each tensor
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("H", [1, 7, 9, 100, 511, 514, 1001])
+def test_embedding_rows_of_any_length(H, dt):
+    say(f"[embedding] rows of any length H={H} dt={dt}")
+    d, B, Ln, V = dev(), 19, 23, 40
+    rng = np.random.default_rng(H)
+    tok = _tokens(B, Ln, V, rng)
+    tok[-1, -1], tok[0, 0] = V - 1, 2
+    mk = lambda shape, std: encode(rng.standard_normal(shape, dtype=np.float32) * np.float32(std), dt)  # noqa: E731
+    embs, poss, dys, d0, p0 = mk((V, H), 1), mk((Ln, H), 0.5), mk((B * Ln, H), 0.05), mk((V, H), 0.1), mk((Ln, H), 0.1)
+    t = torch.from_numpy(tok).to(d)
+    # every tensor ends where its allocation's neighbour begins: guard words behind it must keep their value
+    def guarded(a):
+        flat = to_torch(a, dt, d).reshape(-1)
+        buf = torch.full((flat.numel() + 64,), 7.0, dtype=flat.dtype, device=d)
+        buf[:flat.numel()] = flat
+        return buf, buf[:flat.numel()].view(a.shape)
+    bout, out = guarded(np.zeros_like(dys))
+    L.lsq_embedding_fwd(t, to_torch(embs, dt, d), to_torch(poss, dt, d), PAD, 2.0, 0.2, 9, 4, out=out)
+    ref = oracle.embedding_fwd(tok, embs, poss, PAD, 2.0, 0.2, 9, 4, dt)
+    assert_close_store(out, ref, dt, "out", f32_floor=1e-5)
+    assert np.array_equal(decode(from_torch(out, dt), dt).reshape(ref.shape) == 0, ref == 0)
+    (be, demb), (bp, dpos) = guarded(d0), guarded(p0)
+    L.lsq_embedding_bwd(demb, dpos, to_torch(dys, dt, d), t, PAD, 2.0, 0.2, 9, 4)
+    inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.2, 9, 4, dt)
+    assert_close_store(demb, decode(d0, dt).reshape(V, H) + inc_e, dt, "demb", f32_floor=1e-5)
+    assert_close_store(dpos, decode(p0, dt).reshape(Ln, H) + inc_p, dt, "dpos", f32_floor=1e-5)
+    for b in (bout, be, bp):
+        assert (b[-64:] == 7).all()

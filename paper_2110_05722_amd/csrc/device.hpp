@@ -415,22 +415,39 @@ struct RowPackIO {
     __host__ __device__ explicit RowPackIO(int h) : hidden(h), ppr(RAG ? (h + kPack - 1) / kPack : h / kPack) {}
 
     __device__ __forceinline__ int64_t element(int64_t row, int cp) const { return row * hidden + cp * kPack; }
+    // A load in two steps, so that many can be in flight: `ahead` only loads, `settle` (at the first use) makes the pack of it.
     template <bool NT>
     __device__ __forceinline__ RawPack<T> load(const T* __restrict__ base, int64_t row, int cp) const
+    {
+        return settle(ahead<NT>(base, row, cp), cp);
+    }
+    __device__ __forceinline__ RawPack<T> settle(const RawPack<T>& r, int cp) const
+    {
+        if constexpr (!RAG) return r;
+        const int left = hidden - cp * kPack;
+        return shift_down(r, left < kPack && hidden >= kPack ? kPack - left : 0);
+    }
+    template <bool NT>
+    __device__ __forceinline__ RawPack<T> ahead(const T* __restrict__ base, int64_t row, int cp) const
     {
         const T* p = base + element(row, cp);
         if constexpr (!RAG) return load_raw<T, NT>(p);
         const int left = hidden - cp * kPack;
         if (hidden < kPack) {                                    // uniform: rows shorter than a pack
-            float f[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) f[j] = to_f32<T>(p[j < left ? j : 0]);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) f[j] = j < left ? f[j] : 0.0f;
-            return pack_raw<T>(f);                               // exact: the values come from T
+            RawPack<T> r;
+            if constexpr (sizeof(T) == 2) {
+                const uint16_t* q = reinterpret_cast<const uint16_t*>(p);
+                auto at = [&](int j) { const uint32_t v = q[j < left ? j : 0]; return j < left ? v : 0u; };
+                r.u = uvec4{at(0) | at(1) << 16, at(2) | at(3) << 16, at(4) | at(5) << 16, at(6) | at(7) << 16};
+            } else {
+                auto at = [&](int j) { const float v = p[j < left ? j : 0]; return j < left ? v : 0.0f; };
+                r.a = fvec4{at(0), at(1), at(2), at(3)};
+                r.b = fvec4{at(4), at(5), at(6), at(7)};
+            }
+            return r;
         }
-        // the cut pack: the row's last 8 elements, shifted down by those that belong to the pack before (no branch; one
-        // load per element behind branches took 0.8 us each, 14 of them in a row in the forward)
+        // the cut pack: the row's last 8 elements, shifted down (in settle) by those that belong to the pack before (no branch;
+        // one load per element behind branches took 0.8 us each, 14 of them in a row in the embedding's forward)
         const int s = left < kPack ? kPack - left : 0;
         RawPack<T> r;
         if constexpr (sizeof(T) == 2) {
@@ -439,30 +456,39 @@ struct RowPackIO {
             r.a = __builtin_bit_cast(fvec4, static_cast<uvec4>(*reinterpret_cast<const any4*>(p - s)));
             r.b = __builtin_bit_cast(fvec4, static_cast<uvec4>(*reinterpret_cast<const any4*>(p - s + 4)));
         }
-        return shift_down(r, s);
+        return r;
     }
     template <bool NT>
-    __device__ __forceinline__ void store(T* base, int64_t row, int cp, const float (&f)[8]) const
+    __device__ __forceinline__ void put(T* base, int64_t row, int cp, const RawPack<T>& r) const
     {
         T* p = base + element(row, cp);
         if constexpr (!RAG) {
-            store8<T, NT>(p, f);
+            store_raw<T, NT>(p, r);
         } else {
             const int left = hidden - cp * kPack;
             if (left >= kPack) {
-                const RawPack<T> r = pack_raw<T>(f);
                 if constexpr (sizeof(T) == 2) {
                     *reinterpret_cast<any4*>(p) = r.u;
                 } else {
                     *reinterpret_cast<any4*>(p) = __builtin_bit_cast(uvec4, r.a);
                     *reinterpret_cast<any4*>(p + 4) = __builtin_bit_cast(uvec4, r.b);
                 }
+            } else if constexpr (sizeof(T) == 2) {
+                uint16_t* q = reinterpret_cast<uint16_t*>(p);
+#pragma unroll
+                for (int j = 0; j < 7; ++j)
+                    if (j < left) q[j] = static_cast<uint16_t>(r.u[j / 2] >> (16 * (j & 1)));
             } else {
 #pragma unroll
                 for (int j = 0; j < 7; ++j)
-                    if (j < left) p[j] = from_f32<T>(f[j]);
+                    if (j < left) p[j] = j < 4 ? r.a[j & 3] : r.b[j & 3];
             }
         }
+    }
+    template <bool NT>
+    __device__ __forceinline__ void store(T* base, int64_t row, int cp, const float (&f)[8]) const
+    {
+        put<NT>(base, row, cp, pack_raw<T>(f));
     }
     __device__ __forceinline__ void factors(const DropoutParams& d, int64_t row, int cp, float (&k)[8]) const
     {

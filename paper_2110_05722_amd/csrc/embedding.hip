@@ -42,8 +42,9 @@ __global__ __launch_bounds__(256) void emb_fwd_cols(T* __restrict__ out, const i
             const uint32_t t32 = static_cast<uint32_t>(t);           // tokens of a call are below 2^31 (checked at the entry)
             const int l = static_cast<int>(t32 - fastdiv(t32, by_len) * static_cast<uint32_t>(len));
             float e[8], pp[8];
-            unpack<T>(io.template load<false>(emb, w, cp), e);
-            unpack<T>(io.template load<false>(pos, l, cp), pp);
+            const RawPack<T> re = io.template ahead<false>(emb, w, cp), rp = io.template ahead<false>(pos, l, cp);
+            unpack<T>(io.settle(re, cp), e);
+            unpack<T>(io.settle(rp, cp), pp);
 #pragma unroll
             for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, e[j], pp[j]);
             if constexpr (DROP) {
@@ -424,12 +425,12 @@ __global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, floa
     RawPack<T> raw[kEmbWin], dst_raw[kEmbWin];
 #pragma unroll
     for (int k = 0; k < kEmbWin; ++k) {
-        if (emb_live_key(key[k + 1])) raw[k] = io.template load<kNT>(dy, tok[k], cp);
+        if (emb_live_key(key[k + 1])) raw[k] = io.template ahead<kNT>(dy, tok[k], cp);
         else raw[k] = zero_raw<T>();
     }
 #pragma unroll
     for (int k = 0; k < kEmbWin; ++k) {
-        if (action[k] == 1) dst_raw[k] = io.template load<false>(demb, key[k + 1], cp);
+        if (action[k] == 1) dst_raw[k] = io.template ahead<false>(demb, key[k + 1], cp);
         else dst_raw[k] = zero_raw<T>();
     }
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -437,7 +438,7 @@ __global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, floa
     for (int k = 0; k < kEmbWin; ++k) {
         if (emb_live_key(key[k + 1])) {
             float g[8];
-            unpack<T>(raw[k], g);
+            unpack<T>(io.settle(raw[k], cp), g);
             if constexpr (DROP) {
                 float kf[8];
                 io.factors(d, tok[k], cp, kf);
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, floa
         }
         if (action[k] == 1) {
             float o[8];
-            unpack<T>(dst_raw[k], o);
+            unpack<T>(io.settle(dst_raw[k], cp), o);
 #pragma unroll
             for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, acc[j], o[j]);
             io.template store<false>(demb, key[k + 1], cp, o);
@@ -577,7 +578,7 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
                 if (b < batch) {
                     const int64_t t = static_cast<int64_t>(b) * len + l;
                     ok[u] = !emb_is_pad(tokens[t], vocab, pad_idx);
-                    if (ok[u]) raw[u] = io.template load<true>(dy, t, cp);
+                    if (ok[u]) raw[u] = io.template ahead<true>(dy, t, cp);
                 }
                 if (!ok[u]) raw[u] = zero_raw<T>();
             }
@@ -586,7 +587,7 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
                 if (!ok[u]) continue;
                 const int64_t t = static_cast<int64_t>(b0 + u * G) * len + l;
                 float g[8];
-                unpack<T>(raw[u], g);
+                unpack<T>(io.settle(raw[u], cp), g);
                 if constexpr (DROP) {
                     float kf[8];
                     io.factors(d, t, cp, kf);

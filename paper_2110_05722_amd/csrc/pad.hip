@@ -22,7 +22,6 @@ struct PadGeom {
     int64_t rows;           // batch * max_len
     int64_t packed_rows;    // capacity of the packed tensor, rows
     int batch, max_len, hidden;
-    int ppr;                // packs per row (hidden / 8), pack path only
     FastDiv by_max_len;     // padded row -> sentence (rows are below 2^31)
 };
 
@@ -74,13 +73,16 @@ __device__ __forceinline__ int64_t packed_row(const PadGeom& g, const int32_t* _
 
 // RESTORE = false: packed <- padded (rows of padding skipped);
 // RESTORE = true:  padded <- packed, zeros on the padding.
-template <typename T, bool RESTORE>
+// Rows that are not whole packs, or tensors that are not 16-byte aligned, take the same walk with element-aligned packs
+// (RAG): 128 x 64 x 1001 halves, remove / restore 7.2 / 7.9 us against 17.6 / 18.1 with one element per thread.
+template <typename T, bool RESTORE, bool RAG>
 __global__ __launch_bounds__(256) void pad_move_kernel(T* __restrict__ dst, const T* __restrict__ src,
                                                        const int32_t* __restrict__ offsets, PadGeom g)
 {
+    const RowPackIO<T, RAG> io(g.hidden);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int cp = blockIdx.x * 64 + lane;
-    if (cp >= g.ppr) return;
+    if (cp >= io.ppr) return;
     const int64_t stride = static_cast<int64_t>(gridDim.y) * (kPadWaves * kPadRows);
     for (int64_t t0 = (static_cast<int64_t>(blockIdx.y) * kPadWaves + wave) * kPadRows; t0 < g.rows; t0 += stride) {
         int64_t pr[kPadRows];
@@ -89,36 +91,17 @@ __global__ __launch_bounds__(256) void pad_move_kernel(T* __restrict__ dst, cons
         for (int k = 0; k < kPadRows; ++k) {
             pr[k] = packed_row(g, offsets, t0 + k);      // wave-uniform
             const int64_t from = RESTORE ? pr[k] : t0 + k;
-            if (pr[k] >= 0) raw[k] = load_raw<T, kNT>(src + (from * g.ppr + cp) * kPack);
+            if (pr[k] >= 0) raw[k] = io.template ahead<kNT>(src, from, cp);
             else raw[k] = zero_raw<T>();
         }
 #pragma unroll
         for (int k = 0; k < kPadRows; ++k) {
             if (RESTORE) {
-                if (t0 + k < g.rows) store_raw<T, kNT>(dst + ((t0 + k) * g.ppr + cp) * kPack, raw[k]);
+                if (t0 + k < g.rows) io.template put<kNT>(dst, t0 + k, cp, io.settle(raw[k], cp));
             } else {
-                if (pr[k] >= 0) store_raw<T, kNT>(dst + (pr[k] * g.ppr + cp) * kPack, raw[k]);
+                if (pr[k] >= 0) io.template put<kNT>(dst, pr[k], cp, io.settle(raw[k], cp));
             }
         }
-    }
-}
-
-// any hidden size / alignment: one element per thread over the padded tensor
-template <typename T, bool RESTORE>
-__global__ __launch_bounds__(256) void pad_move_flat(T* __restrict__ dst, const T* __restrict__ src,
-                                                     const int32_t* __restrict__ offsets, PadGeom g)
-{
-    const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (e >= g.rows * g.hidden) return;
-    const int64_t t = e / g.hidden;
-    const int c = static_cast<int>(e - t * g.hidden);
-    const int64_t r = packed_row(g, offsets, t);
-    if (RESTORE) {
-        T zero;
-        __builtin_memset(&zero, 0, sizeof(T));
-        dst[e] = r >= 0 ? src[r * g.hidden + c] : zero;
-    } else if (r >= 0) {
-        dst[r * g.hidden + c] = src[e];
     }
 }
 
@@ -127,17 +110,14 @@ static lsq_status pad_dispatch(void* dst, const void* src, const int32_t* offset
 {
     T* d = static_cast<T*>(dst);
     const T* a = static_cast<const T*>(src);
-    if (g.hidden % kPack == 0 && aligned16(dst) && aligned16(src)) {
-        const int gx = static_cast<int>(ceil_div(g.ppr, 64));
-        int64_t gy = ceil_div(g.rows, kPadWaves * kPadRows);
-        const int64_t cap = 16384 / gx > 1 ? 16384 / gx : 1;      // about 64 workgroups per compute unit
-        if (gy > cap) gy = cap;
-        hipLaunchKernelGGL((pad_move_kernel<T, RESTORE>), dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy)),
-                           dim3(256), 0, s, d, a, offsets, g);
-    } else {
-        hipLaunchKernelGGL((pad_move_flat<T, RESTORE>), dim3(static_cast<unsigned>(ceil_div(g.rows * g.hidden, 256))),
-                           dim3(256), 0, s, d, a, offsets, g);
-    }
+    const bool whole = g.hidden % kPack == 0 && aligned16(dst) && aligned16(src);
+    const int gx = static_cast<int>(ceil_div(ceil_div(g.hidden, kPack), 64));
+    int64_t gy = ceil_div(g.rows, kPadWaves * kPadRows);
+    const int64_t cap = 16384 / gx > 1 ? 16384 / gx : 1;      // about 64 workgroups per compute unit
+    if (gy > cap) gy = cap;
+    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy)), block(256);
+    if (whole) hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, false>), grid, block, 0, s, d, a, offsets, g);
+    else hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, true>), grid, block, 0, s, d, a, offsets, g);
     return launch_status();
 }
 
@@ -150,7 +130,6 @@ static lsq_status pad_geom(PadGeom* g, int32_t batch, int32_t max_len, int32_t h
     g->packed_rows = packed_rows;
     g->batch = batch; g->max_len = max_len; g->hidden = hidden;
     g->by_max_len = make_fastdiv(static_cast<uint32_t>(max_len));
-    g->ppr = hidden / kPack;
     if (ceil_div(g->rows * hidden, 256) > 0x7FFFFFFF) return LSQ_INVALID_ARG;
     return LSQ_OK;
 }

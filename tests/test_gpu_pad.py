@@ -135,3 +135,31 @@ def test_softmax_with_query_lengths(B, N, Lq, Lk, causal, p, dt):
     y0, _ = L.lsq_softmax_varlen_fwd(x, kl, None, causal, 0.125, 0.0)
     y1, _ = L.lsq_softmax_fwd(x, kl, causal, 0.125, 0.0)
     assert torch.equal(y0, y1)
+
+
+@pytest.mark.parametrize("dt", ["f16", "f32"])
+@pytest.mark.parametrize("H,shift", [(1, 0), (7, 0), (9, 0), (511, 0), (513, 0), (1001, 0), (64, 3), (1001, 1)])
+def test_rows_of_any_length_and_alignment(H, shift, dt):
+    """Rows that are not whole packs, and tensors that start `shift` elements into an allocation: bit-exact moves (NaN
+    payloads included), nothing outside the tensors written."""
+    say(f"[pad] H={H} shift={shift} dt={dt}")
+    d, B, Lmax = dev(), 9, 21
+    r = np.random.default_rng(H + shift)
+    lens = r.integers(0, Lmax + 1, size=B).astype(np.int32)
+    it, ft = (torch.int16, torch.float16) if dt == "f16" else (torch.int32, torch.float32)
+    mk = lambda n: torch.randint(-2 ** 15, 2 ** 15 - 1, (n + 64,), device=d).to(it)      # noqa: E731  any bit pattern
+    n, total = B * Lmax * H, int(lens.sum())
+    src, back = mk(n), mk(n)
+    out = mk(total * H)
+    view = lambda t, m: t[shift:shift + m]                                               # noqa: E731
+    x, packed = view(src, n).view(ft).view(B, Lmax, H), view(out, total * H).view(ft).view(total, H)
+    keep_out, keep_back = out.clone(), back.clone()
+    off = L.lsq_pad_offsets(torch.from_numpy(lens).to(d), B, Lmax)
+    L.lsq_pad_remove(x, off, total, packed=packed)
+    mask = torch.arange(Lmax, device=d)[None, :] < torch.from_numpy(lens).to(d)[:, None]
+    want = view(src, n).view(B, Lmax, H)[mask]
+    assert torch.equal(view(out, total * H).view(total, H), want)
+    L.lsq_pad_restore(packed, off, B, Lmax, padded=view(back, n).view(ft).view(B, Lmax, H))
+    assert torch.equal(view(back, n).view(B, Lmax, H), torch.where(mask[:, :, None], view(src, n).view(B, Lmax, H), 0))
+    for t, k, m in ((out, keep_out, total * H), (back, keep_back, n)):
+        assert torch.equal(t[:shift], k[:shift]) and torch.equal(t[shift + m:], k[shift + m:])

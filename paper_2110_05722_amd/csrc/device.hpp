@@ -414,7 +414,7 @@ struct RowPackIO {
     int hidden, ppr;                                             // columns; packs per row, the cut one included
     __host__ __device__ explicit RowPackIO(int h) : hidden(h), ppr(RAG ? (h + kPack - 1) / kPack : h / kPack) {}
 
-    __device__ __forceinline__ int64_t element(int64_t row, int cp) const { return row * hidden + cp * kPack; }
+    __device__ __forceinline__ int64_t element(int64_t row, int cp) const { return RAG ? row * hidden + cp * kPack : (row * ppr + cp) * kPack; }
     // A load in two steps, so that many can be in flight: `ahead` only loads, `settle` (at the first use) makes the pack of it.
     template <bool NT>
     __device__ __forceinline__ RawPack<T> load(const T* __restrict__ base, int64_t row, int cp) const

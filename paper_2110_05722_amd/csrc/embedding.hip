@@ -66,7 +66,7 @@ __device__ __forceinline__ unsigned emb_key(int w, int vocab, int pad_idx)
     return emb_is_pad(w, vocab, pad_idx) ? kPadKey : static_cast<unsigned>(w);
 }
 
-// The order of up to kEmbSortMax tokens, without a launch of its own: kSortParts workgroups, each for the ids of one residue
+// The order of up to kEmbSortMax tokens, without a launch of its own: 64 workgroups, each for the ids of one residue
 // class.  What the accumulation needs is that equal ids stand together in ascending position; which id comes before
 // which is free, so a part can be any set of ids whose share does not follow from their frequency (frequent words have
 // small ids).  A workgroup looks at every token once, keeps the positions of its ids, in order, and counts those of the
@@ -81,15 +81,29 @@ __device__ __forceinline__ unsigned emb_key(int w, int vocab, int pad_idx)
 // launch of 4 before it).  One 1024-thread workgroup for all of 8192 tokens took 20 us; with the ids read again from the
 // tokens in every round instead of carried, the part of the most frequent word took 19.  The whole backward in us, before -> now:
 // 8 x 1024 tokens, hidden 1280 38.8 -> 34; 60 x 77, 1024 29 -> 20; 8 x 64, 512 20 -> 16; 300 x 50, 640 77 -> 33.
-constexpr int kSortPartBits = 6, kSortParts = 1 << kSortPartBits, kSortDigits = 64, kSortLds = 2048;
-constexpr int kSortPosBits = 14, kSortMaxIdBits = 32 - kSortPosBits + kSortPartBits;          // ids of up to 24 bits
-static_assert(kEmbSortMax <= 1 << kSortPosBits, "an entry holds the position");
+constexpr int kSortDigits = 64, kSortLds = 2048;
+// How an id is split: `part_bits` low bits choose the part (64 parts; 128 where that makes a 31-bit id of a small call fit), the
+// rest shares a 32-bit entry with the `pos_bits` bits of a position.
+struct EmbSortPlan { int part_bits, pos_bits, passes, pass_bits; bool fits; };
+inline EmbSortPlan emb_sort_plan(int64_t rows, int bits)
+{
+    EmbSortPlan p;
+    p.pos_bits = 1;
+    while ((static_cast<int64_t>(1) << p.pos_bits) < rows) ++p.pos_bits;
+    p.part_bits = bits > 32 - p.pos_bits + 6 && rows <= 256 ? 7 : 6;
+    p.fits = rows <= kEmbSortMax && bits <= 32 - p.pos_bits + p.part_bits;
+    const int rest = bits > p.part_bits ? bits - p.part_bits : 1;
+    p.passes = (rest + 5) / 6;
+    p.pass_bits = (rest + p.passes - 1) / p.passes;
+    return p;
+}
 constexpr int kSortLdsBytes = 2 * kSortLds * 4 + 4 * kSortDigits * 4 + 16 * 4;
 
 // src -> (passes) -> order; src and tmp hold n entries each
 __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t* tmp, int n, int part, int2* __restrict__ order,
-                                              int passes, int pass_bits)
+                                              const EmbSortPlan& pl)
 {
+    const int passes = pl.passes, pass_bits = pl.pass_bits;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rounds = (n + 255) / 256;
     const int first = wave * rounds * kWave + lane;              // entry of round r: first + 64 r
@@ -114,7 +128,7 @@ __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t*
         }
     };
     for (int pass = 0; pass < passes; ++pass) {
-        const int shift = kSortPosBits + pass_bits * pass;
+        const int shift = pl.pos_bits + pass_bits * pass;
         cnt[threadIdx.x] = 0;                                    // 4 waves x 64 digits
         __syncthreads();
         walk(shift, [&](bool valid, uint32_t, int* c, uint64_t same) {
@@ -145,8 +159,8 @@ __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t*
             if (valid && lane == leader) { to = *c; *c = to + __popcll(same); }
             to = __shfl(to, leader) + __popcll(same & ((1ull << lane) - 1ull));
             if (valid) {
-                if (last) order[to] = make_int2(static_cast<int>(e & ((1u << kSortPosBits) - 1u)),
-                                                static_cast<int>((e >> kSortPosBits) << kSortPartBits) | part);
+                if (last) order[to] = make_int2(static_cast<int>(e & ((1u << pl.pos_bits) - 1u)),
+                                                static_cast<int>((e >> pl.pos_bits) << pl.part_bits) | part);
                 else tmp[to] = e;
             }
         });
@@ -156,9 +170,10 @@ __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t*
 }
 
 __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restrict__ order, uint32_t* __restrict__ spill,
-                                              const int32_t* __restrict__ tokens, int rows, int passes, int pass_bits,
+                                              const int32_t* __restrict__ tokens, int rows, const EmbSortPlan& pl,
                                               int vocab, int pad_idx)
 {
+    const int parts = 1 << pl.part_bits;
     __builtin_amdgcn_s_setprio(3);      // a chain of short steps: its instructions go before those of the dP waves on the same unit
     uint32_t* in_lds = reinterpret_cast<uint32_t*>(lds);                                  // [2][kSortLds]
     int* cnt = reinterpret_cast<int*>(lds + 2 * kSortLds * 4);                            // [4][kSortDigits]
@@ -191,10 +206,10 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
         load(r0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int cls = key[u] != kPadKey ? static_cast<int>(key[u] & (kSortParts - 1)) : kSortParts;
+            const int cls = key[u] != kPadKey ? static_cast<int>(key[u] & (parts - 1)) : parts;
             mine += cls == part ? 1 : 0;
             below += cls < part ? 1 : 0;
-            live += cls < kSortParts ? 1 : 0;
+            live += cls < parts ? 1 : 0;
         }
     }
 #pragma unroll
@@ -222,12 +237,12 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (r0 + u >= rounds) break;                         // uniform
-            const bool in = key[u] != kPadKey && static_cast<int>(key[u] & (kSortParts - 1)) == part;
+            const bool in = key[u] != kPadKey && static_cast<int>(key[u] & (parts - 1)) == part;
             const uint64_t m = __ballot(in);
             if (m != 0) {
                 if (in) {
                     const int at = to + __popcll(m & ((1ull << lane) - 1ull));
-                    const uint32_t e = (key[u] >> kSortPartBits) << kSortPosBits | static_cast<uint32_t>(first + (r0 + u) * kWave);
+                    const uint32_t e = (key[u] >> pl.part_bits) << pl.pos_bits | static_cast<uint32_t>(first + (r0 + u) * kWave);
                     if (fits) in_lds[at] = e;
                     else big0[at] = e;
                 }
@@ -235,11 +250,11 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
             }
         }
     }
-    for (int i = all + part * 256 + static_cast<int>(threadIdx.x); i < rows; i += kSortParts * 256)
+    for (int i = all + part * 256 + static_cast<int>(threadIdx.x); i < rows; i += parts * 256)
         order[i] = make_int2(0, static_cast<int>(kPadKey));
     __syncthreads();
-    if (fits) emb_sort_part(cnt, in_lds, in_lds + kSortLds, n, part, order + base, passes, pass_bits);
-    else emb_sort_part(cnt, big0, big1, n, part, order + base, passes, pass_bits);
+    if (fits) emb_sort_part(cnt, in_lds, in_lds + kSortLds, n, part, order + base, pl);
+    else emb_sort_part(cnt, big0, big1, n, part, order + base, pl);
 }
 
 // ---- the same order for MANY tokens: beyond kEmbSortMax the (token, key) pairs go through the same kind of
@@ -623,29 +638,28 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
 // the sort runs, without the sort (many tokens) only dP.
 template <typename T, bool DROP, int W, bool RAG>
 __global__ __launch_bounds__(256) void emb_sort_dpos(int2* __restrict__ order, uint32_t* __restrict__ spill,
-                                                     const int32_t* __restrict__ tokens, int64_t rows, int sorts, int passes,
-                                                     int pass_bits, T* __restrict__ dpos, const T* __restrict__ dy, int batch, int len,
+                                                     const int32_t* __restrict__ tokens, int64_t rows, int sorts, EmbSortPlan pl,
+                                                     T* __restrict__ dpos, const T* __restrict__ dy, int batch, int len,
                                                      RowPackIO<T, RAG> io, int ncb, int vocab, int pad_idx, DropoutParams d)
 {
     __shared__ __align__(16) char lds[kEmbLds];
     const int b = static_cast<int>(blockIdx.x) - sorts;
-    if (b < 0) emb_sort_body(lds, blockIdx.x, order, spill, tokens, static_cast<int>(rows), passes, pass_bits, vocab, pad_idx);
+    if (b < 0) emb_sort_body(lds, blockIdx.x, order, spill, tokens, static_cast<int>(rows), pl, vocab, pad_idx);
     else emb_dpos_body<T, DROP, W, RAG>(reinterpret_cast<float*>(lds), b % ncb, b / ncb, dpos, dy, tokens, batch, len, io, vocab, pad_idx, d);
 }
 
 template <typename T, bool RAG>
-inline void launch_sort_dpos(int2* order, uint32_t* spill, const int32_t* tokens, int64_t rows, bool sort, int bits, T* dpos, const T* dy,
+inline void launch_sort_dpos(int2* order, uint32_t* spill, const int32_t* tokens, int64_t rows, bool sort, const EmbSortPlan& pl, T* dpos, const T* dy,
                              int batch, int len, const RowPackIO<T, RAG>& io, int vocab, int pad_idx, const DropoutParams& d, hipStream_t s)
 {
     const int ppr = io.ppr;
     const int w = batch <= kDposWideBatch || ceil_div(ppr, 64) * len >= kDposManyUnits ? 64 : 16;
     const int ncb = static_cast<int>(ceil_div(ppr, w));
     const int64_t units = dpos ? static_cast<int64_t>(ncb) * len : 0;
-    const int rest = bits > kSortPartBits ? bits - kSortPartBits : 1;           // bits of an id that the parts leave to sort by
-    const int passes = (rest + 5) / 6, pass_bits = (rest + passes - 1) / passes, sorts = sort ? kSortParts : 0;
+    const int sorts = sort ? 1 << pl.part_bits : 0;
     const dim3 grid(static_cast<unsigned>(sorts + units)), block(256);
     if (grid.x == 0) return;
-#define D(DROP, W) hipLaunchKernelGGL((emb_sort_dpos<T, DROP, W, RAG>), grid, block, 0, s, order, spill, tokens, rows, sorts, passes, pass_bits, dpos, dy, batch, len, io, ncb, vocab, pad_idx, d)
+#define D(DROP, W) hipLaunchKernelGGL((emb_sort_dpos<T, DROP, W, RAG>), grid, block, 0, s, order, spill, tokens, rows, sorts, pl, dpos, dy, batch, len, io, ncb, vocab, pad_idx, d)
     if (d.on) { if (w == 64) D(true, 64); else D(true, 16); }
     else { if (w == 64) D(false, 64); else D(false, 16); }
 #undef D
@@ -688,11 +702,16 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
     int bits = 1;
     while ((static_cast<int64_t>(1) << bits) <= vocab) ++bits;                 // 2^bits > vocab: padding (all ones) comes last
     const int passes = (bits + 7) / 8;
-    const bool few = rows <= kEmbSortMax && bits <= kSortMaxIdBits;
-    int32_t* hist = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + plan.order_bytes + plan.win_bytes);     // [256][radix blocks]
-    int2* tmp = reinterpret_cast<int2*>(reinterpret_cast<char*>(hist) + plan.radix_hist_bytes);                 // [rows]
+    const EmbSortPlan pl = emb_sort_plan(rows, bits);
+    const bool few = pl.fits;
+    char* scratch = static_cast<char*>(ws) + plan.order_bytes + plan.win_bytes;
+    uint32_t* spill = reinterpret_cast<uint32_t*>(scratch);                     // two entries per token, used beyond kSortLds tokens only
+    int32_t* hist = reinterpret_cast<int32_t*>(scratch);                        // [256][radix blocks]
+    // beyond kEmbSortMax the second buffer has its own place; a small call with ids too long for the in-LDS sort takes the window
+    // rows for it (at least 8 bytes per token, written only after the sort)
+    int2* tmp = reinterpret_cast<int2*>(rows > kEmbSortMax ? scratch + plan.radix_hist_bytes : reinterpret_cast<char*>(win_rows));
     // the position gradient rides along with the in-LDS sort
-    launch_sort_dpos<T, RAG>(order, reinterpret_cast<uint32_t*>(tmp), tokens, rows, few, bits, dp, g, batch, len, io, vocab, pad_idx, d, s);
+    launch_sort_dpos<T, RAG>(order, spill, tokens, rows, few, pl, dp, g, batch, len, io, vocab, pad_idx, d, s);
     if (!few) {
         const int nblocks = plan.radix_blocks;
         const int2* src = nullptr;

@@ -354,8 +354,10 @@ inline int heads_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_ro
 //   order  [rows] (token position, sort key), 8 bytes each
 //   window rows [2 * windows][hidden rounded up to 8] fp32: the partial sums of id segments
 //          that cross a window of kEmbWin sorted entries (at most two per window)
-//   the radix sort's [256][workgroups] digit counts and its second (token, key) buffer, which up to
-//          kEmbSortMax tokens holds the parts of the in-LDS sort that are too large for it
+//   sort scratch: beyond kEmbSortMax tokens the radix sort's [256][workgroups] digit counts and its second
+//          (token, key) buffer; up to there rows * 4 bytes per 256 tokens, which hold the parts of the in-LDS sort that
+//          are too large for it (beyond 2048 tokens), or the digit counts where ids are too long for it (the second
+//          buffer then lies in the window rows, which are written later)
 constexpr int64_t kEmbSortMax = 16384;
 constexpr int kEmbWin = 8;
 struct EmbBwdPlan {
@@ -374,7 +376,8 @@ inline EmbBwdPlan emb_bwd_plan(int64_t rows, int32_t hidden)
     p.win_bytes = 2u * static_cast<size_t>(p.nwin) * colsp * sizeof(float);
     p.radix_blocks = static_cast<int>(ceil_div(rows, 2048));
     p.radix_hist_bytes = (static_cast<size_t>(256) * static_cast<size_t>(p.radix_blocks) * sizeof(int32_t) + 15u) / 16u * 16u;
-    p.sort_bytes = p.radix_hist_bytes + static_cast<size_t>(rows) * 8u;
+    p.sort_bytes = rows > kEmbSortMax ? p.radix_hist_bytes + static_cast<size_t>(rows) * 8u
+                                      : static_cast<size_t>(ceil_div(rows, 256)) * static_cast<size_t>(rows) * sizeof(int32_t);
     return p;
 }
 

@@ -149,3 +149,19 @@ def test_embedding_rows_of_any_length(H, dt):
     assert_close_store(dpos, decode(p0, dt).reshape(Ln, H) + inc_p, dt, "dpos", f32_floor=1e-5)
     for b in (bout, be, bp):
         assert (b[-64:] == 7).all()
+
+
+@pytest.mark.parametrize("Ln", [37, 2300])
+def test_embedding_bwd_ids_beyond_24_bits(Ln):
+    """25-bit ids: beside the positions of 148 tokens they fit an entry of the in-LDS sort, beside those of 9200 they do
+    not and the call goes through the sort over many workgroups."""
+    say(f"[embedding] vocabulary beyond 2^24, L={Ln}")
+    d, dt, B, V = dev(), "f16", 4, (1 << 24) + 100
+    rng = np.random.default_rng(24)
+    tok = rng.choice(np.array([5, 5 + (1 << 24), 99, V - 1], np.int32), size=(B, Ln)).astype(np.int32)
+    dys = encode(rng.standard_normal((B * Ln, 1), dtype=np.float32) * 0.01, dt)
+    demb, dpos = torch.zeros((V, 1), dtype=torch.float16, device=d), torch.zeros((Ln, 1), dtype=torch.float16, device=d)
+    L.lsq_embedding_bwd(demb, dpos, to_torch(dys, dt, d), torch.from_numpy(tok).to(d), PAD, 2.0, 0.1, 3, 7)
+    inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.1, 3, 7, dt)
+    assert_close_store(demb, inc_e, dt, "demb")
+    assert_close_store(dpos, inc_p, dt, "dpos")

@@ -356,6 +356,18 @@ __device__ __forceinline__ void dropout_factors8(const DropoutParams& d, uint64_
     }
 }
 
+// v = keep ? v : 0 for the 8 elements of pack `g`: a dropped infinity or NaN becomes 0, which a factor of 0 would not make it.
+__device__ __forceinline__ void dropout_keep8(const DropoutParams& d, uint64_t g, float (&v)[8])
+{
+    uint32_t w[4];
+    philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), d.ctr2, d.ctr3, d.key0, d.key1, w);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[2 * j] = (w[j] & 0xFFFFu) >= d.t16 ? v[2 * j] : 0.0f;
+        v[2 * j + 1] = (w[j] >> 16) >= d.t16 ? v[2 * j + 1] : 0.0f;
+    }
+}
+
 // The factors of the 8 elements from flat element `e` on, at any alignment: the two groups that they touch are drawn and the
 // sixteen 16-bit lanes shifted down by e % 8 (e is the same for all lanes of a row walk up to multiples of 8: the shifts'
 // conditions are uniform).

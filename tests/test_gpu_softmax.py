@@ -185,3 +185,59 @@ def test_softmax_ragged_rows(Lk, dt, scale, p):
     # in place, forward and backward
     assert torch.equal(L.lsq_softmax_varlen_fwd(x, kl, ql, False, scale, p, 11, 3, y=x)[0], y)
     assert torch.equal(L.lsq_softmax_varlen_bwd(dy, y, kl, ql, False, scale, p, 11, 3, dx=dy), dx)
+
+
+# every path of the dispatch: a lane's own pack, several lanes, a whole wave, a workgroup per row, the element-strided kernel beyond;
+# rows of whole packs and others
+@pytest.mark.parametrize("dt", ["f16", "f32"])
+@pytest.mark.parametrize("Lk", [8, 64, 1024, 2056, 16392, 5, 14, 26, 45, 63, 113, 180, 201, 1001, 2039, 2047, 4099, 16379])
+def test_softmax_nonfinite_values_stay_inside_the_mask(Lk, dt):
+    """Infinities and NaN inside the allowed set (a mixed-precision overflow step) spoil their row's allowed positions only:
+    positions outside the mask are +0, dropped ones of y_drop are 0, and other rows do not change by a bit."""
+    say(f"[softmax] non-finite values inside the mask Lk={Lk} dt={dt}")
+    d, p, seed, offset = dev(), 0.25, 21, 8
+    B, N, Lq = 2, 1, 5
+    t = attention_tensors(CONFIGS[0], dt, batch=B, heads=N, q_len=Lq, k_len=Lk, stream=1300 + Lk)
+    kl = torch.tensor([max(2, Lk // 2), max(3, Lk - 3)], dtype=torch.int32, device=d)
+    x, dy = to_torch(t["x"], dt, d), to_torch(t["dy"], dt, d)
+    a = (kl, None, False, 0.125, p, seed, offset)
+    y, yd = L.lsq_softmax_varlen_fwd(x, *a)
+    dx = L.lsq_softmax_varlen_bwd(dy, y, *a)
+    beyond = (torch.arange(Lk, device=d)[None, None, None, :] >= kl[:, None, None, None]).expand(B, N, Lq, Lk)
+    keep = torch.from_numpy(oracle.dropout_mask(B * N * Lq * Lk, p, seed, offset).reshape(B, N, Lq, Lk) != 0).to(d)
+    inside = ~beyond
+
+    def zero_bits(v, where):
+        return not v[where].view(torch.int16 if dt != "f32" else torch.int32).any()
+
+    xb = x.clone()
+    xb[0, 0, 0, 0], xb[0, 0, 2, 1], xb[1, 0, 3, 1] = float("nan"), float("inf"), float("-inf")   # the last is an ordinary score
+    xb[1, 0, 1] = float("-inf")
+    yb, ydb = L.lsq_softmax_varlen_fwd(xb, *a)
+    for v, w in ((yb, y), (ydb, yd)):
+        assert zero_bits(v, beyond)
+        for b, i in ((0, 1), (0, 3), (0, 4), (1, 0), (1, 2), (1, 4)):
+            assert torch.equal(v[b, 0, i], w[b, 0, i])
+    assert zero_bits(ydb, ~keep)
+    for b, i in ((0, 0), (0, 2), (1, 1)):
+        assert yb[b, 0, i, 0].isnan()
+    assert yb[1, 0, 3].isfinite().all() and yb[1, 0, 3, 1] == 0
+
+    g = dy.clone()
+    hit = []                                             # (batch, row) with an infinity or a NaN at a kept allowed position
+    for b, i, v in ((0, 0, "inf"), (0, 2, "nan"), (1, 1, "-inf"), (1, 4, "nan")):
+        at = (keep & inside)[b, 0, i].nonzero().flatten()
+        at = at[y[b, 0, i][at] > 0]
+        if len(at):
+            g[b, 0, i, at[0]] = float(v)
+            hit.append((b, i))
+    if Lk % 8 and Lk < 2041:
+        g = g.masked_fill(~keep, float("inf"))           # dy where the forward dropped (the other paths multiply it by a factor of 0)
+    dxb = L.lsq_softmax_varlen_bwd(g, y, *a)
+    assert zero_bits(dxb, beyond)
+    for b in range(B):
+        for i in range(Lq):
+            if (b, i) in hit:
+                assert not dxb[b, 0, i].isfinite().all()
+            else:
+                assert torch.equal(dxb[b, 0, i], dx[b, 0, i])

@@ -14,11 +14,12 @@
 // that is padded to its longest sentence; longer rows fall to a three-pass kernel that
 // re-reads the row from cache.
 //
-// The RAG form walks the aligned packs of the flat tensor that a row touches.  What it replaced staged a workgroup's
-// rows in LDS (up to 2048 keys: 2-byte LDS accesses and three barriers bound it) or walked them in 2-byte accesses
-// (beyond).  Forward + backward, fp16 unless stated, before -> now in us: 113 keys padded with dropout 64 x 16 x 113
-// 47 -> 37, 201 keys 73 -> 52, 301 keys 97 -> 61, 751 keys causal 277 -> 97, 2001 keys bf16 415 -> 228, 3001 keys 624 -> 162,
-// 7001 keys 78 -> 25; 17 keys 18 -> 15, 45 keys 30 -> 27, 127 keys 53 -> 50.
+// The RAG form walks the aligned packs of the flat tensor that a row touches.  Many of the shorter such rows are faster through LDS,
+// where every lane is busy whatever the alignment (sm_lds_shape).  With everything through LDS up to 2048 keys (2-byte LDS accesses and
+// three barriers bound it) and 2-byte global accesses beyond, forward + backward took, fp16 unless stated, then -> now in us:
+// 113 keys padded with dropout 64 x 16 x 113 47 -> 37, 201 keys 73 -> 52, 301 keys 97 -> 61, 751 keys causal 277 -> 97,
+// 2001 keys bf16 415 -> 228, 3001 keys 624 -> 162, 7001 keys 78 -> 25.  All in registers lost at 27..63 keys fp16 (29 keys forward
+// of 4 M scores 6.6 -> 8.9) and at 10..90 keys fp32 (29 keys with dropout 9.7 -> 20).
 //
 // Masks restrict the SET the softmax runs over: packs that lie wholly beyond the
 // row's limit (key padding, or the causal diagonal) are not even loaded, and
@@ -125,8 +126,13 @@ struct BlockRows {
 // without the hint up to a wave per row (113 keys, dropout and padding: 21.3 / 20.5 us forward / backward against 28.3 / 21.8),
 // the stores where a store instruction covers 128 bytes of a row or a row takes three (19.3 / 17.6 us; 751 keys causal 43.0 / 53.7
 // against 43.9 / 61.9).  Longer pieces keep it (2001 keys: 101 against 129 us backward; 201: 27.0 against 31.3 us forward).
+// fp32 rows are twice as many lines, and their stores keep the hint with one pack per lane only (201 keys with dropout, 48 M scores:
+// 164 -> 129 us forward; 1001 keys 149 -> 111).
 template <int LPR, int VPL, bool RAG> constexpr bool sm_load_nt() { return !RAG || LPR > kWave; }
-template <int LPR, int VPL, bool RAG> constexpr bool sm_store_nt() { return !RAG || VPL == 1 || LPR >= kWave || (LPR > 8 && VPL == 2); }
+template <typename T, int LPR, int VPL, bool RAG> constexpr bool sm_store_nt()
+{
+    return !RAG || VPL == 1 || LPR > kWave || (sizeof(T) == 2 && (LPR == kWave || (LPR > 8 && VPL == 2)));
+}
 
 // pack `idx` of a row (`base`: the workgroup's first pack); the last pack of the tensor may be cut short
 template <typename T, int LPR, int VPL, bool RAG>
@@ -223,7 +229,7 @@ __device__ __forceinline__ void store_row(T* base, const RowPacks<RAG>& p, int s
     if constexpr (!RAG) {
 #pragma unroll
         for (int k = 0; k < VPL; ++k)
-            if (rv && sub + k * LPR < p.n) store_raw<T, sm_store_nt<LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
+            if (rv && sub + k * LPR < p.n) store_raw<T, sm_store_nt<T, LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
     } else {
         if (k_len <= kPack) {                                         // uniform
 #pragma unroll
@@ -245,7 +251,7 @@ __device__ __forceinline__ void store_row(T* base, const RowPacks<RAG>& p, int s
             const bool head = k == 0 && sub == 0 && p.s > 0;
             const bool last = idx == p.n - 1 && cut > 0;
             if (last) tail = pk[k];
-            if (rv && idx < p.n && !head && !last) store_raw<T, sm_store_nt<LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
+            if (rv && idx < p.n && !head && !last) store_raw<T, sm_store_nt<T, LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
         }
         const int kt = (p.n - 1) / LPR;                               // the last pack is pack kt of lane (n - 1) % LPR
         const bool mine = rv && cut > 0 && sub + kt * LPR == p.n - 1;
@@ -265,7 +271,7 @@ __device__ __forceinline__ void store_row(T* base, const RowPacks<RAG>& p, int s
                 else
                     t.w[i] = cut > i ? t.w[i] : o;
             }
-            if (whole) store_raw<T, sm_store_nt<LPR, VPL, RAG>()>(tail_at, __builtin_bit_cast(RawPack<T>, t));
+            if (whole) store_raw<T, sm_store_nt<T, LPR, VPL, RAG>()>(tail_at, __builtin_bit_cast(RawPack<T>, t));
             if (rv && p.s > 0 && lane == 0) store_part<T, false>(at, pk[0], p.s);
         } else {
             if (rv && p.s > 0 && sub == 0) store_part<T, false>(at, pk[0], p.s);
@@ -505,6 +511,169 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
         if (spoilt) mask_packs<T, LPR, false>(pk, sub, rp[r].s, lim);           // 0 * (0 - dot) is NaN there
         store_row<T, LPR, VPL, RAG>(dx, rp[r], sub, row[r] < blk.rows, row[r] + 1 < blk.rows, g.k_len, pk);
     }
+}
+
+// ---- the same rows through LDS (k_len % 8 != 0, up to 512 keys), where the register form is the slower one (sm_lds_shape below has
+// the lines).  A workgroup's rows are one contiguous element range [e0, e1) of the tensor: the aligned packs that cover
+// it are copied to LDS, LPR lanes per row work on LDS with element accesses, every lane EPL elements that lie LPR apart, and the
+// results leave in packs again.  The first and the last pack may be shared with the neighbouring workgroups: reading
+// them is harmless, writing is done element by element for the part that belongs here.  Element i of LDS = element
+// (e0 & ~7) + i of the tensor.  One Philox call per pack, its keep decisions as bits in LDS.  What bounds it is LDS issue (two accesses
+// per element) and three barriers; every lane is busy whatever the row's alignment, where the register form
+// idles the lanes between the packs that a row touches and the next shape.
+template <int LPR, int EPL> constexpr int lds_rows_elems() { return 256 * EPL + 16; }     // of a staged tensor: 256 / LPR rows of LPR * EPL, and their cut packs
+
+// the keep bits of the packs [p0, p1) (bit j = element j survives)
+template <int NBYTES>
+__device__ __forceinline__ void lds_keep_bits(uint8_t (&keep)[NBYTES], const DropoutParams& d, int64_t p0, int64_t p1)
+{
+    for (int64_t pk = p0 + threadIdx.x; pk < p1; pk += 256) {
+        uint32_t w[4], bits = 0;
+        philox4x32_10(static_cast<uint32_t>(pk), static_cast<uint32_t>(static_cast<uint64_t>(pk) >> 32), d.ctr2, d.ctr3, d.key0, d.key1, w);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            bits |= ((w[j] & 0xFFFFu) >= d.t16 ? 1u : 0u) << (2 * j);
+            bits |= ((w[j] >> 16) >= d.t16 ? 1u : 0u) << (2 * j + 1);
+        }
+        keep[pk - p0] = static_cast<uint8_t>(bits);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void lds_rows_in(T* buf, const T* src, int64_t e0, int64_t e1, int64_t total)
+{
+    const int64_t p0 = e0 >> 3, p1 = (e1 + 7) >> 3;
+    for (int64_t pk = p0 + threadIdx.x; pk < p1; pk += 256) {
+        T* dst = buf + (pk - p0) * kPack;
+        const int64_t base = pk * kPack;
+        if (base + kPack <= total) {
+            *reinterpret_cast<RawPack<T>*>(dst) = load_raw<T, true>(src + base);
+        } else {
+            for (int j = 0; j < kPack; ++j)
+                if (base + j < total) dst[j] = src[base + j];
+        }
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void lds_rows_out(T* dst, const T* buf, int64_t e0, int64_t e1)
+{
+    const int64_t p0 = e0 >> 3, p1 = (e1 + 7) >> 3;
+    for (int64_t pk = p0 + threadIdx.x; pk < p1; pk += 256) {
+        const T* from = buf + (pk - p0) * kPack;
+        const int64_t base = pk * kPack;
+        if (base >= e0 && base + kPack <= e1) {
+            store_raw<T, true>(dst + base, *reinterpret_cast<const RawPack<T>*>(from));
+        } else {
+            for (int j = 0; j < kPack; ++j)
+                if (base + j >= e0 && base + j < e1) dst[base + j] = from[j];
+        }
+    }
+}
+
+template <typename T, int LPR, int EPL, bool DROP>
+__global__ __launch_bounds__(256) void softmax_fwd_lds(T* y, T* __restrict__ yd, const T* x, SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
+{
+    constexpr int RPB = 256 / LPR, NBUF = lds_rows_elems<LPR, EPL>();
+    __shared__ uint8_t keep[DROP ? NBUF / kPack : 1];
+    __shared__ __align__(16) T xs[NBUF];
+    __shared__ __align__(16) T ys[NBUF];
+    __shared__ __align__(16) T yds[DROP ? NBUF : 8];
+    const int sub = threadIdx.x % LPR;
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * RPB;
+    const int64_t row = row0 + threadIdx.x / LPR;
+    const bool rv = row < g.nrows;
+    const int limit = rv ? row_limit(g, len, row) : 0;
+    const int64_t ro = row * g.k_len;
+    const int64_t e0 = row0 * g.k_len, e1 = min(row0 + RPB, g.nrows) * g.k_len;
+    const int lo = static_cast<int>(ro - (e0 & ~static_cast<int64_t>(7)));     // this row's first element in LDS
+    lds_rows_in<T>(xs, x, e0, e1, g.nrows * g.k_len);
+    if constexpr (DROP) lds_keep_bits(keep, d, e0 >> 3, (e1 + 7) >> 3);
+    __syncthreads();
+    float v[EPL];
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) {
+        const int j = sub + m * LPR;
+        v[m] = j < limit ? to_f32<T>(xs[lo + j]) * g.scale : -INFINITY;
+    }
+    float mx = v[0];
+#pragma unroll
+    for (int m = 1; m < EPL; ++m) mx = fmaxf(mx, v[m]);
+    mx = group_max<LPR>(mx);
+    const float mxs = (limit > 0 ? mx : 0.0f) * kLog2e;
+    float z = 0.0f;
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) {
+        v[m] = __builtin_amdgcn_exp2f(fmaf(v[m], kLog2e, -mxs));
+        z += v[m];
+    }
+    z = group_sum<LPR>(z);
+    const float inv = limit > 0 ? 1.0f / z : 0.0f;
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) v[m] *= inv;       // 0 beyond the limit (exp2(-inf)), and on empty rows
+    if (__ballot(z != z) != 0) {                     // a NaN row stays NaN inside the mask only
+#pragma unroll
+        for (int m = 0; m < EPL; ++m) v[m] = sub + m * LPR < limit ? v[m] : 0.0f;
+    }
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) {
+        const int j = sub + m * LPR;
+        if (rv && j < g.k_len) {
+            ys[lo + j] = from_f32<T>(v[m]);
+            if constexpr (DROP) {
+                const bool kept = (keep[(lo + j) >> 3] >> ((lo + j) & 7)) & 1;
+                yds[lo + j] = from_f32<T>(kept ? v[m] * d.scale : 0.0f);
+            }
+        }
+    }
+    __syncthreads();
+    lds_rows_out<T>(y, ys, e0, e1);
+    if constexpr (DROP) lds_rows_out<T>(yd, yds, e0, e1);
+}
+
+template <typename T, int LPR, int EPL, bool DROP>
+__global__ __launch_bounds__(256) void softmax_bwd_lds(T* dx, const T* dy, const T* __restrict__ y, SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
+{
+    constexpr int RPB = 256 / LPR, NBUF = lds_rows_elems<LPR, EPL>();
+    __shared__ uint8_t keep[DROP ? NBUF / kPack : 1];
+    __shared__ __align__(16) T ysh[NBUF];
+    __shared__ __align__(16) T gsh[NBUF];        // dy in, dx out
+    const int sub = threadIdx.x % LPR;
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * RPB;
+    const int64_t row = row0 + threadIdx.x / LPR;
+    const bool rv = row < g.nrows;
+    const int limit = rv ? row_limit(g, len, row) : 0;
+    const int64_t ro = row * g.k_len;
+    const int64_t e0 = row0 * g.k_len, e1 = min(row0 + RPB, g.nrows) * g.k_len;
+    const int lo = static_cast<int>(ro - (e0 & ~static_cast<int64_t>(7)));
+    lds_rows_in<T>(ysh, y, e0, e1, g.nrows * g.k_len);
+    lds_rows_in<T>(gsh, dy, e0, e1, g.nrows * g.k_len);
+    if constexpr (DROP) lds_keep_bits(keep, d, e0 >> 3, (e1 + 7) >> 3);
+    __syncthreads();
+    float yv[EPL], gv[EPL];
+    float dot = 0.0f;
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) {
+        const int j = sub + m * LPR;
+        yv[m] = j < limit ? to_f32<T>(ysh[lo + j]) : 0.0f;
+        gv[m] = j < limit ? to_f32<T>(gsh[lo + j]) : 0.0f;
+        if constexpr (DROP) {
+            if (j < limit) {
+                const bool kept = (keep[(lo + j) >> 3] >> ((lo + j) & 7)) & 1;
+                gv[m] = kept ? gv[m] * d.scale : 0.0f;
+            }
+        }
+        dot = fmaf(gv[m], yv[m], dot);
+    }
+    dot = group_sum<LPR>(dot);
+#pragma unroll
+    for (int m = 0; m < EPL; ++m) {
+        const int j = sub + m * LPR;
+        // every element is read and written by one lane only
+        if (rv && j < g.k_len) gsh[lo + j] = from_f32<T>(j < limit ? g.scale * yv[m] * (gv[m] - dot) : 0.0f);
+    }
+    __syncthreads();
+    lds_rows_out<T>(dx, gsh, e0, e1);
 }
 
 // ---- long rows (257..2048 packs: about 2048 < k_len <= 16384): one workgroup per row, VPL packs per thread in
@@ -816,6 +985,49 @@ inline SmCand sm_ragged_choose(const SmRagged (&table)[N], int np)
     return {0, 0, 0};                       // not reached: the tables end at 256 packs
 }
 
+// ---- which rows that are not whole packs go through LDS instead (lpr = 0: none).  Both forms were measured at every such length up
+// to 135 and some up to 2047 (fp16 and fp32; 1, 6, 20 and 48 M scores; no mask, key padding, causal; with and without dropout); the lines
+// below are where the LDS form was the faster one.  Four things decide:
+//  - how well the packs that a row touches fill the register shape: 5 to 8 packs in 8 lanes (29 keys fp16 forward 6.6 us against 8.9,
+//    with dropout 9.5 against 13.7), and one pack more than a power of two, "brim" (127 keys with dropout 12.1 against 14.6);
+//  - fp32 packs are two accesses and eight registers: short fp32 rows lose from about 12 keys on (29 keys with dropout 9.7 against 20 us);
+//  - tensors beyond the 256 MB last-level cache ("far"), where a line that is written in pieces goes out twice (63 keys fp16 backward
+//    of 48 M scores 52 us against 73); and calls of under 2 M scores ("small"), where the registers' longer code shows;
+//  - a mask: the register form skips what lies beyond it, the LDS form reads it (`lens`: lengths given; `open`: no mask at all).
+struct SmLds { int lpr, epl; };
+inline SmLds sm_lds_shape(int dir, size_t elem, int k, bool drop, bool lens, bool causal, int64_t total)
+{
+    const bool open = !lens && !causal;
+    const int64_t bytes = total * static_cast<int64_t>(elem) * (dir == 0 && !drop ? 2 : 3);
+    const bool far = bytes > (static_cast<int64_t>(256) << 20), small = total < (1 << 21), mid = total >= (1 << 22);
+    const int np = sm_ragged_packs(k);
+    const bool brim8 = np == 9 && k < 64, brim16 = np == 17 && k < 128, brim32 = np == 33 && k < 256, brim64 = np == 65 && k < 512;
+    bool lds = false;
+    if (elem == 2 && dir == 0) {
+        lds = (np >= 5 && np <= 8) || (brim8 && (drop || !lens)) || (np == 3 && k < 16 && (small || (drop && !lens))) ||
+              (drop && ((brim16 && !lens) || (brim32 && (!lens || small)) || (brim64 && open))) ||
+              (drop && k > 64 && ((k < 128 && !lens && far) || (k <= 112 && small) || (k > 128 && k < 190 && small)));
+    } else if (elem == 2) {
+        lds = (far && !drop && ((open && k >= 36 && k < 128) || (!lens && ((k >= 36 && k < 64) || (k > 102 && k < 128))))) ||
+              (far && (brim8 || brim16) && (!drop || open)) || (mid && !drop && !lens && brim8) || (mid && !drop && open && brim32);
+    } else if (dir == 0) {
+        const bool filled = k == 52 || k == 60 || (k == 44 && !lens);    // whole half-packs, 6 to 8 of them: the register shape is full
+        lds = (drop && k <= 58 && (k >= 12 || (k >= 10 && !small)) && !filled) ||
+              (!drop && k <= 58 && (lens ? (k == 12 && mid) || k == 19 || k >= 21 : k >= 12) && !filled) ||
+              (k >= 5 && k <= 7 && (small ? drop || k > 5 : drop && !lens && k > 5)) || (brim8 && (small || (open && !drop))) ||
+              (k > 64 && k < 88 && (open || far || small)) || (far && drop && !causal && k >= 88 && k <= 108) || (far && open && k >= 88 && k <= 96) ||
+              (drop && small && k > 96 && k < 190) || (open && far && k > 128 && k <= 175);
+    } else {
+        lds = (far && k >= (lens ? 20 : drop ? 14 : 10) && k <= (open ? 128 : 88)) || (far && open && k > 128 && k <= 195) ||
+              (k >= 18 && k <= 28 && k != 27 && (!lens || k >= 21) && !(drop && k < 20)) || (!lens && !drop && k == 12) ||
+              (small && !drop && !lens && (k == 7 || (k >= 13 && k <= 17))) ||
+              (open && !drop && ((mid && k > 28 && k < 48) || (k > 64 && k < 88)));
+    }
+    if (!lds) return {0, 0};
+    return k <= 8 ? SmLds{8, 1} : k <= 16 ? SmLds{8, 2} : k <= 32 ? SmLds{8, 4} : k <= 64 ? SmLds{8, 8} : k <= 128 ? SmLds{16, 8} : k <= 256 ? SmLds{32, 8} : SmLds{64, 8};
+}
+#define LSQ_SM_LDS_CASES(X) X(8, 1) X(8, 2) X(8, 4) X(8, 8) X(16, 8) X(32, 8) X(64, 8)
+
 // The paths by row length, with `np` the packs a row touches (base pointers are 16-byte aligned, checked at the entry):
 // up to 256 packs the lanes of a wave, up to 2048 a workgroup per row, beyond that the element-strided kernels; each in a
 // form for rows of whole packs and one for any other length.
@@ -843,6 +1055,20 @@ static lsq_status softmax_fwd_dispatch(void* y, void* yd, const void* x, Softmax
         W(2) W(4) W(8)
 #undef W
         return launch_status();
+    }
+    if (rag) {
+        const SmLds l = sm_lds_shape(0, sizeof(T), g.k_len, drop, key_len.key || key_len.query, g.causal != 0, g.nrows * g.k_len);
+        if (l.lpr != 0) {
+            const dim3 grid(static_cast<unsigned>(ceil_div(g.nrows, 256 / l.lpr)));
+#define X(L, E)                                                                                              \
+            if (l.lpr == L && l.epl == E) {                                                                  \
+                if (drop) hipLaunchKernelGGL((softmax_fwd_lds<T, L, E, true>), grid, dim3(256), 0, s, yp, ydp, xp, key_len, g, d); \
+                else hipLaunchKernelGGL((softmax_fwd_lds<T, L, E, false>), grid, dim3(256), 0, s, yp, ydp, xp, key_len, g, d);    \
+            }
+            LSQ_SM_LDS_CASES(X)
+#undef X
+            return launch_status();
+        }
     }
     const SmCand c = rag ? sm_ragged_choose(kSmRaggedFwd, np) : sm_choose(key_len, g, drop, sizeof(T), 0, forced);
     const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgFwd / c.lpr), c.rpt)));
@@ -885,6 +1111,20 @@ static lsq_status softmax_bwd_dispatch(void* dx, const void* dy, const void* y, 
         W(2) W(4) W(8)
 #undef W
         return launch_status();
+    }
+    if (rag) {
+        const SmLds l = sm_lds_shape(1, sizeof(T), g.k_len, drop, key_len.key || key_len.query, g.causal != 0, g.nrows * g.k_len);
+        if (l.lpr != 0) {
+            const dim3 grid(static_cast<unsigned>(ceil_div(g.nrows, 256 / l.lpr)));
+#define X(L, E)                                                                                              \
+            if (l.lpr == L && l.epl == E) {                                                                  \
+                if (drop) hipLaunchKernelGGL((softmax_bwd_lds<T, L, E, true>), grid, dim3(256), 0, s, dxp, dyp, yp, key_len, g, d); \
+                else hipLaunchKernelGGL((softmax_bwd_lds<T, L, E, false>), grid, dim3(256), 0, s, dxp, dyp, yp, key_len, g, d);    \
+            }
+            LSQ_SM_LDS_CASES(X)
+#undef X
+            return launch_status();
+        }
     }
     const SmCand c = rag ? sm_ragged_choose(kSmRaggedBwd, np) : sm_choose(key_len, g, drop, sizeof(T), 1, forced);
     const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgBwd / c.lpr), c.rpt)));

@@ -153,7 +153,7 @@ def test_softmax_full_size_transformer_big_with_dropout():
 
 # rows that are not whole packs: both sides of every bucket edge (a row of k keys touches up to (k + 14) / 8 packs for odd
 # k, fewer for k = 2 or 4 mod 8), one row, and a tensor whose last pack is cut short
-RAGGED = [2, 9, 10, 25, 26, 57, 58, 121, 122, 124, 185, 187, 249, 251, 377, 379, 505, 507, 761, 763, 1017, 1019, 1529, 1531, 2041, 2043,
+RAGGED = [2, 9, 10, 12, 15, 25, 26, 28, 57, 58, 63, 66, 100, 121, 122, 124, 185, 187, 249, 251, 377, 379, 505, 507, 761, 763, 1017, 1019, 1529, 1531, 2041, 2043,
           4089, 4091, 8185, 8187, 16377, 16379]
 
 
@@ -241,3 +241,35 @@ def test_softmax_nonfinite_values_stay_inside_the_mask(Lk, dt):
                 assert not dxb[b, 0, i].isfinite().all()
             else:
                 assert torch.equal(dxb[b, 0, i], dx[b, 0, i])
+
+
+# the lines between the register and the LDS form of rows that are not whole packs: each LDS shape and direction, at the sizes and masks
+# that send a call there (whole rows of the workgroup's range, a cut last workgroup, tensors beyond 256 MB)
+LDS_ROWS = [("f32", 3, 2, 7, 7, "none", 0.1), ("f32", 5, 2, 13, 12, "none", 0.0), ("f32", 3, 2, 17, 17, "none", 0.0), ("f32", 2, 3, 33, 28, "pad", 0.1),
+            ("f16", 4, 3, 15, 15, "none", 0.1), ("f16", 4, 3, 29, 29, "causal", 0.0), ("f16", 3, 2, 45, 45, "pad", 0.1), ("f16", 140, 8, 63, 63, "causal", 0.0),
+            ("f32", 500, 8, 33, 34, "none", 0.0), ("f32", 2, 3, 20, 70, "none", 0.0), ("f16", 2, 3, 20, 127, "none", 0.1), ("f16", 2, 3, 20, 255, "causal", 0.1),
+            ("f16", 9, 8, 255, 255, "none", 0.0), ("f16", 2, 2, 9, 511, "none", 0.1), ("f16", 2, 2, 9, 150, "pad", 0.1), ("f32", 2, 2, 9, 150, "none", 0.1),
+            ("f32", 4, 6, 7000, 134, "none", 0.0), ("f16", 2, 4, 56000, 100, "none", 0.0), ("f16", 2, 4, 56000, 101, "none", 0.1)]
+
+
+@pytest.mark.parametrize("dt,B,N,Lq,Lk,mask,p", LDS_ROWS)
+def test_softmax_rows_through_lds(dt, B, N, Lq, Lk, mask, p):
+    say(f"[softmax] rows through LDS {dt} {B}x{N}x{Lq}x{Lk} mask={mask} p={p}")
+    d, scale, causal = dev(), 0.125, mask == "causal"
+    x, dy = (device_normal((B, N, Lq, Lk), 1.0, dt, seed=s, device=d) for s in (1, 2))
+    key_len = np.array([max(1, Lk * (b + 1) // B) for b in range(B)], np.int32) if mask == "pad" else None
+    kl = None if key_len is None else torch.from_numpy(key_len).to(d)
+    y, yd = L.lsq_softmax_fwd(x, kl, causal, scale, p, 5, 6)
+    dx = L.lsq_softmax_bwd(dy, y, kl, causal, scale, p, 5, 6)
+    n = x.numel()
+    few = n > 1 << 20                                                # the first and the last sentences' first head only
+    for b in (range(0, B, max(1, B - 1)) if few else [slice(None)]):
+        at = np.s_[b:b + 1, :1] if few else np.s_[:, :]
+        lens = None if key_len is None else key_len[at[0]]
+        e0 = b * N * Lq * Lk if few else 0
+        ry, ryd = oracle.softmax_fwd(from_torch(x[at].contiguous(), dt), lens, causal, scale, dt, p, 5, 6, e0=e0)
+        assert_close_store(y[at], ry, dt, "y", f32_floor=1e-7)
+        if p > 0:
+            assert_close_store(yd[at], ryd, dt, "y_drop", f32_floor=1e-7)
+        rdx = oracle.softmax_bwd(from_torch(dy[at].contiguous(), dt), from_torch(y[at].contiguous(), dt), lens, causal, scale, dt, p, 5, 6, e0=e0)
+        assert_close_store(dx[at], rdx, dt, "dx", f32_floor=1e-7)

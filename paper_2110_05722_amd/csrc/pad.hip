@@ -6,8 +6,7 @@
 // published always work on the padded batch.
 //
 // Pure data movement, bit-exact.  A wave owns 64 consecutive packs of a row (1 KiB)
-// and walks down the padded rows four at a time (four loads in flight before the
-// first store); rows of padding cost one scalar compare.  The packed position of a
+// and walks down the padded rows, one per trip; rows of padding cost one scalar compare.  The packed position of a
 // row comes from the prefix sums written by pad_offsets_kernel, so nothing is
 // copied to the host and the sequence can be captured in a graph.
 #include "host.hpp"
@@ -74,7 +73,7 @@ __device__ __forceinline__ int64_t packed_row(const PadGeom& g, const int32_t* _
 // RESTORE = false: packed <- padded (rows of padding skipped);
 // RESTORE = true:  padded <- packed, zeros on the padding.
 // Rows that are not whole packs, or tensors that are not 16-byte aligned, take the same walk with element-aligned packs
-// (RAG): 128 x 64 x 1001 halves, remove / restore 7.2 / 7.9 us against 17.6 / 18.1 with one element per thread.
+// (RAG) from kPadFlat columns on: 128 x 64 x 1001 halves, remove / restore 7.2 / 7.9 us against 17.6 / 18.1 with one element per thread.
 template <typename T, bool RESTORE, bool RAG>
 __global__ __launch_bounds__(256) void pad_move_kernel(T* __restrict__ dst, const T* __restrict__ src,
                                                        const int32_t* __restrict__ offsets, PadGeom g)
@@ -105,12 +104,38 @@ __global__ __launch_bounds__(256) void pad_move_kernel(T* __restrict__ dst, cons
     }
 }
 
+// The same with one element per thread, for narrow rows: a wave per row would leave most of its lanes without a pack.  128 x 512 rows,
+// remove / restore in us against the wave per row: 9 halves 3.7 / 3.6 against 12.1 / 13.6, 63 8.6 / 9.2 against 12.9 / 14.9, 97 12.0 / 12.8
+// against 13.0 / 15.2; 129 14.6 / 16.2 against 13.2 / 16.0, 257 30.4 / 33.3 against 15.3 / 16.9 (fp32 alike).
+constexpr int kPadFlat = 129;
+template <typename T, bool RESTORE>
+__global__ __launch_bounds__(256) void pad_move_flat(T* __restrict__ dst, const T* __restrict__ src,
+                                                     const int32_t* __restrict__ offsets, PadGeom g)
+{
+    const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (e >= g.rows * g.hidden) return;
+    const int64_t t = e / g.hidden;
+    const int c = static_cast<int>(e - t * g.hidden);
+    const int64_t r = packed_row(g, offsets, t);
+    if (RESTORE) {
+        T zero;
+        __builtin_memset(&zero, 0, sizeof(T));
+        dst[e] = r >= 0 ? src[r * g.hidden + c] : zero;
+    } else if (r >= 0) {
+        dst[r * g.hidden + c] = src[e];
+    }
+}
+
 template <typename T, bool RESTORE>
 static lsq_status pad_dispatch(void* dst, const void* src, const int32_t* offsets, const PadGeom& g, hipStream_t s)
 {
     T* d = static_cast<T*>(dst);
     const T* a = static_cast<const T*>(src);
     const bool whole = g.hidden % kPack == 0 && aligned16(dst) && aligned16(src);
+    if (!whole && g.hidden < kPadFlat) {
+        hipLaunchKernelGGL((pad_move_flat<T, RESTORE>), dim3(static_cast<unsigned>(ceil_div(g.rows * g.hidden, 256))), dim3(256), 0, s, d, a, offsets, g);
+        return launch_status();
+    }
     const int gx = static_cast<int>(ceil_div(ceil_div(g.hidden, kPack), 64));
     int64_t gy = ceil_div(g.rows, kPadWaves * kPadRows);
     const int64_t cap = 16384 / gx > 1 ? 16384 / gx : 1;      // about 64 workgroups per compute unit

@@ -138,10 +138,10 @@ def test_softmax_with_query_lengths(B, N, Lq, Lk, causal, p, dt):
 
 
 @pytest.mark.parametrize("dt", ["f16", "f32"])
-@pytest.mark.parametrize("H,shift", [(1, 0), (7, 0), (9, 0), (511, 0), (513, 0), (1001, 0), (64, 3), (1001, 1)])
+@pytest.mark.parametrize("H,shift", [(1, 0), (7, 0), (9, 0), (127, 0), (129, 0), (511, 0), (513, 0), (1001, 0), (64, 3), (128, 1), (136, 3), (1001, 1)])
 def test_rows_of_any_length_and_alignment(H, shift, dt):
-    """Rows that are not whole packs, and tensors that start `shift` elements into an allocation: bit-exact moves (NaN
-    payloads included), nothing outside the tensors written."""
+    """Rows that are not whole packs, and tensors that start `shift` elements into an allocation, on both sides of 129 columns (one
+    element per thread below, a wave per row from there): bit-exact moves (NaN payloads included), nothing outside the tensors written."""
     say(f"[pad] H={H} shift={shift} dt={dt}")
     d, B, Lmax = dev(), 9, 21
     r = np.random.default_rng(H + shift)

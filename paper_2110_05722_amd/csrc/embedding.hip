@@ -58,6 +58,29 @@ __global__ __launch_bounds__(256) void emb_fwd_cols(T* __restrict__ out, const i
     }
 }
 
+// Rows that are not whole packs, one element per thread: faster than a wave per row while the rows are narrow (few lanes have a pack) or
+// the call small (two groups are drawn per pack).  32 x 1024 tokens, dropout, fp16, in us: 9 columns 3.7 against 17.9, 100 13.4 against 17.9,
+// 161 20.1 against 18.6; 8 x 64 tokens, fp32: 257 3.2 against 3.6, 1001 4.4 against 3.9.
+constexpr int kEmbFlatColumns = 145;
+constexpr int64_t kEmbFlatElements = 400000;
+template <typename T>
+__global__ __launch_bounds__(256) void emb_fwd_flat(T* __restrict__ out, const int32_t* __restrict__ tokens,
+                                                    const T* __restrict__ emb, const T* __restrict__ pos, int64_t rows,
+                                                    int len, int hidden, int vocab, int pad_idx, float scale, DropoutParams d)
+{
+    const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (e >= rows * hidden) return;
+    const int64_t t = e / hidden;
+    const int i = static_cast<int>(e - t * hidden);
+    const int w = tokens[t];
+    float v = 0.0f;
+    if (!emb_is_pad(w, vocab, pad_idx)) {
+        v = fmaf(scale, to_f32<T>(emb[static_cast<int64_t>(w) * hidden + i]), to_f32<T>(pos[(t % len) * hidden + i]));
+        if (d.on) v *= dropout_factor1(d, static_cast<uint64_t>(e));
+    }
+    out[e] = from_f32<T>(v);
+}
+
 // sort key of a token: its id, with padding last; kNoKey stands for "beyond the data"
 constexpr unsigned kPadKey = 0x7FFFFFFFu;
 constexpr unsigned kNoKey = 0xFFFFFFFFu;
@@ -673,6 +696,13 @@ static lsq_status emb_fwd_dispatch(void* out, const int32_t* tokens, const void*
     T* o = static_cast<T*>(out);
     const T* e = static_cast<const T*>(emb);
     const T* p = static_cast<const T*>(pos);
+    if constexpr (RAG) {
+        if (hidden < kEmbFlatColumns || rows * hidden < kEmbFlatElements) {
+            hipLaunchKernelGGL((emb_fwd_flat<T>), dim3(static_cast<unsigned>(ceil_div(rows * hidden, 256))), dim3(256), 0, s,
+                               o, tokens, e, p, rows, len, hidden, vocab, pad_idx, scale, d);
+            return launch_status();
+        }
+    }
     const RowPackIO<T, RAG> io(hidden);
     // one row per wave up to 65536 rows: 5.9 / 8.0 us at 4096 x 1024 / 8192 x 1280 against 6.6 / 8.15 with four
     int64_t rb = ceil_div(rows, kEmbWaves);

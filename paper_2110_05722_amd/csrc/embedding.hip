@@ -95,22 +95,26 @@ __device__ __forceinline__ unsigned emb_key(int w, int vocab, int pad_idx)
     return emb_is_pad(w, vocab, pad_idx) ? kPadKey : static_cast<unsigned>(w);
 }
 
-// The order of up to kEmbSortMax tokens, without a launch of its own: 64 workgroups, each for the ids of one residue
-// class.  What the accumulation needs is that equal ids stand together in ascending position; which id comes before
-// which is free, so a part can be any set of ids whose share does not follow from their frequency (frequent words have
-// small ids).  A workgroup looks at every token once, keeps the positions of its ids, in order, and counts those of the
+// The order of up to kEmbSortMax tokens, without a launch of its own: 64 workgroups, each for the ids of one class.
+// What the accumulation needs is that equal ids stand together in ascending position; which id comes before
+// which is free, so a class can be any set of ids whose share does not follow from their frequency (frequent words have
+// small ids) or their spacing: the low bits of the id with the next two groups of bits folded in (sort_mix).  A workgroup looks at every token
+// once, keeps the positions of its ids, in order, and counts those of the
 // parts before it, which is where its own begin; then it sorts its positions by the rest of the id: a stable least-
 // significant-digit radix sort, at most 6 bits per pass.  The lanes of a round of 64 entries that hold the same digit find
 // each other with ballots, the lowest takes as many places as they are from the wave's counter of that digit (waves
 // apart: nothing depends on timing).  An entry is 32 bits, the position and what the part leaves of the id, in LDS, or in
-// the workspace where a part is larger than kSortLds (one id everywhere).  Padding is not
+// the workspace where a part is larger than kSortLds.  Padding is not
 // sorted: what is left of `order` behind the live tokens is filled with it.
+// A part larger than kSortHeavy has a frequent id in it nearly always.  The id that most of its lanes meet first is taken out of
+// the sort: its positions need none, they go to the end of the part's range in the order they are met.
+// Whole backward, 8192 tokens x 1024 in us, one id everywhere / half of the tokens / 12 % of them / ids that are multiples of 64 / words:
+// 53 / 40 / 30 / 26 / 28; by the low bits alone and all of it sorted 106 / 63 / 32 / 81 / 28; the rank count 54 / 40 / 29 / 29 / 29.
 // What bounds it is the latency of its steps, 13 us alone at 8192 tokens, most of it behind the dP stream that shares the
 // launch (together 15, bf16 hidden 1280; the quadratic rank count over 1024 workgroups with dP 15.7 and a scatter
 // launch of 4 before it).  One 1024-thread workgroup for all of 8192 tokens took 20 us; with the ids read again from the
-// tokens in every round instead of carried, the part of the most frequent word took 19.  The whole backward in us, before -> now:
-// 8 x 1024 tokens, hidden 1280 38.8 -> 34; 60 x 77, 1024 29 -> 20; 8 x 64, 512 20 -> 16; 300 x 50, 640 77 -> 33.
-constexpr int kSortDigits = 64, kSortLds = 2048;
+// tokens in every round instead of carried, the part of the most frequent word took 19.
+constexpr int kSortDigits = 64, kSortLds = 2048, kSortHeavy = 512;
 // How an id is split: `part_bits` low bits choose the part (64 parts; 128 where that makes a 31-bit id of a small call fit), the
 // rest shares a 32-bit entry with the `pos_bits` bits of a position.
 struct EmbSortPlan { int part_bits, pos_bits, passes, pass_bits; bool fits; };
@@ -127,6 +131,12 @@ inline EmbSortPlan emb_sort_plan(int64_t rows, int bits)
     return p;
 }
 constexpr int kSortLdsBytes = 2 * kSortLds * 4 + 4 * kSortDigits * 4 + 16 * 4;
+
+// An id with its low `part_bits` bits replaced by its class.  Its own inverse: the bits above are the id's.
+__device__ __forceinline__ unsigned sort_mix(unsigned id, int part_bits)
+{
+    return id ^ (((id >> part_bits) ^ (id >> (2 * part_bits))) & ((1u << part_bits) - 1u));
+}
 
 // src -> (passes) -> order; src and tmp hold n entries each
 __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t* tmp, int n, int part, int2* __restrict__ order,
@@ -189,7 +199,7 @@ __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t*
             to = __shfl(to, leader) + __popcll(same & ((1ull << lane) - 1ull));
             if (valid) {
                 if (last) order[to] = make_int2(static_cast<int>(e & ((1u << pl.pos_bits) - 1u)),
-                                                static_cast<int>((e >> pl.pos_bits) << pl.part_bits) | part);
+                                                static_cast<int>(sort_mix((e >> pl.pos_bits) << pl.part_bits | static_cast<unsigned>(part), pl.part_bits)));
                 else tmp[to] = e;
             }
         });
@@ -210,7 +220,8 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rounds = (rows + 255) / 256;
     const int first = wave * rounds * kWave + lane;              // token of round r: first + 64 r
-    constexpr int U = 32;                                        // rounds whose loads are in flight together (8192 tokens)
+    constexpr int U = 32;                                        // rounds whose loads are in flight together (8192 tokens, half of the most)
+    static_assert(2 * U * 256 >= kEmbSortMax, "two halves");
     unsigned key[U];
     auto load = [&](int r0) {
         int w[U];
@@ -227,15 +238,16 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool there = r0 + u < rounds && first + (r0 + u) * kWave < rows;
-            key[u] = there ? emb_key(w[u], vocab, pad_idx) : kPadKey;
+            key[u] = there && !emb_is_pad(w[u], vocab, pad_idx) ? sort_mix(static_cast<unsigned>(w[u]), pl.part_bits) : kNoKey;
         }
     };
+    auto member = [&](unsigned k) { return k != kNoKey && static_cast<int>(k & (parts - 1)) == part; };
     int mine = 0, below = 0, live = 0;                           // of the lane, then of the wave
     for (int r0 = 0; r0 < rounds; r0 += U) {
         load(r0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int cls = key[u] != kPadKey ? static_cast<int>(key[u] & (parts - 1)) : parts;
+            const int cls = key[u] != kNoKey ? static_cast<int>(key[u] & (parts - 1)) : parts;
             mine += cls == part ? 1 : 0;
             below += cls < part ? 1 : 0;
             live += cls < parts ? 1 : 0;
@@ -249,7 +261,7 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     }
     if (lane == 0) { sums[wave] = mine; sums[4 + wave] = below; sums[8 + wave] = live; }
     __syncthreads();
-    int to = 0, n = 0, base = 0, all = 0;
+    int to = 0, n = 0, base = 0, all = 0;                        // the wave's first place in the part; the part's size and begin; live tokens
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const int c = sums[w];
@@ -258,20 +270,71 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
         base += sums[4 + w];
         all += sums[8 + w];
     }
+    unsigned frequent = kNoKey - 1u;                             // no id
+    int tf = 0;                                                  // its first place for the wave, behind the n others
+    const bool heavy = n > kSortHeavy;                           // uniform over the workgroup
+    if (heavy) {
+        unsigned met = kNoKey;                                   // the first id of the part that the lane holds
+#pragma unroll
+        for (int u = U - 1; u >= 0; --u) met = member(key[u]) ? key[u] : met;
+        int votes = 0;
+#pragma unroll
+        for (int l = 0; l < kWave; ++l) votes += met == static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(met), l)) ? 1 : 0;
+        if (met == kNoKey) votes = 0;
+        int most = votes;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
+        const unsigned elect = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(met), __builtin_ctzll(__ballot(votes == most))));
+        __syncthreads();                                         // everyone has read the sums
+        if (lane == 0) { sums[wave] = most; sums[4 + wave] = static_cast<int>(elect); }
+        __syncthreads();
+        most = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (sums[w] > most) { most = sums[w]; frequent = static_cast<unsigned>(sums[4 + w]); }
+        int c = 0, nf = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c += key[u] == frequent ? 1 : 0;
+        if (rounds > U) {                                        // the second half was here: the first one is what the next loop begins with
+            load(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) c += key[u] == frequent ? 1 : 0;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+        if (lane == 0) sums[8 + wave] = c;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            tf += w < wave ? sums[8 + w] : 0;
+            nf += sums[8 + w];
+        }
+        to -= tf;
+        n -= nf;
+    }
     uint32_t* big0 = spill + base;                               // parts are disjoint: base + n <= live tokens <= rows
     uint32_t* big1 = spill + rows + base;
     const bool fits = n <= kSortLds;                             // uniform over the workgroup
     for (int r0 = 0; r0 < rounds; r0 += U) {
-        if (rounds > U) load(r0);                                // up to U rounds they are still here
+        if (rounds > U && (r0 > 0 || !heavy)) load(r0);          // up to U rounds they are still here
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (r0 + u >= rounds) break;                         // uniform
-            const bool in = key[u] != kPadKey && static_cast<int>(key[u] & (parts - 1)) == part;
+            bool in = member(key[u]);
+            const uint64_t before = (1ull << lane) - 1ull;
+            const int pos = first + (r0 + u) * kWave;
+            if (heavy) {
+                const bool out = key[u] == frequent;
+                const uint64_t m = __ballot(out);
+                if (out) order[base + n + tf + __popcll(m & before)] = make_int2(pos, static_cast<int>(sort_mix(frequent, pl.part_bits)));
+                tf += __popcll(m);
+                in = in && !out;
+            }
             const uint64_t m = __ballot(in);
             if (m != 0) {
                 if (in) {
-                    const int at = to + __popcll(m & ((1ull << lane) - 1ull));
-                    const uint32_t e = (key[u] >> pl.part_bits) << pl.pos_bits | static_cast<uint32_t>(first + (r0 + u) * kWave);
+                    const int at = to + __popcll(m & before);
+                    const uint32_t e = (key[u] >> pl.part_bits) << pl.pos_bits | static_cast<uint32_t>(pos);
                     if (fits) in_lds[at] = e;
                     else big0[at] = e;
                 }

@@ -19,7 +19,7 @@ CASES = [(8, 64, 8000, 512, 0.1), (128, 32, 32768, 512, 0.1), (16, 128, 4096, 10
          (36, 512, 100, 16, 0.1), (9, 2048, 70001, 16, 0.1),      # one pass (ids below 256) and three (above 65535)
          (550, 2000, 3000, 8, 0.1),     # 1.1 M tokens: the radix passes with the stand-alone offset scan
          (1, 70000, 500, 8, 0.1),       # one sentence longer than 65535 positions
-         (4, 4096, 50257, 8, 0.0)]      # exactly 16384 tokens: the largest one-workgroup sort
+         (4, 4096, 50257, 8, 0.0)]      # exactly 16384 tokens: the most that the in-LDS sort takes
 
 
 def _tokens(B, Ln, V, rng):
@@ -100,9 +100,10 @@ def test_embedding_bwd_degenerate_batches(kind):
         assert np.array_equal(from_torch(demb, dt), d0) and np.array_equal(from_torch(dpos, dt), p0)
 
 
-# the one-workgroup sort: rounds of 1024 tokens (edges of one, of eight, of the largest), ids of one, two and three digits, the
-# hand-over to the sort over many workgroups; and the position gradient on both sides of 16 sentences
-@pytest.mark.parametrize("B,Ln,V", [(1, 63, 255), (1, 64, 256), (3, 341, 65535), (1, 1024, 65536), (25, 41, 300), (16, 512, 50257),
+# the in-LDS sort (64 workgroups, rounds of 256 tokens): one token less than a round and so on up to its largest, on both sides of the
+# 8192 tokens that a workgroup holds at once, ids of one, two and three digits, the hand-over to the sort over many workgroups; and
+# the position gradient on both sides of 16 sentences
+@pytest.mark.parametrize("B,Ln,V", [(1, 63, 255), (1, 64, 256), (1, 255, 300), (1, 257, 300), (3, 341, 65535), (1, 8191, 50257), (1, 8193, 50257), (1, 1024, 65536), (25, 41, 300), (16, 512, 50257),
                                     (17, 482, 70000), (17, 71, 9), (64, 255, 40), (4, 1500, 3), (1, 16384, 50257), (5, 3277, 50257)])
 def test_embedding_bwd_token_order(B, Ln, V):
     say(f"[embedding] token order B={B} L={Ln} V={V}")
@@ -165,3 +166,53 @@ def test_embedding_bwd_ids_beyond_24_bits(Ln):
     inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.1, 3, 7, dt)
     assert_close_store(demb, inc_e, dt, "demb")
     assert_close_store(dpos, inc_p, dt, "dpos")
+
+
+def _class_of(ids, part_bits=6):
+    """The class by which the in-LDS sort splits ids among its workgroups."""
+    return (ids ^ (ids >> part_bits) ^ (ids >> 2 * part_bits)) & ((1 << part_bits) - 1)
+
+
+# one class of ids at its edges (512 entries: from the next on the id that most lanes meet is taken out; 2048 entries left to sort, as
+# 2600 - 552 is: from the next on in the workspace), with a frequent id, none, or nothing else; one and two halves of tokens
+@pytest.mark.parametrize("tokens", [4096, 12000])
+@pytest.mark.parametrize("n,frequent", [(512, 0), (513, 0), (513, 400), (2048, 0), (2049, 0), (2600, 552), (2600, 551), (3000, 2999), (3000, 3000)])
+def test_embedding_bwd_large_classes(n, frequent, tokens):
+    say(f"[embedding] a class of {n} tokens, {frequent} of one id, of {tokens}")
+    d, dt, H, V = dev(), "f16", 8, 40000
+    rng = np.random.default_rng(n + frequent + tokens)
+    every = np.arange(2, V)
+    own, others = every[_class_of(every) == 5], every[_class_of(every) != 5]
+    tok = np.concatenate([np.full(frequent, own[17]), rng.choice(own[18:], n - frequent), rng.choice(others[:3000], tokens - n)]).astype(np.int32)
+    tok[-40:] = PAD
+    tok = rng.permutation(tok).reshape(1, tokens)
+    dys = encode(rng.standard_normal((tokens, H), dtype=np.float32) * 0.02, dt)
+    ref = None
+    for _ in range(2):                                   # bit-reproducible
+        demb, dpos = torch.zeros((V, H), dtype=torch.float16, device=d), torch.zeros((tokens, H), dtype=torch.float16, device=d)
+        L.lsq_embedding_bwd(demb, dpos, to_torch(dys, dt, d), torch.from_numpy(tok).to(d), PAD, 2.0, 0.1, 3, 7)
+        inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.1, 3, 7, dt)
+        assert_close_store(demb, inc_e, dt, "demb")
+        assert_close_store(dpos, inc_p, dt, "dpos")
+        assert ref is None or torch.equal(ref, demb)
+        ref = demb
+
+
+@pytest.mark.parametrize("tokens", [129, 256])
+def test_embedding_bwd_ids_of_31_bits(tokens):
+    """Ids of 31 bits beside positions of 8: the sort splits them among 128 workgroups instead of 64."""
+    say(f"[embedding] 31-bit ids, {tokens} tokens")
+    d, dt, V = dev(), "f16", 1 << 30
+    rng = np.random.default_rng(tokens)
+    ids = np.array([2, 3, 2 + (1 << 29), V - 1, V - 2, 77 + (1 << 24), 77, 64, 128], np.int32)
+    tok = rng.choice(ids, size=(1, tokens)).astype(np.int32)
+    dys = encode(rng.standard_normal((tokens, 1), dtype=np.float32) * 0.02, dt)
+    demb, dpos = torch.zeros((V, 1), dtype=torch.float16, device=d), torch.zeros((tokens, 1), dtype=torch.float16, device=d)
+    L.lsq_embedding_bwd(demb, dpos, to_torch(dys, dt, d), torch.from_numpy(tok).to(d), PAD, 2.0, 0.0, 3, 7)
+    # the oracle on the same tokens with the ids numbered in their order
+    small = np.searchsorted(np.sort(ids), tok).astype(np.int32) + PAD + 1
+    inc_e, inc_p = oracle.embedding_bwd(dys, small, len(ids) + PAD + 1, PAD, 2.0, 0.0, 3, 7, dt)
+    got = demb[torch.from_numpy(np.sort(ids).astype(np.int64)).to(d)]
+    assert_close_store(got, np.asarray(inc_e).reshape(-1, 1)[PAD + 1:], dt, "demb")
+    assert_close_store(dpos, inc_p, dt, "dpos")
+    assert int((demb != 0).sum()) <= len(ids)

@@ -144,12 +144,17 @@ def _dt(t) -> int:
         raise LsqError(f"unsupported dtype {t.dtype}") from None
 
 
+# torch's raw stream and device queries are not public: where a build has them under other names, the public call serves
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
     """The current device's current stream, as an int.  torch.cuda.current_stream() builds a Stream object for it, 2.75 us of
     a 13 us call; the raw query takes 0.19.  It wants an initialised runtime, which the public call sees to."""
-    if not torch.cuda.is_initialized():
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_raw_device())
 
 
 def _need(name: str, t, numel: int, dtype=None):

@@ -201,3 +201,27 @@ def test_binding_refuses_operands_shorter_than_the_call_needs(lib):
         L.lsq_adam_step(p, p.clone(), p[:8].clone(), p.half(), None, lr=1e-3, beta1=0.9, beta2=0.98, eps=1e-8, step=1)
     with pytest.raises(L.LsqError, match="mean is torch.float16"):
         L.lsq_layernorm_fwd(x, x[0], x[0], mean=torch.zeros(4, dtype=torch.float16))
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device"])
+def test_the_public_stream_query_serves_where_torch_lacks_the_raw_one(monkeypatch, missing):
+    import torch
+
+    monkeypatch.setattr(binding, missing, None)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: type("S", (), {"cuda_stream": 1234})())
+    assert binding._stream() == 1234
+
+
+@pytest.mark.gpu
+def test_the_raw_stream_query_is_the_current_stream(monkeypatch):
+    import torch
+
+    torch.cuda.init()
+    side = torch.cuda.Stream()
+    for stream in (torch.cuda.default_stream(), side):
+        with torch.cuda.stream(stream):
+            assert binding._stream() == stream.cuda_stream
+            with monkeypatch.context() as m:
+                m.setattr(binding, "_raw_stream", None)
+                assert binding._stream() == stream.cuda_stream

@@ -220,16 +220,21 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rounds = (rows + 255) / 256;
     const int first = wave * rounds * kWave + lane;              // token of round r: first + 64 r
+    const int end = min(rows, (wave + 1) * rounds * kWave);      // of the wave's tokens
     constexpr int U = 32;                                        // rounds whose loads are in flight together (8192 tokens, half of the most)
     static_assert(2 * U * 256 >= kEmbSortMax, "two halves");
     unsigned key[U];
     auto load = [&](int r0) {
         int w[U];
+        const int left = end - first - r0 * kWave;
 #pragma unroll
         for (int g = 0; g < U; g += 8) {
             if (r0 + g < rounds) {                               // uniform; loads only, all in flight
 #pragma unroll
-                for (int u = g; u < g + 8; ++u) w[u] = tokens[min(first + (r0 + u) * kWave, rows - 1)];
+                for (int u = g; u < g + 8; ++u) {                // a scalar base and a 32-bit offset
+                    const uint32_t at = 4u * static_cast<uint32_t>(min(first + (r0 + u) * kWave, rows - 1));
+                    w[u] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(tokens) + at);
+                }
             } else {
 #pragma unroll
                 for (int u = g; u < g + 8; ++u) w[u] = pad_idx;
@@ -237,20 +242,22 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool there = r0 + u < rounds && first + (r0 + u) * kWave < rows;
-            key[u] = there && !emb_is_pad(w[u], vocab, pad_idx) ? sort_mix(static_cast<unsigned>(w[u]), pl.part_bits) : kNoKey;
+            const bool there = (u * kWave < left) & (w[u] != pad_idx) & (static_cast<unsigned>(w[u]) < static_cast<unsigned>(vocab));
+            const unsigned mixed = sort_mix(static_cast<unsigned>(w[u]), pl.part_bits);      // (selected, not branched over)
+            key[u] = there ? mixed : kNoKey;
         }
     };
-    auto member = [&](unsigned k) { return k != kNoKey && static_cast<int>(k & (parts - 1)) == part; };
+    const unsigned cls = 0x80000000u | static_cast<unsigned>(parts - 1);        // what of a key says whether and where it belongs
+    auto member = [&](unsigned k) { return ((k ^ static_cast<unsigned>(part)) & cls) == 0; };
     int mine = 0, below = 0, live = 0;                           // of the lane, then of the wave
     for (int r0 = 0; r0 < rounds; r0 += U) {
         load(r0);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int cls = key[u] != kNoKey ? static_cast<int>(key[u] & (parts - 1)) : parts;
-            mine += cls == part ? 1 : 0;
-            below += cls < part ? 1 : 0;
-            live += cls < parts ? 1 : 0;
+            const unsigned c = key[u] & cls;
+            mine += c == static_cast<unsigned>(part) ? 1 : 0;
+            below += c < static_cast<unsigned>(part) ? 1 : 0;
+            live += static_cast<int>(key[u]) >= 0 ? 1 : 0;
         }
     }
 #pragma unroll
@@ -278,7 +285,7 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
 #pragma unroll
         for (int u = U - 1; u >= 0; --u) met = member(key[u]) ? key[u] : met;
         int votes = 0;
-#pragma unroll
+#pragma unroll 4
         for (int l = 0; l < kWave; ++l) votes += met == static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(met), l)) ? 1 : 0;
         if (met == kNoKey) votes = 0;
         int most = votes;
@@ -293,10 +300,8 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
         for (int w = 0; w < 4; ++w)
             if (sums[w] > most) { most = sums[w]; frequent = static_cast<unsigned>(sums[4 + w]); }
         int c = 0, nf = 0;
-#pragma unroll
-        for (int u = 0; u < U; ++u) c += key[u] == frequent ? 1 : 0;
-        if (rounds > U) {                                        // the second half was here: the first one is what the next loop begins with
-            load(0);
+        for (int r0 = rounds > U ? U : 0; r0 >= 0; r0 -= U) {    // the half that is here; the next loop begins with the first one
+            if (r0 + U < rounds) load(r0);
 #pragma unroll
             for (int u = 0; u < U; ++u) c += key[u] == frequent ? 1 : 0;
         }
@@ -315,30 +320,38 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     uint32_t* big0 = spill + base;                               // parts are disjoint: base + n <= live tokens <= rows
     uint32_t* big1 = spill + rows + base;
     const bool fits = n <= kSortLds;                             // uniform over the workgroup
+    const uint64_t before = (1ull << lane) - 1ull;
+    auto keep = [&](unsigned k, bool in, int pos) {
+        const uint64_t m = __ballot(in);
+        if (m != 0) {
+            if (in) {
+                const int at = to + __popcll(m & before);
+                const uint32_t e = (k >> pl.part_bits) << pl.pos_bits | static_cast<uint32_t>(pos);
+                if (fits) in_lds[at] = e;
+                else big0[at] = e;
+            }
+            to += __popcll(m);
+        }
+    };
     for (int r0 = 0; r0 < rounds; r0 += U) {
         if (rounds > U && (r0 > 0 || !heavy)) load(r0);          // up to U rounds they are still here
+        if (!heavy) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (r0 + u >= rounds) break;                         // uniform
-            bool in = member(key[u]);
-            const uint64_t before = (1ull << lane) - 1ull;
-            const int pos = first + (r0 + u) * kWave;
-            if (heavy) {
+            for (int u = 0; u < U; ++u) {
+                if (u % 8 == 0 && r0 + u >= rounds) break;       // uniform
+                keep(key[u], member(key[u]), first + (r0 + u) * kWave);
+            }
+        } else {
+            const int2 entry = make_int2(0, static_cast<int>(sort_mix(frequent, pl.part_bits)));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u % 8 == 0 && r0 + u >= rounds) break;
+                const int pos = first + (r0 + u) * kWave;
                 const bool out = key[u] == frequent;
                 const uint64_t m = __ballot(out);
-                if (out) order[base + n + tf + __popcll(m & before)] = make_int2(pos, static_cast<int>(sort_mix(frequent, pl.part_bits)));
+                if (out) order[base + n + tf + __popcll(m & before)] = make_int2(pos, entry.y);
                 tf += __popcll(m);
-                in = in && !out;
-            }
-            const uint64_t m = __ballot(in);
-            if (m != 0) {
-                if (in) {
-                    const int at = to + __popcll(m & before);
-                    const uint32_t e = (key[u] >> pl.part_bits) << pl.pos_bits | static_cast<uint32_t>(pos);
-                    if (fits) in_lds[at] = e;
-                    else big0[at] = e;
-                }
-                to += __popcll(m);
+                keep(key[u], member(key[u]) & !out, pos);
             }
         }
     }
@@ -672,10 +685,10 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
 {
     constexpr int U = 4, G = 256 / W;
     const int lane = threadIdx.x % W, grp = threadIdx.x / W;
-    const bool active = cb * W + lane < io.ppr;
-    const int cp = min(cb * W + lane, io.ppr - 1);
+    const int cp = cb * W + lane;
+    const bool active = cp < io.ppr;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (active || lane < kBusyLanes) {
+    if (active) {
         for (int b0 = grp; b0 < batch; b0 += G * U) {
             RawPack<T> raw[U];
             bool ok[U];
@@ -729,6 +742,7 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
 // The sort is a few workgroups' work, the position gradient a stream over dy; neither needs the other.  One launch holds
 // both, the sort first (workgroups 0 .. sorts - 1), so that they overlap instead of running back to back.  Without dP (units = 0) only
 // the sort runs, without the sort (many tokens) only dP.
+// The sort's registers are the stream's too: with 108 of them (four waves per SIMD, not six) 8192 x 1280 took 1.2 us longer.
 template <typename T, bool DROP, int W, bool RAG>
 __global__ __launch_bounds__(256) void emb_sort_dpos(int2* __restrict__ order, uint32_t* __restrict__ spill,
                                                      const int32_t* __restrict__ tokens, int64_t rows, int sorts, EmbSortPlan pl,

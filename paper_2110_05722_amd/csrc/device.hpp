@@ -504,9 +504,8 @@ struct RowPackIO {
     }
     __device__ __forceinline__ void factors(const DropoutParams& d, int64_t row, int cp, float (&k)[8]) const
     {
-        const uint64_t e = static_cast<uint64_t>(element(row, cp));
-        if constexpr (RAG) dropout_factors8_any(d, e, k);
-        else dropout_factors8(d, e >> 3, k);
+        if constexpr (RAG) dropout_factors8_any(d, static_cast<uint64_t>(element(row, cp)), k);
+        else dropout_factors8(d, static_cast<uint64_t>(row * ppr + cp), k);
     }
 };
 

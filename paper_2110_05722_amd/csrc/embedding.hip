@@ -23,7 +23,7 @@ namespace lsq {
 constexpr bool kNT = true;
 constexpr int kEmbWaves = 4;
 
-// Lanes that stay at work in a wave whatever its row has for them (beyond the row they repeat its last pack and store nothing).  Dependent
+// Lanes of the accumulation that stay at work in a wave whatever its row has for them (beyond the row they repeat its last pack and store nothing).  Dependent
 // vector instructions run 2.3-3 times slower with up to 16 lanes active (quarter-rate ones, Philox's 64-bit products, with up
 // to 8): 2048 tokens, fp16, dropout, backward in us at 64 columns (8 lanes) 18.9 -> 15.6, 63 26.3 -> 19.0; and likewise a row's last block of 64 packs.
 constexpr int kBusyLanes = 32;
@@ -37,15 +37,15 @@ __global__ __launch_bounds__(256) void emb_fwd_cols(T* __restrict__ out, const i
                                                     DropoutParams d, FastDiv by_len)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const bool mine = blockIdx.x * 64 + lane < static_cast<unsigned>(io.ppr);
-    if (!mine && lane >= kBusyLanes) return;
-    const int cp = min(static_cast<int>(blockIdx.x) * 64 + lane, io.ppr - 1);
+    const int cp = blockIdx.x * 64 + lane;
+    if (cp >= io.ppr) return;
     const int64_t stride = static_cast<int64_t>(gridDim.y) * kEmbWaves;
     for (int64_t t = static_cast<int64_t>(blockIdx.y) * kEmbWaves + wave; t < rows; t += stride) {
         const int w = tokens[t];
+        const int t31 = static_cast<int>(t);                         // tokens of a call are below 2^31 (checked at the entry): one 32 x 32 product
         float o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (!emb_is_pad(w, vocab, pad_idx)) {
-            const uint32_t t32 = static_cast<uint32_t>(t);           // tokens of a call are below 2^31 (checked at the entry)
+            const uint32_t t32 = static_cast<uint32_t>(t31);
             const int l = static_cast<int>(t32 - fastdiv(t32, by_len) * static_cast<uint32_t>(len));
             float e[8], pp[8];
             const RawPack<T> re = io.template ahead<false>(emb, w, cp), rp = io.template ahead<false>(pos, l, cp);
@@ -55,12 +55,12 @@ __global__ __launch_bounds__(256) void emb_fwd_cols(T* __restrict__ out, const i
             for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, e[j], pp[j]);
             if constexpr (DROP) {
                 float k[8];
-                io.factors(d, t, cp, k);
+                io.factors(d, t31, cp, k);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] *= k[j];
             }
         }
-        if (mine) io.template store<kNT>(out, t, cp, o);
+        io.template store<kNT>(out, t31, cp, o);
     }
 }
 

@@ -184,8 +184,8 @@ constexpr bool ln_bwd_slots_parallel()
 
 // partial: [gridDim.x][2][hidden] fp32 (dgamma row, then dbeta row).
 // THREADS lanes per workgroup: THREADS/LPR rows in flight per workgroup (plus their
-// prefetched successors).  With one wave per SIMD the kernel is bound by memory latency,
-// not bandwidth: the bytes in flight per compute unit are what THREADS buys.
+// prefetched successors).  With one wave per SIMD the kernel is bound by the chain of a row that nothing
+// overlaps (8192 x 1280: vector ALU busy 24-32 %, memory units stalled under 0.5 %, occupancy 7-8 %).
 // FUSE: the LayerNorm gradient (plus dres) is the gradient of h = residual + Dropout(x + bias): it is
 // stored (the residual branch's gradient), then masked and scaled from its STORED value into
 // fz.out (the projection's gradient), whose column sums (dbias) join dgamma/dbeta as a third

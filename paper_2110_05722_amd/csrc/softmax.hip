@@ -6,8 +6,7 @@
 // "thousands to millions" of rows) by tuning templates at run time.  Here the
 // shape picks a compile-time bucket instead: LPR lanes share a row (1..64 lanes
 // of a wave64), each lane keeps VPL packs of 8 scores in registers, so a row is
-// read from HBM once, both reductions run on DPP inside the wave, and nothing
-// goes through LDS.  Short rows put many rows in one wave (k_len 32 -> 16 rows per
+// read from HBM once, and both reductions run on DPP inside the wave.  Short rows put many rows in one wave (k_len 32 -> 16 rows per
 // wave) so lanes are never idle.  Rows of 257..2048 packs take one workgroup
 // each (the reductions cross its four waves through LDS).  Both exist in a form for rows
 // of whole packs and in one for any other length (RAG), the common case of a batch

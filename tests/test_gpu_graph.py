@@ -79,7 +79,7 @@ def test_newer_entry_points_replay_under_a_hip_graph():
     say("[graph] capture + 3 replays: padding removal, fused boundary, query-length and unaligned softmax, blocked "
         "trainers, one-pass criterion, embedding backward")
     d = dev()
-    B, Ln, H, N = 6, 37, 256, 4                       # 37 keys: the LDS-staged softmax path
+    B, Ln, H, N = 6, 37, 256, 4                       # 37 keys: the softmax forward goes through LDS, its backward stays in registers
     T = B * Ln
     g0 = torch.Generator(device="cpu").manual_seed(3)
     rn = lambda *s: torch.randn(*s, generator=g0).to(torch.float16).to(d)

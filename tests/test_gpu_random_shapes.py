@@ -153,7 +153,7 @@ def test_criterion_and_trainers_random(seed):
 
 @pytest.mark.parametrize("seed", range(12))
 def test_embedding_random(seed):
-    """Token counts on both sides of the switch from counted ranks to the radix sort, vocabularies that take one,
+    """Token counts on both sides of the switch from the in-LDS sort to the one over many workgroups, vocabularies that take one,
     two or three radix passes, id distributions from all-distinct to a few ids only, random padding."""
     r = np.random.default_rng(5000 + seed)
     dt = DTS[seed % 3]

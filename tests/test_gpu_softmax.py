@@ -18,14 +18,14 @@ CASES = [
     (2, 16, 512, 512, "none", 0.0),                                           # config 4 shape (2 of 16 batches)
     (1, 20, 1024, 1024, "causal", 0.0),                                       # config 5 shape (1 of 8 batches)
     (3, 2, 5, 8, "pad", 0.25), (3, 2, 16, 16, "pad+causal", 0.25),            # 1 and 2 lanes per row
-    (2, 3, 50, 50, "pad", 0.1), (2, 3, 33, 33, "pad+causal", 0.2),            # odd lengths: generic path
+    (2, 3, 50, 50, "pad", 0.1), (2, 3, 33, 33, "pad+causal", 0.2),            # odd lengths
     (2, 2, 7, 24, "causal", 0.0), (2, 2, 24, 40, "pad+causal", 0.1),          # q_len != k_len, end-aligned
     (2, 2, 9, 256, "pad", 0.0), (2, 2, 9, 768, "pad", 0.1), (1, 2, 5, 1536, "causal", 0.0),
     (1, 2, 3, 2048, "pad", 0.1), (1, 1, 3, 4096, "pad", 0.1), (1, 1, 2, 1, "none", 0.0),
     # long rows: one workgroup per row (2048 < k_len <= 16384), and the fallback beyond
     (2, 1, 4, 2056, "pad", 0.1), (1, 2, 3, 8192, "pad+causal", 0.1), (1, 1, 2, 16384, "pad", 0.0),
     (1, 1, 2, 16392, "pad", 0.1), (2, 1, 5, 4099, "pad+causal", 0.1),
-    # lengths that are not a multiple of 8: element-granular lanes (every bucket, both sides of each edge)
+    # lengths that are not a multiple of 8, over both forms of such rows (registers and LDS)
     (3, 2, 5, 7, "pad", 0.25), (3, 2, 9, 9, "pad+causal", 0.1), (4, 2, 17, 17, "pad", 0.1), (2, 2, 31, 33, "pad+causal", 0.0),
     (2, 2, 63, 63, "pad", 0.1), (2, 2, 65, 65, "causal", 0.1), (64, 4, 100, 100, "pad", 0.1), (2, 3, 127, 127, "pad+causal", 0.1),
     (2, 2, 20, 129, "pad", 0.0), (2, 2, 12, 255, "pad", 0.1), (2, 1, 9, 500, "pad", 0.1), (2, 1, 6, 513, "causal", 0.1),

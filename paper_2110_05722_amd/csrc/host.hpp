@@ -90,7 +90,9 @@ __device__ __forceinline__ uint32_t fastdiv(uint32_t n, const FastDiv& f)
 // kernel: 1.4 us).
 constexpr int kFinalizeSlices = 8, kFinalizeLoads = 32;
 
-template <int = 0>
+// WHOLE: P is a whole number of batches (256 partial rows).  Otherwise a batch that runs past the slice's rows reads its last
+// row again and drops it: a loop over the left-over rows paid one latency each (170 x 1536: 4.2 us, now 2.4).
+template <bool WHOLE>
 __global__ __launch_bounds__(32 * kFinalizeSlices) void colsum_finalize_kernel(float* __restrict__ out0,
                                                                                float* __restrict__ out1,
                                                                                float* __restrict__ out2, int split,
@@ -105,22 +107,19 @@ __global__ __launch_bounds__(32 * kFinalizeSlices) void colsum_finalize_kernel(f
     const int y0 = slice * chunk, y1 = min(P, y0 + chunk);
     float s = 0.0f;
     if (c < C) {
-        int y = y0;
-        for (; y + kFinalizeLoads <= y1; y += kFinalizeLoads) {
+        for (int y = y0; y < y1; y += kFinalizeLoads) {
             float t[kFinalizeLoads];
 #pragma unroll
-            for (int k = 0; k < kFinalizeLoads; ++k) t[k] = partial[static_cast<int64_t>(y + k) * C + c];
+            for (int k = 0; k < kFinalizeLoads; ++k) t[k] = partial[static_cast<int64_t>(WHOLE ? y + k : min(y + k, y1 - 1)) * C + c];
 #pragma unroll
-            for (int k = 0; k < kFinalizeLoads; ++k) s += t[k];
+            for (int k = 0; k < kFinalizeLoads; ++k) t[k] = WHOLE || y + k < y1 ? t[k] : 0.0f;
+            // pairwise: five roundings on a batch's way into the sum instead of up to 32
+#pragma unroll
+            for (int w = kFinalizeLoads / 2; w > 0; w /= 2)
+#pragma unroll
+                for (int k = 0; k < w; ++k) t[k] += t[k + w];
+            s += t[0];
         }
-        for (; y + 8 <= y1; y += 8) {
-            float t[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) t[k] = partial[static_cast<int64_t>(y + k) * C + c];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) s += t[k];
-        }
-        for (; y < y1; ++y) s += partial[static_cast<int64_t>(y) * C + c];
     }
     sm[slice][lane] = s;
     __syncthreads();
@@ -137,8 +136,11 @@ __global__ __launch_bounds__(32 * kFinalizeSlices) void colsum_finalize_kernel(f
 inline void launch_colsum_finalize(float* out0, float* out1, int split, const float* partial, int P, int C, hipStream_t s,
                                    float* out2 = nullptr, int split2 = 0x7FFFFFFF)
 {
-    hipLaunchKernelGGL((colsum_finalize_kernel<0>), dim3(static_cast<unsigned>((C + 31) / 32)), dim3(32 * kFinalizeSlices), 0, s,
-                       out0, out1, out2, split, split2, partial, P, C);
+    const dim3 grid(static_cast<unsigned>((C + 31) / 32)), block(32 * kFinalizeSlices);
+    if (P % (kFinalizeSlices * kFinalizeLoads) == 0)
+        hipLaunchKernelGGL((colsum_finalize_kernel<true>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
+    else
+        hipLaunchKernelGGL((colsum_finalize_kernel<false>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
 }
 
 // ---- rows that are not a whole number of packs (hidden % 8 != 0): element-wise operators
@@ -270,11 +272,49 @@ inline size_t flat_workspace_bytes(int64_t rows, int32_t hidden)
     return static_cast<size_t>(flat_plan(rows * hidden, true).blocks) * static_cast<size_t>(hidden) * sizeof(float);
 }
 
-// Number of partial-sum rows the column reductions write to the workspace.
-// One per workgroup; sized so the grid fills 256 compute units a few times over
-// while the partials stay a small fraction of the tensor traffic.
-inline int ln_bwd_blocks(int64_t rows, int32_t /*hidden*/)
+// LayerNorm backward, launch shape of the kernel whose rows span several waves (512..8192 columns, whole packs): lanes per
+// row, rows a workgroup holds at a time, workgroups (= partial rows of the column sums).
+constexpr int kLnSpanThreads = 768;          // three waves per SIMD; wider rows take up to 1024 threads
+struct LnBwdPlan { int lanes, slots, blocks; };
+inline bool ln_bwd_spans(int32_t hidden) { return hidden % kPack == 0 && hidden >= 512 && hidden <= 8192; }
+inline LnBwdPlan ln_bwd_span_plan(int64_t rows, int32_t hidden)
 {
+    constexpr int kMaxBlocks = 256;          // one per compute unit (8192 x 1280 fused: 26.0 us with the second stage, 512 of half the rows: 28.6)
+    LnBwdPlan p;
+    p.lanes = (hidden / kPack + 31) / 32 * 32;
+    const bool half_wave = p.lanes % 64 != 0;                     // then rows come in pairs
+    // Of the slot counts that give 384..768 threads, the one that leaves the fewest slots idle in the last trip, the larger
+    // among equals (8192 x 1024: 4 slots 21.5, 6 slots 23.2 us; 16000 x 640: 8 slots 25.9, 4 slots 27.3 us).  Short batches: no more
+    // than leave three trips, which the loads ahead can overlap (2200 x 512: 3 slots 8.8, 8 slots 9.4 us).
+    const int most = kLnSpanThreads / p.lanes;
+    int64_t cap = ceil_div(rows, static_cast<int64_t>(kMaxBlocks) * 3);
+    if (cap > most) cap = most;
+    p.slots = 0;
+    int64_t best = 0;
+    for (int n = 1; n <= cap; ++n) {
+        if (half_wave && n % 2 != 0) continue;
+        if (n * p.lanes < kLnSpanThreads / 2 && n + (half_wave ? 2 : 1) <= cap) continue;
+        const int64_t cost = ceil_div(rows, static_cast<int64_t>(kMaxBlocks) * n) * n;
+        if (p.slots == 0 || cost <= best) { p.slots = n; best = cost; }
+    }
+    if (p.slots == 0) {                       // one row at a time, in whole waves
+        p.slots = 1;
+        p.lanes = (p.lanes + 63) / 64 * 64;
+    }
+    // partial rows: at least 8 rows each where 256 of them would be more than 8 MiB (rows of more than 4096 columns)
+    int64_t b = (8 << 20) / (2 * static_cast<int64_t>(sizeof(float)) * hidden);
+    if (b < ceil_div(rows, 8)) b = ceil_div(rows, 8);
+    if (b > kMaxBlocks) b = kMaxBlocks;
+    if (b > ceil_div(rows, p.slots)) b = ceil_div(rows, p.slots);
+    p.blocks = static_cast<int>(b < 1 ? 1 : b);
+    return p;
+}
+
+// Number of partial-sum rows LayerNorm backward writes to the workspace: one per workgroup, so that the grid fills the 256
+// compute units while the partials stay a small fraction of the tensor traffic.
+inline int ln_bwd_blocks(int64_t rows, int32_t hidden)
+{
+    if (ln_bwd_spans(hidden)) return ln_bwd_span_plan(rows, hidden).blocks;
     int64_t b = ceil_div(rows, 8);       // at least 8 rows per workgroup
     if (b > 256) b = 256;   // one workgroup per compute unit: measured best at 8192 rows
     if (b < 1) b = 1;

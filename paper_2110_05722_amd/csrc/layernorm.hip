@@ -9,10 +9,10 @@
 // its two row sums (sum g, sum g*xhat) are independent given the saved mean and
 // rstd, and run side by side in the same DPP reduction steps.
 //
-// Layout: LPR lanes share a row (8..64 lanes of one wave, or a whole 256- or 1024-thread
-// workgroup for rows of 2049..8192 and 8193..16384 columns); each lane holds VPL packs of 8 columns, strided
-// by LPR packs so that a wave's loads are contiguous.  gamma/beta stay in
-// registers while the workgroup walks down its rows.  dgamma/dbeta: every lane
+// Layout: LPR lanes share a row (8..64 lanes of one wave, or a whole workgroup); each lane holds VPL packs of 8
+// columns, strided by LPR packs so that a wave's loads are contiguous.  gamma/beta stay in
+// registers while the workgroup walks down its rows.  Backward of 512..8192 columns: one pack per lane, a row over several
+// waves.  dgamma/dbeta: every lane
 // accumulates its own columns over its rows, the row slots of a workgroup are
 // summed in a fixed order through LDS, one partial row per workgroup goes to the
 // workspace and a second small kernel sums the partial rows in order.  No atomics.
@@ -173,19 +173,10 @@ __global__ __launch_bounds__(LPR > 256 ? LPR : 256) void ln_fwd_kernel(T* __rest
 
 constexpr int kLnBwdThreads = 256;
 
-// Whether every row slot of a workgroup gets its own LDS copy of the column accumulators
-// (one barrier in the epilogue) or the slots take turns on one copy: decided by the LDS
-// it takes for the widest row of the bucket, kept under 64 KiB.
-template <int LPR, int VPL, int THREADS, int NACC>
-constexpr bool ln_bwd_slots_parallel()
-{
-    return LPR < 256 && static_cast<long>(THREADS / LPR) * NACC * 8 * ((LPR * VPL) | 1) * 4 <= 63 * 1024;
-}
-
 // partial: [gridDim.x][2][hidden] fp32 (dgamma row, then dbeta row).
 // THREADS lanes per workgroup: THREADS/LPR rows in flight per workgroup (plus their
-// prefetched successors).  With one wave per SIMD the kernel is bound by the chain of a row that nothing
-// overlaps (8192 x 1280: vector ALU busy 24-32 %, memory units stalled under 0.5 %, occupancy 7-8 %).
+// prefetched successors).  Serves rows of up to 504 columns (a row within a wave, one pack per lane: 8000 x 256 fused 9.8 us,
+// as with ln_bwd_span_kernel's shape) and those of 8193..16384.
 // FUSE: the LayerNorm gradient (plus dres) is the gradient of h = residual + Dropout(x + bias): it is
 // stored (the residual branch's gradient), then masked and scaled from its STORED value into
 // fz.out (the projection's gradient), whose column sums (dbias) join dgamma/dbeta as a third
@@ -194,19 +185,18 @@ constexpr bool ln_bwd_slots_parallel()
 // registers: too few for the row, its prefetched successor and the column accumulators.  There the
 // accumulators live in LDS instead, each thread reading and writing only its own columns' entries
 // (131 KB for 16384 columns: no barrier, no conflict, and the LDS traffic hides behind the row
-// stream).  COLS = false computes dx only.
-template <typename T, int LPR, int VPL, bool HAS_RES, int THREADS, bool FUSE = false, bool DROP = false, bool COLS = true>
+// stream).
+template <typename T, int LPR, int VPL, bool HAS_RES, int THREADS, bool FUSE = false, bool DROP = false>
 __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restrict__ partial, const T* dy,
                                                          const T* __restrict__ x, const T* __restrict__ gamma,
                                                          const float* __restrict__ mean, const float* __restrict__ rstd,
                                                          const T* dres, int64_t rows, int hidden, BdrFuse<T> fz)
 {
     constexpr int NACC = FUSE ? 3 : 2;        // column accumulators: dgamma, dbeta (, dbias)
-    constexpr bool kColsInRegs = COLS && LPR <= 256, kColsInLds = COLS && LPR > 256;
-    extern __shared__ float colbuf[];         // [NACC][8][packs | 1]: the slots' exchange when LPR < 256, the accumulators themselves when LPR > 256
+    constexpr bool kColsInLds = LPR > 256;
+    extern __shared__ float colbuf[];         // [NACC][8][packs | 1]: the slots' exchange, or the accumulators themselves when LPR > 256
     __shared__ float lds[16];
-    static_assert(LPR < 256 || THREADS == LPR, "a whole-workgroup row takes the whole workgroup");
-    static_assert(COLS || !FUSE, "the fused boundary needs the column sums");
+    static_assert(LPR <= 64 || THREADS == LPR, "a whole-workgroup row takes the whole workgroup");
     constexpr int RPB = THREADS / LPR;
     const int sub = threadIdx.x % LPR;
     const int slot = threadIdx.x / LPR;
@@ -286,10 +276,10 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float xhat = fmaf(xv[j], rs, nmr);
-                if constexpr (kColsInRegs) {
+                if constexpr (!kColsInLds) {
                     dg[k][j] = fmaf(gy[j], xhat, dg[k][j]);
                     db[k][j] += gy[j];
-                } else if constexpr (kColsInLds) {
+                } else {
                     if (sub + k * LPR < nv) {              // rows that do not exist hold dy = 0 and add nothing
                         float* a = colbuf + j * cstride + (sub + k * LPR);
                         a[0] = fmaf(gy[j], xhat, a[0]);
@@ -347,7 +337,6 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
         }
     }
 
-    if constexpr (!COLS) return;
     float* prow = partial + static_cast<int64_t>(blockIdx.x) * NACC * hidden;
     if constexpr (kColsInLds) {
 #pragma unroll
@@ -361,89 +350,194 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
                 store8<float>(prow + hidden + idx * kPack, b);
             }
         }
-    } else if constexpr (LPR >= 256) {        // every thread owns its columns: nothing to combine
-#pragma unroll
-        for (int k = 0; k < VPL; ++k) {
-            const int idx = sub + k * LPR;
-            if (idx < nv) {
-                store8<float>(prow + idx * kPack, dg[k]);
-                store8<float>(prow + hidden + idx * kPack, db[k]);
-                if constexpr (FUSE) store8<float>(prow + 2 * hidden + idx * kPack, dbi[k]);
-            }
-        }
     } else {
         // Sum the RPB row slots in slot order through LDS.  Layout [dgamma|dbeta(|dbias)][j][pack] with
         // an odd pack stride: consecutive lanes (consecutive packs) fall in consecutive banks.  A
         // [column] layout would put the lanes of a wave 8 floats apart: a 16-way bank conflict.
         const int stride = nv | 1;
-        if constexpr (ln_bwd_slots_parallel<LPR, VPL, THREADS, NACC>()) {
-            // every slot has its own copy: all slots write at once, one barrier, then all threads
-            // add the RPB copies of their columns in slot order (same sums as taking turns)
-            const int per_slot = NACC * 8 * stride;
-            float* mine = colbuf + slot * per_slot;
+        // every slot has its own copy: all slots write at once, one barrier, then all threads
+        // add the RPB copies of their columns in slot order (same sums as taking turns)
+        const int per_slot = NACC * 8 * stride;
+        float* mine = colbuf + slot * per_slot;
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) {
-                const int idx = sub + k * LPR;
-                if (idx < nv) {
+        for (int k = 0; k < VPL; ++k) {
+            const int idx = sub + k * LPR;
+            if (idx < nv) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        mine[j * stride + idx] = dg[k][j];
-                        mine[8 * stride + j * stride + idx] = db[k][j];
-                        if constexpr (FUSE) mine[16 * stride + j * stride + idx] = dbi[k][j];
-                    }
+                for (int j = 0; j < 8; ++j) {
+                    mine[j * stride + idx] = dg[k][j];
+                    mine[8 * stride + j * stride + idx] = db[k][j];
+                    if constexpr (FUSE) mine[16 * stride + j * stride + idx] = dbi[k][j];
                 }
-            }
-            __syncthreads();
-            for (int c = threadIdx.x; c < NACC * hidden; c += THREADS) {
-                const int which = c / hidden;
-                const int cc = c - which * hidden;
-                const int off = which * 8 * stride + (cc & 7) * stride + (cc >> 3);
-                float t = colbuf[off];
-#pragma unroll
-                for (int sl = 1; sl < RPB; ++sl) t += colbuf[sl * per_slot + off];
-                prow[c] = t;
-            }
-        } else {
-            float* cg = colbuf;
-            float* cb = colbuf + 8 * stride;
-            float* ci = colbuf + 16 * stride;      // FUSE only
-            for (int turn = 0; turn < RPB; ++turn) {
-                if (slot == turn) {
-                    // all reads of the turn first, then the adds, then all writes: a read-add-write
-                    // per element would pay one LDS round trip each, 48 in a row
-                    if (turn > 0) {
-#pragma unroll
-                        for (int k = 0; k < VPL; ++k) {
-                            const int idx = min(sub + k * LPR, nv - 1);
-#pragma unroll
-                            for (int j = 0; j < 8; ++j) {
-                                dg[k][j] += cg[j * stride + idx];
-                                db[k][j] += cb[j * stride + idx];
-                                if constexpr (FUSE) dbi[k][j] += ci[j * stride + idx];
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int k = 0; k < VPL; ++k) {
-                        const int idx = sub + k * LPR;
-                        if (idx < nv) {
-#pragma unroll
-                            for (int j = 0; j < 8; ++j) {
-                                cg[j * stride + idx] = dg[k][j];
-                                cb[j * stride + idx] = db[k][j];
-                                if constexpr (FUSE) ci[j * stride + idx] = dbi[k][j];
-                            }
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-            for (int c = threadIdx.x; c < NACC * hidden; c += THREADS) {
-                const int which = c / hidden;
-                const int cc = c - which * hidden;
-                prow[c] = colbuf[which * 8 * stride + (cc & 7) * stride + (cc >> 3)];
             }
         }
+        __syncthreads();
+        for (int c = threadIdx.x; c < NACC * hidden; c += THREADS) {
+            const int which = c / hidden;
+            const int cc = c - which * hidden;
+            const int off = which * 8 * stride + (cc & 7) * stride + (cc >> 3);
+            float t = colbuf[off];
+#pragma unroll
+            for (int sl = 1; sl < RPB; ++sl) t += colbuf[sl * per_slot + off];
+            prow[c] = t;
+        }
+    }
+}
+
+// Rows of 512..8192 columns: a row spans LR lanes (a multiple of 32, several waves for all but 512 columns) and every lane
+// owns ONE pack of columns, so a lane keeps 16 or 24 column accumulators instead of 16-24 per pack held, a thread needs
+// 90-125 registers and three or four waves share a SIMD.  With a whole row per wave (up to 264 registers, one wave per
+// SIMD) nothing overlapped a row's chain of loads, two reductions, dropout draw and stores.  A workgroup holds
+// `slots` rows at a time; the waves of a row meet in LDS once per row: every 32 lanes leave their two sums, a barrier, then
+// every 32 lanes read all of them (at most 32) back with one access and add them by DPP.  Two buffers make the one
+// barrier enough: a buffer is written again only behind the next row's barrier.  The next row is loaded ahead, the dropout
+// words are drawn between the reductions and the barrier, where they fill the wait for the slowest wave.  No lane shares its
+// columns with another lane of its row, so the epilogue only adds the slots (a tree over LDS, fixed order).
+// Fused with dropout and residual gradient, bf16 8192 x 1280: 27.8 -> 23.1 us, 3000 x 3072: 38 -> 21; plain 2600 x 2048: 14.0 -> 10.8;
+// f32 fused 4000 x 1280: 27.5 -> 23.9 (second stage not counted).  What is left above the copy of the bytes (17 us at 8192 x 1280)
+// is first load, epilogue and partial row.
+// LRC = 64: 512 columns, a row per wave, no exchange.  Partial rows as ln_bwd_kernel's.
+template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP>
+__global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restrict__ partial, const T* dy,
+                                                           const T* __restrict__ x, const T* __restrict__ gamma,
+                                                           const float* __restrict__ mean, const float* __restrict__ rstd,
+                                                           const T* dres, int64_t rows, int hidden, int lanes, BdrFuse<T> fz)
+{
+    constexpr int NACC = FUSE ? 3 : 2;        // column accumulators: dgamma, dbeta (, dbias)
+    extern __shared__ float span_lds[];       // the rows' exchange [2][32-lane groups][2], later the slots' [slots / 2][NACC * 8][lanes]
+    const int LR = LRC ? LRC : lanes;
+    const int slots = blockDim.x / LR;
+    const int slot = threadIdx.x / LR, sub = threadIdx.x - slot * LR;
+    const int nv = hidden / kPack;
+    const bool on = sub < nv;
+    const float inv_h = 1.0f / static_cast<float>(hidden);
+    const int64_t gstride = static_cast<int64_t>(gridDim.x) * slots;
+
+    float g8[8];
+    unpack<T>(on ? load_raw<T>(gamma + sub * kPack) : zero_raw<T>(), g8);
+    float acc[NACC][8];
+#pragma unroll
+    for (int a = 0; a < NACC; ++a)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[a][j] = 0.0f;
+
+    RawPack<T> ndy, nx, nres;
+    float nmu, nrs;
+    auto fetch = [&](int64_t r) {             // zeros where the row or the pack does not exist
+        ndy = zero_raw<T>(); nx = zero_raw<T>();
+        if constexpr (HAS_RES) nres = zero_raw<T>();
+        nmu = 0.0f; nrs = 0.0f;
+        if (r < rows) {
+            if (on) {
+                const int64_t e = r * hidden + sub * kPack;
+                ndy = load_raw<T, kNT>(dy + e);
+                nx = load_raw<T, kNT>(x + e);
+                if constexpr (HAS_RES) nres = load_raw<T, kNT>(dres + e);
+            }
+            nmu = mean[r]; nrs = rstd[r];
+        }
+    };
+    int64_t base = static_cast<int64_t>(blockIdx.x) * slots;
+    fetch(base + slot);
+    float* sums = span_lds;                   // of this row; the other buffer next
+    float* other = span_lds + blockDim.x / 16;
+    for (; base < rows; base += gstride) {    // the same trips for every thread
+        const int64_t r = base + slot;
+        const RawPack<T> cdy = ndy, cx = nx, cres = nres;
+        const float mu = nmu, rs = nrs;
+        if (base + gstride < rows) fetch(r + gstride);
+
+        // the two row sums and the column sums; absent packs and rows hold dy = 0
+        const float nmr = -mu * rs;
+        float gy[8], xh[8], s1 = 0.0f, s2 = 0.0f;
+        unpack<T>(cdy, gy);
+        unpack<T>(cx, xh);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            xh[j] = fmaf(xh[j], rs, nmr);
+            acc[0][j] = fmaf(gy[j], xh[j], acc[0][j]);
+            acc[1][j] += gy[j];
+            gy[j] *= g8[j];
+            s1 += gy[j];
+            s2 = fmaf(gy[j], xh[j], s2);
+        }
+        uint32_t w[4];
+        if constexpr (LRC == 64) {
+            s1 = group_sum<64>(s1);
+            s2 = group_sum<64>(s2);
+        } else {
+            s1 = group_sum<32>(s1);
+            s2 = group_sum<32>(s2);
+            if ((threadIdx.x & 31) == 0) {
+                sums[threadIdx.x / 16] = s1;
+                sums[threadIdx.x / 16 + 1] = s2;
+            }
+        }
+        if constexpr (FUSE && DROP) {
+            const uint64_t g = static_cast<uint64_t>(r) * nv + sub;
+            philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), fz.d.ctr2, fz.d.ctr3, fz.d.key0, fz.d.key1, w);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(w[j]));      // drawn here, not behind the barrier
+        }
+        if constexpr (LRC != 64) {
+            __syncthreads();
+            const int l = threadIdx.x & 31, groups = LR / 32, at = 2 * (slot * groups + (l < groups ? l : 0));
+            s1 = group_sum<32>(l < groups ? sums[at] : 0.0f);
+            s2 = group_sum<32>(l < groups ? sums[at + 1] : 0.0f);
+            float* t = sums; sums = other; other = t;
+        }
+        // dx = rstd*(g - (s1 + xhat*s2)/hidden) = g*rstd + xhat*c1 + c0
+        const float c0 = -rs * s1 * inv_h, c1 = -rs * s2 * inv_h;
+        if (r < rows && on) {
+            const int64_t e = r * hidden + sub * kPack;
+            float o[8];
+            if constexpr (HAS_RES) unpack<T>(cres, o);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float v = fmaf(gy[j], rs, fmaf(xh[j], c1, c0));
+                o[j] = HAS_RES ? o[j] + v : v;
+            }
+            pin_f32(o);                       // the fused and the plain kernel round alike
+            const RawPack<T> hp = pack_raw<T>(o);
+            store_raw<T, kNT>(dx + e, hp);
+            if constexpr (FUSE) {
+                float gq[8];
+                unpack<T>(hp, gq);
+                if constexpr (DROP) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        gq[2 * j] *= (w[j] & 0xFFFFu) >= fz.d.t16 ? fz.d.scale : 0.0f;
+                        gq[2 * j + 1] *= (w[j] >> 16) >= fz.d.t16 ? fz.d.scale : 0.0f;
+                    }
+                }
+                pin_f32(gq);
+                store8<T, kNT>(fz.out + e, gq);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[2][j] += gq[j];
+            }
+        }
+    }
+
+    for (int left = slots; left > 1;) {       // slot k takes slot k + half, until one is left
+        const int half = (left + 1) / 2;
+        __syncthreads();                      // the exchange, or the step before, has been read
+        if (slot >= half && slot < left) {
+            float* m = span_lds + (slot - half) * NACC * 8 * LR + sub;
+#pragma unroll
+            for (int a = 0; a < NACC * 8; ++a) m[a * LR] = acc[a / 8][a % 8];
+        }
+        __syncthreads();
+        if (slot + half < left) {
+            const float* m = span_lds + slot * NACC * 8 * LR + sub;
+#pragma unroll
+            for (int a = 0; a < NACC * 8; ++a) acc[a / 8][a % 8] += m[a * LR];
+        }
+        left = half;
+    }
+    if (slot == 0 && on) {
+        float* prow = partial + static_cast<int64_t>(blockIdx.x) * NACC * hidden + sub * kPack;
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) store8<float>(prow + a * hidden, acc[a]);
     }
 }
 
@@ -665,17 +759,6 @@ inline LnShape ln_shape(int hidden)
     return {0, 0};
 }
 
-// Backward keeps 2 (3 when fused) fp32 column accumulators per element of a lane next to the rows in
-// flight and sums the row slots of a workgroup through LDS: from three packs per lane on, 64 lanes per
-// row with an idle tail beat the exact fit on 32 (8192 rows: 1280 columns 18.9 against 20.7 us as 32 x 5,
-// 1024 columns 16.9 against 20.0 us as 32 x 4); 512 columns stay on 32 x 2 (11.5 against 12.9 us as 64 x 1).
-inline LnShape ln_bwd_shape(int hidden)
-{
-    const LnShape f = ln_shape(hidden);
-    if (f.lpr != 32 || f.vpl <= 2) return f;
-    return {64, (hidden / kPack + 63) / 64};
-}
-
 inline int ln_fwd_blocks(int64_t rows, int lpr)
 {
     const int rpb = lpr > 256 ? 1 : 256 / lpr;
@@ -685,7 +768,8 @@ inline int ln_fwd_blocks(int64_t rows, int lpr)
     return static_cast<int>(b);
 }
 
-#define LSQ_LN_CASES_COMMON(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(64, 5) X(64, 6) X(256, 2) X(256, 3) X(256, 4)
+#define LSQ_LN_FWD_CASES(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(64, 5) X(64, 6) X(256, 2) X(256, 3) X(256, 4) \
+    X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(32, 6) X(256, 6) X(256, 8)
 
 // fuse != nullptr: x is the projection output and *fuse carries h / residual / bias / dropout
 template <typename T>
@@ -723,7 +807,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
         else if (fuse->d.on) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, true>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
         else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
     }
-    LSQ_LN_CASES_COMMON(X) X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(32, 6) X(256, 6) X(256, 8)
+    LSQ_LN_FWD_CASES(X)
 #undef X
     return launch_status();
 }
@@ -737,8 +821,8 @@ static lsq_status ln_bwd_wide(T* dxp, float* partial, const T* dyp, const T* xp,
     constexpr int TH = L >= 256 ? L : 256;
     const BdrFuse<T> nofuse{};
     const size_t shmem = sizeof(float) * 16 * ((hidden / kPack) | 1);
-    auto* kres = &ln_bwd_kernel<T, L, V, true, TH, false, false, true>;
-    auto* kplain = &ln_bwd_kernel<T, L, V, false, TH, false, false, true>;
+    auto* kres = &ln_bwd_kernel<T, L, V, true, TH, false, false>;
+    auto* kplain = &ln_bwd_kernel<T, L, V, false, TH, false, false>;
     // once per residual variant and device (a host-side note, guarded for concurrent host threads)
     static std::mutex mu;
     static bool ready[2][64] = {};
@@ -770,7 +854,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
     const T* xp = static_cast<const T*>(x);
     const T* gp = static_cast<const T*>(gamma);
     const T* rp = static_cast<const T*>(dres);
-    const LnShape sh = ln_bwd_shape(hidden);
+    const LnShape sh = ln_shape(hidden);
     if (sh.lpr == 0) {
         const int Pg = ln_bwd_blocks(rows, hidden);
         float* gpartial = static_cast<float*>(workspace);
@@ -802,14 +886,35 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
         launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 2 * hidden, s);
         return launch_status();
     }
-    const int nacc = fuse ? 3 : 2;
-    const size_t one_copy = sh.lpr >= 256 ? 0 : sizeof(float) * 8 * nacc * ((hidden / kPack) | 1);
     const BdrFuse<T> none{};
+    if (ln_bwd_spans(hidden)) {
+        const LnBwdPlan pl = ln_bwd_span_plan(rows, hidden);
+        const dim3 grid(P), block(pl.slots * pl.lanes);
+        const size_t exchange = sizeof(float) * (block.x / 8), tree = sizeof(float) * (pl.slots / 2) * (fuse ? 3 : 2) * 8 * pl.lanes;
+        const size_t shmem = exchange > tree ? exchange : tree;
+#define X(C, M)                                                                                              \
+    if (!fuse) {                                                                                             \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, false, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none); \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, false, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none);   \
+    } else if (fuse->d.on) {                                                                                 \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);  \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);    \
+    } else {                                                                                                 \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse); \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);   \
+    }
+        if (pl.lanes == 64) { X(64, kLnSpanThreads) }
+        else if (block.x <= kLnSpanThreads) { X(0, kLnSpanThreads) }
+        else { X(0, 1024) }
+#undef X
+    }
+    // shorter rows: lanes of one wave, one pack each
+    const int nacc = fuse ? 3 : 2;
+    const size_t one_copy = sizeof(float) * 8 * nacc * ((hidden / kPack) | 1);
 #define X(L, V)                                                                                              \
-    if (sh.lpr == L && sh.vpl == V) {                                                                        \
-        constexpr int TH = L >= 256 ? L : kLnBwdThreads;                                                   \
-        const bool par = fuse ? ln_bwd_slots_parallel<L, V, TH, 3>() : ln_bwd_slots_parallel<L, V, TH, 2>(); \
-        const size_t shmem = par ? one_copy * (TH / L) : one_copy;                                           \
+    if (!ln_bwd_spans(hidden) && sh.lpr == L && sh.vpl == V) {                                                                        \
+        constexpr int TH = kLnBwdThreads;                                                                 \
+        const size_t shmem = one_copy * (TH / L);                                                            \
         const dim3 grid(P), block(TH);                                                                       \
         if (!fuse) {                                                                                         \
             if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, none); \
@@ -822,7 +927,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
             else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
         }                                                                                                    \
     }
-    LSQ_LN_CASES_COMMON(X) X(32, 2)
+    X(8, 1) X(16, 1) X(32, 1) X(64, 1)
 #undef X
     if (fuse) launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 3 * hidden, s, dbias, 2 * hidden);
     else launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 2 * hidden, s);

@@ -225,3 +225,11 @@ def test_the_raw_stream_query_is_the_current_stream(monkeypatch):
             with monkeypatch.context() as m:
                 m.setattr(binding, "_raw_stream", None)
                 assert binding._stream() == stream.cuda_stream
+
+
+def test_layernorm_bwd_partial_rows_fit_the_no_alloc_scratch_as_before(lib):
+    """Up to 4096 columns any row count fits the 8 MiB; beyond, no call needs more than 8 MiB that took 8 or more rows per partial row."""
+    for hidden in (8, 504, 512, 520, 1280, 2056, 4096, 4104, 6912, 8192, 8200, 16384):
+        for rows in (1, 7, 255, 256, 257, 511, 768, 1105, 2047, 2048, 2049, 8192, 1 << 24):
+            before = 2 * hidden * 4 * min(256, -(-rows // 8))
+            assert L.lsq_workspace_bytes(0, rows, hidden) <= max(8 << 20, before), (rows, hidden)

@@ -97,3 +97,34 @@ def test_layernorm_empty():
     dx, dg, db = L.lsq_layernorm_bwd(x, x, g, mean, rstd)
     torch.cuda.synchronize()
     assert y.numel() == 0 and dg.abs().sum().item() == 0 and db.abs().sum().item() == 0
+
+
+# the backward whose rows span several waves: one pack per lane, 512..8192 columns.  Widths at the edges of its lane counts
+# (whole and half waves, 32-lane remainders, one row per workgroup up to 768 and up to 1024 threads), rows at the edges of
+# its slots and trips (one row, less than a slot, one more than a round of 256 workgroups).
+SPAN = [(1, 512), (257, 512), (1537, 512), (770, 520), (5, 520), (1, 776), (2049, 776), (1025, 1272), (1025, 1288), (600, 1280),
+        (3, 2040), (515, 2056), (257, 3064), (257, 3080), (259, 4096), (3, 6136), (257, 6152), (70, 8184), (2, 8192)]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("rows,hidden", SPAN)
+def test_layernorm_bwd_rows_over_several_waves(rows, hidden, dt):
+    say(f"[layernorm] spanning rows={rows} hidden={hidden} dt={dt}")
+    t = _case(rows, hidden, dt)
+    d = dev()
+    x, gamma, beta, dy, res = (to_torch(t[k], dt, d) for k in ("x", "gamma", "beta", "dy", "residual"))
+    y, mean, rstd = L.lsq_layernorm_fwd(x, gamma, beta, EPS)
+    floor = 1e-6 * np.sqrt(rows) * 4
+    for with_res in (False, True):
+        kept = dict(dres_in=res) if with_res else {}
+        dx, dgamma, dbeta = L.lsq_layernorm_bwd(dy, x, gamma, mean, rstd, **kept)
+        rdx, rdg, rdb = oracle.layernorm_bwd(t["dy"], t["x"], t["gamma"], EPS, dt, dres_in=t["residual"] if with_res else None)
+        assert_close_store(dx, rdx, dt, f"dx(res={with_res})")
+        assert_close_f32(dgamma, rdg, "dgamma", floor=floor)
+        assert_close_f32(dbeta, rdb, "dbeta", floor=floor)
+        for p in (0.0, 0.3):
+            dh, ddx, dg2, db2, dbias = L.lsq_bdr_layernorm_bwd(dy, x, gamma, mean, rstd, p, 9, 3, **kept)
+            assert torch.equal(dh, dx) and torch.equal(dg2, dgamma) and torch.equal(db2, dbeta)
+            two, two_bias = L.lsq_bias_dropout_residual_bwd(dh, p, 9, 3)
+            assert torch.equal(ddx, two)
+            assert_close_f32(dbias, two_bias.cpu().numpy(), "dbias", floor=2 * floor)

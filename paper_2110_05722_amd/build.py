@@ -1,4 +1,4 @@
-"""Builds `liblsq.so` (the C-ABI library of include/lsq.h) for gfx950 with hipcc.
+"""Builds `liblsq.so` (the C-ABI library of include/lsq.h) for gfx950 with hipcc, and `_calls.so` (how Python calls it) with g++.
 
     python -m paper_2110_05722_amd.build
 
@@ -11,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,7 +20,9 @@ LIB = os.path.join(HERE, "liblsq.so")
 OBJ_DIR = os.path.join(HERE, "_build", "liblsq.so")
 SOURCES = ["api", "calibrate", "adam", "bias_dropout_residual", "bias_act_dropout", "heads", "embedding", "pad", "layernorm", "softmax",
            "ls_xent"]
+CALLS = os.path.join(HERE, "_calls.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-command-line-argument",
     # packed fp32 VALU forms are switched off for the device pass (the host pass warns that it
@@ -49,7 +52,27 @@ def build(verbose: bool = True, lib: str = LIB, obj_dir: str = OBJ_DIR, extra: t
                    capture_output=not verbose)
     if verbose:
         print(f"built {lib}")
+    if lib == LIB:
+        build_calls(verbose)
     return lib
+
+
+def build_calls(verbose: bool = True) -> str:
+    """`_calls.so`, the CPython extension of csrc/calls.cpp (host code; linked against liblsq.so beside it and torch's libraries,
+    which the process has loaded by then)."""
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-I{i}" for i in inc), os.path.join(CSRC, "calls.cpp"), "-o", CALLS, f"-L{HERE}", "-l:liblsq.so",
+           f"-L{os.path.join(t, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{CXX} failed on calls.cpp:\n{r.stderr}")
+    if verbose:
+        print(f"built {CALLS}")
+    return CALLS
 
 
 if __name__ == "__main__":

@@ -250,7 +250,9 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
     if (!bad_is_flat(hidden)) {
         const int ppr = hidden / kPack;
         // two rows per wave: 28.1 / 23.1 us at 8192 x 5120 / 4096 x 4096 against 29.0 / 23.8 with four and 28.1 / 24.3 with one
+        // (one where those workgroups are few: 512 x 2048 f32 3.5 against 3.8 us, 2694 x 1392 5.4 against 5.9; 2200 x 2048 5.5 against 5.2)
         int64_t rb = ceil_div(rows, 2 * kBadWaves);
+        if (rb * ceil_div(ppr, 64) <= 1024) rb = ceil_div(rows, kBadWaves);
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(ceil_div(ppr, 64)), static_cast<unsigned>(rb)), block(256);
         const bool drop = d.on != 0;

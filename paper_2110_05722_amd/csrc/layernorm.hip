@@ -759,17 +759,36 @@ inline LnShape ln_shape(int hidden)
     return {0, 0};
 }
 
+// Forward: the shape above, but more lanes per row (a shorter chain per row) where the calls are short or the shape leaves a lane
+// four packs or more.  Measured, fused / plain: 512 x 512 f32 64 x 1 3.9 / 3.1 us, 32 x 2 4.7 / 3.2; 3000 x 1024 64 x 2 7.4 / 4.7, 32 x 4
+// 7.7 / 5.1 (4096 rows 9.0 / 5.8 against 8.3 / 5.4: the line is between).  600 x 3072 256 x 2 6.0 / 4.3, 64 x 6 7.0 / 4.6; 600 x 2048 256 x 1
+// 5.1 / 3.9, 64 x 4 5.6 / 4.1.  8192 x 2048 256 x 1 27.8 / 15.8, 64 x 4 29.6 / 17.4; 8192 x 2560 256 x 2 34.3 / 18.6, 64 x 5 35.8 / 19.0; rows that fill
+// three quarters of such lanes or less stay (4096 x 3072 256 x 2 21.2 / 12.2, 64 x 6 22.2 / 11.2; 8192 x 1536 21.1 / 11.9 against 22.9 / 10.2).
+// Fused and plain calls take the same shape, so their results stay bit-identical.
+inline LnShape ln_fwd_shape(int64_t rows, int hidden)
+{
+    const LnShape s = ln_shape(hidden);
+    const int nv = hidden / kPack;
+    if (s.lpr == 0 || s.lpr >= 256) return s;
+    if (nv > 128 && nv <= 256 && (nv > 224 || rows <= 1024)) return {256, 1};
+    if (nv > 256 && (nv <= 320 || rows <= 1024)) return {256, 2};
+    if (s.lpr == 32 && s.vpl % 2 == 0 && rows <= 3072) return {64, s.vpl / 2};
+    return s;
+}
+
 inline int ln_fwd_blocks(int64_t rows, int lpr)
 {
-    const int rpb = lpr > 256 ? 1 : 256 / lpr;
-    int64_t b = ceil_div(rows, static_cast<int64_t>(rpb) * 2);   // two row groups per workgroup (one: 11.1, two: 9.2, four: 10.4 us at 8192 x 1280)
+    // two row groups per workgroup, the second loaded ahead (one: 11.1, two: 9.2, four: 10.4 us at 8192 x 1280); one where that
+    // leaves compute units idle (512 x 512 f32 fused 5.7 -> 4.7 us, 1000 x 768 6.2 -> 4.7, 4096 x 1024 9.0 -> 8.3)
+    const int64_t groups = ceil_div(rows, static_cast<int64_t>(lpr > 256 ? 1 : 256 / lpr));
+    int64_t b = groups <= 768 ? groups : ceil_div(groups, 2);
     if (b > 8192) b = 8192;
     if (b < 1) b = 1;
     return static_cast<int>(b);
 }
 
 #define LSQ_LN_FWD_CASES(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(64, 5) X(64, 6) X(256, 2) X(256, 3) X(256, 4) \
-    X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(32, 6) X(256, 6) X(256, 8)
+    X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(32, 6) X(256, 6) X(256, 8) X(256, 1)
 
 // fuse != nullptr: x is the projection output and *fuse carries h / residual / bias / dropout
 template <typename T>
@@ -781,7 +800,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
     const T* xp = static_cast<const T*>(x);
     const T* gp = static_cast<const T*>(gamma);
     const T* bp = static_cast<const T*>(beta);
-    LnShape sh = ln_shape(hidden);
+    LnShape sh = ln_fwd_shape(rows, hidden);
     // rows of 8193..16384 columns: the forward has the registers for 6 or 8 packs per lane of a 256-thread
     // workgroup (0.70 of peak at 12288 columns against 0.53 with the backward's 1024 lanes x 2 packs).  The fused
     // boundary follows (it would be 10 % faster on 1024 lanes, but then no longer bit-identical to the two calls).

@@ -128,3 +128,25 @@ def test_layernorm_bwd_rows_over_several_waves(rows, hidden, dt):
             two, two_bias = L.lsq_bias_dropout_residual_bwd(dh, p, 9, 3)
             assert torch.equal(ddx, two)
             assert_close_f32(dbias, two_bias.cpu().numpy(), "dbias", floor=2 * floor)
+
+
+# the forward's choice of lanes per row and of row groups per workgroup: both sides of every line
+FWD_LINES = [(1024, 1032), (1025, 1032), (6, 1784), (6, 1792), (1025, 1800), (1025, 2048), (1024, 2056), (1025, 2560), (1025, 2568), (1024, 3072),
+             (3072, 512), (3073, 512), (3072, 1536), (3073, 1024), (767, 2048), (769, 2048), (1537, 2568), (6144, 256), (6145, 256)]
+
+
+@pytest.mark.parametrize("rows,hidden", FWD_LINES)
+def test_layernorm_fwd_shapes(rows, hidden):
+    dt, d = "f16", dev()
+    say(f"[layernorm] forward shapes rows={rows} hidden={hidden}")
+    t = _case(rows, hidden, dt)
+    x, gamma, beta, bias, res = (to_torch(t[k], dt, d) for k in ("x", "gamma", "beta", "bias", "residual"))
+    y, mean, rstd = L.lsq_layernorm_fwd(x, gamma, beta, EPS)
+    ry, rmean, rrstd = oracle.layernorm_fwd(t["x"], t["gamma"], t["beta"], EPS, dt)
+    assert_close_store(y, ry, dt, "y")
+    assert_close_f32(mean, rmean, "mean", floor=2e-7)
+    assert_close_f32(rstd, rrstd, "rstd")
+    h, y2, mean2, rstd2 = L.lsq_bdr_layernorm_fwd(x, bias, res, gamma, beta, 0.2, 5, 1)
+    h3 = L.lsq_bias_dropout_residual_fwd(x, bias, res, 0.2, 5, 1)
+    y3, mean3, rstd3 = L.lsq_layernorm_fwd(h3, gamma, beta, EPS)
+    assert torch.equal(h, h3) and torch.equal(y2, y3) and torch.equal(mean2, mean3) and torch.equal(rstd2, rstd3)

@@ -99,23 +99,25 @@ __device__ __forceinline__ unsigned emb_key(int w, int vocab, int pad_idx)
 // What the accumulation needs is that equal ids stand together in ascending position; which id comes before
 // which is free, so a class can be any set of ids whose share does not follow from their frequency (frequent words have
 // small ids) or their spacing: the low bits of the id with the next two groups of bits folded in (sort_mix).  A workgroup looks at every token
-// once, keeps the positions of its ids, in order, and counts those of the
-// parts before it, which is where its own begin; then it sorts its positions by the rest of the id: a stable least-
+// once, keeps the positions of its ids and counts those of the parts before it, which is where its own begin.  An entry is 32
+// bits, what the part leaves of the id and the position: no two are equal, so a part of up to kSortRank entries needs no order on
+// its way into LDS (a lane writes its own one after the other) and is sorted by counting the smaller ones of every entry.  Larger
+// parts are kept in order and sorted by the rest of the id: a stable least-
 // significant-digit radix sort, at most 6 bits per pass.  The lanes of a round of 64 entries that hold the same digit find
 // each other with ballots, the lowest takes as many places as they are from the wave's counter of that digit (waves
-// apart: nothing depends on timing).  An entry is 32 bits, the position and what the part leaves of the id, in LDS, or in
-// the workspace where a part is larger than kSortLds.  Padding is not
+// apart: nothing depends on timing), in LDS, or in the workspace where a part is larger than kSortLds.  Padding is not
 // sorted: what is left of `order` behind the live tokens is filled with it.
-// A part larger than kSortHeavy has a frequent id in it nearly always.  The id that most of its lanes meet first is taken out of
-// the sort: its positions need none, they go to the end of the part's range in the order they are met.
-// Whole backward, 8192 tokens x 1024 in us, one id everywhere / half of the tokens / 12 % of them / ids that are multiples of 64 / words:
-// 53 / 40 / 30 / 26 / 28; by the low bits alone and all of it sorted 106 / 63 / 32 / 81 / 28; the rank count 54 / 40 / 29 / 29 / 29.
-// What bounds it is the latency of its steps, 13 us alone at 8192 tokens, most of it behind the dP stream that shares the
-// launch (together 15, bf16 hidden 1280; the quadratic rank count over 1024 workgroups with dP 15.7 and a scatter
-// launch of 4 before it).  One 1024-thread workgroup for all of 8192 tokens took 20 us; with the ids read again from the
+// A part larger than kSortRank has a frequent id in it nearly always.  Of four ids that lanes of a wave meet first, the one that most
+// lanes do is taken out of the sort: its positions need none, they go to the end of the part's range in the order they are met.
+// What bounds it is the latency of its steps, in cycles of the slowest part at 8192 tokens (words, vocabulary 50257): tokens, keys and counts
+// 4900, sums 600, the frequent id 2800, into LDS 7100, sort 1800; 17200 together, 26600 when every part went through the radix sort, in order,
+// and the frequent id was found by a vote of all lanes.  Whole backward, bf16, in us before and now: 8192 x 1280 words 31.5 / 28.6
+// (without dP 31.1 / 27.5), one id everywhere 56 / 54, half of them 43 / 41, multiples of 64 32.5 / 30; 16384 x 1024 words 44.6 / 41 (128 parts);
+// 790 x 600 15.7 / 13.4.  One 1024-thread workgroup for all of 8192 tokens took 20 us; with the ids read again from the
 // tokens in every round instead of carried, the part of the most frequent word took 19.
-constexpr int kSortDigits = 64, kSortLds = 2048, kSortHeavy = 512;
-// How an id is split: `part_bits` low bits choose the part (64 parts; 128 where that makes a 31-bit id of a small call fit), the
+constexpr int kSortDigits = 64, kSortLds = 2048, kSortRank = 256;
+// How an id is split: `part_bits` low bits choose the part (64 parts; 128 beyond 8192 tokens, where parts of 64 would be too large to
+// rank, and where that makes a 31-bit id of a small call fit), the
 // rest shares a 32-bit entry with the `pos_bits` bits of a position.
 struct EmbSortPlan { int part_bits, pos_bits, passes, pass_bits; bool fits; };
 inline EmbSortPlan emb_sort_plan(int64_t rows, int bits)
@@ -123,7 +125,7 @@ inline EmbSortPlan emb_sort_plan(int64_t rows, int bits)
     EmbSortPlan p;
     p.pos_bits = 1;
     while ((static_cast<int64_t>(1) << p.pos_bits) < rows) ++p.pos_bits;
-    p.part_bits = bits > 32 - p.pos_bits + 6 && rows <= 256 ? 7 : 6;
+    p.part_bits = rows > 8192 || (bits > 32 - p.pos_bits + 6 && rows <= 256) ? 7 : 6;
     p.fits = rows <= kEmbSortMax && bits <= 32 - p.pos_bits + p.part_bits;
     const int rest = bits > p.part_bits ? bits - p.part_bits : 1;
     p.passes = (rest + 5) / 6;
@@ -208,6 +210,42 @@ __device__ __forceinline__ void emb_sort_part(int* cnt, uint32_t* src, uint32_t*
     }
 }
 
+// inclusive sum over the lanes up to this one (row shifts, then the row totals handed on)
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // row_bcast 15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);      // row_bcast 31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ int wave_total(int scanned) { return __builtin_amdgcn_readlane(scanned, 63); }
+
+// up to kSortRank entries in any order -> order: an entry's place is the number of smaller ones (no two are equal), counted by
+// 1, 2 or 4 neighbouring threads per entry.  The entries lie in LDS, kNoKey behind them up to a multiple of sixteen.
+__device__ __forceinline__ void emb_rank_part(const uint32_t* src, int n, int part, int2* __restrict__ order, const EmbSortPlan& pl)
+{
+    if (n == 0) return;                                                   // uniform
+    const int each = n <= 64 ? 4 : n <= 128 ? 2 : 1;                      // uniform
+    const int i = static_cast<int>(threadIdx.x) / each, q = static_cast<int>(threadIdx.x) % each;
+    const uint32_t e = src[min(i, n - 1)];
+    int rank = 0;
+    for (int k = 16 * q; k < n; k += 16 * each) {
+        uvec4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const uvec4*>(src + k + 4 * u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rank += (v[u].x < e ? 1 : 0) + (v[u].y < e ? 1 : 0) + (v[u].z < e ? 1 : 0) + (v[u].w < e ? 1 : 0);
+    }
+    if (each >= 2) rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, false);      // quad_perm [1,0,3,2]
+    if (each >= 4) rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, false);      // quad_perm [2,3,0,1]
+    if (i < n && q == 0)
+        order[rank] = make_int2(static_cast<int>(e & ((1u << pl.pos_bits) - 1u)),
+                                static_cast<int>(sort_mix((e >> pl.pos_bits) << pl.part_bits | static_cast<unsigned>(part), pl.part_bits)));
+}
+
 __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restrict__ order, uint32_t* __restrict__ spill,
                                               const int32_t* __restrict__ tokens, int rows, const EmbSortPlan& pl,
                                               int vocab, int pad_idx)
@@ -260,13 +298,9 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
             live += static_cast<int>(key[u]) >= 0 ? 1 : 0;
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        mine += __shfl_xor(mine, o);
-        below += __shfl_xor(below, o);
-        live += __shfl_xor(live, o);
-    }
-    if (lane == 0) { sums[wave] = mine; sums[4 + wave] = below; sums[8 + wave] = live; }
+    // a lane has at most 64 of each, a wave 4096: two of the sums share a register
+    const int mine_upto = wave_scan(mine), others = wave_total(wave_scan(below | live << 16));
+    if (lane == 0) { sums[wave] = wave_total(mine_upto); sums[4 + wave] = others & 0xFFFF; sums[8 + wave] = others >> 16; }
     __syncthreads();
     int to = 0, n = 0, base = 0, all = 0;                        // the wave's first place in the part; the part's size and begin; live tokens
 #pragma unroll
@@ -279,19 +313,24 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     }
     unsigned frequent = kNoKey - 1u;                             // no id
     int tf = 0;                                                  // its first place for the wave, behind the n others
-    const bool heavy = n > kSortHeavy;                           // uniform over the workgroup
+    int lane_to = mine_upto - mine;                              // the lane's first place among the wave's, in any order
+    const bool heavy = n > kSortRank;                            // uniform over the workgroup
     if (heavy) {
         unsigned met = kNoKey;                                   // the first id of the part that the lane holds
 #pragma unroll
         for (int u = U - 1; u >= 0; --u) met = member(key[u]) ? key[u] : met;
-        int votes = 0;
-#pragma unroll 4
-        for (int l = 0; l < kWave; ++l) votes += met == static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(met), l)) ? 1 : 0;
-        if (met == kNoKey) votes = 0;
-        int most = votes;
+        // each of four lanes spread over the wave proposes its own; the one that most lanes met is the wave's
+        const uint64_t has = __ballot(met != kNoKey);
+        int most = 0;
+        unsigned elect = kNoKey;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
-        const unsigned elect = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(met), __builtin_ctzll(__ballot(votes == most))));
+        for (int c = 0; c < 4; ++c) {
+            const uint64_t from = has >> (16 * c) << (16 * c);
+            if (from == 0) continue;                             // uniform over the wave
+            const unsigned id = static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(met), __builtin_ctzll(from)));
+            const int votes = __popcll(__ballot(met == id));
+            if (votes > most) { most = votes; elect = id; }
+        }
         __syncthreads();                                         // everyone has read the sums
         if (lane == 0) { sums[wave] = most; sums[4 + wave] = static_cast<int>(elect); }
         __syncthreads();
@@ -305,9 +344,9 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
 #pragma unroll
             for (int u = 0; u < U; ++u) c += key[u] == frequent ? 1 : 0;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-        if (lane == 0) sums[8 + wave] = c;
+        const int c_upto = wave_scan(c);
+        lane_to -= c_upto - c;
+        if (lane == 0) sums[8 + wave] = wave_total(c_upto);
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -319,7 +358,8 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     }
     uint32_t* big0 = spill + base;                               // parts are disjoint: base + n <= live tokens <= rows
     uint32_t* big1 = spill + rows + base;
-    const bool fits = n <= kSortLds;                             // uniform over the workgroup
+    const bool fits = n <= kSortLds, rank = n <= kSortRank;      // uniform over the workgroup
+    lane_to += to;
     const uint64_t before = (1ull << lane) - 1ull;
     auto keep = [&](unsigned k, bool in, int pos) {
         const uint64_t m = __ballot(in);
@@ -335,30 +375,38 @@ __device__ __forceinline__ void emb_sort_body(char* lds, int part, int2* __restr
     };
     for (int r0 = 0; r0 < rounds; r0 += U) {
         if (rounds > U && (r0 > 0 || !heavy)) load(r0);          // up to U rounds they are still here
-        if (!heavy) {
+        if (heavy) {                                             // the frequent id's positions, ascending
+            const int id = static_cast<int>(sort_mix(frequent, pl.part_bits));
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (u % 8 == 0 && r0 + u >= rounds) break;       // uniform
-                keep(key[u], member(key[u]), first + (r0 + u) * kWave);
+                const bool out = key[u] == frequent;
+                const uint64_t m = __ballot(out);
+                if (out) order[base + n + tf + __popcll(m & before)] = make_int2(first + (r0 + u) * kWave, id);
+                tf += __popcll(m);
+                key[u] = out ? kNoKey : key[u];
             }
-        } else {
-            const int2 entry = make_int2(0, static_cast<int>(sort_mix(frequent, pl.part_bits)));
+        }
+        if (rank) {                                              // no order needed: a lane writes its own one after the other
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (u % 8 == 0 && r0 + u >= rounds) break;
-                const int pos = first + (r0 + u) * kWave;
-                const bool out = key[u] == frequent;
-                const uint64_t m = __ballot(out);
-                if (out) order[base + n + tf + __popcll(m & before)] = make_int2(pos, entry.y);
-                tf += __popcll(m);
-                keep(key[u], member(key[u]) & !out, pos);
+                if (member(key[u])) in_lds[lane_to++] = (key[u] >> pl.part_bits) << pl.pos_bits | static_cast<uint32_t>(first + (r0 + u) * kWave);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (u % 8 == 0 && r0 + u >= rounds) break;
+                keep(key[u], member(key[u]), first + (r0 + u) * kWave);
             }
         }
     }
+    if (rank && threadIdx.x < 16) in_lds[n + threadIdx.x] = kNoKey;
     for (int i = all + part * 256 + static_cast<int>(threadIdx.x); i < rows; i += parts * 256)
         order[i] = make_int2(0, static_cast<int>(kPadKey));
     __syncthreads();
-    if (fits) emb_sort_part(cnt, in_lds, in_lds + kSortLds, n, part, order + base, pl);
+    if (rank) emb_rank_part(in_lds, n, part, order + base, pl);
+    else if (fits) emb_sort_part(cnt, in_lds, in_lds + kSortLds, n, part, order + base, pl);
     else emb_sort_part(cnt, big0, big1, n, part, order + base, pl);
 }
 
@@ -669,11 +717,12 @@ __global__ __launch_bounds__(256) void emb_combine(T* __restrict__ demb, const f
 }
 
 // dP[l,:] += sum over the batch.  256 threads own W packs of one position; 256 / W groups of W lanes take every
-// (256 / W)-th sentence each (four loads in flight per lane) and their partial sums are added in group order, so the
+// (256 / W)-th sentence each (four or eight loads in flight per lane) and their partial sums are added in group order, so the
 // result does not depend on timing.  W = 64 up to 16 sentences (one trip of 4 x 4 loads), and where there are many positions
 // to stream (fp32, 20 x 900, hidden 1600: 33 us, 59 as W = 16).  Otherwise 16 lanes per group, four times the sentences in
-// flight and four times the workgroups: with few positions and long batches the serial trips were the whole time
-// (250 sentences of 77, hidden 512: 48 us, now 20.6; 100 of 20, hidden 1024: 22 with the rank count, now 11.8).
+// flight and four times the workgroups: with few positions and long batches the serial trips were the whole time.  Whole
+// backward in us with a token's look before its row's load, and now: 600 sentences of 17, hidden 512 41.6 / 24.8; 333 of 29, 1960 41.0 / 32.8;
+// 300 of 50, 640 39.5 / 35.3.
 constexpr int kDposWideBatch = 16, kDposManyUnits = 1024;
 template <int W> constexpr int dpos_lds_floats() { return (256 / W - 1) * 8 * W; }
 constexpr int kEmbLds = dpos_lds_floats<16>() * 4 > kSortLdsBytes ? dpos_lds_floats<16>() * 4 : kSortLdsBytes;
@@ -683,26 +732,30 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
                                               const int32_t* __restrict__ tokens, int batch, int len,
                                               const RowPackIO<T, RAG>& io, int vocab, int pad_idx, const DropoutParams& d)
 {
-    constexpr int U = 4, G = 256 / W;
+    constexpr int U = W == 16 ? 8 : 4, G = 256 / W;              // (600 sentences of 17, hidden 512: 24.8 us, 26.6 with four as W = 16)
     const int lane = threadIdx.x % W, grp = threadIdx.x / W;
     const int cp = cb * W + lane;
     const bool active = cp < io.ppr;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (active) {
+        // the next trip's tokens are loaded ahead, without conditions: a load behind a look at its token, one sentence after the
+        // other, paid a token's latency each
+        int next[U];
+        auto fetch = [&](int b0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) next[u] = tokens[static_cast<int64_t>(min(b0 + u * G, batch - 1)) * len + l];
+        };
+        fetch(grp);
         for (int b0 = grp; b0 < batch; b0 += G * U) {
             RawPack<T> raw[U];
             bool ok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int b = b0 + u * G;
-                ok[u] = false;
-                if (b < batch) {
-                    const int64_t t = static_cast<int64_t>(b) * len + l;
-                    ok[u] = !emb_is_pad(tokens[t], vocab, pad_idx);
-                    if (ok[u]) raw[u] = io.template ahead<true>(dy, t, cp);
-                }
-                if (!ok[u]) raw[u] = zero_raw<T>();
+                ok[u] = (b0 + u * G < batch) & !emb_is_pad(next[u], vocab, pad_idx);
+                if (ok[u]) raw[u] = io.template ahead<true>(dy, static_cast<int64_t>(b0 + u * G) * len + l, cp);
+                else raw[u] = zero_raw<T>();
             }
+            if (b0 + G * U < batch) fetch(b0 + G * U);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (!ok[u]) continue;

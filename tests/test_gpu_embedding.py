@@ -216,3 +216,34 @@ def test_embedding_bwd_ids_of_31_bits(tokens):
     assert_close_store(got, np.asarray(inc_e).reshape(-1, 1)[PAD + 1:], dt, "demb")
     assert_close_store(dpos, inc_p, dt, "dpos")
     assert int((demb != 0).sum()) <= len(ids)
+
+
+# one class at the edges of the sort by counting (1, 2 or 4 threads per entry up to 64, 128 and 256 entries; from 257 on an id is taken out and
+# what is left counted or radix-sorted), with 64 classes (4096 tokens) and 128 (8200: both halves of the token walk), ids met in no order
+@pytest.mark.parametrize("tokens,parts", [(4096, 64), (8200, 128)])
+@pytest.mark.parametrize("n,frequent", [(1, 0), (2, 0), (15, 0), (16, 0), (17, 0), (64, 0), (65, 0), (128, 0), (129, 0), (255, 3), (256, 0), (256, 256), (257, 0),
+                                        (257, 1), (257, 257), (400, 143), (400, 144), (600, 344)])
+def test_embedding_bwd_class_sorted_by_counting(n, frequent, tokens, parts):
+    B, H, V = 2, 16, parts * 1200
+    d = dev()
+    r = np.random.default_rng(n * 7 + frequent + tokens)
+    bits = parts.bit_length() - 1
+    mix = lambda w: (w ^ (w >> bits) ^ (w >> (2 * bits))) & (parts - 1)
+    ids = np.arange(V)
+    mine, others = r.permutation(ids[mix(ids) == 5]), ids[mix(ids) == 6]
+    tok = np.repeat(r.choice(others, 100, replace=False), -(-tokens // 100))[:tokens].astype(np.int32)       # somewhere else
+    at = r.permutation(tokens)[:n]
+    tok[at[:frequent]] = mine[0]
+    tok[at[frequent:]] = mine[1 + np.arange(n - frequent) % (len(mine) - 1)] if n - frequent < 300 else mine[1 + r.integers(0, len(mine) - 1, n - frequent)]
+    tok = tok.reshape(B, tokens // B)
+    dy = encode(r.standard_normal((tokens, H), dtype=np.float32), "f32")
+    demb = torch.zeros((V, H), dtype=torch.float32, device=d)
+    L.lsq_embedding_bwd(demb, None, to_torch(dy, "f32", d), torch.from_numpy(tok).to(d), V, 1.0, 0.0, 1, 0)
+    want = np.zeros((V, H))
+    np.add.at(want, tok.reshape(-1), np.asarray(dy, dtype=np.float64).reshape(tokens, H))
+    count = np.bincount(tok.reshape(-1), minlength=V)[:, None]
+    # each addition rounds once: 2^-24 of a partial sum of at most sqrt-like size; 4 sigma inputs bound a sum of k by 4 k
+    assert (np.abs(demb.cpu().numpy() - want) <= 2.0 ** -24 * 4 * count * np.maximum(count - 1, 0)).all()
+    again = torch.zeros_like(demb)
+    L.lsq_embedding_bwd(again, None, to_torch(dy, "f32", d), torch.from_numpy(tok).to(d), V, 1.0, 0.0, 1, 0)
+    assert torch.equal(again, demb)

@@ -8,8 +8,7 @@
 // dropout mask is rebuilt from the Philox counter of the pack in both directions;
 // backward recomputes the activation slope from the saved pre-activation input
 // and accumulates dbias per lane (no atomics; partial rows + ordered second stage).
-// HBM traffic: forward 2 tensors, backward 3.  Rows of up to 32 packs, and rows that are not whole
-// packs, take the flat walk of host.hpp instead.
+// HBM traffic: forward 2 tensors, backward 3.  Rows of up to 32 packs take the flat walk of host.hpp instead.
 #include "host.hpp"
 
 namespace lsq {
@@ -79,83 +78,94 @@ template <int ACT> __device__ __forceinline__ float act_slope(float z)
     }
 }
 
-template <typename T, int ACT, bool HAS_BIAS, bool DROP>
+// keep / scale of the pack at flat element e (lane i of a wave holding pack i of its row if RAG)
+template <bool RAG>
+__device__ __forceinline__ void bad_factors(const DropoutParams& d, int64_t e, float (&k)[8])
+{
+    if constexpr (RAG) dropout_factors8_row(d, static_cast<uint64_t>(e), k);
+    else dropout_factors8(d, static_cast<uint64_t>(e) >> 3, k);
+}
+
+// RAG: rows that are not whole packs, walked in packs counted from the row's start (RowPackIO); a wave then holds kRagLanes packs and
+// all its lanes stay, because a pack's dropout words come from two lanes.  Forward / backward in us, the flat walk in brackets: 8192 x 1281
+// bf16 GELU with dropout 16.0 / 27.2 (19.1 / 41.9: a gather per bias element, column sums through LDS), 600 x 16001 14.2 / 22.8
+// (18.6 / 98.6), 500 x 1027 fp16 ReLU 3.4 / 7.2 (7.1 / 13.7), 2000 x 5001 f32 without dropout 21.0 / 29.5 (34.2 / 69.4).
+template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG>
 __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T* __restrict__ bias, int64_t rows,
-                                                    int ppr, DropoutParams d)
+                                                    RowPackIO<T, RAG> io, DropoutParams d)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cp = blockIdx.x * 64 + lane;
-    if (cp >= ppr) return;
+    const int col = blockIdx.x * (RAG ? kRagLanes : 64) + lane, cp = RAG ? min(col, io.ppr - 1) : col;
+    const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
+    if (!RAG && !mine) return;
     float b[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if constexpr (HAS_BIAS) load8<T>(bias + static_cast<int64_t>(cp) * kPack, b);
+    if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, cp), b);
     const int64_t stride = static_cast<int64_t>(gridDim.y) * kBadWaves;
     // the pack of the next row is loaded before this row's is used
     int64_t r = static_cast<int64_t>(blockIdx.y) * kBadWaves + wave;
-    RawPack<T> nx = r < rows ? load_raw<T, kNT>(x + (r * ppr + cp) * kPack) : zero_raw<T>();
+    RawPack<T> nx = r < rows ? io.template ahead<kNT>(x, r, cp) : zero_raw<T>();
     for (; r < rows; r += stride) {
         const RawPack<T> cx = nx;
-        if (r + stride < rows) nx = load_raw<T, kNT>(x + ((r + stride) * ppr + cp) * kPack);
-        const int64_t pack = r * ppr + cp;
+        if (r + stride < rows) nx = io.template ahead<kNT>(x, r + stride, cp);
         float xf[8], k[8];
-        if constexpr (DROP) dropout_factors8(d, static_cast<uint64_t>(pack), k);
-        unpack<T>(cx, xf);
+        if constexpr (DROP) bad_factors<RAG>(d, io.element(r, col), k);
+        unpack<T>(io.settle(cx, cp), xf);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float a = act_value<ACT>(xf[j] + b[j]);
             xf[j] = DROP ? a * k[j] : a;
         }
-        store8<T, kNT>(out + pack * kPack, xf);
+        if (mine) io.template store<kNT>(out, r, cp, xf);
     }
 }
 
-template <typename T, int ACT, bool HAS_BIAS, bool DROP>
+template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG>
 __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ partial, const T* dy, const T* x,
-                                                    const T* __restrict__ bias, int64_t rows, int ppr, DropoutParams d)
+                                                    const T* __restrict__ bias, int64_t rows, RowPackIO<T, RAG> io, DropoutParams d)
 {
     __shared__ float sm[kBadWaves][8][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cp = blockIdx.x * 64 + lane;
-    const bool active = cp < ppr;
+    const int col = blockIdx.x * (RAG ? kRagLanes : 64) + lane, cp = RAG ? min(col, io.ppr - 1) : col;
+    const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const int64_t stride = static_cast<int64_t>(gridDim.y) * kBadWaves;
-    if (active) {
+    if (RAG || mine) {
         float b[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if constexpr (HAS_BIAS) load8<T>(bias + static_cast<int64_t>(cp) * kPack, b);
+        if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, cp), b);
         // the packs of the next row are loaded before this row's are used, and the dropout factors, which need
         // no data, are drawn while the loads are in flight
         int64_t r = static_cast<int64_t>(blockIdx.y) * kBadWaves + wave;
         RawPack<T> ng = zero_raw<T>(), nx = zero_raw<T>();
         if (r < rows) {
-            ng = load_raw<T, kNT>(dy + (r * ppr + cp) * kPack);
-            nx = load_raw<T, kNT>(x + (r * ppr + cp) * kPack);
+            ng = io.template ahead<kNT>(dy, r, cp);
+            nx = io.template ahead<kNT>(x, r, cp);
         }
         for (; r < rows; r += stride) {
             const RawPack<T> cg = ng, cx = nx;
             const int64_t rn = r + stride;
             if (rn < rows) {
-                ng = load_raw<T, kNT>(dy + (rn * ppr + cp) * kPack);
-                nx = load_raw<T, kNT>(x + (rn * ppr + cp) * kPack);
+                ng = io.template ahead<kNT>(dy, rn, cp);
+                nx = io.template ahead<kNT>(x, rn, cp);
             }
-            const int64_t pack = r * ppr + cp;
             float g[8], xf[8], k[8];
-            if constexpr (DROP) dropout_factors8(d, static_cast<uint64_t>(pack), k);
-            unpack<T>(cg, g);
-            unpack<T>(cx, xf);
+            if constexpr (DROP) bad_factors<RAG>(d, io.element(r, col), k);
+            unpack<T>(io.settle(cg, cp), g);
+            unpack<T>(io.settle(cx, cp), xf);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float s = act_slope<ACT>(xf[j] + b[j]);
                 g[j] = DROP ? g[j] * k[j] * s : g[j] * s;
                 acc[j] += g[j];
             }
-            store8<T, kNT>(dx + pack * kPack, g);
+            if (mine) io.template store<kNT>(dx, r, cp, g);
         }
     }
     if (partial == nullptr) return;        // uniform over the grid
 #pragma unroll
     for (int j = 0; j < 8; ++j) sm[wave][j][lane] = acc[j];
     __syncthreads();
-    if (wave == 0 && active) {
-        float* dst = partial + static_cast<int64_t>(blockIdx.y) * ppr * kPack + static_cast<int64_t>(cp) * kPack;
+    if (wave == 0 && mine) {
+        float* dst = partial + static_cast<int64_t>(blockIdx.y) * io.hidden + cp * kPack;
         float s[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -164,7 +174,13 @@ __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ p
             for (int w = 1; w < kBadWaves; ++w) t += sm[w][j][lane];
             s[j] = t;
         }
-        store8<float>(dst, s);
+        if constexpr (RAG) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (cp * kPack + j < io.hidden) dst[j] = s[j];
+        } else {
+            store8<float>(dst, s);
+        }
     }
 }
 
@@ -248,18 +264,22 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
     const T* xp = static_cast<const T*>(x);
     const T* bp = static_cast<const T*>(bias);
     if (!bad_is_flat(hidden)) {
-        const int ppr = hidden / kPack;
+        const int cb = bad_col_blocks(hidden);
         // two rows per wave: 28.1 / 23.1 us at 8192 x 5120 / 4096 x 4096 against 29.0 / 23.8 with four and 28.1 / 24.3 with one
         // (one where those workgroups are few: 512 x 2048 f32 3.5 against 3.8 us, 2694 x 1392 5.4 against 5.9; 2200 x 2048 5.5 against 5.2)
         int64_t rb = ceil_div(rows, 2 * kBadWaves);
-        if (rb * ceil_div(ppr, 64) <= 1024) rb = ceil_div(rows, kBadWaves);
+        if (rb * cb <= 1024) rb = ceil_div(rows, kBadWaves);
         if (rb > 8192) rb = 8192;
-        const dim3 grid(static_cast<unsigned>(ceil_div(ppr, 64)), static_cast<unsigned>(rb)), block(256);
+        const dim3 grid(static_cast<unsigned>(cb), static_cast<unsigned>(rb)), block(256);
+#define LSQ_BAD_FWD(BIAS, DROP)                                                                                                            \
+        if (hidden % kPack == 0) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, true>(hidden), d)
         const bool drop = d.on != 0;
-        if (bp && drop) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, true, true>), grid, block, 0, s, o, xp, bp, rows, ppr, d);
-        else if (bp) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, true, false>), grid, block, 0, s, o, xp, bp, rows, ppr, d);
-        else if (drop) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, false, true>), grid, block, 0, s, o, xp, bp, rows, ppr, d);
-        else hipLaunchKernelGGL((bad_fwd_cols<T, ACT, false, false>), grid, block, 0, s, o, xp, bp, rows, ppr, d);
+        if (bp && drop) { LSQ_BAD_FWD(true, true); }
+        else if (bp) { LSQ_BAD_FWD(true, false); }
+        else if (drop) { LSQ_BAD_FWD(false, true); }
+        else { LSQ_BAD_FWD(false, false); }
+#undef LSQ_BAD_FWD
     } else {
         launch_flat_packs(BadFwdFlat<T, ACT>{o, xp, bp, hidden, d}, nullptr, nullptr, rows, hidden, s);
     }
@@ -275,15 +295,18 @@ static lsq_status bad_bwd_dispatch(void* dx, float* dbias, const void* dy, const
     const T* xp = static_cast<const T*>(x);
     const T* bp = static_cast<const T*>(bias);
     if (!bad_is_flat(hidden)) {
-        const int ppr = hidden / kPack;
         const int rb = bad_bwd_row_blocks(rows, hidden);
-        const dim3 grid(static_cast<unsigned>(ceil_div(ppr, 64)), static_cast<unsigned>(rb)), block(256);
+        const dim3 grid(static_cast<unsigned>(bad_col_blocks(hidden)), static_cast<unsigned>(rb)), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
+#define LSQ_BAD_BWD(BIAS, DROP)                                                                                                            \
+        if (hidden % kPack == 0) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, true>(hidden), d)
         const bool drop = d.on != 0;
-        if (bp && drop) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, true, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, ppr, d);
-        else if (bp) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, true, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, ppr, d);
-        else if (drop) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, false, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, ppr, d);
-        else hipLaunchKernelGGL((bad_bwd_cols<T, ACT, false, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, ppr, d);
+        if (bp && drop) { LSQ_BAD_BWD(true, true); }
+        else if (bp) { LSQ_BAD_BWD(true, false); }
+        else if (drop) { LSQ_BAD_BWD(false, true); }
+        else { LSQ_BAD_BWD(false, false); }
+#undef LSQ_BAD_BWD
         if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, rb, hidden, s);
     } else {
         launch_flat_packs(BadBwdFlat<T, ACT>{o, g, xp, bp, hidden, d}, dbias, workspace, rows, hidden, s);

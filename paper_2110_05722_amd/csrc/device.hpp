@@ -368,6 +368,26 @@ __device__ __forceinline__ void dropout_keep8(const DropoutParams& d, uint64_t g
     }
 }
 
+// factors from the sixteen 16-bit lanes of two groups, from lane s (0..7) on.  The words are pinned as single registers: left as arrays,
+// `by4 ? w[1] : w[0]` becomes an access by a selected address, which puts the array into LDS or scratch memory (feed-forward
+// forward of 500 x 1027: 16.7 us).
+__device__ __forceinline__ void dropout_lanes8(const DropoutParams& d, unsigned s, uint32_t (&lo)[4], uint32_t (&hi)[4], float (&k)[8])
+{
+    uint32_t l0 = lo[0], l1 = lo[1], l2 = lo[2], l3 = lo[3], h0 = hi[0], h1 = hi[1], h2 = hi[2], h3 = hi[3];
+    asm volatile("" : "+v"(l0), "+v"(l1), "+v"(l2), "+v"(l3), "+v"(h0), "+v"(h1), "+v"(h2), "+v"(h3));
+    const bool by4 = s & 4u, by2 = s & 2u, by1 = s & 1u;
+    const uint32_t a0 = by4 ? l2 : l0, a1 = by4 ? l3 : l1, a2 = by4 ? h0 : l2, a3 = by4 ? h1 : l3;
+    const uint32_t a4 = by4 ? h2 : h0, a5 = by4 ? h3 : h1;
+    const uint32_t b0 = by2 ? a1 : a0, b1 = by2 ? a2 : a1, b2 = by2 ? a3 : a2, b3 = by2 ? a4 : a3, b4 = by2 ? a5 : a4;
+    const uint32_t w[4] = {by1 ? (b0 >> 16) | (b1 << 16) : b0, by1 ? (b1 >> 16) | (b2 << 16) : b1,
+                           by1 ? (b2 >> 16) | (b3 << 16) : b2, by1 ? (b3 >> 16) | (b4 << 16) : b3};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        k[2 * j] = (w[j] & 0xFFFFu) >= d.t16 ? d.scale : 0.0f;
+        k[2 * j + 1] = (w[j] >> 16) >= d.t16 ? d.scale : 0.0f;
+    }
+}
+
 // The factors of the 8 elements from flat element `e` on, at any alignment: the two groups that they touch are drawn and the
 // sixteen 16-bit lanes shifted down by e % 8 (e is the same for all lanes of a row walk up to multiples of 8: the shifts'
 // conditions are uniform).
@@ -377,19 +397,22 @@ __device__ __forceinline__ void dropout_factors8_any(const DropoutParams& d, uin
     uint32_t lo[4], hi[4];
     philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), d.ctr2, d.ctr3, d.key0, d.key1, lo);
     philox4x32_10(static_cast<uint32_t>(g + 1), static_cast<uint32_t>((g + 1) >> 32), d.ctr2, d.ctr3, d.key0, d.key1, hi);
-    const unsigned s = static_cast<unsigned>(e) & 7u;
-    // (scalars, not an array in a loop: selected by element address it would live in scratch memory)
-    const bool by4 = s & 4u, by2 = s & 2u, by1 = s & 1u;
-    const uint32_t a0 = by4 ? lo[2] : lo[0], a1 = by4 ? lo[3] : lo[1], a2 = by4 ? hi[0] : lo[2], a3 = by4 ? hi[1] : lo[3];
-    const uint32_t a4 = by4 ? hi[2] : hi[0], a5 = by4 ? hi[3] : hi[1];
-    const uint32_t b0 = by2 ? a1 : a0, b1 = by2 ? a2 : a1, b2 = by2 ? a3 : a2, b3 = by2 ? a4 : a3, b4 = by2 ? a5 : a4;
-    const uint32_t w[4] = {by1 ? (b0 >> 16) | (b1 << 16) : b0, by1 ? (b1 >> 16) | (b2 << 16) : b1,
-                           by1 ? (b2 >> 16) | (b3 << 16) : b2, by1 ? (b3 >> 16) | (b4 << 16) : b3};
+    dropout_lanes8(d, static_cast<unsigned>(e) & 7u, lo, hi, k);
+}
+
+// The same where lane i of the wave holds pack cp + i of one row: the second group is the next lane's first one, so a lane draws one
+// group and takes the other's words from its neighbour.  All 64 lanes call it; lane 63 has no neighbour and holds no pack
+// of its own (kRagLanes packs per wave).
+constexpr int kRagLanes = 63;
+__device__ __forceinline__ void dropout_factors8_row(const DropoutParams& d, uint64_t e, float (&k)[8])
+{
+    uint32_t lo[4], hi[4];
+    const uint64_t g = e >> 3;
+    philox4x32_10(static_cast<uint32_t>(g), static_cast<uint32_t>(g >> 32), d.ctr2, d.ctr3, d.key0, d.key1, lo);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        k[2 * j] = (w[j] & 0xFFFFu) >= d.t16 ? d.scale : 0.0f;
-        k[2 * j + 1] = (w[j] >> 16) >= d.t16 ? d.scale : 0.0f;
-    }
+    for (int j = 0; j < 4; ++j)      // wave_shl 1
+        hi[j] = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(lo[j]), 0x130, 0xF, 0xF, false));
+    dropout_lanes8(d, static_cast<unsigned>(e) & 7u, lo, hi, k);
 }
 
 // a pack moved down by s elements (0..7), zeros from above

@@ -346,7 +346,9 @@ inline bool bdr_fwd_is_flat(int hidden) { return hidden % kPack != 0 || hidden <
 inline bool bdr_bwd_is_flat(int hidden) { return hidden % kPack != 0 || hidden < 128; }
 // bias + activation + dropout works in column blocks of 64 packs: rows of up to 32 packs take the flat walk
 // (8 columns: 1629 / 10103 us in column blocks at 32 Mi elements, 51 / 95 us flat; 256 columns: 56 / 138 us).
-inline bool bad_is_flat(int hidden) { return hidden % kPack != 0 || hidden <= 256; }
+inline bool bad_is_flat(int hidden) { return hidden <= 256; }
+// column blocks: 64 packs, 63 where rows are not whole packs
+inline int bad_col_blocks(int hidden) { return static_cast<int>(ceil_div(ceil_div(hidden, kPack), hidden % kPack == 0 ? 64 : kRagLanes)); }
 
 // Backward launch shape: column blocks of w packs; row blocks (= partial rows of the column sums) of
 // `trips` consecutive groups of waves * 64 / w rows.

@@ -65,3 +65,29 @@ def test_bias_act_empty():
     dx, dbias = L.lsq_bias_act_dropout_bwd(x, x, None, "gelu", 0.1, 1, 0)
     torch.cuda.synchronize()
     assert out.numel() == 0 and dbias.abs().sum().item() == 0
+
+
+# rows that are not whole packs, in packs counted from the row's start: 63 of them per wave (the 64th lane draws for its neighbour), the cut
+# pack alone in a column block, every remainder; the narrowest that is not walked flat, and the widest that is
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("rows,hidden", [(5, 249), (9, 255), (70, 257), (33, 258), (9, 503), (9, 505), (600, 509), (2049, 511), (3, 1007), (3, 1009), (41, 1014),
+                                         (17, 2013), (1, 4103), (2, 8065)])
+def test_bias_act_dropout_rows_of_any_length(rows, hidden, dt):
+    say(f"[bias_act_dropout] any length rows={rows} hidden={hidden} dt={dt}")
+    t = layer_tensors(CONFIGS[0], dt, rows=rows, hidden=hidden, stream=900 + rows % 83 + hidden)
+    d = dev()
+    x, bias, dy = (to_torch(t[k], dt, d) for k in ("x", "bias", "dy"))
+    for act, p in (("relu", 0.0), ("gelu", 0.3), ("gelu_tanh", 0.1)):
+        out = L.lsq_bias_act_dropout_fwd(x, bias, act, p, 7, hidden)
+        assert_close_store(out, oracle.bias_act_dropout_fwd(t["x"], t["bias"], act, p, 7, hidden, dt), dt, "out", f32_floor=2e-6)
+        dx, dbias = L.lsq_bias_act_dropout_bwd(dy, x, bias, act, p, 7, hidden)
+        rdx, rdb = oracle.bias_act_dropout_bwd(t["dy"], t["x"], t["bias"], act, p, 7, hidden, dt)
+        assert_close_store(dx, rdx, dt, "dx", f32_floor=4e-6)
+        assert_close_f32(dbias, rdb, "dbias", floor=1e-6 * np.sqrt(rows) * 4)
+        # in place, and without the column sums or the bias
+        same, _ = L.lsq_bias_act_dropout_bwd(dy.clone(), x, bias, act, p, 7, hidden, want_dbias=False)
+        over = x.clone()
+        L.lsq_bias_act_dropout_fwd(over, bias, act, p, 7, hidden, out=over)
+        assert torch.equal(same, dx) and torch.equal(over, out)
+        nb = L.lsq_bias_act_dropout_fwd(x, None, act, p, 7, hidden)
+        assert_close_store(nb, oracle.bias_act_dropout_fwd(t["x"], None, act, p, 7, hidden, dt), dt, "out(no bias)", f32_floor=2e-6)

@@ -21,6 +21,7 @@ extern "C" size_t lsq_workspace_bytes(int32_t op, int64_t rows, int32_t cols)
             // one [cols] fp32 partial row (dbias) per row block
             if (!bdr_bwd_is_flat(cols))
                 return static_cast<size_t>(bdr_bwd_plan(rows, cols).row_blocks) * static_cast<size_t>(cols) * sizeof(float);
+            if (bdr_is_rag(cols)) return static_cast<size_t>(bdr_rag_row_blocks(rows, cols)) * static_cast<size_t>(cols) * sizeof(float);
             return flat_workspace_bytes(rows, cols);        // one per workgroup of the flat walk
         case LSQ_OP_BIAS_ACT_DROPOUT_BWD:
             if (bad_is_flat(cols)) return flat_workspace_bytes(rows, cols);

@@ -1,7 +1,7 @@
 // Fused bias + dropout + residual, forward and backward (Sec. IV-A of the paper,
 // Transformer layers: "bias adding, dropout, and residual" in one launch).
 //
-// Layout of the fast path (hidden % 8 == 0): W lanes of a wave (W = 32 or 16, the wider
+// Layout for rows of whole packs (hidden % 8 == 0): W lanes of a wave (W = 32 or 16, the wider
 // that divides the packs of a row, so no lane idles on a ragged last column block) own W
 // consecutive packs of one row and the wave covers 64 / W rows at a time; a workgroup's column
 // block is fixed, so the bias pack is loaded once into registers, every access is a 128-bit one,
@@ -142,6 +142,77 @@ __global__ __launch_bounds__(64 * kBdrBwdWaves) void bdr_bwd_cols(T* dx, float* 
     }
 }
 
+// ---- rows that are not whole packs, walked in packs counted from the row's start (RowPackIO): a wave holds kRagLanes packs of a row, all its
+// lanes stay, because a pack's dropout words come from two lanes.  Forward / backward in us, the flat walk in brackets: 8192 x 1281 bf16 with
+// dropout 15.9 / 18.0 (19.2 / 25.0), 2000 x 5001 14.6 / 14.8 (19.4 / 32.2), 600 x 7001 fp16 8.9 / 11.1 (10.6 / 25.4), 500 x 259 f32 3.2 / 7.1 (8.9 / 9.1).
+constexpr int kBdrRagWaves = 4;
+
+template <typename T, bool DROP>
+__global__ __launch_bounds__(64 * kBdrRagWaves) void bdr_fwd_rag(T* out, const T* x, const T* __restrict__ bias, const T* res,
+                                                                 int64_t rows, RowPackIO<T, true> io, DropoutParams d)
+{
+    const int lane = threadIdx.x & 63, col = blockIdx.x * kRagLanes + lane, cp = min(col, io.ppr - 1);
+    RawPack<T> braw = bias ? io.template ahead<false>(bias, 0, cp) : zero_raw<T>();      // uniform
+    for (int64_t r = static_cast<int64_t>(blockIdx.y) * kBdrRagWaves + (threadIdx.x >> 6); r < rows; r += static_cast<int64_t>(gridDim.y) * kBdrRagWaves) {
+        const RawPack<T> xr = io.template ahead<kNT>(x, r, cp), rr = io.template ahead<kNT>(res, r, cp);
+        float xf[8], rf[8], b[8], k[8];
+        if constexpr (DROP) dropout_factors8_row(d, static_cast<uint64_t>(io.element(r, col)), k);
+        unpack<T>(io.settle(xr, cp), xf);
+        unpack<T>(io.settle(rr, cp), rf);
+        opaque<T>(braw);
+        unpack<T>(io.settle(braw, cp), b);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float z = xf[j] + b[j];
+            rf[j] = DROP ? fmaf(z, k[j], rf[j]) : rf[j] + z;
+        }
+        pin_f32(rf);
+        if (col < io.ppr && lane < kRagLanes) io.template store<kNT>(out, r, cp, rf);
+    }
+}
+
+template <typename T, bool DROP>
+__global__ __launch_bounds__(64 * kBdrRagWaves) void bdr_bwd_rag(T* dx, float* __restrict__ partial, const T* dy, int64_t rows,
+                                                                 RowPackIO<T, true> io, DropoutParams d)
+{
+    __shared__ float sm[kBdrRagWaves][8][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = blockIdx.x * kRagLanes + lane, cp = min(col, io.ppr - 1);
+    const bool mine = col < io.ppr && lane < kRagLanes;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    const int64_t stride = static_cast<int64_t>(gridDim.y) * kBdrRagWaves;
+    int64_t r = static_cast<int64_t>(blockIdx.y) * kBdrRagWaves + wave;
+    RawPack<T> nxt = r < rows ? io.template ahead<kNT>(dy, r, cp) : zero_raw<T>();
+    for (; r < rows; r += stride) {
+        const RawPack<T> cur = nxt;
+        if (r + stride < rows) nxt = io.template ahead<kNT>(dy, r + stride, cp);
+        float g[8], k[8];
+        if constexpr (DROP) dropout_factors8_row(d, static_cast<uint64_t>(io.element(r, col)), k);
+        unpack<T>(io.settle(cur, cp), g);
+        if constexpr (DROP) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) g[j] *= k[j];
+        }
+        pin_f32(g);
+        if (mine) io.template store<kNT>(dx, r, cp, g);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] += g[j];
+    }
+    if (partial == nullptr) return;        // uniform over the grid
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sm[wave][j][lane] = acc[j];
+    __syncthreads();
+    if (wave == 0 && mine) {
+        float* dst = partial + static_cast<int64_t>(blockIdx.y) * io.hidden + cp * kPack;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            float t = sm[0][j][lane];
+#pragma unroll
+            for (int w = 1; w < kBdrRagWaves; ++w) t += sm[w][j][lane];
+            if (cp * kPack + j < io.hidden) dst[j] = t;
+        }
+    }
+}
+
 // ---- any hidden (rows are not a whole number of packs): the operators for flat_packs_kernel
 template <typename T>
 struct BdrFwdFlat {
@@ -232,6 +303,13 @@ static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, c
         }
         LSQ_BDR_FWD(32) LSQ_BDR_FWD(16)
 #undef LSQ_BDR_FWD
+    } else if (bdr_is_rag(hidden)) {
+        const RowPackIO<T, true> io(hidden);
+        int64_t rb = ceil_div(rows, kBdrRagWaves);
+        if (rb > 8192) rb = 8192;
+        const dim3 grid(static_cast<unsigned>(ceil_div(io.ppr, kRagLanes)), static_cast<unsigned>(rb)), block(64 * kBdrRagWaves);
+        if (d.on) hipLaunchKernelGGL((bdr_fwd_rag<T, true>), grid, block, 0, s, o, xp, bp, rp, rows, io, d);
+        else hipLaunchKernelGGL((bdr_fwd_rag<T, false>), grid, block, 0, s, o, xp, bp, rp, rows, io, d);
     } else {
         launch_flat_packs(BdrFwdFlat<T>{o, xp, bp, rp, hidden, d}, nullptr, nullptr, rows, hidden, s);
     }
@@ -257,6 +335,14 @@ static lsq_status bdr_bwd_dispatch(void* dx, float* dbias, const void* dy, int64
         LSQ_BDR_BWD(32) LSQ_BDR_BWD(16)
         if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, pl.row_blocks, hidden, s);
 #undef LSQ_BDR_BWD
+    } else if (bdr_is_rag(hidden)) {
+        const RowPackIO<T, true> io(hidden);
+        const int rb = bdr_rag_row_blocks(rows, hidden);
+        const dim3 grid(static_cast<unsigned>(ceil_div(io.ppr, kRagLanes)), static_cast<unsigned>(rb)), block(64 * kBdrRagWaves);
+        float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
+        if (d.on) hipLaunchKernelGGL((bdr_bwd_rag<T, true>), grid, block, 0, s, o, partial, g, rows, io, d);
+        else hipLaunchKernelGGL((bdr_bwd_rag<T, false>), grid, block, 0, s, o, partial, g, rows, io, d);
+        if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, rb, hidden, s);
     } else {
         // every pack is read and written by one thread, which also hands its fp32 results to the column sums: in place is fine
         launch_flat_packs(BdrBwdFlat<T>{o, g, d}, dbias, workspace, rows, hidden, s);

@@ -143,7 +143,7 @@ inline void launch_colsum_finalize(float* out0, float* out1, int split, const fl
         hipLaunchKernelGGL((colsum_finalize_kernel<false>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
 }
 
-// ---- rows that are not a whole number of packs (hidden % 8 != 0): element-wise operators
+// ---- short rows (up to 256 columns) of the element-wise operators
 // The tensor is walked as ONE flat array in aligned packs (a pack may straddle two rows), so every
 // access stays a 128-bit one and a pack still costs one Philox call (the dropout contract counts
 // packs over the flat tensor).  F supplies the operator:
@@ -153,13 +153,11 @@ inline void launch_colsum_finalize(float* out0, float* out1, int split, const fl
 // With COLS the fp32 results also feed column sums (a bias gradient): a workgroup parks the
 // results of a trip (256 threads x 4 packs, consecutive) in LDS, then every thread adds up, in
 // ascending element order, the entries of the columns it owns (c = thread, thread + 256, ...); the
-// owner alone touches a column's accumulator (in LDS up to 8192 columns, else straight in the
-// workgroup's partial row), so no atomics and a fixed order.  One partial row per workgroup, summed
+// owner alone touches a column's accumulator, so no atomics and a fixed order.  One partial row per workgroup, summed
 // by colsum_finalize_kernel.
 constexpr int kFlatPacks = 4;                                    // packs per thread and trip
 constexpr int kFlatChunk = 256 * kFlatPacks * kPack;             // elements per trip
 constexpr int kFlatMaxBlocks = 512;                              // partial rows at most
-constexpr int kFlatLdsColumns = 8192;                            // accumulators in LDS up to this row length
 
 struct FlatPlan { int blocks, trips; };
 inline FlatPlan flat_plan(int64_t total, bool cols)
@@ -174,14 +172,14 @@ inline FlatPlan flat_plan(int64_t total, bool cols)
     return p;
 }
 
-template <typename F, bool COLS, bool ACC_LDS>
+template <typename F, bool COLS>
 __global__ __launch_bounds__(256) void flat_packs_kernel(F f, float* __restrict__ partial, int64_t total, int hidden, int trips)
 {
-    extern __shared__ float flat_lds[];        // COLS: [kFlatChunk] results of the trip (, [hidden] accumulators)
+    extern __shared__ float flat_lds[];        // COLS: [kFlatChunk] results of the trip, [hidden] accumulators
     const int tid = threadIdx.x;
     float* acc = nullptr;
     if constexpr (COLS) {
-        acc = ACC_LDS ? flat_lds + kFlatChunk : partial + static_cast<int64_t>(blockIdx.x) * hidden;
+        acc = flat_lds + kFlatChunk;
         for (int c = tid; c < hidden; c += 256) acc[c] = 0.0f;     // read again by this thread only
     }
     for (int t = 0; t < trips; ++t) {
@@ -240,7 +238,7 @@ __global__ __launch_bounds__(256) void flat_packs_kernel(F f, float* __restrict_
             }
         }
     }
-    if constexpr (COLS && ACC_LDS) {
+    if constexpr (COLS) {
         float* prow = partial + static_cast<int64_t>(blockIdx.x) * hidden;
         for (int c = tid; c < hidden; c += 256) prow[c] = acc[c];
     }
@@ -254,16 +252,11 @@ inline void launch_flat_packs(const F& f, float* dbias, void* workspace, int64_t
     const FlatPlan pl = flat_plan(total, dbias != nullptr);
     const dim3 grid(static_cast<unsigned>(pl.blocks)), block(256);
     if (!dbias) {
-        hipLaunchKernelGGL((flat_packs_kernel<F, false, false>), grid, block, 0, s, f, nullptr, total, hidden, 1);
+        hipLaunchKernelGGL((flat_packs_kernel<F, false>), grid, block, 0, s, f, nullptr, total, hidden, 1);
         return;
     }
     float* partial = static_cast<float*>(workspace);
-    if (hidden <= kFlatLdsColumns)
-        hipLaunchKernelGGL((flat_packs_kernel<F, true, true>), grid, block, (kFlatChunk + hidden) * sizeof(float), s, f, partial,
-                           total, hidden, pl.trips);
-    else
-        hipLaunchKernelGGL((flat_packs_kernel<F, true, false>), grid, block, kFlatChunk * sizeof(float), s, f, partial, total,
-                           hidden, pl.trips);
+    hipLaunchKernelGGL((flat_packs_kernel<F, true>), grid, block, (kFlatChunk + hidden) * sizeof(float), s, f, partial, total, hidden, pl.trips);
     launch_colsum_finalize(dbias, dbias, hidden, partial, pl.blocks, hidden, s);
 }
 
@@ -276,12 +269,15 @@ inline size_t flat_workspace_bytes(int64_t rows, int32_t hidden)
 // row, rows a workgroup holds at a time, workgroups (= partial rows of the column sums).
 constexpr int kLnSpanThreads = 768;          // three waves per SIMD; wider rows take up to 1024 threads
 struct LnBwdPlan { int lanes, slots, blocks; };
-inline bool ln_bwd_spans(int32_t hidden) { return hidden % kPack == 0 && hidden >= 512 && hidden <= 8192; }
+// rows that are not whole packs: both directions, from 129 columns on
+inline bool ln_rag_spans(int32_t hidden) { return hidden % kPack != 0 && hidden > 128 && hidden < 8192; }
+inline bool ln_bwd_spans(int32_t hidden) { return ln_rag_spans(hidden) || (hidden % kPack == 0 && hidden >= 512 && hidden <= 8192); }
+inline int ln_span_lanes(int32_t hidden) { return ((hidden + kPack - 1) / kPack + 31) / 32 * 32; }
 inline LnBwdPlan ln_bwd_span_plan(int64_t rows, int32_t hidden)
 {
     constexpr int kMaxBlocks = 256;          // one per compute unit (8192 x 1280 fused: 26.0 us with the second stage, 512 of half the rows: 28.6)
     LnBwdPlan p;
-    p.lanes = (hidden / kPack + 31) / 32 * 32;
+    p.lanes = ln_span_lanes(hidden);
     const bool half_wave = p.lanes % 64 != 0;                     // then rows come in pairs
     // Of the slot counts that give 384..768 threads, the one that leaves the fewest slots idle in the last trip, the larger
     // among equals (8192 x 1024: 4 slots 21.5, 6 slots 23.2 us; 16000 x 640: 8 slots 25.9, 4 slots 27.3 us).  Short batches: no more
@@ -390,6 +386,13 @@ inline int colsum_row_blocks(int64_t rows, int32_t hidden, int target)
     const int64_t most = ceil_div(rows, rows <= 2048 ? 8 : 16);
     if (b > most) b = most;
     return static_cast<int>(b < 1 ? 1 : b);
+}
+// rows that are not whole packs in packs of their own: bias + dropout + residual from 257 columns on (see bad_is_flat)
+inline bool bdr_is_rag(int hidden) { return hidden % kPack != 0 && hidden > 256; }
+inline int bdr_rag_row_blocks(int64_t rows, int32_t hidden)
+{
+    const int b = colsum_row_blocks(rows, hidden, kBdrBwdWorkgroups);
+    return b < kBdrBwdMaxPartials ? b : kBdrBwdMaxPartials;
 }
 inline int bad_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_row_blocks(rows, hidden, kBadBwdWorkgroups); }
 inline int heads_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_row_blocks(rows, hidden, kHeadsBwdWorkgroups); }

@@ -397,24 +397,27 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
 // f32 fused 4000 x 1280: 27.5 -> 23.9 (second stage not counted).  What is left above the copy of the bytes (17 us at 8192 x 1280)
 // is first load, epilogue and partial row.
 // LRC = 64: 512 columns, a row per wave, no exchange.  Partial rows as ln_bwd_kernel's.
-template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP>
+// RAG: rows that are not whole packs, in packs counted from the row's start (RowPackIO; not fused).
+template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP, bool RAG = false>
 __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restrict__ partial, const T* dy,
                                                            const T* __restrict__ x, const T* __restrict__ gamma,
                                                            const float* __restrict__ mean, const float* __restrict__ rstd,
                                                            const T* dres, int64_t rows, int hidden, int lanes, BdrFuse<T> fz)
 {
+    static_assert(!RAG || !FUSE, "the fused boundary is for rows of whole packs");
     constexpr int NACC = FUSE ? 3 : 2;        // column accumulators: dgamma, dbeta (, dbias)
     extern __shared__ float span_lds[];       // the rows' exchange [2][32-lane groups][2], later the slots' [slots / 2][NACC * 8][lanes]
     const int LR = LRC ? LRC : lanes;
     const int slots = blockDim.x / LR;
     const int slot = threadIdx.x / LR, sub = threadIdx.x - slot * LR;
-    const int nv = hidden / kPack;
+    const RowPackIO<T, RAG> io(hidden);
+    const int nv = io.ppr;
     const bool on = sub < nv;
     const float inv_h = 1.0f / static_cast<float>(hidden);
     const int64_t gstride = static_cast<int64_t>(gridDim.x) * slots;
 
     float g8[8];
-    unpack<T>(on ? load_raw<T>(gamma + sub * kPack) : zero_raw<T>(), g8);
+    unpack<T>(on ? io.template load<false>(gamma, 0, sub) : zero_raw<T>(), g8);
     float acc[NACC][8];
 #pragma unroll
     for (int a = 0; a < NACC; ++a)
@@ -429,10 +432,9 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         nmu = 0.0f; nrs = 0.0f;
         if (r < rows) {
             if (on) {
-                const int64_t e = r * hidden + sub * kPack;
-                ndy = load_raw<T, kNT>(dy + e);
-                nx = load_raw<T, kNT>(x + e);
-                if constexpr (HAS_RES) nres = load_raw<T, kNT>(dres + e);
+                ndy = io.template ahead<kNT>(dy, r, sub);
+                nx = io.template ahead<kNT>(x, r, sub);
+                if constexpr (HAS_RES) nres = io.template ahead<kNT>(dres, r, sub);
             }
             nmu = mean[r]; nrs = rstd[r];
         }
@@ -450,8 +452,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         // the two row sums and the column sums; absent packs and rows hold dy = 0
         const float nmr = -mu * rs;
         float gy[8], xh[8], s1 = 0.0f, s2 = 0.0f;
-        unpack<T>(cdy, gy);
-        unpack<T>(cx, xh);
+        unpack<T>(io.settle(cdy, sub), gy);
+        unpack<T>(io.settle(cx, sub), xh);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             xh[j] = fmaf(xh[j], rs, nmr);
@@ -489,9 +491,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         // dx = rstd*(g - (s1 + xhat*s2)/hidden) = g*rstd + xhat*c1 + c0
         const float c0 = -rs * s1 * inv_h, c1 = -rs * s2 * inv_h;
         if (r < rows && on) {
-            const int64_t e = r * hidden + sub * kPack;
             float o[8];
-            if constexpr (HAS_RES) unpack<T>(cres, o);
+            if constexpr (HAS_RES) unpack<T>(io.settle(cres, sub), o);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float v = fmaf(gy[j], rs, fmaf(xh[j], c1, c0));
@@ -499,7 +500,7 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
             }
             pin_f32(o);                       // the fused and the plain kernel round alike
             const RawPack<T> hp = pack_raw<T>(o);
-            store_raw<T, kNT>(dx + e, hp);
+            io.template put<kNT>(dx, r, sub, hp);
             if constexpr (FUSE) {
                 float gq[8];
                 unpack<T>(hp, gq);
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
                     }
                 }
                 pin_f32(gq);
-                store8<T, kNT>(fz.out + e, gq);
+                store8<T, kNT>(fz.out + io.element(r, sub), gq);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[2][j] += gq[j];
             }
@@ -537,7 +538,68 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
     if (slot == 0 && on) {
         float* prow = partial + static_cast<int64_t>(blockIdx.x) * NACC * hidden + sub * kPack;
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) store8<float>(prow + a * hidden, acc[a]);
+        for (int a = 0; a < NACC; ++a) {
+            if constexpr (RAG) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (sub * kPack + j < hidden) prow[a * hidden + j] = acc[a][j];
+            } else {
+                store8<float>(prow + a * hidden, acc[a]);
+            }
+        }
+    }
+}
+
+// Forward of rows that are not whole packs: a row over LR lanes, one pack per lane, as in ln_bwd_span_kernel; mean and variance are
+// two exchanges through LDS (their buffers alternate, so a barrier each is enough).  Forward / backward with residual gradient in us, one wave or
+// workgroup per row with element accesses in brackets: 8192 x 1281 bf16 13.2 / 27.7 (23.5 / 54.9), 3000 x 1999 f32 10.8 / 28.2 (32.6 / 50.9),
+// 600 x 7001 fp16 11.2 / 39.8 (21.0 / 44.6), 6000 x 300 5.8 / 11.4 (6.2 / 25.9), 500 x 259 f32 3.3 / 7.8 (3.5 / 12.2).
+template <typename T, int MAXT>
+__global__ __launch_bounds__(MAXT) void ln_fwd_rag_kernel(T* __restrict__ y, float* __restrict__ mean, float* __restrict__ rstd,
+                                                          const T* __restrict__ x, const T* __restrict__ gamma, const T* __restrict__ beta,
+                                                          int64_t rows, int hidden, float eps, int LR)
+{
+    __shared__ float sums[2][MAXT / 32];
+    const RowPackIO<T, true> io(hidden);
+    const int slots = blockDim.x / LR, slot = threadIdx.x / LR, sub = threadIdx.x - slot * LR;
+    const bool on = sub < io.ppr;
+    const int left = on ? hidden - sub * kPack : 0;                // columns of this pack, 8 or more but for the last
+    const float inv_h = 1.0f / static_cast<float>(hidden);
+    const int64_t gstride = static_cast<int64_t>(gridDim.x) * slots;
+    auto total = [&](float v, float* buf) {
+        v = group_sum<32>(v);
+        if ((threadIdx.x & 31) == 0) buf[threadIdx.x / 32] = v;
+        __syncthreads();
+        const int l = threadIdx.x & 31, groups = LR / 32;
+        return group_sum<32>(l < groups ? buf[slot * groups + l] : 0.0f);
+    };
+    const RawPack<T> gm = on ? io.template ahead<false>(gamma, 0, sub) : zero_raw<T>(), bt = on ? io.template ahead<false>(beta, 0, sub) : zero_raw<T>();
+    int64_t base = static_cast<int64_t>(blockIdx.x) * slots;
+    RawPack<T> nxt = base + slot < rows && on ? io.template ahead<kNT>(x, base + slot, sub) : zero_raw<T>();
+    for (; base < rows; base += gstride) {                         // the same trips for every thread
+        const int64_t r = base + slot;
+        const RawPack<T> cur = nxt;
+        if (r + gstride < rows && on) nxt = io.template ahead<kNT>(x, r + gstride, sub);
+        float v[8], s = 0.0f, q = 0.0f;
+        unpack<T>(io.settle(cur, sub), v);                         // absent columns are zeros: they add nothing to the sum
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += v[j];
+        const float mu = total(s, sums[0]) * inv_h;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            v[j] -= mu;
+            q = j < left ? fmaf(v[j], v[j], q) : q;
+        }
+        const float rs = 1.0f / sqrtf(fmaf(total(q, sums[1]), inv_h, eps));
+        if (r < rows && on) {
+            if (sub == 0) { mean[r] = mu; rstd[r] = rs; }
+            float o[8], g8[8], b8[8];
+            unpack<T>(io.settle(gm, sub), g8);
+            unpack<T>(io.settle(bt, sub), b8);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = fmaf(v[j] * rs, g8[j], b8[j]);
+            io.template store<kNT>(y, r, sub, o);
+        }
     }
 }
 
@@ -805,6 +867,15 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
     // workgroup (0.70 of peak at 12288 columns against 0.53 with the backward's 1024 lanes x 2 packs).  The fused
     // boundary follows (it would be 10 % faster on 1024 lanes, but then no longer bit-identical to the two calls).
     if (sh.lpr > 256) sh = hidden / kPack <= 1536 ? LnShape{256, 6} : LnShape{256, 8};
+    if (ln_rag_spans(hidden)) {
+        const int quarter = 256 / ln_span_lanes(hidden);           // rows at a time: 256 threads, or one row
+        const int lanes = quarter < 2 ? static_cast<int>(ceil_div(ln_span_lanes(hidden), 64)) * 64 : ln_span_lanes(hidden), slots = quarter < 2 ? 1 : quarter / 2 * 2;
+        const int64_t groups = ceil_div(rows, slots);
+        const dim3 g(static_cast<unsigned>(groups <= 768 ? groups : groups <= 16384 ? ceil_div(groups, 2) : 8192)), b(static_cast<unsigned>(slots * lanes));
+        if (b.x <= 512) hipLaunchKernelGGL((ln_fwd_rag_kernel<T, 512>), g, b, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, lanes);
+        else hipLaunchKernelGGL((ln_fwd_rag_kernel<T, 1024>), g, b, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, lanes);
+        return launch_status();
+    }
     if (sh.lpr == 0) {
         // rows too long for the register buckets come in small numbers: a whole workgroup per row
         if (hidden % kPack == 0)
@@ -874,7 +945,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
     const T* gp = static_cast<const T*>(gamma);
     const T* rp = static_cast<const T*>(dres);
     const LnShape sh = ln_shape(hidden);
-    if (sh.lpr == 0) {
+    if (sh.lpr == 0 && !ln_rag_spans(hidden)) {
         const int Pg = ln_bwd_blocks(rows, hidden);
         float* gpartial = static_cast<float*>(workspace);
         if (hidden % kPack == 0)
@@ -922,7 +993,12 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
         if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse); \
         else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);   \
     }
-        if (pl.lanes == 64) { X(64, kLnSpanThreads) }
+        if (ln_rag_spans(hidden)) {
+#define R(H, M) hipLaunchKernelGGL((ln_bwd_span_kernel<T, 0, H, M, false, false, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none)
+            if (rp) { if (block.x <= kLnSpanThreads) R(true, kLnSpanThreads); else R(true, 1024); }
+            else { if (block.x <= kLnSpanThreads) R(false, kLnSpanThreads); else R(false, 1024); }
+#undef R
+        } else if (pl.lanes == 64) { X(64, kLnSpanThreads) }
         else if (block.x <= kLnSpanThreads) { X(0, kLnSpanThreads) }
         else { X(0, 1024) }
 #undef X

@@ -150,3 +150,46 @@ def test_layernorm_fwd_shapes(rows, hidden):
     h3 = L.lsq_bias_dropout_residual_fwd(x, bias, res, 0.2, 5, 1)
     y3, mean3, rstd3 = L.lsq_layernorm_fwd(h3, gamma, beta, EPS)
     assert torch.equal(h, h3) and torch.equal(y2, y3) and torch.equal(mean2, mean3) and torch.equal(rstd2, rstd3)
+
+
+# rows that are not whole packs, one pack per lane: the narrowest and widest, every remainder, one more pack than 32 lanes hold, rows
+# that fill a workgroup and one that does not
+RAG = [(9, 127), (9, 129), (770, 131), (1537, 255), (5, 257), (257, 261), (2, 505), (770, 511), (1025, 513), (40, 1022), (257, 1273), (1, 1281), (515, 2049),
+       (9, 4091), (3, 6137), (300, 6146), (2, 8185), (1, 8191), (3, 8193)]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("rows,hidden", RAG)
+def test_layernorm_rows_of_any_length(rows, hidden, dt):
+    say(f"[layernorm] any length rows={rows} hidden={hidden} dt={dt}")
+    t = _case(rows, hidden, dt)
+    d = dev()
+    x, gamma, beta, dy, res, bias = (to_torch(t[k], dt, d) for k in ("x", "gamma", "beta", "dy", "residual", "bias"))
+    y, mean, rstd = L.lsq_layernorm_fwd(x, gamma, beta, EPS)
+    ry, rmean, rrstd = oracle.layernorm_fwd(t["x"], t["gamma"], t["beta"], EPS, dt)
+    assert_close_store(y, ry, dt, "y")
+    assert_close_f32(mean, rmean, "mean", floor=2e-7)
+    assert_close_f32(rstd, rrstd, "rstd")
+    floor = 1e-6 * np.sqrt(rows) * 4
+    for with_res in (False, True):
+        kept = dict(dres_in=res) if with_res else {}
+        dx, dgamma, dbeta = L.lsq_layernorm_bwd(dy, x, gamma, mean, rstd, **kept)
+        rdx, rdg, rdb = oracle.layernorm_bwd(t["dy"], t["x"], t["gamma"], EPS, dt, dres_in=t["residual"] if with_res else None)
+        assert_close_store(dx, rdx, dt, f"dx(res={with_res})")
+        assert_close_f32(dgamma, rdg, "dgamma", floor=floor)
+        assert_close_f32(dbeta, rdb, "dbeta", floor=floor)
+        over = dy.clone()                                     # in place
+        L.lsq_layernorm_bwd(over, x, gamma, mean, rstd, dx=over, **kept)
+        assert torch.equal(over, dx)
+    # the boundary is the two operators, in these rows too
+    h, y2, mean2, rstd2 = L.lsq_bdr_layernorm_fwd(x, bias, res, gamma, beta, 0.2, 5, 1)
+    h3 = L.lsq_bias_dropout_residual_fwd(x, bias, res, 0.2, 5, 1)
+    assert_close_store(h3, oracle.bias_dropout_residual_fwd(t["x"], t["bias"], t["residual"], 0.2, 5, 1, dt), dt, "h")
+    y3, mean3, rstd3 = L.lsq_layernorm_fwd(h3, gamma, beta, EPS)
+    assert torch.equal(h, h3) and torch.equal(y2, y3) and torch.equal(mean2, mean3) and torch.equal(rstd2, rstd3)
+    dbx, dbias = L.lsq_bias_dropout_residual_bwd(dy, 0.2, 5, 1)
+    rdbx, rdbias = oracle.bias_dropout_residual_bwd(t["dy"], 0.2, 5, 1, dt)
+    assert_close_store(dbx, rdbx, dt, "bdr dx")
+    assert_close_f32(dbias, rdbias, "dbias", floor=2 * floor)
+    over = res.clone()
+    assert torch.equal(L.lsq_bias_dropout_residual_fwd(x, bias, over, 0.2, 5, 1, out=over), h3)

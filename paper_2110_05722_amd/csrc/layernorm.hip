@@ -838,12 +838,13 @@ inline LnShape ln_fwd_shape(int64_t rows, int hidden)
     return s;
 }
 
-inline int ln_fwd_blocks(int64_t rows, int lpr)
+inline int ln_fwd_blocks(int64_t rows, LnShape sh)
 {
     // two row groups per workgroup, the second loaded ahead (one: 11.1, two: 9.2, four: 10.4 us at 8192 x 1280); one where that
-    // leaves compute units idle (512 x 512 f32 fused 5.7 -> 4.7 us, 1000 x 768 6.2 -> 4.7, 4096 x 1024 9.0 -> 8.3)
-    const int64_t groups = ceil_div(rows, static_cast<int64_t>(lpr > 256 ? 1 : 256 / lpr));
-    int64_t b = groups <= 768 ? groups : ceil_div(groups, 2);
+    // leaves compute units idle (512 x 512 f32 fused 5.7 -> 4.7 us, 1000 x 768 6.2 -> 4.7, 4096 x 1024 9.0 -> 8.3; not for the widest rows:
+    // 500 x 8192 f32 11.1 -> 12.9)
+    const int64_t groups = ceil_div(rows, static_cast<int64_t>(256 / sh.lpr));
+    int64_t b = groups <= 768 && (sh.lpr < 256 || sh.vpl < 4) ? groups : ceil_div(groups, 2);
     if (b > 8192) b = 8192;
     if (b < 1) b = 1;
     return static_cast<int>(b);
@@ -889,7 +890,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
                                yp, mean, rstd, xp, gp, bp, rows, hidden, eps);
         return launch_status();
     }
-    const dim3 grid(ln_fwd_blocks(rows, sh.lpr)), block(sh.lpr > 256 ? sh.lpr : 256);
+    const dim3 grid(ln_fwd_blocks(rows, sh)), block(256);
     const BdrFuse<T> none{};
 #define X(L, V)                                                                                              \
     if (sh.lpr == L && sh.vpl == V) {                                                                        \

@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2110_05722_amd as L
 from tests._util import assert_close_store, dev, say, to_np64
-from workloads import CONFIGS, attention_tensors, device_normal, from_torch, to_torch
+from workloads import CONFIGS, attention_tensors, device_normal, encode, from_torch, to_torch
 
 pytestmark = pytest.mark.gpu
 
@@ -273,3 +273,32 @@ def test_softmax_rows_through_lds(dt, B, N, Lq, Lk, mask, p):
             assert_close_store(yd[at], ryd, dt, "y_drop", f32_floor=1e-7)
         rdx = oracle.softmax_bwd(from_torch(dy[at].contiguous(), dt), from_torch(y[at].contiguous(), dt), lens, causal, scale, dt, p, 5, 6, e0=e0)
         assert_close_store(dx[at], rdx, dt, "dx", f32_floor=1e-7)
+
+
+# waves whose rows are all empty leave early and write their rows as one range of zeros: rows of every lane count, whole packs and not,
+# ranges that begin and end anywhere in a pack, an empty tensor beside a full one, and rows above a causal mask's first key
+@pytest.mark.parametrize("dt", ["f16", "f32"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Lq,Lk", [(70, 3), (70, 8), (66, 13), (70, 24), (131, 31), (70, 64), (67, 113), (70, 128), (41, 130), (37, 256), (33, 301), (19, 512), (19, 701),
+                                   (17, 1000), (70, 9)])
+def test_softmax_rows_of_padded_queries(Lq, Lk, causal, dt):
+    say(f"[softmax] padded queries {Lq} x {Lk} causal={causal} {dt}")
+    B, N, p, d = 5, 3, 0.2, dev()
+    r = np.random.default_rng(Lq * 1000 + Lk)
+    xs, dys = (encode(r.standard_normal((B, N, Lq, Lk), dtype=np.float32), dt) for _ in range(2))
+    klen, qlen = np.array([Lk, 1, Lk // 2, Lk, 0], np.int32), np.array([1, Lq, 0, Lq // 2, Lq], np.int32)
+    kl, ql = torch.from_numpy(klen).to(d), torch.from_numpy(qlen).to(d)
+    y, yd = L.lsq_softmax_varlen_fwd(to_torch(xs, dt, d), kl, ql, causal, 0.4, p, 3, 5)
+    ry, ryd = oracle.softmax_fwd(xs, klen, causal, 0.4, dt, p, 3, 5, query_len=qlen)
+    assert_close_store(y, ry, dt, "y")
+    assert_close_store(yd, ryd, dt, "y_drop")
+    dx = L.lsq_softmax_varlen_bwd(to_torch(dys, dt, d), y, kl, ql, causal, 0.4, p, 3, 5)
+    assert_close_store(dx, oracle.softmax_bwd(dys, from_torch(y, dt).reshape(ry.shape), klen, causal, 0.4, dt, p, 3, 5, query_len=qlen), dt, "dx")
+    for t in (y, yd, dx):                                   # +0 to the bit where nothing is allowed, and nothing is read there
+        t = t.view(B, N, Lq, Lk)
+        for b in range(B):
+            assert not t[b, :, qlen[b]:].view(torch.int32 if dt == "f32" else torch.int16).any()
+    spoilt = to_torch(xs, dt, d).view(B, N, Lq, Lk).clone()
+    for b in range(B):
+        spoilt[b, :, qlen[b]:] = float("nan")
+    assert torch.equal(L.lsq_softmax_varlen_fwd(spoilt, kl, ql, causal, 0.4, 0.0)[0], L.lsq_softmax_varlen_fwd(to_torch(xs, dt, d).view(B, N, Lq, Lk), kl, ql, causal, 0.4, 0.0)[0])

@@ -97,9 +97,9 @@ const char* lsq_status_string(lsq_status s);
  *   registers, so it cannot go negative.
  * x, y: [rows, hidden] dt;  gamma, beta: [hidden] dt;  mean, rstd: [rows] fp32
  * (saved for backward).  Errors: null pointers, rows < 0, hidden <= 0, eps < 0.
- * Speed: rows of up to 16384 columns, hidden a multiple of 8, stay in registers (one
- * pass over memory, forward and backward); any other hidden takes a generic path that
- * re-reads the row from cache and takes about twice the time. */
+ * Speed: rows of up to 16384 columns (8191 where hidden is not a multiple of 8, and from 129 there) stay
+ * in registers: one pass over memory, forward and backward.  Other rows take a generic path that
+ * re-reads them from cache. */
 lsq_status lsq_layernorm_fwd(void* y, float* mean, float* rstd,
                              const void* x, const void* gamma, const void* beta,
                              int64_t rows, int32_t hidden, float eps,
@@ -143,10 +143,9 @@ lsq_status lsq_layernorm_bwd_noalloc(void* dx, float* dgamma, float* dbeta,
  * x, residual, out: [rows, hidden] dt;  bias: nullable [hidden] dt.
  * out may alias x or residual.  p in [0,1).  Dropout contract above, flat index
  * e = r*hidden + i.
- * Speed: hidden a multiple of 8 takes the column-block kernels; any other hidden is walked as one
- * flat array in aligned 128-bit packs (a pack may straddle two rows; the bias is gathered per
- * element), forward and backward, about 1.5 x the time; the same holds for
- * lsq_bias_act_dropout_fwd/bwd (about 2 x). */
+ * Speed: rows of any length run in 128-bit packs counted from the row's start, 1.3-1.5 x the time of
+ * the next multiple of 8 where hidden is none; up to 256 such columns the tensor is walked as one flat
+ * array instead.  The same holds for lsq_bias_act_dropout_fwd/bwd. */
 lsq_status lsq_bias_dropout_residual_fwd(void* out, const void* x, const void* bias,
                                          const void* residual, int64_t rows, int32_t hidden,
                                          float p, uint64_t seed, uint64_t offset,

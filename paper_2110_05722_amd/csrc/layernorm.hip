@@ -175,7 +175,7 @@ constexpr int kLnBwdThreads = 256;
 
 // partial: [gridDim.x][2][hidden] fp32 (dgamma row, then dbeta row).
 // THREADS lanes per workgroup: THREADS/LPR rows in flight per workgroup (plus their
-// prefetched successors).  Serves rows of up to 504 columns (a row within a wave, one pack per lane: 8000 x 256 fused 9.8 us,
+// prefetched successors).  Serves rows of up to 504 columns (a row within a wave, one pack per lane or two: 8000 x 256 fused 9.8 us,
 // as with ln_bwd_span_kernel's shape) and those of 8193..16384.
 // FUSE: the LayerNorm gradient (plus dres) is the gradient of h = residual + Dropout(x + bias): it is
 // stored (the residual branch's gradient), then masked and scaled from its STORED value into
@@ -1004,7 +1004,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
         else { X(0, 1024) }
 #undef X
     }
-    // shorter rows: lanes of one wave, one pack each
+    // shorter rows: lanes of one wave, one pack each, or two of 32 lanes
     const int nacc = fuse ? 3 : 2;
     const size_t one_copy = sizeof(float) * 8 * nacc * ((hidden / kPack) | 1);
 #define X(L, V)                                                                                              \
@@ -1023,7 +1023,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
             else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
         }                                                                                                    \
     }
-    X(8, 1) X(16, 1) X(32, 1) X(64, 1)
+    X(8, 1) X(16, 1) X(32, 1) X(32, 2)       // what ln_shape gives up to 63 packs
 #undef X
     if (fuse) launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 3 * hidden, s, dbias, 2 * hidden);
     else launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 2 * hidden, s);

@@ -193,3 +193,51 @@ def test_layernorm_rows_of_any_length(rows, hidden, dt):
     assert_close_f32(dbias, rdbias, "dbias", floor=2 * floor)
     over = res.clone()
     assert torch.equal(L.lsq_bias_dropout_residual_fwd(x, bias, over, 0.2, 5, 1, out=over), h3)
+
+
+def _every_width(lo, hi, step, rows, dt):
+    """Forward and backward, plain and as the boundary, at every width: whichever kernel a width selects, there is one, and it is right."""
+    d = dev()
+    g = torch.Generator(device=d)
+    g.manual_seed(lo)
+    r = lambda *shape: torch.randn(shape, generator=g, device=d).to(dt)
+    tol = 1e-5 if dt == torch.float32 else 1e-2
+    bad = []
+    for H in range(lo, hi, step):
+        x, dy, res, gamma, beta, bias = r(rows, H), r(rows, H), r(rows, H), r(H) * 0.1 + 1, r(H), r(H)
+        outs = [torch.full((rows, H), float("nan"), device=d, dtype=dt) for _ in range(5)]
+        vecs = [torch.full((n,), float("nan"), device=d) for n in (rows, rows, H, H, H)]
+        L.lsq_bdr_layernorm_fwd(x, bias, res, gamma, beta, 0.0, 1, 1, h=outs[0], y=outs[1], mean=vecs[0], rstd=vecs[1])
+        L.lsq_bdr_layernorm_bwd(dy, outs[0], gamma, vecs[0], vecs[1], 0.0, 1, 1, dres_in=res, dh=outs[2], dx=outs[3], dgamma=vecs[2], dbeta=vecs[3], dbias=vecs[4])
+        L.lsq_layernorm_bwd(dy, outs[0], gamma, vecs[0], vecs[1], dx=outs[4], dgamma=torch.empty_like(vecs[2]), dbeta=torch.empty_like(vecs[3]))
+        h = outs[0].double()
+        mu, rs = h.mean(1, keepdim=True), torch.rsqrt(h.var(1, unbiased=False, keepdim=True) + EPS)
+        xh, gy = (h - mu) * rs, dy.double() * gamma.double()
+        dh = rs * (gy - gy.mean(1, keepdim=True) - xh * (gy * xh).mean(1, keepdim=True))
+        want = [x.double() + bias.double() + res.double(), xh * gamma.double() + beta.double(), dh + res.double(), dh + res.double(), dh,
+                mu[:, 0], rs[:, 0], (dy.double() * xh).sum(0), dy.double().sum(0), outs[2].double().sum(0)]
+        for name, a, b in zip(("h", "y", "dh", "dx", "plain dx", "mean", "rstd", "dgamma", "dbeta", "dbias"), [*outs, *vecs], want):
+            e = (a.double() - b).norm() / (b.norm() + 1e-3 * b.numel() ** 0.5)
+            if not e <= tol * (10 if H < 8 else 1):
+                bad.append((H, name, float(e)))
+    assert not bad, bad[:8]
+
+
+@pytest.mark.parametrize("lo", range(8, 2104, 256))
+def test_layernorm_every_width_of_whole_packs(lo):
+    say(f"[layernorm] every width from {lo} in eights")
+    _every_width(lo, lo + 256, 8, 9, torch.float32)
+    _every_width(lo, lo + 256, 8, 9, torch.float16)
+
+
+# from 3: with two columns xhat is +-1 and the gradient without a residual is 0 but for eps, so what is computed is the rounding of terms
+# of size rstd * |dy| <= 316 |dy|, 2^-24 of each, against a result that can be as small: no relative bound holds
+@pytest.mark.parametrize("lo", [3, 130, 258, 386, 510, 1000, 2040, 4090])
+def test_layernorm_every_width(lo):
+    say(f"[layernorm] every width from {lo}")
+    _every_width(lo, lo + 40, 1, 5, torch.float32)
+
+
+def test_layernorm_wide_widths():
+    say("[layernorm] widths to 9000")
+    _every_width(2112, 9000, 312, 3, torch.float16)

@@ -890,17 +890,19 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
                                yp, mean, rstd, xp, gp, bp, rows, hidden, eps);
         return launch_status();
     }
+    bool launched = false;
     const dim3 grid(ln_fwd_blocks(rows, sh)), block(256);
     const BdrFuse<T> none{};
 #define X(L, V)                                                                                              \
     if (sh.lpr == L && sh.vpl == V) {                                                                        \
+        launched = true;                                                                                     \
         if (!fuse) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, none); \
         else if (fuse->d.on) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, true>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
         else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
     }
     LSQ_LN_FWD_CASES(X)
 #undef X
-    return launch_status();
+    return launched ? launch_status() : LSQ_LAUNCH_FAILED;      // a shape without its kernel
 }
 
 // Backward of rows with 1025..2048 packs: the column accumulators are thread-private LDS entries
@@ -978,7 +980,8 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
         return launch_status();
     }
     const BdrFuse<T> none{};
-    if (ln_bwd_spans(hidden)) {
+    bool launched = ln_bwd_spans(hidden);
+    if (launched) {
         const LnBwdPlan pl = ln_bwd_span_plan(rows, hidden);
         const dim3 grid(P), block(pl.slots * pl.lanes);
         const size_t exchange = sizeof(float) * (block.x / 8), tree = sizeof(float) * (pl.slots / 2) * (fuse ? 3 : 2) * 8 * pl.lanes;
@@ -1009,6 +1012,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
     const size_t one_copy = sizeof(float) * 8 * nacc * ((hidden / kPack) | 1);
 #define X(L, V)                                                                                              \
     if (!ln_bwd_spans(hidden) && sh.lpr == L && sh.vpl == V) {                                                                        \
+        launched = true;                                                                                     \
         constexpr int TH = kLnBwdThreads;                                                                 \
         const size_t shmem = one_copy * (TH / L);                                                            \
         const dim3 grid(P), block(TH);                                                                       \
@@ -1025,6 +1029,7 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
     }
     X(8, 1) X(16, 1) X(32, 1) X(32, 2)       // what ln_shape gives up to 63 packs
 #undef X
+    if (!launched) return LSQ_LAUNCH_FAILED;                    // a shape without its kernel
     if (fuse) launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 3 * hidden, s, dbias, 2 * hidden);
     else launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 2 * hidden, s);
     return launch_status();

@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
     }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
-    if (len.query || g.causal) {                                      // uniform: only there do rows come up empty in numbers
+    if (len.query) {                                                  // uniform: only there do rows come up empty in numbers
         bool empty = true;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) empty = empty && limit[r] <= 0;
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
     }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
-    if (len.query || g.causal) {                                      // uniform: only there do rows come up empty in numbers
+    if (len.query) {                                                  // uniform: only there do rows come up empty in numbers
         bool empty = true;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) empty = empty && limit[r] <= 0;

@@ -83,6 +83,7 @@ typedef enum {
 typedef enum { LSQ_ACT_RELU = 0, LSQ_ACT_GELU = 1 /* erf form */, LSQ_ACT_GELU_TANH = 2 /* tanh approximation */ } lsq_act;
 
 /* Bytes of device workspace `op` needs for a [rows, cols] problem (0 if none).
+ * It never falls as rows grow: a workspace for the longest batch serves every shorter one.
  * Contents on entry are ignored; contents on exit are unspecified. */
 size_t lsq_workspace_bytes(int32_t op, int64_t rows, int32_t cols);
 

@@ -8,30 +8,21 @@ extern "C" size_t lsq_workspace_bytes(int32_t op, int64_t rows, int32_t cols)
     switch (op) {
         case LSQ_OP_LAYERNORM_BWD:
             // one [2][cols] fp32 partial row (dgamma, dbeta) per workgroup
-            return static_cast<size_t>(ln_bwd_blocks(rows, cols)) * 2u * static_cast<size_t>(cols) * sizeof(float);
+            return ln_bwd_bytes(rows, cols, 2);
         case LSQ_OP_BDR_LAYERNORM_BWD:
             // one [3][cols] fp32 partial row (dgamma, dbeta, dbias) per workgroup; also enough for the
             // two separate operators that serve row lengths without a register bucket
             {
-                const size_t fused = static_cast<size_t>(ln_bwd_blocks(rows, cols)) * 3u * static_cast<size_t>(cols) * sizeof(float);
-                const size_t apart = lsq_workspace_bytes(LSQ_OP_BIAS_DROPOUT_RESIDUAL_BWD, rows, cols);
+                const size_t fused = ln_bwd_bytes(rows, cols, 3), apart = bdr_bwd_bytes_upto(rows, cols);
                 return fused > apart ? fused : apart;
             }
-        case LSQ_OP_BIAS_DROPOUT_RESIDUAL_BWD:
-            // one [cols] fp32 partial row (dbias) per row block
-            if (!bdr_bwd_is_flat(cols))
-                return static_cast<size_t>(bdr_bwd_plan(rows, cols).row_blocks) * static_cast<size_t>(cols) * sizeof(float);
-            if (bdr_is_rag(cols)) return static_cast<size_t>(bdr_rag_row_blocks(rows, cols)) * static_cast<size_t>(cols) * sizeof(float);
-            return flat_workspace_bytes(rows, cols);        // one per workgroup of the flat walk
-        case LSQ_OP_BIAS_ACT_DROPOUT_BWD:
-            if (bad_is_flat(cols)) return flat_workspace_bytes(rows, cols);
-            return static_cast<size_t>(bad_bwd_row_blocks(rows, cols)) * static_cast<size_t>(cols) * sizeof(float);
-        case LSQ_OP_SPLIT_HEADS_BWD:
-            // one [cols] fp32 partial row (dbias) per row block
-            return static_cast<size_t>(heads_bwd_row_blocks(rows, cols)) * static_cast<size_t>(cols) * sizeof(float);
+        // one [cols] fp32 partial row (dbias) per row block, or per workgroup of the flat walk
+        case LSQ_OP_BIAS_DROPOUT_RESIDUAL_BWD: return bdr_bwd_bytes_upto(rows, cols);
+        case LSQ_OP_BIAS_ACT_DROPOUT_BWD: return bad_bwd_bytes_upto(rows, cols);
+        case LSQ_OP_SPLIT_HEADS_BWD: return heads_bwd_bytes_upto(rows, cols);
         case LSQ_OP_EMBEDDING_BWD:
             // sorted order, fp32 rows of the id segments that cross a window, the sort of many tokens
-            return emb_bwd_plan(rows, cols).total();
+            return emb_bwd_bytes_upto(rows, cols);
         default:
             return 0;
     }

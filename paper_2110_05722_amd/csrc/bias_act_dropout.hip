@@ -377,7 +377,7 @@ extern "C" lsq_status lsq_bias_act_dropout_bwd(void* dx, float* dbias, const voi
     LSQ_ALIGNED(dx); LSQ_ALIGNED(dy); LSQ_ALIGNED(x); LSQ_ALIGNED(bias); LSQ_ALIGNED(dbias); LSQ_ALIGNED(workspace);
     LSQ_REQUIRE(ceil_div(rows * hidden, 256) <= 0x7FFFFFFF);
     if (dbias) {
-        const size_t need = lsq_workspace_bytes(LSQ_OP_BIAS_ACT_DROPOUT_BWD, rows, hidden);
+        const size_t need = bad_bwd_bytes(rows, hidden);
         if (need && (!workspace || workspace_bytes < need)) return LSQ_WORKSPACE_TOO_SMALL;
     }
     switch (dt) {

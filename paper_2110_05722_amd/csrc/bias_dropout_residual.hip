@@ -392,7 +392,7 @@ extern "C" lsq_status lsq_bias_dropout_residual_bwd(void* dx, float* dbias, cons
     LSQ_ALIGNED(dx); LSQ_ALIGNED(dy); LSQ_ALIGNED(dbias); LSQ_ALIGNED(workspace);
     LSQ_REQUIRE(ceil_div(rows * hidden, 256) <= 0x7FFFFFFF);
     if (dbias) {
-        const size_t need = lsq_workspace_bytes(LSQ_OP_BIAS_DROPOUT_RESIDUAL_BWD, rows, hidden);
+        const size_t need = bdr_bwd_bytes(rows, hidden);
         if (need && (!workspace || workspace_bytes < need)) return LSQ_WORKSPACE_TOO_SMALL;
     }
     switch (dt) {

@@ -945,7 +945,7 @@ extern "C" lsq_status lsq_embedding_bwd(void* demb, void* dpos, const void* dy, 
     LSQ_REQUIRE(ceil_div(rows, 256) * 64 + ceil_div(hidden, 8 * 64) * static_cast<int64_t>(len) < 0x7FFFFFFF);   // (position, column block) pairs
     LSQ_REQUIRE(demb && dy && tokens);
     LSQ_ALIGNED(demb); LSQ_ALIGNED(dpos); LSQ_ALIGNED(dy); LSQ_ALIGNED(workspace);
-    const size_t need = lsq_workspace_bytes(LSQ_OP_EMBEDDING_BWD, rows, hidden);
+    const size_t need = emb_bwd_plan(rows, hidden).total();
     if (!workspace || workspace_bytes < need) return LSQ_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     void* ws = workspace;

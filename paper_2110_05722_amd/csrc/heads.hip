@@ -277,7 +277,7 @@ extern "C" lsq_status lsq_split_heads_bwd(void* din, float* dbias, const void* d
     LSQ_REQUIRE(din && d0 && (parts < 2 || d1) && (parts < 3 || d2));
     LSQ_ALIGNED(din); LSQ_ALIGNED(d0); LSQ_ALIGNED(d1); LSQ_ALIGNED(d2); LSQ_ALIGNED(dbias); LSQ_ALIGNED(workspace);
     if (dbias) {
-        const size_t need = lsq_workspace_bytes(LSQ_OP_SPLIT_HEADS_BWD, g.rows, parts * g.hidden);
+        const size_t need = heads_bwd_bytes(g.rows, parts * g.hidden);
         if (need && (!workspace || workspace_bytes < need)) return LSQ_WORKSPACE_TOO_SMALL;
     }
     switch (dt) {

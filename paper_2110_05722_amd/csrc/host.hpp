@@ -264,6 +264,12 @@ inline size_t flat_workspace_bytes(int64_t rows, int32_t hidden)
 {
     return static_cast<size_t>(flat_plan(rows * hidden, true).blocks) * static_cast<size_t>(hidden) * sizeof(float);
 }
+// of the largest call of up to `rows` rows (at most one partial row per chunk, kFlatMaxBlocks in all)
+inline size_t flat_workspace_bytes_upto(int64_t rows, int32_t hidden)
+{
+    const int64_t chunks = ceil_div(rows * hidden, kFlatChunk);
+    return static_cast<size_t>(chunks < kFlatMaxBlocks ? chunks : kFlatMaxBlocks) * static_cast<size_t>(hidden) * sizeof(float);
+}
 
 // LayerNorm backward, launch shape of the kernel whose rows span several waves (512..8192 columns, whole packs): lanes per
 // row, rows a workgroup holds at a time, workgroups (= partial rows of the column sums).
@@ -387,6 +393,12 @@ inline int colsum_row_blocks(int64_t rows, int32_t hidden, int target)
     if (b > most) b = most;
     return static_cast<int>(b < 1 ? 1 : b);
 }
+// the largest of colsum_row_blocks over the calls of up to `rows` rows (it falls from 256 to 129 behind 2048 rows)
+inline int colsum_row_blocks_upto(int64_t rows, int32_t hidden, int target)
+{
+    const int here = colsum_row_blocks(rows, hidden, target), at = rows > 2048 ? colsum_row_blocks(2048, hidden, target) : 0;
+    return here > at ? here : at;
+}
 // rows that are not whole packs in packs of their own: bias + dropout + residual from 257 columns on (see bad_is_flat)
 inline bool bdr_is_rag(int hidden) { return hidden % kPack != 0 && hidden > 256; }
 inline int bdr_rag_row_blocks(int64_t rows, int32_t hidden)
@@ -396,6 +408,45 @@ inline int bdr_rag_row_blocks(int64_t rows, int32_t hidden)
 }
 inline int bad_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_row_blocks(rows, hidden, kBadBwdWorkgroups); }
 inline int heads_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_row_blocks(rows, hidden, kHeadsBwdWorkgroups); }
+
+// ---- workspace of the column sums: what one call's launch writes (the entry points ask for no more), and the same for the
+// largest of all calls of up to `rows` rows, which lsq_workspace_bytes tells.  The launches' numbers of partial rows follow from what
+// is fastest at each size and fall here and there as the rows grow; a program that keeps one workspace of its longest
+// batch's size is not to notice.
+inline size_t partial_bytes(int64_t row_blocks, int32_t cols) { return static_cast<size_t>(row_blocks) * static_cast<size_t>(cols) * sizeof(float); }
+inline size_t bdr_bwd_bytes(int64_t rows, int32_t hidden)
+{
+    if (!bdr_bwd_is_flat(hidden)) return partial_bytes(bdr_bwd_plan(rows, hidden).row_blocks, hidden);
+    if (bdr_is_rag(hidden)) return partial_bytes(bdr_rag_row_blocks(rows, hidden), hidden);
+    return flat_workspace_bytes(rows, hidden);
+}
+inline size_t bdr_bwd_bytes_upto(int64_t rows, int32_t hidden)
+{
+    if (!bdr_bwd_is_flat(hidden)) {                   // at most one per group of rows, and rb_max of bdr_bwd_plan
+        const BdrBwdPlan one = bdr_bwd_plan(1, hidden);
+        const int64_t units = ceil_div(rows, static_cast<int64_t>(kBdrBwdWaves) * (64 / one.w));
+        int64_t most = kBdrBwdWorkgroups / one.col_blocks;
+        if (most > kBdrBwdMaxPartials) most = kBdrBwdMaxPartials;
+        if (most > units) most = units;
+        return partial_bytes(most < 1 ? 1 : most, hidden);
+    }
+    if (bdr_is_rag(hidden)) {
+        const int b = colsum_row_blocks_upto(rows, hidden, kBdrBwdWorkgroups);
+        return partial_bytes(b < kBdrBwdMaxPartials ? b : kBdrBwdMaxPartials, hidden);
+    }
+    return flat_workspace_bytes_upto(rows, hidden);
+}
+inline size_t bad_bwd_bytes(int64_t rows, int32_t hidden)
+{
+    return bad_is_flat(hidden) ? flat_workspace_bytes(rows, hidden) : partial_bytes(bad_bwd_row_blocks(rows, hidden), hidden);
+}
+inline size_t bad_bwd_bytes_upto(int64_t rows, int32_t hidden)
+{
+    return bad_is_flat(hidden) ? flat_workspace_bytes_upto(rows, hidden) : partial_bytes(colsum_row_blocks_upto(rows, hidden, kBadBwdWorkgroups), hidden);
+}
+inline size_t heads_bwd_bytes(int64_t rows, int32_t cols) { return partial_bytes(heads_bwd_row_blocks(rows, cols), cols); }
+inline size_t heads_bwd_bytes_upto(int64_t rows, int32_t cols) { return partial_bytes(colsum_row_blocks_upto(rows, cols, kHeadsBwdWorkgroups), cols); }
+inline size_t ln_bwd_bytes(int64_t rows, int32_t hidden, int sums) { return partial_bytes(static_cast<int64_t>(ln_bwd_blocks(rows, hidden)) * sums, hidden); }
 
 // Workspace of the embedding backward:
 //   order  [rows] (token position, sort key), 8 bytes each
@@ -426,6 +477,12 @@ inline EmbBwdPlan emb_bwd_plan(int64_t rows, int32_t hidden)
     p.sort_bytes = rows > kEmbSortMax ? p.radix_hist_bytes + static_cast<size_t>(rows) * 8u
                                       : static_cast<size_t>(ceil_div(rows, 256)) * static_cast<size_t>(rows) * sizeof(int32_t);
     return p;
+}
+// of the largest call of up to `rows` rows (the sort scratch of kEmbSortMax tokens is larger than that of the next few)
+inline size_t emb_bwd_bytes_upto(int64_t rows, int32_t hidden)
+{
+    const size_t here = emb_bwd_plan(rows, hidden).total(), at = rows > kEmbSortMax ? emb_bwd_plan(kEmbSortMax, hidden).total() : 0;
+    return here > at ? here : at;
 }
 
 }  // namespace lsq

@@ -233,3 +233,15 @@ def test_layernorm_bwd_partial_rows_fit_the_no_alloc_scratch_as_before(lib):
         for rows in (1, 7, 255, 256, 257, 511, 768, 1105, 2047, 2048, 2049, 8192, 1 << 24):
             before = 2 * hidden * 4 * min(256, -(-rows // 8))
             assert L.lsq_workspace_bytes(0, rows, hidden) <= max(8 << 20, before), (rows, hidden)
+
+
+@pytest.mark.parametrize("op", range(6))
+def test_a_workspace_of_the_longest_batch_serves_every_shorter_one(lib, op):
+    """lsq_workspace_bytes never falls as the rows grow, whatever the launches' numbers of partial rows do."""
+    rows = sorted({*range(1, 2600), *range(2600, 9000, 61), 4095, 4096, 4097, 8191, 8192, 8193, 16384, 16385, 32768, 65536, 1 << 20})
+    for cols in (8, 24, 64, 128, 136, 255, 257, 264, 505, 512, 513, 768, 1024, 1025, 1280, 1281, 1536, 2048, 2049, 3072, 4096, 4097, 6145, 8191, 8192, 8193, 16384, 16401):
+        most = 0
+        for r in rows:
+            need = L.lsq_workspace_bytes(op, r, cols)
+            assert need >= most, (op, r, cols, need, most)
+            most = need

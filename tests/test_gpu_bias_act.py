@@ -91,3 +91,21 @@ def test_bias_act_dropout_rows_of_any_length(rows, hidden, dt):
         assert torch.equal(same, dx) and torch.equal(over, out)
         nb = L.lsq_bias_act_dropout_fwd(x, None, act, p, 7, hidden)
         assert_close_store(nb, oracle.bias_act_dropout_fwd(t["x"], None, act, p, 7, hidden, dt), dt, "out(no bias)", f32_floor=2e-6)
+
+
+def test_one_workspace_of_the_longest_batch():
+    """Feed-forward, QKV split and bias+dropout+residual backward take the workspace of 2100 rows at every smaller size."""
+    say("[bias_act_dropout] one workspace for all batches")
+    d = dev()
+    ws = {op: torch.empty(L.lsq_workspace_bytes(op, 2100, cols), dtype=torch.uint8, device=d) for op, cols in ((1, 1281), (2, 1024), (3, 1536))}
+    for rows in (1, 1057, 1600, 2048, 2049, 2100):
+        x = torch.randn(rows, 1024, device=d)
+        dx, db = L.lsq_bias_act_dropout_bwd(x, x, None, "relu", 0.0, 1, 0, workspace=ws[2])
+        assert torch.equal(dx, x * (x > 0)) and torch.allclose(db, (x * (x > 0)).sum(0), rtol=1e-5, atol=2e-6 * rows)
+        x = torch.randn(rows, 1281, device=d)
+        dx, db = L.lsq_bias_dropout_residual_bwd(x, 0.0, 1, 0, workspace=ws[1])
+        assert torch.equal(dx, x) and torch.allclose(db, x.sum(0), rtol=1e-5, atol=2e-6 * rows)
+        g = [torch.randn(1, 8, rows, 64, device=d) for _ in range(3)]
+        din, db = L.lsq_split_heads_bwd(g, 1, rows, 8, 64, workspace=ws[3])
+        want = torch.stack([t[0].transpose(0, 1).reshape(rows, 512) for t in g], 1).reshape(rows, 1536)
+        assert torch.equal(din, want) and torch.allclose(db, want.sum(0), rtol=1e-5, atol=2e-6 * rows)

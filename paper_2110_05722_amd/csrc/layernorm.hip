@@ -24,11 +24,50 @@ namespace lsq {
 
 constexpr bool kNT = true;    // nontemporal hint on the streamed tensors (not on gamma/beta/bias)
 
-template <int LPR>
-__device__ __forceinline__ float row_sum(float v, float* lds)
+// A row's total, forward.  One width may be served by several shapes (lanes x packs per lane) depending on the number of rows
+// (ln_fwd_shape), and a row must not come out with other bits because its batch is larger: all shapes add in ONE order.
+// A lane sums its packs by their index modulo 256 (in LnParts accumulators), these classes add 64 apart in ascending order, then
+// the two half-waves add, then 32 lanes as group_sum<32> does.  So 32 x 2 and 64 x 1, or 64 x 4 and 256 x 1, round alike.
+template <int LPR, int VPL> constexpr int kLnParts = VPL < 256 / LPR ? VPL : 256 / LPR;
+
+// the two half-waves added: lane i has lanes i % 32 and i % 32 + 32
+__device__ __forceinline__ float half_waves_sum(float v)
 {
-    if constexpr (LPR >= 256) return block_allreduce<LPR / 64, OpSum>(v, lds);      // the row spans the workgroup
-    else return group_sum<LPR>(v);
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, v), __builtin_bit_cast(unsigned, v), false, false);
+    const unsigned lower = r.x, upper = r.y;       // (a bit cast of r.y itself reads r.x)
+    return __builtin_bit_cast(float, lower) + __builtin_bit_cast(float, upper);
+}
+
+// `buf`: 256 floats where the row spans the workgroup; it may be written again only behind another barrier
+template <int LPR, int VPL>
+__device__ __forceinline__ float ln_row_total(const float (&part)[kLnParts<LPR, VPL>], float* buf)
+{
+    constexpr int N = kLnParts<LPR, VPL>;
+    if constexpr (LPR <= 16) {
+        return group_sum<LPR>(part[0]);
+    } else if constexpr (LPR == 32) {
+        float v = part[0], w = N > 1 ? part[1] : 0.0f;            // the classes of the lower and of the upper half-wave
+#pragma unroll
+        for (int k = 2; k < N; ++k) (k % 2 ? w : v) += part[k];
+        return group_sum<32>(N > 1 ? v + w : v);
+    } else {
+        float v = part[0];
+        if constexpr (LPR == 256) {
+            buf[threadIdx.x] = v;
+            __syncthreads();
+            const int lane = threadIdx.x % kWave;
+            v = buf[lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) v += buf[lane + w * kWave];
+        } else {
+#pragma unroll
+            for (int k = 1; k < N; ++k) v += part[k];
+        }
+        v = group_sum<16>(half_waves_sum(v));
+        const int iv = __builtin_bit_cast(int, v);
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(iv, 0)) + __builtin_bit_cast(float, __builtin_amdgcn_readlane(iv, 16));
+    }
 }
 
 // Raw packs of row r for this lane (zeros where the row or the pack does not exist).
@@ -58,13 +97,15 @@ struct BdrFuse {
 // two loads, stored once (the next residual) and normalised from its STORED (rounded) value, so the
 // result equals bias+dropout+residual followed by LayerNorm bit for bit while h is never re-read.
 template <typename T, int LPR, int VPL, bool FUSE = false, bool DROP = false>
-__global__ __launch_bounds__(LPR > 256 ? LPR : 256) void ln_fwd_kernel(T* __restrict__ y, float* __restrict__ mean,
+__global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* __restrict__ mean,
                                                      float* __restrict__ rstd, const T* __restrict__ x,
                                                      const T* __restrict__ gamma, const T* __restrict__ beta,
                                                      int64_t rows, int hidden, float eps, BdrFuse<T> fz)
 {
-    __shared__ float lds[16];
-    constexpr int RPB = LPR > 256 ? 1 : 256 / LPR;     // rows a workgroup handles at a time
+    static_assert(LPR <= 256, "a row is at most a workgroup");
+    __shared__ float lds[2][LPR == 256 ? 256 : 1];     // in turn: sum, squares (a barrier lies between two writes of either)
+    constexpr int RPB = 256 / LPR;                     // rows a workgroup handles at a time
+    constexpr int NP = kLnParts<LPR, VPL>;
     const int sub = threadIdx.x % LPR;
     const int slot = threadIdx.x / LPR;
     const int nv = hidden / kPack;
@@ -128,16 +169,18 @@ __global__ __launch_bounds__(LPR > 256 ? LPR : 256) void ln_fwd_kernel(T* __rest
         }
 
         float xv[VPL][8];
-        float s = 0.0f;
+        float part[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) part[k] = 0.0f;
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             unpack<T>(cur[k], xv[k]);         // absent packs are zeros: they add nothing
 #pragma unroll
-            for (int j = 0; j < 8; ++j) s += xv[k][j];
+            for (int j = 0; j < 8; ++j) part[k % NP] += xv[k][j];
         }
-        s = row_sum<LPR>(s, lds);
-        const float mu = s * inv_h;
-        float q = 0.0f;
+        const float mu = ln_row_total<LPR, VPL>(part, lds[0]) * inv_h;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) part[k] = 0.0f;
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const bool ok = sub + k * LPR < nv;
@@ -145,10 +188,10 @@ __global__ __launch_bounds__(LPR > 256 ? LPR : 256) void ln_fwd_kernel(T* __rest
             for (int j = 0; j < 8; ++j) {
                 const float dlt = xv[k][j] - mu;
                 xv[k][j] = dlt;
-                q = ok ? fmaf(dlt, dlt, q) : q;
+                part[k % NP] = ok ? fmaf(dlt, dlt, part[k % NP]) : part[k % NP];
             }
         }
-        q = row_sum<LPR>(q, lds);
+        const float q = ln_row_total<LPR, VPL>(part, lds[1]);
         const float rs = 1.0f / sqrtf(fmaf(q, inv_h, eps));
         if (rv && sub == 0) {
             mean[r] = mu;
@@ -172,6 +215,13 @@ __global__ __launch_bounds__(LPR > 256 ? LPR : 256) void ln_fwd_kernel(T* __rest
 }
 
 constexpr int kLnBwdThreads = 256;
+
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v, float* lds)
+{
+    if constexpr (LPR >= 256) return block_allreduce<LPR / 64, OpSum>(v, lds);      // the row spans the workgroup
+    else return group_sum<LPR>(v);
+}
 
 // partial: [gridDim.x][2][hidden] fp32 (dgamma row, then dbeta row).
 // THREADS lanes per workgroup: THREADS/LPR rows in flight per workgroup (plus their
@@ -826,7 +876,7 @@ inline LnShape ln_shape(int hidden)
 // 7.7 / 5.1 (4096 rows 9.0 / 5.8 against 8.3 / 5.4: the line is between).  600 x 3072 256 x 2 6.0 / 4.3, 64 x 6 7.0 / 4.6; 600 x 2048 256 x 1
 // 5.1 / 3.9, 64 x 4 5.6 / 4.1.  8192 x 2048 256 x 1 27.8 / 15.8, 64 x 4 29.6 / 17.4; 8192 x 2560 256 x 2 34.3 / 18.6, 64 x 5 35.8 / 19.0; rows that fill
 // three quarters of such lanes or less stay (4096 x 3072 256 x 2 21.2 / 12.2, 64 x 6 22.2 / 11.2; 8192 x 1536 21.1 / 11.9 against 22.9 / 10.2).
-// Fused and plain calls take the same shape, so their results stay bit-identical.
+// The shape changes with the number of rows: ln_row_total keeps a row's bits out of it.
 inline LnShape ln_fwd_shape(int64_t rows, int hidden)
 {
     const LnShape s = ln_shape(hidden);

@@ -241,3 +241,30 @@ def test_layernorm_every_width(lo):
 def test_layernorm_wide_widths():
     say("[layernorm] widths to 9000")
     _every_width(2112, 9000, 312, 3, torch.float16)
+
+
+# a row's bits do not depend on how many rows the call has, though the shape that serves it does: row counts on both sides of the forward's
+# lines (1024, 3072, 5120 rows; 256, 512 and 768 row groups), every shape a width can take, rows that are not whole packs
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("hidden", [64, 264, 512, 768, 904, 1024, 1160, 1281, 1400, 1536, 1600, 2048, 2304, 2560, 2568, 3072, 4096])
+def test_layernorm_rows_do_not_depend_on_the_batch(hidden, dt):
+    say(f"[layernorm] rows by themselves, hidden={hidden} dt={dt}")
+    d, rows = dev(), 5125
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    g = torch.Generator(device=d)
+    g.manual_seed(hidden)
+    r = lambda *shape: torch.randn(shape, generator=g, device=d).to(tdt)
+    x, res, dy, gamma, beta, bias = r(rows, hidden), r(rows, hidden), r(rows, hidden), r(hidden), r(hidden), r(hidden)
+    want = L.lsq_layernorm_fwd(x, gamma, beta, EPS)
+    mu, var = x.double().mean(1), x.double().var(1, unbiased=False)
+    # the mean is a sum of at most 2^12 terms in partial sums of 2^7 or fewer: 2^-24 * (7 + log2) of the mean absolute value, 1e-6 of a unit normal
+    assert (want[1].double() - mu).abs().max() < 1e-6 and (want[2].double() * (var + EPS).sqrt() - 1).abs().max() < 1e-5
+    wantf = L.lsq_bdr_layernorm_fwd(x, bias, res, gamma, beta, 0.25, 3, 4)
+    wantb = L.lsq_layernorm_bwd(dy, x, gamma, want[1], want[2])[0]
+    for n in (1, 255, 700, 1024, 1025, 2049, 3072, 3073, 5120):
+        got = L.lsq_layernorm_fwd(x[:n], gamma, beta, EPS)
+        gotf = L.lsq_bdr_layernorm_fwd(x[:n], bias, res[:n], gamma, beta, 0.25, 3, 4)
+        gotb = L.lsq_layernorm_bwd(dy[:n], x[:n], gamma, want[1][:n], want[2][:n])[0]
+        assert all(torch.equal(a, b[:n]) for a, b in zip(got, want)), n
+        assert all(torch.equal(a, b[:n]) for a, b in zip(gotf, wantf)), n
+        assert torch.equal(gotb, wantb[:n]), n

@@ -875,32 +875,39 @@ inline LnShape ln_shape(int hidden)
 // four packs or more.  Measured, fused / plain: 512 x 512 f32 64 x 1 3.9 / 3.1 us, 32 x 2 4.7 / 3.2; 3000 x 1024 64 x 2 7.4 / 4.7, 32 x 4
 // 7.7 / 5.1 (4096 rows 9.0 / 5.8 against 8.3 / 5.4: the line is between).  600 x 3072 256 x 2 6.0 / 4.3, 64 x 6 7.0 / 4.6; 600 x 2048 256 x 1
 // 5.1 / 3.9, 64 x 4 5.6 / 4.1.  8192 x 2048 256 x 1 27.8 / 15.8, 64 x 4 29.6 / 17.4; 8192 x 2560 256 x 2 34.3 / 18.6, 64 x 5 35.8 / 19.0; rows that fill
-// three quarters of such lanes or less stay (4096 x 3072 256 x 2 21.2 / 12.2, 64 x 6 22.2 / 11.2; 8192 x 1536 21.1 / 11.9 against 22.9 / 10.2).
+// three quarters of such lanes or less stay (4096 x 3072 256 x 2 21.2 / 12.2, 64 x 6 22.2 / 11.2; 8192 x 1536 21.1 / 11.9 against 22.9 / 10.2),
+// and so do those of 225..320 packs in 16 bits between 3073 and 5120 rows, where their one-row workgroups just overflow the compute
+// units (4096 x 2560 256 x 2 20.7 / 13.1, 64 x 5 18.8 / 11.4; 3584 x 2048 256 x 1 15.3, 64 x 4 14.2).
 // The shape changes with the number of rows: ln_row_total keeps a row's bits out of it.
-inline LnShape ln_fwd_shape(int64_t rows, int hidden)
+inline LnShape ln_fwd_shape(int64_t rows, int hidden, int elem_bytes)
 {
     const LnShape s = ln_shape(hidden);
     const int nv = hidden / kPack;
     if (s.lpr == 0 || s.lpr >= 256) return s;
-    if (nv > 128 && nv <= 256 && (nv > 224 || rows <= 1024)) return {256, 1};
-    if (nv > 256 && (nv <= 320 || rows <= 1024)) return {256, 2};
+    const bool overflow = elem_bytes == 2 && rows > 3072 && rows <= 5120;
+    if (nv > 128 && nv <= 256 && ((nv > 224 && !overflow) || rows <= 1024)) return {256, 1};
+    if (nv > 256 && ((nv <= 320 && !overflow) || rows <= 1024)) return {256, 2};
     if (s.lpr == 32 && s.vpl % 2 == 0 && rows <= 3072) return {64, s.vpl / 2};
     return s;
 }
 
-inline int ln_fwd_blocks(int64_t rows, LnShape sh)
+// Row groups per workgroup: two, the second loaded ahead (8192 x 1280: one 11.1, two 9.2, four 10.4 us), but one where all groups find
+// a compute unit of their own: up to 256 always (one against two, all shapes: 0.66-0.90), up to 768 where the kernel is small enough for
+// three on a unit.  Time of one over two for 257..512 / 513..768 groups: 16 bits up to 5 packs per lane 0.87-1.02 / 0.90-1.05, more and
+// 256 x 4 0.97-1.29 / 0.98-1.14; fp32 1 pack 0.90-1.03 / 0.97-1.01, more 1.02-1.24 (300 x 5120 fused 10.3 us as two, 13.5 as one; 300 x 2304 plain
+// is the exception, 4.9 against 4.5) / 0.89-1.04.  Beyond 768: 0.95-1.31, above 1 nearly everywhere.
+inline int ln_fwd_blocks(int64_t rows, LnShape sh, int elem_bytes)
 {
-    // two row groups per workgroup, the second loaded ahead (one: 11.1, two: 9.2, four: 10.4 us at 8192 x 1280); one where that
-    // leaves compute units idle (512 x 512 f32 fused 5.7 -> 4.7 us, 1000 x 768 6.2 -> 4.7, 4096 x 1024 9.0 -> 8.3; not for the widest rows:
-    // 500 x 8192 f32 11.1 -> 12.9)
     const int64_t groups = ceil_div(rows, static_cast<int64_t>(256 / sh.lpr));
-    int64_t b = groups <= 768 && (sh.lpr < 256 || sh.vpl < 4) ? groups : ceil_div(groups, 2);
+    const bool small = elem_bytes == 2 ? sh.vpl <= (sh.lpr < 256 ? 5 : 3) : sh.vpl == 1 || groups > 512;
+    int64_t b = groups <= 256 || (groups <= 768 && small) ? groups : ceil_div(groups, 2);
     if (b > 8192) b = 8192;
     if (b < 1) b = 1;
     return static_cast<int>(b);
 }
 
-#define LSQ_LN_FWD_CASES(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(64, 5) X(64, 6) X(256, 2) X(256, 3) X(256, 4) \
+// (64 x 5: 16 bits only, see ln_fwd_shape)
+#define LSQ_LN_FWD_CASES(X) X(8, 1) X(16, 1) X(32, 1) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(64, 6) X(256, 2) X(256, 3) X(256, 4) \
     X(32, 2) X(32, 3) X(32, 4) X(32, 5) X(32, 6) X(256, 6) X(256, 8) X(256, 1)
 
 // fuse != nullptr: x is the projection output and *fuse carries h / residual / bias / dropout
@@ -913,7 +920,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
     const T* xp = static_cast<const T*>(x);
     const T* gp = static_cast<const T*>(gamma);
     const T* bp = static_cast<const T*>(beta);
-    LnShape sh = ln_fwd_shape(rows, hidden);
+    LnShape sh = ln_fwd_shape(rows, hidden, sizeof(T));
     // rows of 8193..16384 columns: the forward has the registers for 6 or 8 packs per lane of a 256-thread
     // workgroup (0.70 of peak at 12288 columns against 0.53 with the backward's 1024 lanes x 2 packs).  The fused
     // boundary follows (it would be 10 % faster on 1024 lanes, but then no longer bit-identical to the two calls).
@@ -941,7 +948,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
         return launch_status();
     }
     bool launched = false;
-    const dim3 grid(ln_fwd_blocks(rows, sh)), block(256);
+    const dim3 grid(ln_fwd_blocks(rows, sh, sizeof(T))), block(256);
     const BdrFuse<T> none{};
 #define X(L, V)                                                                                              \
     if (sh.lpr == L && sh.vpl == V) {                                                                        \
@@ -951,6 +958,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
         else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
     }
     LSQ_LN_FWD_CASES(X)
+    if constexpr (sizeof(T) == 2) { X(64, 5) }
 #undef X
     return launched ? launch_status() : LSQ_LAUNCH_FAILED;      // a shape without its kernel
 }

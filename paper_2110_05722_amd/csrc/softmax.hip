@@ -79,6 +79,11 @@ __device__ __forceinline__ int row_limit(const SoftmaxGeom& g, const SoftmaxLens
     return limit;
 }
 
+// Whether the pack that starts at position j0 of a row holds an allowed key.  The first pack of a ragged row starts before the row
+// (j0 < 0), below the limit even of an empty or absent one.
+template <bool RAG>
+__device__ __forceinline__ bool pack_needed(int j0, int limit) { return j0 < limit && (!RAG || limit > 0); }
+
 // ---- where the packs of a row lie.  RAG = false: rows are whole packs (k_len % 8 == 0), pack idx of a row starts at
 // its element 8 * idx.  RAG = true: any k_len.  The packs are those of the FLAT tensor (aligned 128-bit accesses, and the
 // groups the dropout contract counts): a row that starts s elements into a pack touches (s + k_len + 7) / 8 of them, pack
@@ -359,7 +364,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
             if (j0 >= kEarly) {
-                if (j0 < limit[r]) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);   // implies a valid row and pack
+                if (pack_needed<RAG>(j0, limit[r])) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);   // implies a valid row and pack
                 else raw[r][k] = zero_raw<T>();
             }
         }
@@ -376,7 +381,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int j0 = (sub + k * LPR) * kPack - rp[r].s;
-            live[k] = __ballot(j0 < lim) != 0;
+            live[k] = __ballot(pack_needed<RAG>(j0, lim)) != 0;
             if (live[k]) {    // a pack that is masked for the whole wave costs no arithmetic
                 unpack<T>(raw[r][k], v[k]);
                 if (!fold) {
@@ -499,7 +504,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
             if (j0 >= kEarly) {
-                if (j0 < limit[r]) {
+                if (pack_needed<RAG>(j0, limit[r])) {
                     ry[r][k] = load_row_pack<T, LPR, VPL, RAG>(y, rp[r], idx, blk.elems);
                     rg[r][k] = load_row_pack<T, LPR, VPL, RAG>(dy, rp[r], idx, blk.elems);
                 } else {

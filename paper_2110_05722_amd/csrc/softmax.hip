@@ -84,6 +84,32 @@ __device__ __forceinline__ int row_limit(const SoftmaxGeom& g, const SoftmaxLens
 template <bool RAG>
 __device__ __forceinline__ bool pack_needed(int j0, int limit) { return j0 < limit && (!RAG || limit > 0); }
 
+// With query lengths the rows of padded queries, often half of the tensor, need no load at all.  Then a row's limit is waited for before anything
+// is loaded (`sm_late_*`; otherwise the first 128 bytes go out before it is known), and a wave whose rows are all empty writes its zeros and
+// leaves (`sm_leaves_*`).  Where which is faster, time of the late loads over the early ones (16 bits / fp32; lengths full, three quarters, half):
+//  - rows of up to 128 bytes are loaded whole before the limit: late 1.1-1.37 / 1.0-1.12 whatever the padding (64 x 16 x 64 x 64 fp16 with
+//    dropout, forward 6.9 -> 8.9 us), leaving gains nothing there;
+//  - forward, whole packs, below 1024 bytes 0.76-1.0; longer ones with half of their rows empty lose (1000 keys fp16 with dropout
+//    1.12, fp32 1.27, 512 keys fp32 1.18), full ones gain 1-4 %; only 16 bits without dropout keep 0.89-1.0 at any length;
+//  - forward, any other length 0.77-1.0 and with the leaving waves up to 0.10 less, but 16 bits beyond 1536 keys 1.0-1.18 (2001 keys),
+//    and with dropout beyond 640 leaving costs 0-0.13 again (1025 keys, half 0.99 -> 1.05, 2001 1.18 -> 1.23);
+//  - backward 0.72-1.0, but fp32 whole packs beyond 1024 keys 1.01-1.07 at half.
+// (empty rows above a causal mask's first key are few: they take the ordinary way.)
+template <typename T, bool DROP, bool RAG>
+__device__ __forceinline__ bool sm_late_fwd(int k_len)
+{
+    const int bytes = k_len * static_cast<int>(sizeof(T));
+    if (RAG) return bytes > 128 && (sizeof(T) == 4 || k_len <= 1536);
+    return bytes > 128 && (bytes < 1024 || (sizeof(T) == 2 && !DROP));
+}
+template <typename T, bool DROP>
+__device__ __forceinline__ bool sm_leaves_fwd(int k_len) { return !(sizeof(T) == 2 && DROP && k_len > 640); }
+template <typename T, bool RAG>
+__device__ __forceinline__ bool sm_late_bwd(int k_len)
+{
+    return k_len * static_cast<int>(sizeof(T)) > 128 && (sizeof(T) == 2 || RAG || k_len <= 1024);
+}
+
 // ---- where the packs of a row lie.  RAG = false: rows are whole packs (k_len % 8 == 0), pack idx of a row starts at
 // its element 8 * idx.  RAG = true: any k_len.  The packs are those of the FLAT tensor (aligned 128-bit accesses, and the
 // groups the dropout contract counts): a row that starts s elements into a pack touches (s + k_len + 7) / 8 of them, pack
@@ -324,9 +350,9 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
     // what lies beyond the limit is masked in registers): with a key-padding mask the limit comes
     // from memory, and waiting for it first would put two dependent round trips in front of
     // every row.  The other packs are loaded only if they reach into the allowed prefix.
-    // (a limit that is computed from the row index alone, causal or none, waits for nothing).  With query lengths the limit comes first:
-    // loads for the rows of padded queries, half of the tensor, cost more than the wait (the two kernels at 113 keys 37.5 -> 33.4 us).
-    const int kEarly = len.query ? -kPack : len.key ? 128 / static_cast<int>(sizeof(T)) : 0;
+    // (a limit that is computed from the row index alone, causal or none, waits for nothing).  With query lengths see sm_late_fwd.
+    const bool late = len.query && sm_late_fwd<T, DROP, RAG>(g.k_len);
+    const int kEarly = late ? -kPack : (len.key || len.query) ? 128 / static_cast<int>(sizeof(T)) : 0;
     RawPack<T> raw[RPT][VPL];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
@@ -343,7 +369,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
     }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
-    if (len.query) {                                                  // uniform: only there do rows come up empty in numbers
+    if (late && sm_leaves_fwd<T, DROP>(g.k_len)) {                    // uniform
         bool empty = true;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) empty = empty && limit[r] <= 0;
@@ -461,8 +487,9 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
     int row[RPT];             // counted from the workgroup's first
     RowPacks<RAG> rp[RPT];
     int limit[RPT];
-    // as in forward: the first 128 bytes of a row are loaded before its limit is known, unless there are query lengths
-    const int kEarly = len.query ? -kPack : len.key ? 128 / static_cast<int>(sizeof(T)) : 0;
+    // as in forward: the first 128 bytes of a row are loaded before its limit is known, unless sm_late_bwd says otherwise
+    const bool late = len.query && sm_late_bwd<T, RAG>(g.k_len);
+    const int kEarly = late ? -kPack : (len.key || len.query) ? 128 / static_cast<int>(sizeof(T)) : 0;
     RawPack<T> ry[RPT][VPL], rg[RPT][VPL];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
@@ -484,7 +511,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
     }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
-    if (len.query) {                                                  // uniform: only there do rows come up empty in numbers
+    if (late) {                                                       // uniform
         bool empty = true;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) empty = empty && limit[r] <= 0;

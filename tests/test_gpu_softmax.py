@@ -276,7 +276,7 @@ def test_softmax_rows_through_lds(dt, B, N, Lq, Lk, mask, p):
 
 
 # waves whose rows are all empty leave early and write their rows as one range of zeros: rows of every lane count, whole packs and not,
-# ranges that begin and end anywhere in a pack, an empty tensor beside a full one, and rows above a causal mask's first key
+# ranges that begin and end anywhere in a pack, an empty sentence beside a full one (rows above a causal mask's first key stay in the ordinary way)
 @pytest.mark.parametrize("dt", ["f16", "f32"])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Lq,Lk", [(70, 3), (70, 8), (66, 13), (70, 24), (131, 31), (70, 64), (67, 113), (70, 128), (41, 130), (37, 256), (33, 301), (19, 512), (19, 701),
@@ -302,3 +302,11 @@ def test_softmax_rows_of_padded_queries(Lq, Lk, causal, dt):
     for b in range(B):
         spoilt[b, :, qlen[b]:] = float("nan")
     assert torch.equal(L.lsq_softmax_varlen_fwd(spoilt, kl, ql, causal, 0.4, 0.0)[0], L.lsq_softmax_varlen_fwd(to_torch(xs, dt, d).view(B, N, Lq, Lk), kl, ql, causal, 0.4, 0.0)[0])
+
+
+# the lines of the loads behind the limit and of the waves that leave (128 and 1024 bytes, 640, 1024 and 1536 keys), both sides
+@pytest.mark.parametrize("dt", ["f16", "f32"])
+@pytest.mark.parametrize("Lq,Lk", [(66, 16), (66, 32), (66, 40), (66, 65), (35, 248), (35, 255), (35, 257), (21, 504), (21, 520), (21, 639), (21, 641), (19, 1023),
+                                   (19, 1024), (19, 1032), (19, 1536), (19, 1537)])
+def test_softmax_padded_queries_at_the_lines(Lq, Lk, dt):
+    test_softmax_rows_of_padded_queries(Lq, Lk, Lk % 2 == 0, dt)

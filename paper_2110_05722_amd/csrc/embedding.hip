@@ -732,7 +732,7 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
                                               const int32_t* __restrict__ tokens, int batch, int len,
                                               const RowPackIO<T, RAG>& io, int vocab, int pad_idx, const DropoutParams& d)
 {
-    constexpr int U = W == 16 ? 8 : 4, G = 256 / W;              // (600 sentences of 17, hidden 512: 24.8 us, 26.6 with four as W = 16)
+    constexpr int U = W == 16 && !RAG ? 8 : 4, G = 256 / W;              // (600 sentences of 17, hidden 512: 24.8 us, 26.6 with four as W = 16)
     const int lane = threadIdx.x % W, grp = threadIdx.x / W;
     const int cp = cb * W + lane;
     const bool active = cp < io.ppr;

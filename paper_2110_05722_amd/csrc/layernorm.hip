@@ -493,11 +493,15 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
     fetch(base + slot);
     float* sums = span_lds;                   // of this row; the other buffer next
     float* other = span_lds + blockDim.x / 16;
+    // Packs at any alignment with a residual gradient take 144 registers (fp32 158) with the next row loaded ahead; a 1024-thread workgroup
+    // has 128 and spilt 17 (46) of them: 700 x 6145 f32 54 us against 34 on the generic path.  Loaded behind the row, 4 (15) are spilt:
+    // 32.8 us, 700 x 7001 fp16 25.0 (before 37.1, generic 38.2).
+    constexpr bool AHEAD = !(RAG && HAS_RES && MAXT > kLnSpanThreads);
     for (; base < rows; base += gstride) {    // the same trips for every thread
         const int64_t r = base + slot;
         const RawPack<T> cdy = ndy, cx = nx, cres = nres;
         const float mu = nmu, rs = nrs;
-        if (base + gstride < rows) fetch(r + gstride);
+        if (AHEAD && base + gstride < rows) fetch(r + gstride);
 
         // the two row sums and the column sums; absent packs and rows hold dy = 0
         const float nmr = -mu * rs;
@@ -567,6 +571,7 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
                 for (int j = 0; j < 8; ++j) acc[2][j] += gq[j];
             }
         }
+        if (!AHEAD && base + gstride < rows) fetch(r + gstride);
     }
 
     for (int left = slots; left > 1;) {       // slot k takes slot k + half, until one is left

@@ -91,8 +91,9 @@ __device__ __forceinline__ uint32_t fastdiv(uint32_t n, const FastDiv& f)
 constexpr int kFinalizeSlices = 8, kFinalizeLoads = 32;
 
 // WHOLE: P is a whole number of batches (256 partial rows).  Otherwise a batch that runs past the slice's rows reads its last
-// row again and drops it: a loop over the left-over rows paid one latency each (170 x 1536: 4.2 us, now 2.4).
-template <bool WHOLE>
+// row again and drops it: a loop over the left-over rows paid one latency each (170 x 1536: 4.2 us, now 2.4).  LOADS: the batch; up to 32 partial
+// rows fit batches of four, whose sums round the same (feed-forward backward of 8 x 1024 with the batch of 32: 0.25 us more).
+template <bool WHOLE, int LOADS>
 __global__ __launch_bounds__(32 * kFinalizeSlices) void colsum_finalize_kernel(float* __restrict__ out0,
                                                                                float* __restrict__ out1,
                                                                                float* __restrict__ out2, int split,
@@ -107,15 +108,15 @@ __global__ __launch_bounds__(32 * kFinalizeSlices) void colsum_finalize_kernel(f
     const int y0 = slice * chunk, y1 = min(P, y0 + chunk);
     float s = 0.0f;
     if (c < C) {
-        for (int y = y0; y < y1; y += kFinalizeLoads) {
-            float t[kFinalizeLoads];
+        for (int y = y0; y < y1; y += LOADS) {
+            float t[LOADS];
 #pragma unroll
-            for (int k = 0; k < kFinalizeLoads; ++k) t[k] = partial[static_cast<int64_t>(WHOLE ? y + k : min(y + k, y1 - 1)) * C + c];
+            for (int k = 0; k < LOADS; ++k) t[k] = partial[static_cast<int64_t>(WHOLE ? y + k : min(y + k, y1 - 1)) * C + c];
 #pragma unroll
-            for (int k = 0; k < kFinalizeLoads; ++k) t[k] = WHOLE || y + k < y1 ? t[k] : 0.0f;
+            for (int k = 0; k < LOADS; ++k) t[k] = WHOLE || y + k < y1 ? t[k] : 0.0f;
             // pairwise: five roundings on a batch's way into the sum instead of up to 32
 #pragma unroll
-            for (int w = kFinalizeLoads / 2; w > 0; w /= 2)
+            for (int w = LOADS / 2; w > 0; w /= 2)
 #pragma unroll
                 for (int k = 0; k < w; ++k) t[k] += t[k + w];
             s += t[0];
@@ -138,9 +139,11 @@ inline void launch_colsum_finalize(float* out0, float* out1, int split, const fl
 {
     const dim3 grid(static_cast<unsigned>((C + 31) / 32)), block(32 * kFinalizeSlices);
     if (P % (kFinalizeSlices * kFinalizeLoads) == 0)
-        hipLaunchKernelGGL((colsum_finalize_kernel<true>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
+        hipLaunchKernelGGL((colsum_finalize_kernel<true, kFinalizeLoads>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
+    else if (P <= kFinalizeSlices * 4)
+        hipLaunchKernelGGL((colsum_finalize_kernel<false, 4>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
     else
-        hipLaunchKernelGGL((colsum_finalize_kernel<false>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
+        hipLaunchKernelGGL((colsum_finalize_kernel<false, kFinalizeLoads>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
 }
 
 // ---- short rows (up to 256 columns) of the element-wise operators

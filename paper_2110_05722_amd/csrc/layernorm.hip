@@ -623,12 +623,12 @@ __global__ __launch_bounds__(MAXT) void ln_fwd_rag_kernel(T* __restrict__ y, flo
     const int64_t gstride = static_cast<int64_t>(gridDim.x) * slots;
     auto total = [&](float v, float* buf) {
         v = group_sum<32>(v);
+        if (LR == 32) return v;                                    // a row within a wave: the same additions without LDS and barrier
+        if (LR == 64) return half_waves_sum(v);
         if ((threadIdx.x & 31) == 0) buf[threadIdx.x / 32] = v;
         __syncthreads();
         const int l = threadIdx.x & 31, groups = LR / 32;
         return group_sum<32>(l < groups ? buf[slot * groups + l] : 0.0f);
-        if (LR == 32) return v;                                    // a row within a wave: the same additions without LDS and barrier
-        if (LR == 64) return half_waves_sum(v);
     };
     const RawPack<T> gm = on ? io.template ahead<false>(gamma, 0, sub) : zero_raw<T>(), bt = on ? io.template ahead<false>(beta, 0, sub) : zero_raw<T>();
     int64_t base = static_cast<int64_t>(blockIdx.x) * slots;

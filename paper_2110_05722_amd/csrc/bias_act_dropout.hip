@@ -115,6 +115,11 @@ __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T*
             const float a = act_value<ACT>(xf[j] + b[j]);
             xf[j] = DROP ? a * k[j] : a;
         }
+        // the product rounds to fp32 first, as in the flat walk: a row's bits do not depend on which of them serves its call
+        if constexpr (RAG && DROP && sizeof(T) == 2) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) asm("" : "+v"(xf[j]));
+        }
         if (mine) io.template store<kNT>(out, r, cp, xf);
     }
 }
@@ -184,7 +189,8 @@ __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ p
     }
 }
 
-// ---- any hidden (rows are not a whole number of packs): the operators for flat_packs_kernel
+// ---- rows of up to 256 columns, and forward of long tensors of odd rows with a thin second column block (bad_fwd_is_flat): the operators for
+// flat_packs_kernel
 template <typename T, int ACT>
 struct BadFwdFlat {
     T* out;
@@ -206,6 +212,7 @@ struct BadFwdFlat {
             g[j] = d.on ? a * k[j] : a;
             c = c + 1 == hidden ? 0 : c + 1;
         }
+        pin_f32(g);                            // (no fused multiply and conversion, see bad_fwd_cols)
         store8<T, kNT>(out + e0, g);
     }
     __device__ __forceinline__ float one(int64_t e, int c) const
@@ -214,6 +221,7 @@ struct BadFwdFlat {
         if (bias) z += to_f32<T>(bias[c]);
         float a = act_value<ACT>(z);
         if (d.on) a *= dropout_factor1(d, static_cast<uint64_t>(e));
+        asm volatile("" : "+v"(a));
         out[e] = from_f32<T>(a);
         return a;
     }
@@ -263,7 +271,7 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
     T* o = static_cast<T*>(out);
     const T* xp = static_cast<const T*>(x);
     const T* bp = static_cast<const T*>(bias);
-    if (!bad_is_flat(hidden)) {
+    if (!bad_fwd_is_flat(rows, hidden, sizeof(T), d.on != 0)) {
         const int cb = bad_col_blocks(hidden);
         // two rows per wave: 28.1 / 23.1 us at 8192 x 5120 / 4096 x 4096 against 29.0 / 23.8 with four and 28.1 / 24.3 with one
         // (one where those workgroups are few: 512 x 2048 f32 3.5 against 3.8 us, 2694 x 1392 5.4 against 5.9; 2200 x 2048 5.5 against 5.2)

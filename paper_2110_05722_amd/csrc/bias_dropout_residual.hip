@@ -145,13 +145,15 @@ __global__ __launch_bounds__(64 * kBdrBwdWaves) void bdr_bwd_cols(T* dx, float* 
 // ---- rows that are not whole packs, walked in packs counted from the row's start (RowPackIO): a wave holds kRagLanes packs of a row, all its
 // lanes stay, because a pack's dropout words come from two lanes.  Forward / backward in us, the flat walk in brackets: 8192 x 1281 bf16 with
 // dropout 15.9 / 18.0 (19.2 / 25.0), 2000 x 5001 14.6 / 14.8 (19.4 / 32.2), 600 x 7001 fp16 8.9 / 11.1 (10.6 / 25.4), 500 x 259 f32 3.2 / 7.1 (8.9 / 9.1).
+// (backward with 4 waves a workgroup; the waves by type and width: bdr_bwd_dispatch)
 constexpr int kBdrRagWaves = 4;
+template <bool DROP> constexpr int kBdrRagLanes = DROP ? kRagLanes : kWave;      // (without dropout no lane needs its neighbour)
 
 template <typename T, bool DROP>
 __global__ __launch_bounds__(64 * kBdrRagWaves) void bdr_fwd_rag(T* out, const T* x, const T* __restrict__ bias, const T* res,
                                                                  int64_t rows, RowPackIO<T, true> io, DropoutParams d)
 {
-    const int lane = threadIdx.x & 63, col = blockIdx.x * kRagLanes + lane, cp = min(col, io.ppr - 1);
+    const int lane = threadIdx.x & 63, col = blockIdx.x * kBdrRagLanes<DROP> + lane, cp = min(col, io.ppr - 1);
     RawPack<T> braw = bias ? io.template ahead<false>(bias, 0, cp) : zero_raw<T>();      // uniform
     for (int64_t r = static_cast<int64_t>(blockIdx.y) * kBdrRagWaves + (threadIdx.x >> 6); r < rows; r += static_cast<int64_t>(gridDim.y) * kBdrRagWaves) {
         const RawPack<T> xr = io.template ahead<kNT>(x, r, cp), rr = io.template ahead<kNT>(res, r, cp);
@@ -167,20 +169,20 @@ __global__ __launch_bounds__(64 * kBdrRagWaves) void bdr_fwd_rag(T* out, const T
             rf[j] = DROP ? fmaf(z, k[j], rf[j]) : rf[j] + z;
         }
         pin_f32(rf);
-        if (col < io.ppr && lane < kRagLanes) io.template store<kNT>(out, r, cp, rf);
+        if (col < io.ppr && lane < kBdrRagLanes<DROP>) io.template store<kNT>(out, r, cp, rf);
     }
 }
 
-template <typename T, bool DROP>
-__global__ __launch_bounds__(64 * kBdrRagWaves) void bdr_bwd_rag(T* dx, float* __restrict__ partial, const T* dy, int64_t rows,
+template <typename T, bool DROP, int W>
+__global__ __launch_bounds__(64 * W) void bdr_bwd_rag(T* dx, float* __restrict__ partial, const T* dy, int64_t rows,
                                                                  RowPackIO<T, true> io, DropoutParams d)
 {
-    __shared__ float sm[kBdrRagWaves][8][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = blockIdx.x * kRagLanes + lane, cp = min(col, io.ppr - 1);
-    const bool mine = col < io.ppr && lane < kRagLanes;
+    __shared__ float sm[W][8][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = blockIdx.x * kBdrRagLanes<DROP> + lane, cp = min(col, io.ppr - 1);
+    const bool mine = col < io.ppr && lane < kBdrRagLanes<DROP>;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int64_t stride = static_cast<int64_t>(gridDim.y) * kBdrRagWaves;
-    int64_t r = static_cast<int64_t>(blockIdx.y) * kBdrRagWaves + wave;
+    const int64_t stride = static_cast<int64_t>(gridDim.y) * W;
+    int64_t r = static_cast<int64_t>(blockIdx.y) * W + wave;
     RawPack<T> nxt = r < rows ? io.template ahead<kNT>(dy, r, cp) : zero_raw<T>();
     for (; r < rows; r += stride) {
         const RawPack<T> cur = nxt;
@@ -207,13 +209,13 @@ __global__ __launch_bounds__(64 * kBdrRagWaves) void bdr_bwd_rag(T* dx, float* _
         for (int j = 0; j < 8; ++j) {
             float t = sm[0][j][lane];
 #pragma unroll
-            for (int w = 1; w < kBdrRagWaves; ++w) t += sm[w][j][lane];
+            for (int w = 1; w < W; ++w) t += sm[w][j][lane];
             if (cp * kPack + j < io.hidden) dst[j] = t;
         }
     }
 }
 
-// ---- any hidden (rows are not a whole number of packs): the operators for flat_packs_kernel
+// ---- short rows, and long tensors of odd rows with a thin second column block (bdr_fwd_is_flat, bdr_bwd_is_flat): the operators for flat_packs_kernel
 template <typename T>
 struct BdrFwdFlat {
     T* out;
@@ -286,7 +288,8 @@ static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, c
     const T* xp = static_cast<const T*>(x);
     const T* bp = static_cast<const T*>(bias);
     const T* rp = static_cast<const T*>(res);
-    if (!bdr_fwd_is_flat(hidden)) {
+    const bool flat = bdr_fwd_is_flat(rows, hidden, sizeof(T), d.on != 0);
+    if (!flat && !odd_in_packs(hidden)) {
         const int ppr = hidden / kPack;
         const int w = bdr_lanes_per_row(ppr);
         const int64_t rpi = static_cast<int64_t>(kBdrFwdWaves) * (64 / w) * kBdrFwdUnroll;     // rows of a workgroup's trip
@@ -303,11 +306,11 @@ static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, c
         }
         LSQ_BDR_FWD(32) LSQ_BDR_FWD(16)
 #undef LSQ_BDR_FWD
-    } else if (bdr_is_rag(hidden)) {
+    } else if (!flat) {
         const RowPackIO<T, true> io(hidden);
         int64_t rb = ceil_div(rows, kBdrRagWaves);
         if (rb > 8192) rb = 8192;
-        const dim3 grid(static_cast<unsigned>(ceil_div(io.ppr, kRagLanes)), static_cast<unsigned>(rb)), block(64 * kBdrRagWaves);
+        const dim3 grid(static_cast<unsigned>(ceil_div(io.ppr, d.on ? kRagLanes : kWave)), static_cast<unsigned>(rb)), block(64 * kBdrRagWaves);
         if (d.on) hipLaunchKernelGGL((bdr_fwd_rag<T, true>), grid, block, 0, s, o, xp, bp, rp, rows, io, d);
         else hipLaunchKernelGGL((bdr_fwd_rag<T, false>), grid, block, 0, s, o, xp, bp, rp, rows, io, d);
     } else {
@@ -322,7 +325,8 @@ static lsq_status bdr_bwd_dispatch(void* dx, float* dbias, const void* dy, int64
 {
     T* o = static_cast<T*>(dx);
     const T* g = static_cast<const T*>(dy);
-    if (!bdr_bwd_is_flat(hidden)) {
+    const bool flat = bdr_bwd_is_flat(rows, hidden, sizeof(T), d.on != 0);
+    if (!flat && !odd_in_packs(hidden)) {
         const int ppr = hidden / kPack;
         const BdrBwdPlan pl = bdr_bwd_plan(rows, hidden);
         const dim3 grid(static_cast<unsigned>(pl.col_blocks), static_cast<unsigned>(pl.row_blocks)), block(64 * kBdrBwdWaves);
@@ -335,13 +339,21 @@ static lsq_status bdr_bwd_dispatch(void* dx, float* dbias, const void* dy, int64
         LSQ_BDR_BWD(32) LSQ_BDR_BWD(16)
         if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, pl.row_blocks, hidden, s);
 #undef LSQ_BDR_BWD
-    } else if (bdr_is_rag(hidden)) {
+    } else if (!flat) {
         const RowPackIO<T, true> io(hidden);
         const int rb = bdr_rag_row_blocks(rows, hidden);
-        const dim3 grid(static_cast<unsigned>(ceil_div(io.ppr, kRagLanes)), static_cast<unsigned>(rb)), block(64 * kBdrRagWaves);
+        const int col_blocks = static_cast<int>(ceil_div(io.ppr, d.on ? kRagLanes : kWave));
+        // 4 / 8 / 16 waves, at most 256 partial rows either way: fp16 with dropout 65536 x 257 48.3 / 32.1 / 27.3 us, 65536 x 505 67 / 50 / 52,
+        // 32768 x 1001 40.7 / 33.6 / 35.6, 4096 x 1281 11.8 / 11.6 / 13.6; fp32 65536 x 257 60.5 / 38.3 / 35.1, but over several column
+        // blocks 32768 x 700 52.0 / 57.7 / 58.8, 4096 x 1281 12.8 / 13.4 / 14.7, and 16 bits beyond three 16384 x 2050 0.62 / 0.65 of the flat walk
+        const int waves = col_blocks <= (sizeof(T) == 2 ? 3 : 1) ? 8 : 4;
+        const dim3 grid(static_cast<unsigned>(col_blocks), static_cast<unsigned>(rb)), block(64 * waves);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        if (d.on) hipLaunchKernelGGL((bdr_bwd_rag<T, true>), grid, block, 0, s, o, partial, g, rows, io, d);
-        else hipLaunchKernelGGL((bdr_bwd_rag<T, false>), grid, block, 0, s, o, partial, g, rows, io, d);
+#define LSQ_BDR_RAG(DROP)                                                                                                       \
+        if (waves == 8) hipLaunchKernelGGL((bdr_bwd_rag<T, DROP, 8>), grid, block, 0, s, o, partial, g, rows, io, d);      \
+        else hipLaunchKernelGGL((bdr_bwd_rag<T, DROP, 4>), grid, block, 0, s, o, partial, g, rows, io, d)
+        if (d.on) { LSQ_BDR_RAG(true); } else { LSQ_BDR_RAG(false); }
+#undef LSQ_BDR_RAG
         if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, rb, hidden, s);
     } else {
         // every pack is read and written by one thread, which also hands its fp32 results to the column sums: in place is fine
@@ -392,7 +404,7 @@ extern "C" lsq_status lsq_bias_dropout_residual_bwd(void* dx, float* dbias, cons
     LSQ_ALIGNED(dx); LSQ_ALIGNED(dy); LSQ_ALIGNED(dbias); LSQ_ALIGNED(workspace);
     LSQ_REQUIRE(ceil_div(rows * hidden, 256) <= 0x7FFFFFFF);
     if (dbias) {
-        const size_t need = bdr_bwd_bytes(rows, hidden);
+        const size_t need = bdr_bwd_bytes(rows, hidden, dt == LSQ_F32 ? 4 : 2, d.on != 0);
         if (need && (!workspace || workspace_bytes < need)) return LSQ_WORKSPACE_TOO_SMALL;
     }
     switch (dt) {

@@ -344,15 +344,41 @@ inline int bdr_lanes_per_row(int ppr)
     return 16;
 }
 
-// Rows of very few packs leave most lanes of a 16-lane row segment idle; they take the flat walk like the
-// rows that are not whole packs (measured at 32 Mi elements: forward 187 / 94 / 63 us at 8 / 16 / 24 columns
-// against 47 us flat; backward 860 / 439 / 175 / 83 / 80 us at 8 / 16 / 24 / 64 / 72 columns against 48 us flat).
-inline bool bdr_fwd_is_flat(int hidden) { return hidden % kPack != 0 || hidden <= 32; }
-inline bool bdr_bwd_is_flat(int hidden) { return hidden % kPack != 0 || hidden < 128; }
-// bias + activation + dropout works in column blocks of 64 packs: rows of up to 32 packs take the flat walk
-// (8 columns: 1629 / 10103 us in column blocks at 32 Mi elements, 51 / 95 us flat; 256 columns: 56 / 138 us).
-inline bool bad_is_flat(int hidden) { return hidden <= 256; }
-// column blocks: 64 packs, 63 where rows are not whole packs
+// Rows that are not whole packs run in packs of their own (RowPackIO) from 257 columns on; shorter ones, and rows of very few packs, take the
+// flat walk.  Rows of few packs leave most lanes of a 16-lane row segment idle (measured at 32 Mi elements: forward
+// 187 / 94 / 63 us at 8 / 16 / 24 columns against 47 us flat; backward 860 / 439 / 175 / 83 / 80 us at 8 / 16 / 24 / 64 / 72
+// columns against 48 us flat), bias + activation + dropout works in column blocks of 64 packs
+// (8 columns: 1629 / 10103 us in column blocks at 32 Mi elements, 51 / 95 us flat; 256 columns: 56 / 138 us).  For odd rows the same line:
+// 257 columns in packs of their own against flat, 64 to 65536 rows, 0.43-1.12 in the four forward and backward kernels, 1.12 once.
+constexpr int kFlatColumns = 256;
+inline bool odd_in_packs(int hidden) { return hidden % kPack != 0 && hidden > kFlatColumns; }
+inline bool bdr_fwd_is_flat(int hidden) { return hidden % kPack != 0 ? hidden <= kFlatColumns : hidden <= 32; }
+inline bool bdr_bwd_is_flat(int hidden) { return hidden % kPack != 0 ? hidden <= kFlatColumns : hidden < 128; }
+inline bool bad_is_flat(int hidden) { return hidden <= kFlatColumns; }
+// A wave holds 64 packs of an odd row, 63 with dropout (dropout_factors8_row) and in bias + activation + dropout.  Rows of a few
+// packs more leave a second column block with as good as nothing to do, and long tensors of them are faster flat.  Packs of
+// their own against flat: bias + activation + dropout forward, 16 bits with dropout 505 columns 8192 / 24000 / 65536 rows 1.14 / 1.20 /
+// 1.12, 513 columns 12000 / 24000 1.15 / 1.20, 545 24000 / 65536 0.93 / 1.10 (4096: 0.91, 0.90; 593 columns 0.78-0.96; fp32 0.83-1.06);
+// bias + dropout + residual fp32, forward 505 with dropout 12000 / 16384 / 65536 0.76 / 1.10 / 1.12, without 513 16384 / 65536 0.93 / 1.06, 545 24000 /
+// 65536 0.92 / 1.08, backward 505 / 513 / 593 / 641 at 24000 1.20 / 1.20 / 1.07 / 1.09 (16384 rows 0.71-0.95; 700 columns 1.00).
+inline int odd_second_block(int hidden, int lanes) { return (hidden + kPack - 1) / kPack - lanes; }       // packs of it
+inline bool bad_fwd_is_flat(int64_t rows, int hidden, int elem_bytes, bool drop)
+{
+    const int n = odd_second_block(hidden, kRagLanes);
+    return bad_is_flat(hidden) ||
+           (odd_in_packs(hidden) && elem_bytes == 2 && drop && n >= 1 && n <= 6 && rows * hidden >= (n == 1 ? 4000000 : n == 2 ? 6000000 : 30000000));
+}
+inline bool bdr_fwd_is_flat(int64_t rows, int hidden, int elem_bytes, bool drop)
+{
+    const int n = odd_second_block(hidden, drop ? kRagLanes : kWave);
+    return bdr_fwd_is_flat(hidden) || (odd_in_packs(hidden) && elem_bytes == 4 && n >= 1 && n <= 6 && rows * hidden >= (n == 1 && drop ? 8000000 : 20000000));
+}
+inline bool bdr_bwd_is_flat(int64_t rows, int hidden, int elem_bytes, bool drop)
+{
+    const int n = odd_second_block(hidden, drop ? kRagLanes : kWave);
+    return bdr_bwd_is_flat(hidden) || (odd_in_packs(hidden) && elem_bytes == 4 && n >= 1 && n <= 18 && rows * hidden >= (n <= 6 ? 10000000 : 14000000));
+}
+// column blocks of bias + activation + dropout: 64 packs, 63 where rows are not whole packs
 inline int bad_col_blocks(int hidden) { return static_cast<int>(ceil_div(ceil_div(hidden, kPack), hidden % kPack == 0 ? 64 : kRagLanes)); }
 
 // Backward launch shape: column blocks of w packs; row blocks (= partial rows of the column sums) of
@@ -402,8 +428,6 @@ inline int colsum_row_blocks_upto(int64_t rows, int32_t hidden, int target)
     const int here = colsum_row_blocks(rows, hidden, target), at = rows > 2048 ? colsum_row_blocks(2048, hidden, target) : 0;
     return here > at ? here : at;
 }
-// rows that are not whole packs in packs of their own: bias + dropout + residual from 257 columns on (see bad_is_flat)
-inline bool bdr_is_rag(int hidden) { return hidden % kPack != 0 && hidden > 256; }
 inline int bdr_rag_row_blocks(int64_t rows, int32_t hidden)
 {
     const int b = colsum_row_blocks(rows, hidden, kBdrBwdWorkgroups);
@@ -417,27 +441,27 @@ inline int heads_bwd_row_blocks(int64_t rows, int32_t hidden) { return colsum_ro
 // is fastest at each size and fall here and there as the rows grow; a program that keeps one workspace of its longest
 // batch's size is not to notice.
 inline size_t partial_bytes(int64_t row_blocks, int32_t cols) { return static_cast<size_t>(row_blocks) * static_cast<size_t>(cols) * sizeof(float); }
-inline size_t bdr_bwd_bytes(int64_t rows, int32_t hidden)
+inline size_t bdr_bwd_bytes(int64_t rows, int32_t hidden, int elem_bytes, bool drop)
 {
-    if (!bdr_bwd_is_flat(hidden)) return partial_bytes(bdr_bwd_plan(rows, hidden).row_blocks, hidden);
-    if (bdr_is_rag(hidden)) return partial_bytes(bdr_rag_row_blocks(rows, hidden), hidden);
-    return flat_workspace_bytes(rows, hidden);
+    if (bdr_bwd_is_flat(rows, hidden, elem_bytes, drop)) return flat_workspace_bytes(rows, hidden);
+    return partial_bytes(odd_in_packs(hidden) ? bdr_rag_row_blocks(rows, hidden) : bdr_bwd_plan(rows, hidden).row_blocks, hidden);
 }
 inline size_t bdr_bwd_bytes_upto(int64_t rows, int32_t hidden)
 {
-    if (!bdr_bwd_is_flat(hidden)) {                   // at most one per group of rows, and rb_max of bdr_bwd_plan
-        const BdrBwdPlan one = bdr_bwd_plan(1, hidden);
-        const int64_t units = ceil_div(rows, static_cast<int64_t>(kBdrBwdWaves) * (64 / one.w));
-        int64_t most = kBdrBwdWorkgroups / one.col_blocks;
-        if (most > kBdrBwdMaxPartials) most = kBdrBwdMaxPartials;
-        if (most > units) most = units;
-        return partial_bytes(most < 1 ? 1 : most, hidden);
-    }
-    if (bdr_is_rag(hidden)) {
+    if (bdr_bwd_is_flat(hidden)) return flat_workspace_bytes_upto(rows, hidden);
+    if (odd_in_packs(hidden)) {                       // the flat walk of a long fp32 call included
         const int b = colsum_row_blocks_upto(rows, hidden, kBdrBwdWorkgroups);
-        return partial_bytes(b < kBdrBwdMaxPartials ? b : kBdrBwdMaxPartials, hidden);
+        const size_t packs = partial_bytes(b < kBdrBwdMaxPartials ? b : kBdrBwdMaxPartials, hidden);
+        const size_t flat = bdr_bwd_is_flat(rows, hidden, 4, true) || bdr_bwd_is_flat(rows, hidden, 4, false) ? flat_workspace_bytes_upto(rows, hidden) : 0;
+        return packs > flat ? packs : flat;
     }
-    return flat_workspace_bytes_upto(rows, hidden);
+    // at most one per group of rows, and rb_max of bdr_bwd_plan
+    const BdrBwdPlan one = bdr_bwd_plan(1, hidden);
+    const int64_t units = ceil_div(rows, static_cast<int64_t>(kBdrBwdWaves) * (64 / one.w));
+    int64_t most = kBdrBwdWorkgroups / one.col_blocks;
+    if (most > kBdrBwdMaxPartials) most = kBdrBwdMaxPartials;
+    if (most > units) most = units;
+    return partial_bytes(most < 1 ? 1 : most, hidden);
 }
 inline size_t bad_bwd_bytes(int64_t rows, int32_t hidden)
 {

@@ -1258,7 +1258,7 @@ extern "C" lsq_status lsq_bdr_layernorm_bwd(void* dh, void* dx, float* dgamma, f
     LSQ_ALIGNED(dh); LSQ_ALIGNED(dx); LSQ_ALIGNED(dy); LSQ_ALIGNED(h); LSQ_ALIGNED(gamma); LSQ_ALIGNED(dres_in);
     LSQ_ALIGNED(workspace);
     LSQ_REQUIRE(ceil_div(rows * hidden, 256) <= 0x7FFFFFFF);
-    const size_t fused = ln_bwd_bytes(rows, hidden, 3), apart = bdr_bwd_bytes(rows, hidden), need = fused > apart ? fused : apart;
+    const size_t fused = ln_bwd_bytes(rows, hidden, 3), apart = bdr_bwd_bytes(rows, hidden, dt == LSQ_F32 ? 4 : 2, d.on != 0), need = fused > apart ? fused : apart;
     if (need && (!workspace || workspace_bytes < need)) return LSQ_WORKSPACE_TOO_SMALL;
     if (ln_shape(hidden).lpr == 0 || ln_shape(hidden).lpr > 256) {      // no fused bucket: the two operators back to back
         const lsq_status st = lsq_layernorm_bwd(dh, dgamma, dbeta, dy, h, gamma, mean, rstd, dres_in, workspace,

@@ -122,3 +122,31 @@ def test_bdr_empty():
     dx, dbias = L.lsq_bias_dropout_residual_bwd(x, 0.1, 1, 0)
     torch.cuda.synchronize()
     assert out.numel() == 0 and dbias.abs().sum().item() == 0
+
+
+# long fp32 tensors of odd rows whose second column block is thin take the flat walk: both sides of its lines, with and without dropout.  A row
+# does not depend on the path (its first rows against a short call's, bit for bit); the column sums against 64 bits.
+@pytest.mark.parametrize("p", [0.0, 0.2])
+@pytest.mark.parametrize("hidden", [505, 511, 513, 545, 553, 641, 657])
+def test_bdr_long_tensors_of_odd_rows(hidden, p):
+    d = dev()
+    g = torch.Generator(device=d)
+    g.manual_seed(hidden)
+    bias = torch.randn(hidden, generator=g, device=d)
+    for elements in (8_000_000, 10_000_000, 14_000_000, 20_000_000):
+        for rows in (elements // hidden, -(-elements // hidden)):
+            say(f"[bdr] long rows={rows} hidden={hidden} p={p}")
+            x, res = (torch.randn(rows, hidden, generator=g, device=d) for _ in range(2))
+            out = L.lsq_bias_dropout_residual_fwd(x, bias, res, p, 3, 1 << 33)
+            dx, dbias = L.lsq_bias_dropout_residual_bwd(x, p, 3, 1 << 33)
+            n = 300
+            assert torch.equal(out[:n], L.lsq_bias_dropout_residual_fwd(x[:n], bias, res[:n], p, 3, 1 << 33))
+            assert torch.equal(dx[:n], L.lsq_bias_dropout_residual_bwd(x[:n], p, 3, 1 << 33)[0])
+            if p == 0.0:
+                assert torch.equal(out, res + (x + bias)) and torch.equal(dx, x)
+            else:
+                kept = (dx != 0) | (x == 0)                   # (a drawn 0 is neither)
+                assert torch.equal(dx[kept], (x * torch.tensor(1 / (1 - p), dtype=torch.float32, device=d))[kept]) and abs(kept.double().mean().item() - 0.8) < 1e-3
+                assert torch.equal(out[~kept], res[~kept])
+            # fp32 sums of `rows` unit terms in partial sums: 2^-24 of a partial sum's size, about sqrt(rows), each
+            assert (dbias.double() - dx.double().sum(0)).abs().max() < 4e-6 * rows ** 0.5

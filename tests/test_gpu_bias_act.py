@@ -109,3 +109,30 @@ def test_one_workspace_of_the_longest_batch():
         din, db = L.lsq_split_heads_bwd(g, 1, rows, 8, 64, workspace=ws[3])
         want = torch.stack([t[0].transpose(0, 1).reshape(rows, 512) for t in g], 1).reshape(rows, 1536)
         assert torch.equal(din, want) and torch.allclose(db, want.sum(0), rtol=1e-5, atol=2e-6 * rows)
+
+
+# forward of long tensors of odd rows whose second column block is thin takes the flat walk: both sides of its lines; a row does not depend on
+# the path (the first rows against a short call's, bit for bit)
+@pytest.mark.parametrize("hidden,elements,dt,p", [(505, 4_000_000, "f16", 0.1), (511, 4_000_000, "bf16", 0.3), (513, 6_000_000, "f16", 0.1), (519, 6_000_000, "bf16", 0.1),
+                                                  (521, 6_000_000, "f16", 0.1), (545, 30_000_000, "f16", 0.1), (553, 30_000_000, "bf16", 0.1), (505, 6_000_000, "f16", 0.0), (513, 6_000_000, "f32", 0.1)])
+def test_bias_act_long_tensors_of_odd_rows(hidden, elements, dt, p):
+    d = dev()
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    g = torch.Generator(device=d)
+    g.manual_seed(hidden)
+    bias = torch.randn(hidden, generator=g, device=d).to(tdt)
+    for rows in (elements // hidden, -(-elements // hidden)):
+        x = torch.randn(rows, hidden, generator=g, device=d).to(tdt)
+        for act in ("relu", "gelu", "gelu_tanh"):
+            say(f"[bias_act_dropout] long rows={rows} hidden={hidden} dt={dt} p={p} {act}")
+            out = L.lsq_bias_act_dropout_fwd(x, bias, act, p, 5, 9)
+            assert torch.equal(out[:300], L.lsq_bias_act_dropout_fwd(x[:300], bias, act, p, 5, 9))
+            z = x.double() + bias.double()
+            ref = z.clamp(min=0) if act == "relu" else torch.nn.functional.gelu(z, approximate="tanh" if act == "gelu_tanh" else "none")
+            kept = out != 0
+            # one rounding to the storage type (2^-11, 2^-8) and fp32 arithmetic: 4e-6 relative to the largest term
+            err = (out.double() - ref / (1 - p)).abs()
+            tol = {"f16": 2.0 ** -10, "bf16": 2.0 ** -7, "f32": 1e-5}[dt] * ref.abs() + 1e-5
+            assert (err[kept] <= tol[kept]).all()
+            share = ((ref.abs() > 1e-2) & ~kept).double().sum() / (ref.abs() > 1e-2).double().sum()
+            assert abs(share.item() - p) < 2e-3

@@ -1,5 +1,5 @@
 """Python binding of include/lsq.h.  Argument marshalling only: the calls themselves go through csrc/calls.cpp (a CPython
-extension, `_calls.so`), `load()` gives the same entry points as ctypes functions.
+extension, `_calls`), `load()` gives the same entry points as ctypes functions.
 
 Every wrapper takes torch tensors that already live on the GPU, passes their
 device pointers, the sizes and the current HIP stream to the C entry point of
@@ -10,12 +10,13 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sysconfig
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "liblsq.so")
-_CALLS_PATH = os.path.join(_HERE, "_calls.so")
+_CALLS_PATH = os.path.join(_HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 _lib = None
 
 LSQ_F16, LSQ_BF16, LSQ_F32 = 0, 1, 2
@@ -179,8 +180,12 @@ class _Native:
         if not os.path.exists(_CALLS_PATH):
             raise LsqError(f"{_CALLS_PATH} is missing: build it with `python -m paper_2110_05722_amd.build` "
                            "(there is no fallback path)")
-        from . import _calls
-
+        try:
+            from . import _calls
+        except ImportError as e:
+            raise LsqError(f"{_CALLS_PATH} does not load here ({e}): build it again") from e
+        if _calls.torch_version != str(torch.__version__):
+            raise LsqError(f"{_CALLS_PATH} was built for torch {_calls.torch_version}, this is {torch.__version__}: build it again")
         _calls.setup(LsqError, C.ArgumentError, lambda: _stream(), _ptr, _need, _empty, lambda t: torch.empty_like(t))
         _native = _calls
         return getattr(_calls, name)

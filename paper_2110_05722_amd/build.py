@@ -1,4 +1,4 @@
-"""Builds `liblsq.so` (the C-ABI library of include/lsq.h) for gfx950 with hipcc, and `_calls.so` (how Python calls it) with g++.
+"""Builds `liblsq.so` (the C-ABI library of include/lsq.h) for gfx950 with hipcc, and `_calls.<interpreter>.so` (how Python calls it) with g++.
 
     python -m paper_2110_05722_amd.build
 
@@ -20,7 +20,8 @@ LIB = os.path.join(HERE, "liblsq.so")
 OBJ_DIR = os.path.join(HERE, "_build", "liblsq.so")
 SOURCES = ["api", "calibrate", "adam", "bias_dropout_residual", "bias_act_dropout", "heads", "embedding", "pad", "layernorm", "softmax",
            "ls_xent"]
-CALLS = os.path.join(HERE, "_calls.so")
+# the interpreter's tag in the name: another Python does not find it (and the torch it was built with is checked when it is loaded)
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 CXX = os.environ.get("CXX", "g++")
 FLAGS = [
@@ -58,18 +59,22 @@ def build(verbose: bool = True, lib: str = LIB, obj_dir: str = OBJ_DIR, extra: t
 
 
 def build_calls(verbose: bool = True) -> str:
-    """`_calls.so`, the CPython extension of csrc/calls.cpp (host code; linked against liblsq.so beside it and torch's libraries,
+    """The CPython extension of csrc/calls.cpp (host code; linked against liblsq.so beside it and torch's libraries,
     which the process has loaded by then)."""
     import torch
 
     t = os.path.dirname(torch.__file__)
     inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
     cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DLSQ_TORCH_VERSION="{torch.__version__}"',
            *(f"-I{i}" for i in inc), os.path.join(CSRC, "calls.cpp"), "-o", CALLS, f"-L{HERE}", "-l:liblsq.so",
            f"-L{os.path.join(t, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"{CXX} failed on calls.cpp:\n{r.stderr}")
+    untagged = os.path.join(HERE, "_calls.so")          # a build of before the tag: any Python would take it
+    if os.path.exists(untagged):
+        os.remove(untagged)
     if verbose:
         print(f"built {CALLS}")
     return CALLS

@@ -255,4 +255,14 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module_def); }
+// It is compiled against torch's own headers (THPDtype, the tensor's layout), which promise nothing from one version to the next:
+// binding.py compares `torch_version` before it uses anything else here.
+PyMODINIT_FUNC PyInit__calls()
+{
+    PyObject* m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "torch_version", LSQ_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -134,3 +134,21 @@ def test_on_the_gpu_parameters_and_subclasses_are_tensors_like_any_other():
         L.lsq_layernorm_fwd(torch.randn(64, 9, device="cuda").t(), g, b)
     with pytest.raises(L.LsqError, match="unsupported dtype torch.float64"):
         L.lsq_layernorm_fwd(x.double(), g.double(), b.double())
+
+
+def test_an_extension_of_another_torch_or_python_is_refused(monkeypatch):
+    """It is built against torch's own headers: what another interpreter or torch would load is refused, before anything in it is used."""
+    import sysconfig
+    assert binding._CALLS_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    assert binding._native.need() is None
+    loaded = binding._native
+    monkeypatch.setattr(binding, "_native", binding._Native())
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "1.0.0")
+        with pytest.raises(L.LsqError, match="built for torch .* this is 1.0.0"):
+            binding._native.need()
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_CALLS_PATH", binding._CALLS_PATH + ".absent")
+        with pytest.raises(L.LsqError, match="is missing"):
+            binding._native.need()
+    assert binding._native.need() is None and binding._native is loaded

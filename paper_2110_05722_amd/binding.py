@@ -665,6 +665,7 @@ def lsq_softmax_varlen_bwd(dy, y, key_len=None, query_len=None, causal: bool = F
 def lsq_calib_stream(kind: str, dst, src=None, nbytes: int = 0):
     """A plain memory stream (measurement aid): kind = "copy" | "read" | "write" | "empty"."""
     k = {"copy": 0, "read": 1, "write": 2, "empty": 3}[kind]
+    _native.need("dst", dst, 0, None, "src", src, 0, None)       # tensors, not addresses
     _native.lsq_calib_stream(k, dst, src, nbytes)
 
 

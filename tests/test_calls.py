@@ -152,3 +152,14 @@ def test_an_extension_of_another_torch_or_python_is_refused(monkeypatch):
         with pytest.raises(L.LsqError, match="is missing"):
             binding._native.need()
     assert binding._native.need() is None and binding._native is loaded
+
+
+def test_addresses_are_not_tensors():
+    """No wrapper takes a bare address in a tensor's place (None in a position that may be empty is another matter)."""
+    for args in (("copy", A, None, 16), ("read", None, A, 16), ("write", True, None, 16)):
+        assert outcome(lambda: L.lsq_calib_stream(*args))[0] is AttributeError
+    t = torch.zeros(4, 8)
+    for call in (lambda: L.lsq_layernorm_fwd(t, A, t[0]), lambda: L.lsq_bias_dropout_residual_fwd(t, None, A, 0.0, 1, 1), lambda: L.lsq_merge_heads_fwd(A),
+                 lambda: L.lsq_adam_step(A, t, t, t, lr=1e-3, beta1=0.9, beta2=0.9, eps=1e-8, step=1), lambda: L.lsq_embedding_fwd(A, t, t, 0, 1.0, 0.0, 1, 1),
+                 lambda: L.lsq_pad_remove(t.view(1, 4, 8), A, 2), lambda: L.lsq_ls_xent_fwd(t, A, 0.1), lambda: L.lsq_softmax_fwd(t.view(1, 1, 4, 8), key_len=A)):
+        assert outcome(call)[0] is AttributeError

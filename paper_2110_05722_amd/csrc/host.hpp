@@ -293,6 +293,7 @@ inline LnBwdPlan ln_bwd_span_plan(int64_t rows, int32_t hidden)
     // than leave three trips, which the loads ahead can overlap (2200 x 512: 3 slots 8.8, 8 slots 9.4 us).
     const int most = kLnSpanThreads / p.lanes;
     int64_t cap = ceil_div(rows, static_cast<int64_t>(kMaxBlocks) * 3);
+    if (half_wave && cap == 3) cap = 4;      // pairs: two would leave five trips (2100 x 520 fp16 9.6 -> 8.9 us)
     if (cap > most) cap = most;
     p.slots = 0;
     int64_t best = 0;

@@ -268,3 +268,9 @@ def test_layernorm_rows_do_not_depend_on_the_batch(hidden, dt):
         assert all(torch.equal(a, b[:n]) for a, b in zip(got, want)), n
         assert all(torch.equal(a, b[:n]) for a, b in zip(gotf, wantf)), n
         assert torch.equal(gotb, wantb[:n]), n
+
+
+# half-wave rows come in pairs: three trips' worth of rows is two pairs (1537..2304 rows)
+@pytest.mark.parametrize("rows,hidden", [(1536, 520), (1537, 640), (2304, 768), (2305, 520), (2100, 1281)])
+def test_layernorm_bwd_pairs_of_rows(rows, hidden):
+    (test_layernorm_bwd_rows_over_several_waves if hidden % 8 == 0 else test_layernorm_rows_of_any_length)(rows, hidden, "f16")

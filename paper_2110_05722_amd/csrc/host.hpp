@@ -91,8 +91,9 @@ __device__ __forceinline__ uint32_t fastdiv(uint32_t n, const FastDiv& f)
 constexpr int kFinalizeSlices = 8, kFinalizeLoads = 32;
 
 // WHOLE: P is a whole number of batches (256 partial rows).  Otherwise a batch that runs past the slice's rows reads its last
-// row again and drops it: a loop over the left-over rows paid one latency each (170 x 1536: 4.2 us, now 2.4).  LOADS: the batch; up to 32 partial
-// rows fit batches of four, whose sums round the same (feed-forward backward of 8 x 1024 with the batch of 32: 0.25 us more).
+// row again and drops it: a loop over the left-over rows paid one latency each (170 x 1536: 4.2 us, now 2.4).  LOADS: the batch, no larger than
+// a slice of few partial rows needs; its sums round the same (feed-forward backward of 8 x 1024 with the batch of 32 0.25 us more, LayerNorm backward
+// of 512 x 264, 64 partial rows, 0.3 us).
 template <bool WHOLE, int LOADS>
 __global__ __launch_bounds__(32 * kFinalizeSlices) void colsum_finalize_kernel(float* __restrict__ out0,
                                                                                float* __restrict__ out1,
@@ -142,6 +143,10 @@ inline void launch_colsum_finalize(float* out0, float* out1, int split, const fl
         hipLaunchKernelGGL((colsum_finalize_kernel<true, kFinalizeLoads>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
     else if (P <= kFinalizeSlices * 4)
         hipLaunchKernelGGL((colsum_finalize_kernel<false, 4>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
+    else if (P <= kFinalizeSlices * 8)
+        hipLaunchKernelGGL((colsum_finalize_kernel<false, 8>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
+    else if (P <= kFinalizeSlices * 16)
+        hipLaunchKernelGGL((colsum_finalize_kernel<false, 16>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
     else
         hipLaunchKernelGGL((colsum_finalize_kernel<false, kFinalizeLoads>), grid, block, 0, s, out0, out1, out2, split, split2, partial, P, C);
 }

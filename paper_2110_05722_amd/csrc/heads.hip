@@ -207,7 +207,7 @@ static lsq_status merge_dispatch(void* out, float* dbias, const void* i0, const 
     const T* a = static_cast<const T*>(i0); const T* b = static_cast<const T*>(i1); const T* c = static_cast<const T*>(i2);
     const int cols = g.parts * g.hidden;
     if (g.head_dim % kPack == 0) {
-        const int rb = heads_bwd_row_blocks(g.rows, cols);
+        const int rb = heads_bwd_row_blocks(g.rows, cols, sizeof(T));
         const dim3 grid(static_cast<unsigned>(ceil_div(g.ppr, 64)), static_cast<unsigned>(dbias ? rb : head_row_blocks(g.rows))), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
         hipLaunchKernelGGL((merge_heads_kernel<T>), grid, block, 0, s, o, partial, a, b, c, g);
@@ -217,7 +217,7 @@ static lsq_status merge_dispatch(void* out, float* dbias, const void* i0, const 
         hipLaunchKernelGGL((merge_heads_flat<T>), dim3(static_cast<unsigned>(ceil_div(total, 256))), dim3(256), 0, s,
                            o, a, b, c, g);
         if (dbias) {
-            const int rb = heads_bwd_row_blocks(g.rows, cols);
+            const int rb = heads_bwd_row_blocks(g.rows, cols, sizeof(T));
             float* partial = static_cast<float*>(workspace);
             hipLaunchKernelGGL((colsum_rows_flat<T>), dim3(static_cast<unsigned>(ceil_div(cols, 256)), static_cast<unsigned>(rb)), dim3(256), 0, s,
                                partial, static_cast<const T*>(o), g.rows, cols, static_cast<int>(ceil_div(g.rows, rb)));
@@ -277,7 +277,7 @@ extern "C" lsq_status lsq_split_heads_bwd(void* din, float* dbias, const void* d
     LSQ_REQUIRE(din && d0 && (parts < 2 || d1) && (parts < 3 || d2));
     LSQ_ALIGNED(din); LSQ_ALIGNED(d0); LSQ_ALIGNED(d1); LSQ_ALIGNED(d2); LSQ_ALIGNED(dbias); LSQ_ALIGNED(workspace);
     if (dbias) {
-        const size_t need = heads_bwd_bytes(g.rows, parts * g.hidden);
+        const size_t need = heads_bwd_bytes(g.rows, parts * g.hidden, dt == LSQ_F32 ? 4 : 2);
         if (need && (!workspace || workspace_bytes < need)) return LSQ_WORKSPACE_TOO_SMALL;
     }
     switch (dt) {

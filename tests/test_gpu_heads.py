@@ -67,3 +67,9 @@ def test_heads_empty():
     din, dbias = L.lsq_split_heads_bwd(outs, 0, 5, 1, 64)
     torch.cuda.synchronize()
     assert din.numel() == 0 and dbias.abs().sum().item() == 0
+
+
+# the column sums' rows per partial row in fp32 on both sides of 3.2 M elements
+@pytest.mark.parametrize("rows", [1666, 1667, 2048])
+def test_split_heads_bwd_rows_per_partial_row(rows):
+    test_split_heads_fwd_bwd(1, rows, 8, 80, 3, "f32")

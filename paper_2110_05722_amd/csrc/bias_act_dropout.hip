@@ -274,9 +274,10 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
     if (!bad_fwd_is_flat(rows, hidden, sizeof(T), d.on != 0)) {
         const int cb = bad_col_blocks(hidden);
         // two rows per wave: 28.1 / 23.1 us at 8192 x 5120 / 4096 x 4096 against 29.0 / 23.8 with four and 28.1 / 24.3 with one
-        // (one where those workgroups are few: 512 x 2048 f32 3.5 against 3.8 us, 2694 x 1392 5.4 against 5.9; 2200 x 2048 5.5 against 5.2)
+        // (one where those workgroups are few: 512 x 2048 f32 3.5 against 3.8 us, 2694 x 1392 fp16 5.4 against 5.9; up to 1024 of them in 16 bits, time of
+        // one over two 0.63-0.98 (2200 x 2048 5.5 against 5.2), in fp32 below 512: 500 0.98, 526..1024 1.0-1.13, 3000 x 520 6.7 against 5.9 us)
         int64_t rb = ceil_div(rows, 2 * kBadWaves);
-        if (rb * cb <= 1024) rb = ceil_div(rows, kBadWaves);
+        if (rb * cb <= (sizeof(T) == 2 ? 1024 : 511)) rb = ceil_div(rows, kBadWaves);
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(cb), static_cast<unsigned>(rb)), block(256);
 #define LSQ_BAD_FWD(BIAS, DROP)                                                                                                            \

@@ -136,3 +136,16 @@ def test_bias_act_long_tensors_of_odd_rows(hidden, elements, dt, p):
             assert (err[kept] <= tol[kept]).all()
             share = ((ref.abs() > 1e-2) & ~kept).double().sum() / (ref.abs() > 1e-2).double().sum()
             assert abs(share.item() - p) < 2e-3
+
+
+# rows per wave of the forward on both sides of its lines (511 workgroups of two rows in fp32, 1024 in 16 bits): a row is what a short call makes of it
+@pytest.mark.parametrize("rows,hidden,dt", [(4088, 512, "f32"), (4089, 512, "f32"), (8192, 512, "bf16"), (8193, 512, "bf16"), (2044, 1281, "f32"), (2720, 1281, "f16")])
+def test_bias_act_rows_per_wave(rows, hidden, dt):
+    say(f"[bias_act_dropout] rows per wave rows={rows} hidden={hidden} dt={dt}")
+    d = dev()
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    x, bias = torch.randn(rows, hidden, device=d).to(tdt), torch.randn(hidden, device=d).to(tdt)
+    out = L.lsq_bias_act_dropout_fwd(x, bias, "gelu", 0.0, 5, 9)
+    for at in (0, rows // 2 // 8 * 8, (rows - 8) // 8 * 8):
+        part = slice(at, min(at + 300, rows))
+        assert torch.equal(out[part], L.lsq_bias_act_dropout_fwd(x[part].clone(), bias, "gelu", 0.0, 5, 9))

@@ -64,7 +64,7 @@ typedef enum {
     LSQ_UNSUPPORTED_DTYPE = 2,
     LSQ_MISALIGNED = 3,          /* a base pointer is not 16-byte aligned */
     LSQ_WORKSPACE_TOO_SMALL = 4,
-    LSQ_LAUNCH_FAILED = 5        /* the HIP runtime rejected a launch */
+    LSQ_LAUNCH_FAILED = 5        /* the HIP runtime rejected a launch, or the library has no kernel for a shape (a defect of the build) */
 } lsq_status;
 
 typedef enum { LSQ_F16 = 0, LSQ_BF16 = 1, LSQ_F32 = 2 } lsq_dtype;
@@ -98,6 +98,8 @@ const char* lsq_status_string(lsq_status s);
  *   registers, so it cannot go negative.
  * x, y: [rows, hidden] dt;  gamma, beta: [hidden] dt;  mean, rstd: [rows] fp32
  * (saved for backward).  Errors: null pointers, rows < 0, hidden <= 0, eps < 0.
+ * A row's y, mean and rstd (and its dx in the backward) do not depend on how many rows the call has; dgamma and
+ * dbeta are added in an order that does.
  * Speed: rows of up to 16384 columns (8191 where hidden is not a multiple of 8, and from 129 there) stay
  * in registers: one pass over memory, forward and backward.  Other rows take a generic path that
  * re-reads them from cache. */
@@ -144,9 +146,9 @@ lsq_status lsq_layernorm_bwd_noalloc(void* dx, float* dgamma, float* dbeta,
  * x, residual, out: [rows, hidden] dt;  bias: nullable [hidden] dt.
  * out may alias x or residual.  p in [0,1).  Dropout contract above, flat index
  * e = r*hidden + i.
- * Speed: rows of any length run in 128-bit packs counted from the row's start, 1.3-1.5 x the time of
- * the next multiple of 8 where hidden is none; up to 256 such columns the tensor is walked as one flat
- * array instead.  The same holds for lsq_bias_act_dropout_fwd/bwd. */
+ * Speed: rows of any length run in 128-bit packs counted from the row's start, 0.7-1.5 x the time of
+ * the next multiple of 8 where hidden is none (about 1.1); up to 256 such columns, and for some long
+ * tensors, the tensor is walked as one flat array instead.  The same holds for lsq_bias_act_dropout_fwd/bwd. */
 lsq_status lsq_bias_dropout_residual_fwd(void* out, const void* x, const void* bias,
                                          const void* residual, int64_t rows, int32_t hidden,
                                          float p, uint64_t seed, uint64_t offset,

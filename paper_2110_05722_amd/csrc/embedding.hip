@@ -95,7 +95,7 @@ __device__ __forceinline__ unsigned emb_key(int w, int vocab, int pad_idx)
     return emb_is_pad(w, vocab, pad_idx) ? kPadKey : static_cast<unsigned>(w);
 }
 
-// The order of up to kEmbSortMax tokens, without a launch of its own: 64 workgroups, each for the ids of one class.
+// The order of up to kEmbSortMax tokens, without a launch of its own: 64 workgroups (128 beyond 8192 tokens), each for the ids of one class.
 // What the accumulation needs is that equal ids stand together in ascending position; which id comes before
 // which is free, so a class can be any set of ids whose share does not follow from their frequency (frequent words have
 // small ids) or their spacing: the low bits of the id with the next two groups of bits folded in (sort_mix).  A workgroup looks at every token
@@ -732,7 +732,10 @@ __device__ __forceinline__ void emb_dpos_body(float* sm, int cb, int l, T* __res
                                               const int32_t* __restrict__ tokens, int batch, int len,
                                               const RowPackIO<T, RAG>& io, int vocab, int pad_idx, const DropoutParams& d)
 {
-    constexpr int U = W == 16 && !RAG ? 8 : 4, G = 256 / W;              // (600 sentences of 17, hidden 512: 24.8 us, 26.6 with four as W = 16)
+    // sentences per lane and trip as W = 16: eight in whole packs (600 sentences of 17, hidden 512: 24.8 us, 26.6 with four), four at any
+    // alignment, where eight take 212-256 registers, for the sort too (eight / four: 40 x 200 x 777 f32 with dropout 51.6 / 37.6, bf16 38.8 /
+    // 34.3, 333 x 29 x 1961 f32 90.4 / 73.4; the longest batches lose, 1000 x 16 x 301 bf16 41.6 / 44.8, 59 before the tokens were loaded ahead)
+    constexpr int U = W == 16 && !RAG ? 8 : 4, G = 256 / W;
     const int lane = threadIdx.x % W, grp = threadIdx.x / W;
     const int cp = cb * W + lane;
     const bool active = cp < io.ppr;

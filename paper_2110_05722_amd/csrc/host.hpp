@@ -279,7 +279,7 @@ inline size_t flat_workspace_bytes_upto(int64_t rows, int32_t hidden)
     return static_cast<size_t>(chunks < kFlatMaxBlocks ? chunks : kFlatMaxBlocks) * static_cast<size_t>(hidden) * sizeof(float);
 }
 
-// LayerNorm backward, launch shape of the kernel whose rows span several waves (512..8192 columns, whole packs): lanes per
+// LayerNorm backward, launch shape of the kernel whose rows span several waves (512..8192 columns in whole packs, 129..8191 others): lanes per
 // row, rows a workgroup holds at a time, workgroups (= partial rows of the column sums).
 constexpr int kLnSpanThreads = 768;          // three waves per SIMD; wider rows take up to 1024 threads
 struct LnBwdPlan { int lanes, slots, blocks; };

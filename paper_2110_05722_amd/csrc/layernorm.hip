@@ -435,17 +435,19 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
 }
 
 // Rows of 512..8192 columns: a row spans LR lanes (a multiple of 32, several waves for all but 512 columns) and every lane
-// owns ONE pack of columns, so a lane keeps 16 or 24 column accumulators instead of 16-24 per pack held, a thread needs
-// 90-125 registers and three or four waves share a SIMD.  With a whole row per wave (up to 264 registers, one wave per
-// SIMD) nothing overlapped a row's chain of loads, two reductions, dropout draw and stores.  A workgroup holds
+// owns ONE pack of columns, so a lane keeps 16 or 24 column accumulators instead of 16-24 per pack held and a thread needs
+// 81-126 registers (RAG: 116-158).  With a whole row per wave (up to 264 registers, one wave per
+// SIMD) nothing overlapped a row's chain of loads, two reductions, dropout draw and stores.  A workgroup, one per compute unit, holds
 // `slots` rows at a time; the waves of a row meet in LDS once per row: every 32 lanes leave their two sums, a barrier, then
 // every 32 lanes read all of them (at most 32) back with one access and add them by DPP.  Two buffers make the one
 // barrier enough: a buffer is written again only behind the next row's barrier.  The next row is loaded ahead, the dropout
 // words are drawn between the reductions and the barrier, where they fill the wait for the slowest wave.  No lane shares its
 // columns with another lane of its row, so the epilogue only adds the slots (a tree over LDS, fixed order).
 // Fused with dropout and residual gradient, bf16 8192 x 1280: 27.8 -> 23.1 us, 3000 x 3072: 38 -> 21; plain 2600 x 2048: 14.0 -> 10.8;
-// f32 fused 4000 x 1280: 27.5 -> 23.9 (second stage not counted).  What is left above the copy of the bytes (17 us at 8192 x 1280)
-// is first load, epilogue and partial row.
+// f32 fused 4000 x 1280: 27.5 -> 23.9 (second stage not counted).  The copy of the bytes takes 17 us at 8192 x 1280.  Counters there / at
+// 8192 x 1024 fp16 / 2100 x 512 f32: 2.5 / 2 / 0.75 waves per SIMD, which wait for memory, LDS or the barrier in 61 / 55 / 65 % of their life
+// and for issue in 13 / 15 / 5 %; vector ALU busy 32 / 23 / 5 %, memory units stalled 0.4 / 0.2 / 0.2 %.  So it is still a row's chain, with
+// too few rows beside it, most of all in short calls.
 // LRC = 64: 512 columns, a row per wave, no exchange.  Partial rows as ln_bwd_kernel's.
 // RAG: rows that are not whole packs, in packs counted from the row's start (RowPackIO; not fused).
 template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP, bool RAG = false>

@@ -206,20 +206,33 @@ def _every_width(lo, hi, step, rows, dt):
     for H in range(lo, hi, step):
         x, dy, res, gamma, beta, bias = r(rows, H), r(rows, H), r(rows, H), r(H) * 0.1 + 1, r(H), r(H)
         outs = [torch.full((rows, H), float("nan"), device=d, dtype=dt) for _ in range(5)]
-        vecs = [torch.full((n,), float("nan"), device=d) for n in (rows, rows, H, H, H)]
+        vecs = [torch.full((n,), float("nan"), device=d) for n in (rows, rows, H, H, H, H, H)]
         L.lsq_bdr_layernorm_fwd(x, bias, res, gamma, beta, 0.0, 1, 1, h=outs[0], y=outs[1], mean=vecs[0], rstd=vecs[1])
         L.lsq_bdr_layernorm_bwd(dy, outs[0], gamma, vecs[0], vecs[1], 0.0, 1, 1, dres_in=res, dh=outs[2], dx=outs[3], dgamma=vecs[2], dbeta=vecs[3], dbias=vecs[4])
-        L.lsq_layernorm_bwd(dy, outs[0], gamma, vecs[0], vecs[1], dx=outs[4], dgamma=torch.empty_like(vecs[2]), dbeta=torch.empty_like(vecs[3]))
+        L.lsq_layernorm_bwd(dy, outs[0], gamma, vecs[0], vecs[1], dx=outs[4], dgamma=vecs[5], dbeta=vecs[6])
         h = outs[0].double()
         mu, rs = h.mean(1, keepdim=True), torch.rsqrt(h.var(1, unbiased=False, keepdim=True) + EPS)
         xh, gy = (h - mu) * rs, dy.double() * gamma.double()
         dh = rs * (gy - gy.mean(1, keepdim=True) - xh * (gy * xh).mean(1, keepdim=True))
         want = [x.double() + bias.double() + res.double(), xh * gamma.double() + beta.double(), dh + res.double(), dh + res.double(), dh,
-                mu[:, 0], rs[:, 0], (dy.double() * xh).sum(0), dy.double().sum(0), outs[2].double().sum(0)]
-        for name, a, b in zip(("h", "y", "dh", "dx", "plain dx", "mean", "rstd", "dgamma", "dbeta", "dbias"), [*outs, *vecs], want):
+                mu[:, 0], rs[:, 0], (dy.double() * xh).sum(0), dy.double().sum(0), outs[2].double().sum(0), (dy.double() * xh).sum(0), dy.double().sum(0)]
+        for name, a, b in zip(("h", "y", "dh", "dx", "plain dx", "mean", "rstd", "dgamma", "dbeta", "dbias", "plain dgamma", "plain dbeta"), [*outs, *vecs], want):
             e = (a.double() - b).norm() / (b.norm() + 1e-3 * b.numel() ** 0.5)
             if not e <= tol * (10 if H < 8 else 1):
                 bad.append((H, name, float(e)))
+        # with dropout: the boundary is the two operators
+        drop = [torch.full((rows, H), float("nan"), device=d, dtype=dt) for _ in range(4)]
+        sums = [torch.full((n,), float("nan"), device=d) for n in (rows, rows, H, H, H)]
+        L.lsq_bdr_layernorm_fwd(x, bias, res, gamma, beta, 0.25, 1, H, h=drop[0], y=drop[1], mean=sums[0], rstd=sums[1])
+        L.lsq_bdr_layernorm_bwd(dy, outs[0], gamma, vecs[0], vecs[1], 0.25, 1, H, dres_in=res, dh=drop[2], dx=drop[3], dgamma=sums[2], dbeta=sums[3], dbias=sums[4])
+        h2 = L.lsq_bias_dropout_residual_fwd(x, bias, res, 0.25, 1, H)
+        y2, mean2, rstd2 = L.lsq_layernorm_fwd(h2, gamma, beta, EPS)
+        dx2, dbias2 = L.lsq_bias_dropout_residual_bwd(outs[2], 0.25, 1, H)
+        same = dict(h=(drop[0], h2), y=(drop[1], y2), mean=(sums[0], mean2), rstd=(sums[1], rstd2), dh=(drop[2], outs[2]), dx=(drop[3], dx2),
+                    dgamma=(sums[2], vecs[2]), dbeta=(sums[3], vecs[3]))
+        bad += [(H, "dropout " + k, 0.0) for k, (a, b) in same.items() if not torch.equal(a, b)]
+        if not torch.allclose(sums[4], dbias2, rtol=1e-5, atol=1e-5):      # rows in another order: at most 9 terms of 1.3 x 4 sigma
+            bad.append((H, "dropout dbias", float((sums[4] - dbias2).abs().max())))
     assert not bad, bad[:8]
 
 

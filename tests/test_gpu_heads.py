@@ -20,6 +20,10 @@ CASES = [(8, 64, 8, 64, 3), (128, 32, 8, 64, 3), (16, 128, 16, 64, 3), (2, 512, 
 def test_split_heads_fwd_bwd(B, Ln, N, D, parts, dt):
     if dt == "f32" and B * Ln * N * D * parts > 1 << 21:
         pytest.skip("fp32 storage is exercised on the small shapes only")
+    split_heads_against_the_oracle(B, Ln, N, D, parts, dt)
+
+
+def split_heads_against_the_oracle(B, Ln, N, D, parts, dt):
     say(f"[heads] B={B} L={Ln} N={N} D={D} parts={parts} dt={dt}")
     d = dev()
     r = np.random.default_rng(B * 1000 + Ln + D)
@@ -72,4 +76,4 @@ def test_heads_empty():
 # the column sums' rows per partial row in fp32 on both sides of 3.2 M elements
 @pytest.mark.parametrize("rows", [1666, 1667, 2048])
 def test_split_heads_bwd_rows_per_partial_row(rows):
-    test_split_heads_fwd_bwd(1, rows, 8, 80, 3, "f32")
+    split_heads_against_the_oracle(1, rows, 8, 80, 3, "f32")

@@ -86,28 +86,38 @@ __device__ __forceinline__ bool pack_needed(int j0, int limit) { return j0 < lim
 
 // With query lengths the rows of padded queries, often half of the tensor, need no load at all.  Then a row's limit is waited for before anything
 // is loaded (`sm_late_*`; otherwise the first 128 bytes go out before it is known), and a wave whose rows are all empty writes its zeros and
-// leaves (`sm_leaves_*`).  Where which is faster, time of the late loads over the early ones (16 bits / fp32; lengths full, three quarters, half):
-//  - rows of up to 128 bytes are loaded whole before the limit: late 1.1-1.37 / 1.0-1.12 whatever the padding (64 x 16 x 64 x 64 fp16 with
-//    dropout, forward 6.9 -> 8.9 us), leaving gains nothing there;
+// leaves (`sm_leaves_fwd`).  Where which is faster, time of the late loads over the early ones (lengths full ... half):
+//  - rows of up to 128 bytes are loaded whole before the limit.  16 bits, whole packs: forward 1.10-1.23 (64 x 16 x 64 x 64 fp16 with dropout
+//    6.9 -> 8.9 us), backward of 4 M elements 1.05-1.22, of 16 M 1.03 ... 0.84; more queries than keys under a causal mask leave most rows
+//    empty: 1.1 ... 0.68.  Any other length and fp32: 1.0-1.06 ... 0.63-1.0, fp32 forward with dropout 0.82-0.88 ... 0.76;
 //  - forward, whole packs, below 1024 bytes 0.76-1.0; longer ones with half of their rows empty lose (1000 keys fp16 with dropout
 //    1.12, fp32 1.27, 512 keys fp32 1.18), full ones gain 1-4 %; only 16 bits without dropout keep 0.89-1.0 at any length;
 //  - forward, any other length 0.77-1.0 and with the leaving waves up to 0.10 less, but 16 bits beyond 1536 keys 1.0-1.18 (2001 keys),
 //    and with dropout beyond 640 leaving costs 0-0.13 again (1025 keys, half 0.99 -> 1.05, 2001 1.18 -> 1.23);
-//  - backward 0.72-1.0, but fp32 whole packs beyond 1024 keys 1.01-1.07 at half.
-// (empty rows above a causal mask's first key are few: they take the ordinary way.)
-template <typename T, bool DROP, bool RAG>
-__device__ __forceinline__ bool sm_late_fwd(int k_len)
+//  - backward 0.72-1.0, but fp32 whole packs beyond 1024 keys 1.01-1.07 at half;
+//  - a causal mask keeps the rows' ends apart: beyond 128 bytes 0.84-1.02 in both directions at every length, leaving included
+//    (409 x 1537 bf16 with dropout 19.0 -> 17.1 us); only 16 bits with dropout, whole packs of 1024 bytes on, lose it again on tensors beyond
+//    the Infinity Cache (1000 x 1000 keys: 15 M scores 0.93, 128 M 1.08).
+template <typename T, bool RAG>
+__device__ __forceinline__ bool sm_late_short(const SoftmaxGeom& g)       // rows of up to 128 bytes
 {
-    const int bytes = k_len * static_cast<int>(sizeof(T));
-    if (RAG) return bytes > 128 && (sizeof(T) == 4 || k_len <= 1536);
-    return bytes > 128 && (bytes < 1024 || (sizeof(T) == 2 && !DROP));
+    return sizeof(T) == 4 || RAG || (g.causal && g.shift < 0);
+}
+template <typename T, bool DROP, bool RAG>
+__device__ __forceinline__ bool sm_late_fwd(const SoftmaxGeom& g)
+{
+    const int bytes = g.k_len * static_cast<int>(sizeof(T));
+    if (bytes <= 128) return sm_late_short<T, RAG>(g);
+    if (g.causal) return RAG || sizeof(T) == 4 || !DROP || bytes < 1024 || g.nrows * g.k_len <= (int64_t{64} << 20);
+    return RAG ? sizeof(T) == 4 || g.k_len <= 1536 : bytes < 1024 || (sizeof(T) == 2 && !DROP);
 }
 template <typename T, bool DROP>
-__device__ __forceinline__ bool sm_leaves_fwd(int k_len) { return !(sizeof(T) == 2 && DROP && k_len > 640); }
+__device__ __forceinline__ bool sm_leaves_fwd(const SoftmaxGeom& g) { return g.causal || !(sizeof(T) == 2 && DROP && g.k_len > 640); }
 template <typename T, bool RAG>
-__device__ __forceinline__ bool sm_late_bwd(int k_len)
+__device__ __forceinline__ bool sm_late_bwd(const SoftmaxGeom& g)
 {
-    return k_len * static_cast<int>(sizeof(T)) > 128 && (sizeof(T) == 2 || RAG || k_len <= 1024);
+    if (g.k_len * static_cast<int>(sizeof(T)) <= 128) return sm_late_short<T, RAG>(g) || g.nrows * g.k_len >= (int64_t{8} << 20);
+    return sizeof(T) == 2 || RAG || g.causal || g.k_len <= 1024;
 }
 
 // ---- where the packs of a row lie.  RAG = false: rows are whole packs (k_len % 8 == 0), pack idx of a row starts at
@@ -351,7 +361,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
     // from memory, and waiting for it first would put two dependent round trips in front of
     // every row.  The other packs are loaded only if they reach into the allowed prefix.
     // (a limit that is computed from the row index alone, causal or none, waits for nothing).  With query lengths see sm_late_fwd.
-    const bool late = len.query && sm_late_fwd<T, DROP, RAG>(g.k_len);
+    const bool late = len.query && sm_late_fwd<T, DROP, RAG>(g);
     const int kEarly = late ? -kPack : (len.key || len.query) ? 128 / static_cast<int>(sizeof(T)) : 0;
     RawPack<T> raw[RPT][VPL];
 #pragma unroll
@@ -369,7 +379,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
     }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) limit[r] = row[r] < blk.rows ? row_limit(g, len, blk.row0 + row[r]) : 0;
-    if (late && sm_leaves_fwd<T, DROP>(g.k_len)) {                    // uniform
+    if (late && sm_leaves_fwd<T, DROP>(g)) {                    // uniform
         bool empty = true;
 #pragma unroll
         for (int r = 0; r < RPT; ++r) empty = empty && limit[r] <= 0;
@@ -488,7 +498,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
     RowPacks<RAG> rp[RPT];
     int limit[RPT];
     // as in forward: the first 128 bytes of a row are loaded before its limit is known, unless sm_late_bwd says otherwise
-    const bool late = len.query && sm_late_bwd<T, RAG>(g.k_len);
+    const bool late = len.query && sm_late_bwd<T, RAG>(g);
     const int kEarly = late ? -kPack : (len.key || len.query) ? 128 / static_cast<int>(sizeof(T)) : 0;
     RawPack<T> ry[RPT][VPL], rg[RPT][VPL];
 #pragma unroll

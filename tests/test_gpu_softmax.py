@@ -304,9 +304,10 @@ def test_softmax_rows_of_padded_queries(Lq, Lk, causal, dt):
     assert torch.equal(L.lsq_softmax_varlen_fwd(spoilt, kl, ql, causal, 0.4, 0.0)[0], L.lsq_softmax_varlen_fwd(to_torch(xs, dt, d).view(B, N, Lq, Lk), kl, ql, causal, 0.4, 0.0)[0])
 
 
-# the lines of the loads behind the limit and of the waves that leave (128 and 1024 bytes, 640, 1024 and 1536 keys), both sides
+# the lines of the loads behind the limit and of the waves that leave (128 and 1024 bytes, 640, 1024 and 1536 keys, more queries than keys), both sides
 @pytest.mark.parametrize("dt", ["f16", "f32"])
-@pytest.mark.parametrize("Lq,Lk", [(66, 16), (66, 32), (66, 40), (66, 65), (35, 248), (35, 255), (35, 257), (21, 504), (21, 520), (21, 639), (21, 641), (19, 1023),
-                                   (19, 1024), (19, 1032), (19, 1536), (19, 1537)])
-def test_softmax_padded_queries_at_the_lines(Lq, Lk, dt):
-    test_softmax_rows_of_padded_queries(Lq, Lk, Lk % 2 == 0, dt)
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Lq,Lk", [(66, 16), (66, 32), (32, 32), (40, 40), (66, 40), (30, 40), (66, 65), (35, 248), (35, 255), (35, 257), (21, 504), (21, 520), (21, 639),
+                                   (21, 641), (19, 1023), (19, 1024), (19, 1032), (19, 1536), (19, 1537)])
+def test_softmax_padded_queries_at_the_lines(Lq, Lk, causal, dt):
+    test_softmax_rows_of_padded_queries(Lq, Lk, causal, dt)

@@ -276,7 +276,7 @@ def test_softmax_rows_through_lds(dt, B, N, Lq, Lk, mask, p):
 
 
 # waves whose rows are all empty leave early and write their rows as one range of zeros: rows of every lane count, whole packs and not,
-# ranges that begin and end anywhere in a pack, an empty sentence beside a full one (rows above a causal mask's first key stay in the ordinary way)
+# ranges that begin and end anywhere in a pack, an empty sentence beside a full one, rows above a causal mask's first key
 @pytest.mark.parametrize("dt", ["f16", "f32"])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("Lq,Lk", [(70, 3), (70, 8), (66, 13), (70, 24), (131, 31), (70, 64), (67, 113), (70, 128), (41, 130), (37, 256), (33, 301), (19, 512), (19, 701),

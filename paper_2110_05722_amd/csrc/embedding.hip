@@ -8,11 +8,9 @@
 //   1. order: the tokens of a call, equal ids together in ascending position.  Up to 16384 tokens a few
 //      workgroups sort them, each the ids of one residue class, in LDS (stable radix sort), while the other workgroups
 //      of the launch stream dy for dP; beyond that the sort runs over many workgroups, two launches per digit;
-//   2. accumulate: the sorted order is cut into windows of 8 entries; one wave per (window,
-//      64-pack column block) sums m (.) dy in ascending position in fp32, the eight rows and
-//      the destination rows in flight together.  An id whose rows lie inside one window is
-//      added to dE[w,:] at once; a more frequent one leaves one fp32 row per window that a
-//      last kernel adds in window order: one rounding of dE per call either way.
+//   2. accumulate: workgroups take 64 entries of the sorted order and 16 packs of the columns and sum m (.) dy of equal
+//      neighbours in ascending position in fp32; an id that goes on beyond its 64 entries has workgroups of its own
+//      that share its columns.  One rounding of dE per call either way.
 // Tokens equal to pad_idx (or outside the vocabulary) produce zero rows and no gradient.
 #include <limits.h>
 
@@ -22,11 +20,6 @@ namespace lsq {
 
 constexpr bool kNT = true;
 constexpr int kEmbWaves = 4;
-
-// Lanes of the accumulation that stay at work in a wave whatever its row has for them (beyond the row they repeat its last pack and store nothing).  Dependent
-// vector instructions run 2.3-3 times slower with up to 16 lanes active (quarter-rate ones, Philox's 64-bit products, with up
-// to 8): 2048 tokens, fp16, dropout, backward in us at 64 columns (8 lanes) 18.9 -> 15.6, 63 26.3 -> 19.0; and likewise a row's last block of 64 packs.
-constexpr int kBusyLanes = 32;
 
 __device__ __forceinline__ bool emb_is_pad(int w, int vocab, int pad_idx) { return w == pad_idx || w < 0 || w >= vocab; }
 
@@ -537,75 +530,78 @@ __global__ __launch_bounds__(256) void emb_radix_scatter(int2* __restrict__ dst,
     }
 }
 
-// The sorted order is cut into windows of kEmbWin entries and 64-pack column blocks; one wave
-// takes one (window, column block).  Lane 0 gets the entry before the window, lanes
-// 1..kEmbWin the window, lane kEmbWin+1 the entry after it; beyond the data the key is kNoKey
-// (-1 as int), which equals no token's key.
-__device__ __forceinline__ int2 emb_window(const int2* __restrict__ order, int64_t win, int64_t rows, int lane)
-{
-    const int64_t idx = win * kEmbWin - 1 + lane;
-    int2 e = make_int2(0, static_cast<int>(kNoKey));
-    if (lane <= kEmbWin + 1 && idx >= 0 && idx < rows) e = order[idx];
-    return e;
-}
+// The sorted order is cut into units of kEmbUnit entries, ranges of kEmbRange entries and column blocks of 16 packs.  A workgroup takes a
+// (range, column block): 16 lanes own a unit's entries, a wave has four units, so no lane idles on a row's last packs, and what a unit's first or last
+// run shares with the unit beside it goes over by lane shuffles in a wave and LDS between the four.  A run that crosses the border of a range has
+// workgroups of its own (emb_border_run) and is left out here.  The destination rows are fetched together with the dy rows.
+// What bounds it is the chain order -> rows -> rows of dE; 4 waves per SIMD at 8192 x 1280.  One wave per (8 entries, 64 packs), which left an fp32 row
+// for every run that crossed its entries, and a last launch that added these took 13.1 + 6.0 us there; whole backward, bf16 with dropout, in us before and now:
+// 8192 x 1280 words 28.6 / 23.4, distinct 29.0 / 23.7, half of one id 40.5 / 31.8, 16384 x 1024 40.9 / 36.4, 2048 x 768 f16 15.3 / 12.6, 1106 calls of 512 to
+// 128000 tokens and 8 to 2048 columns geometric mean 0.795, none above 1.01.  Units of 8 entries 0.84, ranges before borders 0.81, 128 registers forced 0.80.
+constexpr int kEmbUnit = 4;
+static_assert(kEmbRange == 16 * kEmbUnit, "four waves of four units");
 
 __device__ __forceinline__ bool emb_live_key(int key) { return key >= 0 && key != static_cast<int>(kPadKey); }
-
-// Sums m (.) dy over each run of equal ids inside the window, in ascending position.  A run
-// that starts and ends inside the window is added to dE[w,:] at once (the destination row is
-// fetched together with the dy rows).  A run that comes from the previous window or goes on
-// into the next leaves an fp32 row for emb_combine: slot 0 of the window if it is the window's
-// first run, slot 1 otherwise (only the last run can be the other one).
-template <typename T, bool DROP, bool RAG>
-__global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, float* __restrict__ win_rows,
-                                                      const T* __restrict__ dy, const int2* __restrict__ order,
-                                                      int64_t rows, int64_t nwin, int ncb, RowPackIO<T, RAG> io, float scale,
-                                                      DropoutParams d)
+// key of an entry; beyond the data kNoKey (-1 as int), which equals no token's key
+__device__ __forceinline__ int emb_key_at(const int2* __restrict__ order, int64_t i, int64_t rows)
 {
-    const int ppr = io.ppr;
-    const int lane = threadIdx.x & 63;
-    const int64_t gw = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (gw >= nwin * ncb) return;                                   // wave-uniform
-    const int64_t win = gw / ncb;
-    const int col = static_cast<int>(gw % ncb) * 64 + lane, cp = min(col, ppr - 1);
-    const bool mine = col < ppr;
-    const int2 e = emb_window(order, win, rows, lane);
-    int key[kEmbWin + 2], tok[kEmbWin];
-#pragma unroll
-    for (int k = 0; k < kEmbWin + 2; ++k) key[k] = __builtin_amdgcn_readlane(e.y, k);
-#pragma unroll
-    for (int k = 0; k < kEmbWin; ++k) tok[k] = __builtin_amdgcn_readlane(e.x, k + 1);
-    if (!mine && lane >= kBusyLanes) return;
+    return i >= 0 && i < rows ? order[i].y : static_cast<int>(kNoKey);
+}
 
-    // what happens after entry k (all wave-uniform): 0 nothing, 1 add to dE, 2 / 3 leave slot 0 / 1
-    int action[kEmbWin];
-    {
-        bool open_partial = key[1] == key[0], first_run = true;
+template <typename T, bool DROP, bool RAG>
+__device__ __forceinline__ void emb_range_runs(float* lds, T* __restrict__ demb, const T* __restrict__ dy, const int2* __restrict__ order,
+                                               int64_t range, int64_t rows, int cb, const RowPackIO<T, RAG>& io, float scale,
+                                               const DropoutParams& d)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, c = cb * 16 + (lane & 15);
+    const bool mine = c < io.ppr;
+    const int cp = min(c, io.ppr - 1);
+    const int64_t base = range * kEmbRange + (wave * 4 + grp) * kEmbUnit;
+    // `order` has room for whole ranges: what lies beyond the data is read and not used
+    int key[kEmbUnit + 1], tok[kEmbUnit];
 #pragma unroll
-        for (int k = 0; k < kEmbWin; ++k) {
-            const bool live = emb_live_key(key[k + 1]);
-            const bool tail = key[k + 1] != key[k + 2];
-            action[k] = 0;
-            if (live && tail) action[k] = open_partial ? 2 : 1;            // a run from the previous window is the first run
-            else if (live && k == kEmbWin - 1) action[k] = first_run ? 2 : 3;
-            if (tail) { open_partial = false; first_run = false; }
-        }
+    for (int k = 0; k < kEmbUnit; k += 2) {
+        const uvec4 v = *reinterpret_cast<const uvec4*>(order + base + k);
+        tok[k] = static_cast<int>(v.x); key[k] = static_cast<int>(v.y);
+        tok[k + 1] = static_cast<int>(v.z); key[k + 1] = static_cast<int>(v.w);
     }
-    RawPack<T> raw[kEmbWin], dst_raw[kEmbWin];
+    key[kEmbUnit] = emb_key_at(order, base + kEmbUnit, rows);
+    const int prev = emb_key_at(order, base - 1, rows);
+    const int before = emb_key_at(order, range * kEmbRange - 1, rows), after = emb_key_at(order, (range + 1) * kEmbRange, rows);
 #pragma unroll
-    for (int k = 0; k < kEmbWin; ++k) {
-        if (emb_live_key(key[k + 1])) raw[k] = io.template ahead<kNT>(dy, tok[k], cp);
+    for (int k = 0; k < kEmbUnit; ++k)
+        if (base + k >= rows) key[k] = static_cast<int>(kNoKey);
+    bool live[kEmbUnit], ends[kEmbUnit];
+#pragma unroll
+    for (int k = 0; k < kEmbUnit; ++k) live[k] = emb_live_key(key[k]) && key[k] != before && key[k] != after;
+#pragma unroll
+    for (int k = 0; k < kEmbUnit; ++k) ends[k] = live[k] && key[k] != key[k + 1];
+    RawPack<T> raw[kEmbUnit], dst[kEmbUnit];
+#pragma unroll
+    for (int k = 0; k < kEmbUnit; ++k) {
+        if (live[k]) raw[k] = io.template ahead<kNT>(dy, tok[k], cp);
         else raw[k] = zero_raw<T>();
     }
 #pragma unroll
-    for (int k = 0; k < kEmbWin; ++k) {
-        if (action[k] == 1) dst_raw[k] = io.template ahead<false>(demb, key[k + 1], cp);
-        else dst_raw[k] = zero_raw<T>();
+    for (int k = 0; k < kEmbUnit; ++k) {
+        if (ends[k]) dst[k] = io.template ahead<false>(demb, key[k], cp);
+        else dst[k] = zero_raw<T>();
     }
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    auto add_to = [&](int row, const RawPack<T>& to, const float (&a)[8]) {
+        float o[8];
+        unpack<T>(io.settle(to, cp), o);
 #pragma unroll
-    for (int k = 0; k < kEmbWin; ++k) {
-        if (emb_live_key(key[k + 1])) {
+        for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, a[j], o[j]);
+        if (mine) io.template store<false>(demb, row, cp, o);
+    };
+    bool open = live[0] && key[0] == prev;                         // the run at hand came from the unit before
+    const bool came = open;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, head[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    RawPack<T> head_dst = zero_raw<T>();
+    bool head_ends = false;
+#pragma unroll
+    for (int k = 0; k < kEmbUnit; ++k) {
+        if (live[k]) {
             float g[8];
             unpack<T>(io.settle(raw[k], cp), g);
             if constexpr (DROP) {
@@ -618,102 +614,191 @@ __global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, floa
                 for (int j = 0; j < 8; ++j) acc[j] += g[j];
             }
         }
-        if (action[k] == 1) {
-            float o[8];
-            unpack<T>(io.settle(dst_raw[k], cp), o);
+        if (ends[k]) {
+            if (open) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, acc[j], o[j]);
-            if (mine) io.template store<false>(demb, key[k + 1], cp, o);
-        } else if (action[k] >= 2 && mine) {
-            store8<float>(win_rows + ((2 * win + (action[k] - 2)) * ppr + cp) * kPack, acc);
-        }
-        if (action[k] != 0) {
+                for (int j = 0; j < 8; ++j) head[j] = acc[j];
+                head_dst = dst[k];
+                head_ends = true;
+            } else {
+                add_to(key[k], dst[k], acc);
+            }
+            open = false;
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
         }
     }
-}
-
-// The workgroup of the (window, column block) in which a window-crossing id segment ENDS adds
-// the segment's fp32 rows and rounds dE[w,:] once.  The segment's first window is found by looking
-// back, 64 windows per trip: window v is the first one if the entry before it has another key
-// (or v = 0).  The four waves take every fourth row each, eight in flight, and their sums are
-// added in wave order: a fixed association, so the result does not depend on timing.
-template <typename T, bool RAG>
-__global__ __launch_bounds__(256) void emb_combine(T* __restrict__ demb, const float* __restrict__ win_rows,
-                                                   const int2* __restrict__ order, int64_t rows, int ncb, RowPackIO<T, RAG> io,
-                                                   float scale)
-{
-    const int ppr = io.ppr;
-    __shared__ float sm[kEmbWaves - 1][8][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t win = blockIdx.x / ncb;
-    const int cp = static_cast<int>(blockIdx.x % ncb) * 64 + lane;
-    // every wave reads the same entries and takes the same decisions: the exits are workgroup-uniform
-    const int2 e = emb_window(order, win, rows, lane);
-    const int key = __builtin_amdgcn_readlane(e.y, 1);
-    if (!emb_live_key(key) || __builtin_amdgcn_readlane(e.y, 0) != key) return;   // first run starts here: nothing to combine
-    constexpr uint64_t kAll = ((1ull << (kEmbWin + 1)) - 1) << 1;  // lanes 1..kEmbWin+1
-    if ((__ballot(e.y == key) & kAll) == kAll) return;              // the run goes on into the next window
-    // here win >= 1 (the entry before the window exists), so the search starts at a valid window
-    int64_t head = 0;
-    int head_first_key = 0;
-    for (int64_t base = win - 1;; base -= 64) {
-        const int64_t v = base - lane;
-        bool stop = false;
-        int first_key = 0;
-        if (v >= 0) {
-            first_key = order[v * kEmbWin].y;
-            stop = v == 0 || order[v * kEmbWin - 1].y != key;
-        }
-        const uint64_t m = __ballot(stop);
-        if (m != 0) {                                               // v = 0 stops: every wave leaves the loop
-            const int l = __builtin_ctzll(m);
-            head = base - l;
-            head_first_key = __builtin_amdgcn_readlane(first_key, l);
-            break;
-        }
-    }
-    const bool active = cp < ppr;
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (active) {
-        // the segment is the first run of its first window exactly if it starts at that window's first entry
-        if (wave == 0) load8<float>(win_rows + ((2 * head + (head_first_key == key ? 0 : 1)) * ppr + cp) * kPack, acc);
-        constexpr int U = 8;
-        for (int64_t v0 = head + 1 + wave; v0 <= win; v0 += U * kEmbWaves) {
-            float r[U][8];
+    // acc: what goes on into the next unit (0 if nothing does); `open` still: the whole unit is the middle of one run
+    const bool middle = open;
+    const uint64_t middles = __ballot(middle);
+    if (middles != 0) {                                            // uniform; group after group
 #pragma unroll
-            for (int k = 0; k < U; ++k) {
-                const int64_t v = v0 + k * kEmbWaves;
-                if (v <= win) {
-                    load8<float>(win_rows + (2 * v * ppr + cp) * kPack, r[k]);
-                } else {
+        for (int s = 1; s < 4; ++s)
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) r[k][j] = 0.0f;
-                }
+            for (int j = 0; j < 8; ++j) {
+                const float t = __shfl_up(acc[j], 16);
+                if (middle && grp == s) acc[j] += t;
             }
-#pragma unroll
-            for (int k = 0; k < U; ++k)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[j] += r[k][j];
-        }
     }
-    if (wave > 0) {
+    float* vals = lds;                                             // [4][8][16]
+    int* through = reinterpret_cast<int*>(lds + 4 * 128);          // [4]: the whole wave is the middle of one run
+    if (grp == 3) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sm[wave - 1][j][lane] = acc[j];
+        for (int j = 0; j < 8; ++j) vals[wave * 128 + j * 16 + (lane & 15)] = acc[j];
+        if (lane == 63) through[wave] = middles == ~0ull;
     }
     __syncthreads();
-    if (wave == 0 && active) {
+    if (__ballot(came && head_ends) == 0) return;
+    float in[8];
 #pragma unroll
-        for (int w = 0; w < kEmbWaves - 1; ++w)
+    for (int j = 0; j < 8; ++j) in[j] = __shfl_up(acc[j], 16);
+    // the units before this one in the wave are all middles: the sum of the waves before comes on top
+    const bool reach = (middles & ((1ull << (16 * grp)) - 1ull)) == (1ull << (16 * grp)) - 1ull;
+    if (grp == 0)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += sm[w][j][lane];
+        for (int j = 0; j < 8; ++j) in[j] = 0.0f;
+    if (reach) {
+        float sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int v = 0; v < wave; ++v) {
+            const bool t = through[v] != 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sum[j] = vals[v * 128 + j * 16 + (lane & 15)] + (t ? sum[j] : 0.0f);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) in[j] += sum[j];
+    }
+    if (came && head_ends) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) in[j] += head[j];
+        add_to(key[0], head_dst, in);
+    }
+}
+
+// A run that crosses borders of ranges.  Every border that it crosses has a workgroup per column block for it, and these share its
+// COLUMNS: each takes a slice of the 16 packs, a power of two, and holds 256 / slice rows of the run at once, so it has as many loads as a range's
+// workgroup, whatever the run's length (down to slices of one pack), and no sum has to meet another workgroup's.  The lane groups add their rows in
+// ascending position and meet in a butterfly, the waves in LDS: a fixed order.
+// (8 in flight: two waves per SIMD fewer, 16384 x 2048 f32 with dropout 87 us, 80 with 4)
+constexpr int kEmbBorderRows = 4;                                  // loads in flight per lane
+template <typename T, bool DROP, bool RAG>
+__device__ __forceinline__ void emb_border_run(float* lds, T* __restrict__ demb, const T* __restrict__ dy, const int2* __restrict__ order,
+                                               int64_t border, int64_t rows, int cb, const RowPackIO<T, RAG>& io, float scale,
+                                               const DropoutParams& d)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t base = border * kEmbRange - 32;                  // a view of 64 entries about the border: most runs begin and end in it
+    int2 e = make_int2(0, static_cast<int>(kNoKey));
+    if (base + lane < rows) e = order[base + lane];
+    // every wave reads the same entries and takes the same decisions: the exits are workgroup-uniform
+    const int key = __builtin_amdgcn_readlane(e.y, 32);
+    if (!emb_live_key(key) || __builtin_amdgcn_readlane(e.y, 31) != key) return;
+    const uint64_t run = __ballot(e.y == key);                     // entries of one id stand together
+    const int lo = __builtin_ctzll(run), hi = 63 - __builtin_clzll(run);
+    // [from, to): the run, or where it leaves the view the ranges that it touches (entries of others are told by their key)
+    int64_t from = base + lo, to = base + hi + 1;
+    bool seen = true;
+    if (lo == 0) {                                                 // 64 ranges per trip: v is the first one if the entry before it has another key
+        seen = false;
+        for (int64_t b = border - 1;; b -= 64) {
+            const int64_t v = b - lane;
+            const bool stop = v == 0 || (v > 0 && order[v * kEmbRange - 1].y != key);
+            const uint64_t m = __ballot(stop);
+            if (m != 0) { from = (b - __builtin_ctzll(m)) * kEmbRange; break; }       // v = 0 stops
+        }
+    }
+    if (hi == 63) {
+        seen = false;
+        const int64_t end = (rows + kEmbRange - 1) / kEmbRange - 1;     // the last range
+        for (int64_t b = border;; b += 64) {
+            const int64_t v = b + lane;
+            const bool stop = v == end || (v < end && order[(v + 1) * kEmbRange].y != key);
+            const uint64_t m = __ballot(stop);
+            if (m != 0) { to = min(rows, (b + __builtin_ctzll(m) + 1) * kEmbRange); break; }
+        }
+    }
+    const int64_t first = from / kEmbRange + 1, crossed = (to - 1) / kEmbRange + 1 - first;      // borders
+    const int here = min(16, io.ppr - cb * 16);                    // packs of the column block
+    int width = 16;                                                // of a slice
+    while (width >= 2 * here) width >>= 1;
+    for (int64_t n = crossed; n >= 2 && width > 1; n >>= 1) width >>= 1;
+    if ((border - first) * width >= here) return;                  // fewer slices than borders
+    const int groups = 64 / width, grp = lane / width, c = static_cast<int>(border - first) * width + lane % width;
+    const bool mine = c < here;
+    const int cp = cb * 16 + min(c, here - 1);
+    RawPack<T> dst = zero_raw<T>();
+    const bool writes = wave == 0 && grp == 0 && mine;
+    if (writes) dst = io.template ahead<false>(demb, key, cp);
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    constexpr int U = kEmbBorderRows;
+    const int step = 4 * groups, at = wave * groups + grp;
+    for (int64_t r0 = from; r0 < to; r0 += U * step) {
+        int tok[U];
+        bool ok[U];
+        RawPack<T> raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = r0 + u * step + at;
+            ok[u] = r < to;
+            if (seen) {
+                tok[u] = __shfl(e.x, static_cast<int>(r - base) & 63);
+            } else {
+                const int2 x = order[min(r, to - 1)];
+                ok[u] = ok[u] && x.y == key;
+                tok[u] = x.x;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (ok[u]) raw[u] = io.template ahead<false>(dy, tok[u], cp);
+            else raw[u] = zero_raw<T>();
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u * step >= to) break;                        // uniform
+            float g[8];
+            unpack<T>(io.settle(raw[u], cp), g);
+            if constexpr (DROP) {
+                float kf[8];
+                io.factors(d, tok[u], cp, kf);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] = fmaf(g[j], kf[j], acc[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] += g[j];
+            }
+        }
+    }
+    for (int w = width; w < 64; w <<= 1) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], w);
+    }
+    if (wave > 0 && grp == 0) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) lds[((wave - 1) * 8 + j) * 16 + lane] = acc[j];
+    }
+    __syncthreads();
+    if (writes) {
+#pragma unroll
+        for (int w = 0; w < 3; ++w)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += lds[(w * 8 + j) * 16 + lane];
         float o[8];
-        unpack<T>(io.template load<false>(demb, key, cp), o);
+        unpack<T>(io.settle(dst, cp), o);
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, acc[j], o[j]);
         io.template store<false>(demb, key, cp, o);
     }
+}
+
+template <typename T, bool DROP, bool RAG>
+__global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, const T* __restrict__ dy, const int2* __restrict__ order,
+                                                      int64_t rows, int borders, int ncb, RowPackIO<T, RAG> io, float scale,
+                                                      DropoutParams d)
+{
+    __shared__ float lds[4 * 128 + 4];
+    const int unit = static_cast<int>(blockIdx.x) / ncb, cb = static_cast<int>(blockIdx.x) % ncb;
+    if (unit < borders) emb_border_run<T, DROP, RAG>(lds, demb, dy, order, unit + 1, rows, cb, io, scale, d);
+    else emb_range_runs<T, DROP, RAG>(lds, demb, dy, order, unit - borders, rows, cb, io, scale, d);
 }
 
 // dP[l,:] += sum over the batch.  256 threads own W packs of one position; 256 / W groups of W lanes take every
@@ -860,26 +945,22 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
                                    const DropoutParams& d, hipStream_t s)
 {
     const int64_t rows = static_cast<int64_t>(batch) * len;
-    const EmbBwdPlan plan = emb_bwd_plan(rows, hidden);
+    const EmbBwdPlan plan = emb_bwd_plan(rows);
     int2* order = reinterpret_cast<int2*>(ws);
-    float* win_rows = reinterpret_cast<float*>(static_cast<char*>(ws) + plan.order_bytes);
     T* de = static_cast<T*>(demb);
     T* dp = static_cast<T*>(dpos);
     const T* g = static_cast<const T*>(dy);
     // the dropout scale 1/(1-p) is carried by the per-element factors; `scale` is the embedding scale
     const RowPackIO<T, RAG> io(hidden);
-    const int ncb = static_cast<int>(ceil_div(io.ppr, 64));
     int bits = 1;
     while ((static_cast<int64_t>(1) << bits) <= vocab) ++bits;                 // 2^bits > vocab: padding (all ones) comes last
     const int passes = (bits + 7) / 8;
     const EmbSortPlan pl = emb_sort_plan(rows, bits);
     const bool few = pl.fits;
-    char* scratch = static_cast<char*>(ws) + plan.order_bytes + plan.win_bytes;
-    uint32_t* spill = reinterpret_cast<uint32_t*>(scratch);                     // two entries per token, used beyond kSortLds tokens only
-    int32_t* hist = reinterpret_cast<int32_t*>(scratch);                        // [256][radix blocks]
-    // beyond kEmbSortMax the second buffer has its own place; a small call with ids too long for the in-LDS sort takes the window
-    // rows for it (at least 8 bytes per token, written only after the sort)
-    int2* tmp = reinterpret_cast<int2*>(rows > kEmbSortMax ? scratch + plan.radix_hist_bytes : reinterpret_cast<char*>(win_rows));
+    // the radix sort's second buffer; the in-LDS sort's two words per token for parts that LDS does not hold
+    int2* tmp = reinterpret_cast<int2*>(static_cast<char*>(ws) + plan.pair_bytes);
+    uint32_t* spill = reinterpret_cast<uint32_t*>(tmp);
+    int32_t* hist = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + 2 * plan.pair_bytes);    // [256][radix blocks]
     // the position gradient rides along with the in-LDS sort
     launch_sort_dpos<T, RAG>(order, spill, tokens, rows, few, pl, dp, g, batch, len, io, vocab, pad_idx, d, s);
     if (!few) {
@@ -897,11 +978,10 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
             src = dst;
         }
     }
-    const unsigned pairs = static_cast<unsigned>(plan.nwin * ncb);      // (window, column block) pairs
-    const dim3 grid(static_cast<unsigned>(ceil_div(pairs, 4))), block(256);   // one wave per pair
-    if (d.on) hipLaunchKernelGGL((emb_accumulate<T, true, RAG>), grid, block, 0, s, de, win_rows, g, order, rows, plan.nwin, ncb, io, scale, d);
-    else hipLaunchKernelGGL((emb_accumulate<T, false, RAG>), grid, block, 0, s, de, win_rows, g, order, rows, plan.nwin, ncb, io, scale, d);
-    hipLaunchKernelGGL((emb_combine<T, RAG>), dim3(pairs), block, 0, s, de, win_rows, order, rows, ncb, io, scale);   // one workgroup per pair
+    const int ranges = static_cast<int>(ceil_div(rows, kEmbRange)), ncb = static_cast<int>(ceil_div(io.ppr, 16));
+    const dim3 grid(static_cast<unsigned>(2 * ranges - 1) * static_cast<unsigned>(ncb)), block(256);
+    if (d.on) hipLaunchKernelGGL((emb_accumulate<T, true, RAG>), grid, block, 0, s, de, g, order, rows, ranges - 1, ncb, io, scale, d);
+    else hipLaunchKernelGGL((emb_accumulate<T, false, RAG>), grid, block, 0, s, de, g, order, rows, ranges - 1, ncb, io, scale, d);
     return launch_status();
 }
 
@@ -944,11 +1024,11 @@ extern "C" lsq_status lsq_embedding_bwd(void* demb, void* dpos, const void* dy, 
     const int64_t rows = static_cast<int64_t>(batch) * len;
     if (rows == 0) return LSQ_OK;
     LSQ_REQUIRE(rows <= 0x7FFFFFFF / 2);
-    LSQ_REQUIRE(ceil_div(rows, kEmbWin) * ceil_div(hidden, 8 * 64) < 0x7FFFFFFF);   // one workgroup per (window, column block)
+    LSQ_REQUIRE(ceil_div(rows, 8) * ceil_div(hidden, 8 * 64) < 0x7FFFFFFF);         // the accumulation's workgroups are not more than these and a few
     LSQ_REQUIRE(ceil_div(rows, 256) * 64 + ceil_div(hidden, 8 * 64) * static_cast<int64_t>(len) < 0x7FFFFFFF);   // (position, column block) pairs
     LSQ_REQUIRE(demb && dy && tokens);
     LSQ_ALIGNED(demb); LSQ_ALIGNED(dpos); LSQ_ALIGNED(dy); LSQ_ALIGNED(workspace);
-    const size_t need = emb_bwd_plan(rows, hidden).total();
+    const size_t need = emb_bwd_plan(rows).total();
     if (!workspace || workspace_bytes < need) return LSQ_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     void* ws = workspace;

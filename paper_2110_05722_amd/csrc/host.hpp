@@ -489,39 +489,22 @@ inline size_t ln_bwd_bytes(int64_t rows, int32_t hidden, int sums) { return part
 
 // Workspace of the embedding backward:
 //   order  [rows] (token position, sort key), 8 bytes each
-//   window rows [2 * windows][hidden rounded up to 8] fp32: the partial sums of id segments
-//          that cross a window of kEmbWin sorted entries (at most two per window)
-//   sort scratch: beyond kEmbSortMax tokens the radix sort's [256][workgroups] digit counts and its second
-//          (token, key) buffer; up to there rows * 4 bytes per 256 tokens, which hold the parts of the in-LDS sort that
-//          are too large for it (beyond 2048 tokens), or the digit counts where ids are too long for it (the second
-//          buffer then lies in the window rows, which are written later)
+//   second buffer of the radix sort, as many; the parts of the in-LDS sort that are too large for it (beyond 2048 tokens) lie there too
+//   digit counts of the radix sort [256][workgroups]
 constexpr int64_t kEmbSortMax = 16384;
-constexpr int kEmbWin = 8;
+constexpr int kEmbRange = 64;        // entries of the sorted order that a workgroup of the accumulation owns
 struct EmbBwdPlan {
     int radix_blocks;
-    size_t radix_hist_bytes;
-    int64_t nwin;
-    size_t order_bytes, win_bytes, sort_bytes;
-    size_t total() const { return order_bytes + win_bytes + sort_bytes; }
+    size_t pair_bytes, hist_bytes;
+    size_t total() const { return 2u * pair_bytes + hist_bytes; }        // never falls as the rows grow
 };
-inline EmbBwdPlan emb_bwd_plan(int64_t rows, int32_t hidden)
+inline EmbBwdPlan emb_bwd_plan(int64_t rows)
 {
     EmbBwdPlan p;
-    p.nwin = ceil_div(rows, kEmbWin);
-    const size_t colsp = (static_cast<size_t>(hidden) + 7u) / 8u * 8u;
-    p.order_bytes = (static_cast<size_t>(rows) * 8u + 15u) / 16u * 16u;
-    p.win_bytes = 2u * static_cast<size_t>(p.nwin) * colsp * sizeof(float);
+    p.pair_bytes = static_cast<size_t>(ceil_div(rows, kEmbRange)) * kEmbRange * 8u;        // whole ranges
     p.radix_blocks = static_cast<int>(ceil_div(rows, 2048));
-    p.radix_hist_bytes = (static_cast<size_t>(256) * static_cast<size_t>(p.radix_blocks) * sizeof(int32_t) + 15u) / 16u * 16u;
-    p.sort_bytes = rows > kEmbSortMax ? p.radix_hist_bytes + static_cast<size_t>(rows) * 8u
-                                      : static_cast<size_t>(ceil_div(rows, 256)) * static_cast<size_t>(rows) * sizeof(int32_t);
+    p.hist_bytes = static_cast<size_t>(256) * static_cast<size_t>(p.radix_blocks) * sizeof(int32_t);
     return p;
-}
-// of the largest call of up to `rows` rows (the sort scratch of kEmbSortMax tokens is larger than that of the next few)
-inline size_t emb_bwd_bytes_upto(int64_t rows, int32_t hidden)
-{
-    const size_t here = emb_bwd_plan(rows, hidden).total(), at = rows > kEmbSortMax ? emb_bwd_plan(kEmbSortMax, hidden).total() : 0;
-    return here > at ? here : at;
 }
 
 }  // namespace lsq

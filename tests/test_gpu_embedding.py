@@ -247,3 +247,31 @@ def test_embedding_bwd_class_sorted_by_counting(n, frequent, tokens, parts):
     again = torch.zeros_like(demb)
     L.lsq_embedding_bwd(again, None, to_torch(dy, "f32", d), torch.from_numpy(tok).to(d), V, 1.0, 0.0, 1, 0)
     assert torch.equal(again, demb)
+
+
+# runs of one id at the edges of the accumulation: a unit of 4 entries, a wave of 16, a range of 64 and a view of 32 about its border, slices of 8, 4, 2 packs
+# and one (2, 4, 8 and 16 borders crossed), fewer slices than borders, more ranges than one look back (64); below and beyond 16384 tokens (the two sorts);
+# rows of part of a column block, of one and a bit, cut packs.  Whole numbers, p = 0.5 (factors 0 and 2): every sum is exact in fp32.
+@pytest.mark.parametrize("H", [8, 40, 136, 203])
+@pytest.mark.parametrize("lengths,tokens", [((1, 3, 4, 5), 1500), ((15, 16, 17, 2), 1500), ((31, 33, 63, 64, 65, 1), 2000), ((127, 129, 200, 256, 6), 2500),
+                                            ((500, 560, 1100, 1200, 2), 8000), ((5000, 7, 3), 6000), ((9000, 64, 1), 17000), ((66,), 66), ((65,), 65), ((64,), 64)])
+def test_embedding_bwd_runs(lengths, tokens, H):
+    say(f"[embedding] runs of {lengths} in {tokens} tokens, H={H}")
+    d, V = dev(), 3000
+    rng = np.random.default_rng(tokens + H)
+    ids = rng.permutation(np.arange(2, V))
+    tok, i = np.zeros(0, np.int32), 0
+    while len(tok) < tokens:
+        tok = np.concatenate([tok, np.full(lengths[i % len(lengths)], ids[i], np.int32)])
+        i += 1
+    tok = rng.permutation(tok[:tokens]).reshape(1, tokens)
+    dys = rng.integers(-8, 9, size=(tokens, H)).astype(np.float32)
+    d0 = rng.integers(-8, 9, size=(V, H)).astype(np.float32)
+    inc_e, inc_p = oracle.embedding_bwd(dys, tok, V, PAD, 2.0, 0.5, 3, 7, "f32")
+    demb, dpos = torch.from_numpy(d0).to(d), torch.zeros((tokens, H), device=d)
+    L.lsq_embedding_bwd(demb, dpos, torch.from_numpy(dys).to(d), torch.from_numpy(tok).to(d), PAD, 2.0, 0.5, 3, 7)
+    assert np.array_equal(demb.cpu().numpy(), (d0 + inc_e).astype(np.float32))
+    assert np.array_equal(dpos.cpu().numpy(), inc_p.astype(np.float32))
+    half = torch.from_numpy(d0).to(d).half()
+    L.lsq_embedding_bwd(half, None, torch.from_numpy(dys).to(d).half(), torch.from_numpy(tok).to(d), PAD, 2.0, 0.5, 3, 7)
+    assert torch.equal(half, demb.half())                    # one rounding per call

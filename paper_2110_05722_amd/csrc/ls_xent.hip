@@ -12,6 +12,8 @@
 // 30522) do not start on 16-byte boundaries: a row is split into a scalar head up
 // to the next pack boundary of the flat tensor, a body of aligned 128-bit packs,
 // and a scalar tail, so the body keeps full-width accesses for any vocab.
+#include <type_traits>
+
 #include "host.hpp"
 
 namespace lsq {
@@ -25,9 +27,18 @@ constexpr float kLn2X = 0.6931471805599453f;
 // no faster (within 2 %) or slower (1024 threads: -10 %)
 constexpr int kXentThreads = 256;
 // the flat backward runs as one-wave workgroups: 259 against 263 us at 8192 x 50257, 134 against 137 us at the
-// transformer-big shape, 103 against 109 us on a masked-LM batch (256 threads per workgroup; 128: 266 / 136 / 102)
+// transformer-big shape, 103 against 109 us on a masked-LM batch (256 threads per workgroup; 128: 266 / 136 / 102); two 16-byte accesses per lane, 2 KB per
+// wave: 256 / 100 us at the first and the last (four 262 / 105, eight 275 / 105, one 283 / 118), 40000 x 8000 with 80 % counting 182 (191, 198, 219)
 constexpr int kXbThreads = 64;
 constexpr int kXentUnroll = 4;
+// The forward's loads skip the caches (nontemporal) unless few rows are read: where at most one of the three tokens beside a token counts (15 % counting: 94 % of the
+// rows, 80 %: 10 %, all: none), its row is left in the 256 MB Infinity Cache for the backward, which reads it next; in tensors of up to 1.3 GB, 200 MB of which
+// are 15 %.  Forward alone / with the backward in us, every row skipping and every row cached, fp16 x 50257: 823 MB with 15 % counting 36.9 / 198.8 and
+// 35.7 / 175.6, 400 MB with 50 % 46.6 / 143.3 and 49.4 / 125.0; with 80 % 63.0 / 174.1 and 69.3 / 171.2, all 72.6 / 195.2 and 81.8 / 195.9: there the forward
+// alone loses.  Looks at 64 targets (a vector load) or 16 took 92 to 102 and 112 us for the forward of 40000 x 8000.  fp32 is always cached: its packs take
+// two accesses of half a line each (200 MB x 30522 with 80 % 42.7 / 100.4 and 39.2 / 90.0).
+constexpr int64_t kKeepBytes = 1300000000;
+constexpr int kKeepRow = 16384;          // shorter rows lose by the look (the forward of 40000 x 8000 with 80 % counting 92 to 100 us)
 
 struct RowSplit {
     int64_t begin, head_end, pack_begin, pack_end, tail_begin, end;
@@ -122,7 +133,7 @@ __global__ __launch_bounds__(TH * R) void xent_fwd_kernel(float* __restrict__ lo
                                                           float* __restrict__ lse,
                                                           const T* __restrict__ logits,
                                                           const int32_t* __restrict__ target, int64_t tokens, int vocab,
-                                                          float alpha, int ignore_index)
+                                                          int keep, float alpha, int ignore_index)
 {
     static_assert(R == 1 || TH == 64, "several rows per workgroup only with one wave per row");
     __shared__ float lds[TH / 64];
@@ -130,6 +141,7 @@ __global__ __launch_bounds__(TH * R) void xent_fwd_kernel(float* __restrict__ lo
     const int tid = threadIdx.x % TH;
     if (t >= tokens) return;                      // whole waves (R > 1 only)
     const int k0 = target[t];
+    bool cached = sizeof(T) == 4;
     if (is_ignored(k0, vocab, ignore_index)) {    // uniform over the row's threads: a padded token's row is not read
         if (tid == 0) {
             loss[t] = 0.0f;
@@ -137,6 +149,15 @@ __global__ __launch_bounds__(TH * R) void xent_fwd_kernel(float* __restrict__ lo
             if (nll) nll[t] = 0.0f;
         }
         return;
+    }
+    if constexpr (R == 1 && sizeof(T) == 2) {     // scalar loads from the line that this target came in
+        const int64_t about = t & ~static_cast<int64_t>(3);
+        if (keep && about + 3 < tokens) {
+            int others = -1;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) others += is_ignored(target[about + i], vocab, ignore_index) ? 0 : 1;
+            cached = others <= 1;
+        }
     }
     // (Issuing the first loads before the target is known was measured too: no faster on rows
     // that count, 15-60 % slower on batches with padding.)
@@ -149,29 +170,33 @@ __global__ __launch_bounds__(TH * R) void xent_fwd_kernel(float* __restrict__ lo
     // line-aligned.  (Started at the pack, each 1 KiB request straddles nine lines and,
     // with nontemporal loads, the shared line is fetched from HBM twice: +6 % traffic.)
     const int64_t base = r.pack_begin & ~static_cast<int64_t>(7);
-    for (int64_t p = base + tid; p < r.pack_end; p += kXentUnroll * TH) {
-        RawPack<T> raw[kXentUnroll];
-        bool ok[kXentUnroll];
+    auto sweep = [&](auto nt) {
+        for (int64_t p = base + tid; p < r.pack_end; p += kXentUnroll * TH) {
+            RawPack<T> raw[kXentUnroll];
+            bool ok[kXentUnroll];
 #pragma unroll
-        for (int u = 0; u < kXentUnroll; ++u) {
-            const int64_t q = p + u * TH;
-            ok[u] = q >= r.pack_begin && q < r.pack_end;
-            if (ok[u]) raw[u] = load_raw<T, kNT>(logits + q * kPack);
-            else raw[u] = zero_raw<T>();
-        }
+            for (int u = 0; u < kXentUnroll; ++u) {
+                const int64_t q = p + u * TH;
+                ok[u] = q >= r.pack_begin && q < r.pack_end;
+                if (ok[u]) raw[u] = load_raw<T, nt.value>(logits + q * kPack);
+                else raw[u] = zero_raw<T>();
+            }
 #pragma unroll
-        for (int u = 0; u < kXentUnroll; ++u) {
-            if (ok[u]) {
-                if constexpr (kIsF16<T>) {
-                    st.add_pack_f16(__builtin_bit_cast(Half8, raw[u].u));
-                } else {
-                    float h[8];
-                    unpack<T>(raw[u], h);
-                    st.add8(h);
+            for (int u = 0; u < kXentUnroll; ++u) {
+                if (ok[u]) {
+                    if constexpr (kIsF16<T>) {
+                        st.add_pack_f16(__builtin_bit_cast(Half8, raw[u].u));
+                    } else {
+                        float h[8];
+                        unpack<T>(raw[u], h);
+                        st.add8(h);
+                    }
                 }
             }
         }
-    }
+    };
+    if (cached) sweep(std::integral_constant<bool, false>{});
+    else sweep(std::integral_constant<bool, true>{});
     const float M = block_allreduce<TH / 64, OpMax>(st.m, lds);
     const float S = block_allreduce<TH / 64, OpSum>(st.s * __builtin_amdgcn_exp2f(st.m - M), lds);
     const float SH = block_allreduce<TH / 64, OpSum>(st.sh, lds);
@@ -238,6 +263,21 @@ __global__ __launch_bounds__(kXentThreads) void xent_bwd_kernel(T* dlogits, cons
     }
 }
 
+// 16 bytes per lane: 8 elements of 16 bits (load8, store8), 4 of 32: an access of a wave then covers 1 KB without gaps, also in fp32, where two accesses
+// per pack of 8 cover half of each line (3000 x 50257, half of the rows ignored: 198 us with four packs of 8 per lane, 187 with two, 145 like this)
+template <typename T, bool NT, int V>
+__device__ __forceinline__ void load16(const T* p, float (&f)[V])
+{
+    if constexpr (V == 8) load8<T, NT>(p, f);
+    else load4<T, NT>(p, f);
+}
+template <typename T, bool NT, int V>
+__device__ __forceinline__ void store16(T* p, const float (&f)[V])
+{
+    if constexpr (V == 8) store8<T, NT>(p, f);
+    else store4<T, NT>(p, f);
+}
+
 // Backward over the FLAT [tokens*vocab] tensor: a workgroup owns a contiguous chunk
 // of U*64 aligned packs whatever rows they fall in, so the access pattern is that
 // of a plain copy (few DRAM pages open at a time, every access 128-bit and aligned,
@@ -253,10 +293,11 @@ __global__ __launch_bounds__(kXbThreads) void xent_bwd_flat_kernel(T* dlogits, c
                                                             const int32_t* __restrict__ target, int64_t tokens,
                                                             int vocab, float alpha, int ignore_index, float grad_scale)
 {
+    constexpr int V = 16 / sizeof(T);                         // elements of a 16-byte access; "pack" below is one
     const int64_t total = tokens * vocab;
-    const int64_t npacks = total / kPack;                     // full packs; the ragged end is handled below
+    const int64_t npacks = total / V;                         // full packs; the ragged end is handled below
     const int64_t pb = static_cast<int64_t>(blockIdx.x) * (U * kXbThreads);
-    const int64_t tA = (pb * kPack) / vocab;                  // row of the chunk's first element (uniform)
+    const int64_t tA = (pb * V) / vocab;                  // row of the chunk's first element (uniform)
     const int64_t baseA = tA * vocab;
     const int64_t bnd = baseA + vocab;                        // first element of row B
     const bool hasB = tA + 1 < tokens;
@@ -272,49 +313,49 @@ __global__ __launch_bounds__(kXbThreads) void xent_bwd_flat_kernel(T* dlogits, c
     const int64_t hitB = bnd + (liveB ? kB : -1);
 
     if (!liveA && !liveB && blockIdx.x != gridDim.x - 1) {    // a chunk of ignored rows only (masked-LM: most): zeros, nothing else
-        const float zero[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        const float zero[V] = {};
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t q = pb + u * kXbThreads + threadIdx.x;
-            if (q < npacks) store8<T, kBwdNTS>(dlogits + q * kPack, zero);
+            if (q < npacks) store16<T, kBwdNTS>(dlogits + q * V, zero);
         }
         return;
     }
 
-    float h[U][8];
+    float h[U][V];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t q = pb + u * kXbThreads + threadIdx.x;
-        const int64_t e0 = q * kPack;
-        const bool need = q < npacks && ((e0 < bnd && liveA) || (e0 + kPack > bnd && liveB));
+        const int64_t e0 = q * V;
+        const bool need = q < npacks && ((e0 < bnd && liveA) || (e0 + V > bnd && liveB));
         if (need) {
-            load8<T, kBwdNTL>(logits + e0, h[u]);
+            load16<T, kBwdNTL>(logits + e0, h[u]);
         } else {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) h[u][j] = 0.0f;
+            for (int j = 0; j < V; ++j) h[u][j] = 0.0f;
         }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t q = pb + u * kXbThreads + threadIdx.x;
         if (q >= npacks) continue;
-        const int64_t e0 = q * kPack;
-        float o[8];
-        if (e0 + kPack <= bnd || e0 >= bnd) {                 // the whole pack lies in one row
+        const int64_t e0 = q * V;
+        float o[V];
+        if (e0 + V <= bnd || e0 >= bnd) {                     // the whole pack lies in one row
             const bool inB = e0 >= bnd;
             const bool live = inB ? liveB : liveA;
             const float ls = inB ? lsB : lsA;
             const int64_t hp = (inB ? hitB : hitA) - e0;      // 0..7 iff the target element is in this pack
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
+            for (int j = 0; j < V; ++j)
                 o[j] = live ? grad_scale * (__builtin_amdgcn_exp2f(fmaf(h[u][j], kLog2eX, -ls)) - smooth) : 0.0f;
-            if (live && hp >= 0 && hp < kPack) {
+            if (live && hp >= 0 && hp < V) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) o[j] -= (j == static_cast<int>(hp)) ? hit : 0.0f;
+                for (int j = 0; j < V; ++j) o[j] -= (j == static_cast<int>(hp)) ? hit : 0.0f;
             }
         } else {                                              // straddles the boundary: select per element
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < V; ++j) {
                 const bool inB = e0 + j >= bnd;
                 const bool live = inB ? liveB : liveA;
                 const float ls = inB ? lsB : lsA;
@@ -323,11 +364,11 @@ __global__ __launch_bounds__(kXbThreads) void xent_bwd_flat_kernel(T* dlogits, c
                 o[j] = live ? gq : 0.0f;
             }
         }
-        store8<T, kBwdNTS>(dlogits + e0, o);
+        store16<T, kBwdNTS>(dlogits + e0, o);
     }
     // ragged end of the whole tensor (total % 8 elements): last workgroup, scalar
     if (blockIdx.x == gridDim.x - 1) {
-        const int64_t e = npacks * kPack + threadIdx.x;
+        const int64_t e = npacks * V + threadIdx.x;
         if (e < total) {
             const int64_t t = e / vocab;
             const int k = target[t];
@@ -628,12 +669,13 @@ static lsq_status xent_fwd_dispatch(float* loss, float* nll, float* lse, float* 
                                     int64_t tokens, int32_t vocab, float alpha, int32_t ignore_index, hipStream_t s)
 {
     const T* lp = static_cast<const T*>(logits);
+    const int keep = vocab >= kKeepRow && tokens * vocab * static_cast<int64_t>(sizeof(T)) <= kKeepBytes;
     if (vocab <= 2048)
         hipLaunchKernelGGL((xent_fwd_kernel<T, 64, 4>), dim3(static_cast<unsigned>(ceil_div(tokens, 4))), dim3(256), 0, s,
-                           loss, nll, lse, lp, target, tokens, vocab, alpha, ignore_index);
+                           loss, nll, lse, lp, target, tokens, vocab, keep, alpha, ignore_index);
     else
         hipLaunchKernelGGL((xent_fwd_kernel<T>), dim3(static_cast<unsigned>(tokens)), dim3(kXentThreads), 0, s,
-                           loss, nll, lse, lp, target, tokens, vocab, alpha, ignore_index);
+                           loss, nll, lse, lp, target, tokens, vocab, keep, alpha, ignore_index);
     if (sums)
         hipLaunchKernelGGL((xent_sums_kernel<T>), dim3(1), dim3(1024), 0, s, sums, loss, nll, lse, lp, target, tokens,
                            vocab, ignore_index);
@@ -645,19 +687,18 @@ static lsq_status xent_bwd_dispatch(void* dlogits, const void* logits, const flo
                                     int64_t tokens, int32_t vocab, float alpha, int32_t ignore_index, float grad_scale,
                                     hipStream_t s)
 {
-    // the flat kernel needs chunk <= vocab (a chunk touches at most two rows): pick the unroll by vocab
-    const int64_t npacks = tokens * vocab / kPack;
-    const int U = vocab >= 4 * kXbThreads * kPack ? 4 : vocab >= 2 * kXbThreads * kPack ? 2 : vocab >= kXbThreads * kPack ? 1 : 0;
+    // the flat kernel needs chunk <= vocab (a chunk touches at most two rows): pick the unroll by vocab; and no more than 2^32 threads
+    constexpr int V = 16 / sizeof(T);
+    const int64_t npacks = tokens * vocab / V;
+    const int U = vocab >= 2 * kXbThreads * V ? 2 : vocab >= kXbThreads * V ? 1 : 0;
     const int64_t blocks = U ? ceil_div(npacks, U * kXbThreads) : 0;
+    constexpr int64_t kMostBlocks = 0xFFFFFFFFll / kXbThreads;
     T* dp = static_cast<T*>(dlogits);
     const T* lp = static_cast<const T*>(logits);
-    if (U == 4 && blocks <= 0x7FFFFFFF)
-        hipLaunchKernelGGL((xent_bwd_flat_kernel<T, 4>), dim3(static_cast<unsigned>(blocks)), dim3(kXbThreads), 0, s, dp, lp, lse,
-                           target, tokens, vocab, alpha, ignore_index, grad_scale);
-    else if (U == 2 && blocks <= 0x7FFFFFFF)
+    if (U == 2 && blocks <= kMostBlocks)
         hipLaunchKernelGGL((xent_bwd_flat_kernel<T, 2>), dim3(static_cast<unsigned>(blocks)), dim3(kXbThreads), 0, s, dp, lp, lse,
                            target, tokens, vocab, alpha, ignore_index, grad_scale);
-    else if (U == 1 && blocks <= 0x7FFFFFFF)
+    else if (U == 1 && blocks <= kMostBlocks)
         hipLaunchKernelGGL((xent_bwd_flat_kernel<T, 1>), dim3(static_cast<unsigned>(blocks)), dim3(kXbThreads), 0, s, dp, lp, lse,
                            target, tokens, vocab, alpha, ignore_index, grad_scale);
     else

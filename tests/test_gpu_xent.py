@@ -6,7 +6,7 @@ import torch
 import oracle
 import paper_2110_05722_amd as L
 from tests._util import assert_close_f32, assert_close_store, dev, say
-from workloads import CONFIGS, IGNORE_INDEX, criterion_tensors, device_normal, from_torch, to_torch
+from workloads import CONFIGS, IGNORE_INDEX, criterion_tensors, device_normal, encode, from_torch, to_torch
 
 pytestmark = pytest.mark.gpu
 
@@ -171,3 +171,18 @@ def test_ls_xent_every_token_ignored():
     floss, fnll, flse, fsums, fdl = L.lsq_ls_xent_fwd_bwd(logits, target, 0.1, IGNORE_INDEX, 1.0)
     for t in (loss, nll, lse, sums, dl, floss, fnll, flse, fsums, fdl):
         assert not t.float().ne(0).any()
+
+
+# the flat backward's chunks: one and two 16-byte accesses per lane begin at 64 and 128 accesses of 8 (fp32: 4) logits, rows a chunk long or one logit more or
+# less, totals that end inside an access; tails of four tokens and rows on both sides of 16384 logits for the forward that leaves sparse rows in the cache
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("T,V,active", [(7, 255, 1.0), (9, 256, 0.5), (5, 257, 1.0), (6, 511, 0.5), (3, 512, 1.0), (11, 513, 0.5), (5, 1023, 0.3), (4, 1024, 1.0), (7, 1025, 0.5),
+                                        (5, 16383, 0.5), (9, 16384, 0.3), (13, 16387, 0.3), (3, 20001, 1.0)])
+def test_ls_xent_chunk_edges(T, V, active, dt):
+    say(f"[xent] chunk edges T={T} V={V} active={active} {dt}")
+    rng = np.random.default_rng(T * 1000 + V)
+    target = rng.integers(0, V, size=T).astype(np.int32)
+    target[rng.random(T) >= active] = IGNORE_INDEX
+    target[-1] = V - 1
+    t = dict(logits=encode(rng.standard_normal((T, V), dtype=np.float32) * 3, dt), target=target)
+    _run(t, T, V, 0.1, dt)

@@ -95,21 +95,30 @@ __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T*
                                                     RowPackIO<T, RAG> io, DropoutParams d)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * (RAG ? kRagLanes : 64) + lane, cp = RAG ? min(col, io.ppr - 1) : col;
+    using P = LanePacks<T, RAG ? 1 : 64>;
+    const int col = blockIdx.x * (RAG ? kRagLanes : 64) + P::pack(lane), cp = RAG ? min(col, io.ppr - 1) : col;
     const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
-    if (!RAG && !mine) return;
+    if (!RAG && !P::kPaired && !mine) return;
     float b[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, cp), b);
+    if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, P::kPaired ? min(col, io.ppr - 1) : cp), b);
+    auto fetch = [&](const T* t, int64_t row) {
+        if constexpr (P::kPaired) return P::template load<kNT>(t + io.element(row, cp), mine);
+        else return io.template ahead<kNT>(t, row, cp);
+    };
+    auto settle = [&](const RawPack<T>& v) {
+        if constexpr (P::kPaired) return P::settle(v);
+        else return io.settle(v, cp);
+    };
     const int64_t stride = static_cast<int64_t>(gridDim.y) * kBadWaves;
     // the pack of the next row is loaded before this row's is used
     int64_t r = static_cast<int64_t>(blockIdx.y) * kBadWaves + wave;
-    RawPack<T> nx = r < rows ? io.template ahead<kNT>(x, r, cp) : zero_raw<T>();
+    RawPack<T> nx = r < rows ? fetch(x, r) : zero_raw<T>();
     for (; r < rows; r += stride) {
         const RawPack<T> cx = nx;
-        if (r + stride < rows) nx = io.template ahead<kNT>(x, r + stride, cp);
+        if (r + stride < rows) nx = fetch(x, r + stride);
         float xf[8], k[8];
         if constexpr (DROP) bad_factors<RAG>(d, io.element(r, col), k);
-        unpack<T>(io.settle(cx, cp), xf);
+        unpack<T>(settle(cx), xf);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float a = act_value<ACT>(xf[j] + b[j]);
@@ -120,7 +129,8 @@ __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T*
 #pragma unroll
             for (int j = 0; j < 8; ++j) asm("" : "+v"(xf[j]));
         }
-        if (mine) io.template store<kNT>(out, r, cp, xf);
+        if constexpr (P::kPaired) P::template store<kNT>(out + io.element(r, cp), xf, mine);
+        else if (mine) io.template store<kNT>(out, r, cp, xf);
     }
 }
 
@@ -130,39 +140,49 @@ __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ p
 {
     __shared__ float sm[kBadWaves][8][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * (RAG ? kRagLanes : 64) + lane, cp = RAG ? min(col, io.ppr - 1) : col;
+    using P = LanePacks<T, RAG ? 1 : 64>;
+    const int col = blockIdx.x * (RAG ? kRagLanes : 64) + P::pack(lane), cp = RAG ? min(col, io.ppr - 1) : col;
     const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
+    auto fetch = [&](const T* t, int64_t row) {
+        if constexpr (P::kPaired) return P::template load<kNT>(t + io.element(row, cp), mine);
+        else return io.template ahead<kNT>(t, row, cp);
+    };
+    auto settle = [&](const RawPack<T>& v) {
+        if constexpr (P::kPaired) return P::settle(v);
+        else return io.settle(v, cp);
+    };
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const int64_t stride = static_cast<int64_t>(gridDim.y) * kBadWaves;
-    if (RAG || mine) {
+    if (RAG || P::kPaired || mine) {
         float b[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, cp), b);
+        if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, P::kPaired ? min(col, io.ppr - 1) : cp), b);
         // the packs of the next row are loaded before this row's are used, and the dropout factors, which need
         // no data, are drawn while the loads are in flight
         int64_t r = static_cast<int64_t>(blockIdx.y) * kBadWaves + wave;
         RawPack<T> ng = zero_raw<T>(), nx = zero_raw<T>();
         if (r < rows) {
-            ng = io.template ahead<kNT>(dy, r, cp);
-            nx = io.template ahead<kNT>(x, r, cp);
+            ng = fetch(dy, r);
+            nx = fetch(x, r);
         }
         for (; r < rows; r += stride) {
             const RawPack<T> cg = ng, cx = nx;
             const int64_t rn = r + stride;
             if (rn < rows) {
-                ng = io.template ahead<kNT>(dy, rn, cp);
-                nx = io.template ahead<kNT>(x, rn, cp);
+                ng = fetch(dy, rn);
+                nx = fetch(x, rn);
             }
             float g[8], xf[8], k[8];
             if constexpr (DROP) bad_factors<RAG>(d, io.element(r, col), k);
-            unpack<T>(io.settle(cg, cp), g);
-            unpack<T>(io.settle(cx, cp), xf);
+            unpack<T>(settle(cg), g);
+            unpack<T>(settle(cx), xf);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float s = act_slope<ACT>(xf[j] + b[j]);
                 g[j] = DROP ? g[j] * k[j] * s : g[j] * s;
                 acc[j] += g[j];
             }
-            if (mine) io.template store<kNT>(dx, r, cp, g);
+            if constexpr (P::kPaired) P::template store<kNT>(dx + io.element(r, cp), g, mine);
+            else if (mine) io.template store<kNT>(dx, r, cp, g);
         }
     }
     if (partial == nullptr) return;        // uniform over the grid

@@ -21,8 +21,8 @@ constexpr bool kNT = true;    // nontemporal hint on the streamed tensors (not o
 // A wave as 64 / W row segments of W packs: lane -> (row of the group, pack of the column block).
 template <int W> struct BdrLane {
     static constexpr int SUB = 64 / W;
-    int col, sub;
-    __device__ __forceinline__ BdrLane() : col((threadIdx.x & 63) % W), sub((threadIdx.x & 63) / W) {}
+    int lane, sub;
+    __device__ __forceinline__ BdrLane() : lane((threadIdx.x & 63) % W), sub((threadIdx.x & 63) / W) {}
 };
 
 template <typename T, bool HAS_BIAS, bool DROP, int W>
@@ -30,26 +30,24 @@ __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const 
                                                                   const T* res, int64_t rows, int ppr, DropoutParams d)
 {
     constexpr int SUB = 64 / W, U = kBdrFwdUnroll, RPI = kBdrFwdWaves * SUB * U;
+    using P = LanePacks<T, W>;
     const BdrLane<W> ln;
     const int wave = threadIdx.x >> 6;
-    const int cp = blockIdx.x * W + ln.col;
-    if (cp >= ppr) return;
+    const int cp = blockIdx.x * W + P::pack(ln.lane);
+    const bool mine = cp < ppr;
+    if (!P::kPaired && !mine) return;
     // the bias stays packed and is widened where it is used: widening it here would make the
     // row loads below wait for its arrival
     RawPack<T> braw = zero_raw<T>();
-    if constexpr (HAS_BIAS) braw = load_raw<T>(bias + static_cast<int64_t>(cp) * kPack);
+    if constexpr (HAS_BIAS) braw = load_raw<T>(bias + static_cast<int64_t>(P::kPaired ? min(cp, ppr - 1) : cp) * kPack);
     for (int64_t base = static_cast<int64_t>(blockIdx.y) * RPI; base < rows; base += static_cast<int64_t>(gridDim.y) * RPI) {
         RawPack<T> xr[U], rr[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t r = base + (u * kBdrFwdWaves + wave) * SUB + ln.sub;
-            if (r < rows) {
-                xr[u] = load_raw<T, kNT>(x + (r * ppr + cp) * kPack);
-                rr[u] = load_raw<T, kNT>(res + (r * ppr + cp) * kPack);
-            } else {
-                xr[u] = zero_raw<T>();
-                rr[u] = zero_raw<T>();
-            }
+            const bool ok = r < rows && (!P::kPaired || mine);
+            xr[u] = P::template load<kNT>(x + (r * ppr + cp) * kPack, ok);
+            rr[u] = P::template load<kNT>(res + (r * ppr + cp) * kPack, ok);
         }
         // the dropout factors need no data: they are drawn while the loads are in flight
         float k[DROP ? U : 1][8];
@@ -63,11 +61,11 @@ __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t r = base + (u * kBdrFwdWaves + wave) * SUB + ln.sub;
-            if (r < rows) {
+            if (r < rows) {                   // (the lanes of a pair share the row)
                 const int64_t pack = r * ppr + cp;
                 float xf[8], rf[8], b[8];
-                unpack<T>(xr[u], xf);
-                unpack<T>(rr[u], rf);
+                unpack<T>(P::settle(xr[u]), xf);
+                unpack<T>(P::settle(rr[u]), rf);
                 if constexpr (HAS_BIAS) opaque<T>(braw);
                 unpack<T>(braw, b);
 #pragma unroll
@@ -76,7 +74,7 @@ __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const 
                     rf[j] = DROP ? fmaf(z, k[DROP ? u : 0][j], rf[j]) : rf[j] + z;
                 }
                 pin_f32(rf);                  // rounds like the kernel that fuses the LayerNorm behind it
-                store8<T, kNT>(out + pack * kPack, rf);
+                P::template store<kNT>(out + pack * kPack, rf, !P::kPaired || mine);
             }
         }
     }
@@ -90,33 +88,34 @@ __global__ __launch_bounds__(64 * kBdrBwdWaves) void bdr_bwd_cols(T* dx, float* 
 {
     constexpr int SUB = 64 / W, NW = kBdrBwdWaves, THREADS = 64 * NW;
     __shared__ float sm[NW * 8 * 64];      // the lanes' sums
+    using P = LanePacks<T, W>;
     const BdrLane<W> ln;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cp = blockIdx.x * W + ln.col;
-    const bool active = cp < ppr;
+    const int wave = threadIdx.x >> 6, lane = ln.sub * W + P::pack(ln.lane);      // by pack
+    const int cp = blockIdx.x * W + P::pack(ln.lane);
+    const bool mine = cp < ppr, active = P::kPaired || mine;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (active) {
         // A workgroup walks `trips` consecutive groups of NW * SUB rows; the pack of the next trip is
         // loaded before this trip's is used, and the dropout factors, which need no data, are
         // drawn while the loads are in flight.
         const int64_t first = static_cast<int64_t>(blockIdx.y) * trips * (NW * SUB) + wave * SUB + ln.sub;
-        RawPack<T> nxt = first < rows ? load_raw<T, kNT>(dy + (first * ppr + cp) * kPack) : zero_raw<T>();
+        RawPack<T> nxt = P::template load<kNT>(dy + (first * ppr + cp) * kPack, first < rows && mine);
         for (int t = 0; t < trips; ++t) {
             const int64_t r = first + static_cast<int64_t>(t) * (NW * SUB);
             const RawPack<T> cur = nxt;
             const int64_t rn = r + NW * SUB;
-            if (t + 1 < trips && rn < rows) nxt = load_raw<T, kNT>(dy + (rn * ppr + cp) * kPack);
+            if (t + 1 < trips && rn < rows) nxt = P::template load<kNT>(dy + (rn * ppr + cp) * kPack, mine);
             if (r < rows) {
                 const int64_t pack = r * ppr + cp;
                 float g[8], k[8];
                 if constexpr (DROP) dropout_factors8(d, static_cast<uint64_t>(pack), k);
-                unpack<T>(cur, g);
+                unpack<T>(P::settle(cur), g);
                 if constexpr (DROP) {
 #pragma unroll
                     for (int j = 0; j < 8; ++j) g[j] *= k[j];
                 }
                 pin_f32(g);
-                store8<T, kNT>(dx + pack * kPack, g);
+                P::template store<kNT>(dx + pack * kPack, g, mine);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[j] += g[j];
             }

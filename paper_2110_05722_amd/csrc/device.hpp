@@ -169,6 +169,78 @@ __device__ __forceinline__ RawPack<T> pack_raw(const float (&f)[8])
     return r;
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+
+// fp32 packs of a group of G lanes that hold G consecutive packs.  A pack is two 16-byte accesses, and with pack = lane each of them covers every
+// second 16 bytes: half of each line, twice, which with nontemporal hints moves half lines to and from memory.  Here lane l holds pack
+// (l / 2) + (l % 2) G / 2: its accesses are the 16-byte pieces l and G + l of the group, which cover it without gaps, and each pair of lanes exchanges one
+// piece.  Both lanes of a pair have to be there; `ok` says whether the lane's own pack is (the packs that are there come first in the group).
+// 16-bit packs are one access: pack = lane.  fp32, us with pack = lane and like this, inputs cold: bias+dropout+residual forward / backward 16384 x 1024
+// 40.0 / 37.6 and 32.8 / 30.0 (the copy of the forward's bytes 32), 8192 x 1280 26.3 / 23.5 and 22.0 / 20.5, 2000 x 1024 7.2 / 8.4 and 6.5 / 7.9; GELU with dropout
+// 16384 x 1024 29.4 / 43.8 and 25.0 / 38.5, 8192 x 1280 20.5 / 32.4 and 18.6 / 27.9.  Without the hints, pack = lane: 37.1 / 35.7 and 28.7 / 40.9.
+template <typename T, int G>
+struct LanePacks {
+    static constexpr bool kPaired = sizeof(T) == 4 && G >= 8;      // (below, no line is covered either way)
+    static __device__ __forceinline__ int pack(int l)
+    {
+        if constexpr (kPaired) return (l & ~(G - 1)) | ((l & (G - 1)) >> 1) | ((l & 1) * (G / 2));
+        else return l;
+    }
+    static __device__ __forceinline__ fvec4 other(const fvec4& v)  // the other lane's of the pair: quad_perm [1,0,3,2]
+    {
+        return fvec4{dpp_mov<0xB1>(v.x), dpp_mov<0xB1>(v.y), dpp_mov<0xB1>(v.z), dpp_mov<0xB1>(v.w)};
+    }
+    static __device__ __forceinline__ bool other(bool ok) { return __builtin_amdgcn_update_dpp(0, ok ? 1 : 0, 0xB1, 0xF, 0xF, false) != 0; }
+    template <bool NT>
+    static __device__ __forceinline__ RawPack<T> load(const T* p, bool ok)        // p: the lane's own pack
+    {
+        if constexpr (kPaired) {
+            const bool odd = threadIdx.x & 1, ok2 = other(ok);
+            const float* a = reinterpret_cast<const float*>(p) + (odd ? 4 - 4 * G : 0);
+            fvec4 va = {0, 0, 0, 0}, vb = {0, 0, 0, 0};
+            if (odd ? ok2 : ok) va = ld_f4<NT>(a);
+            if (odd ? ok : ok2) vb = ld_f4<NT>(a + 4 * G);
+            RawPack<T> r;
+            r.a = va;
+            r.b = vb;
+            return r;                                              // settled where it is used: the exchange would wait for it
+        } else {
+            return ok ? load_raw<T, NT>(p) : zero_raw<T>();
+        }
+    }
+    static __device__ __forceinline__ RawPack<T> settle(const RawPack<T>& r)
+    {
+        if constexpr (kPaired) {
+            const bool odd = threadIdx.x & 1;
+            const fvec4 t = other(odd ? r.a : r.b);
+            RawPack<T> o;
+            o.a = odd ? t : r.a;
+            o.b = odd ? r.b : t;
+            return o;
+        } else {
+            return r;
+        }
+    }
+    template <bool NT>
+    static __device__ __forceinline__ void store(T* p, const float (&f)[8], bool ok)
+    {
+        if constexpr (kPaired) {
+            const bool odd = threadIdx.x & 1, ok2 = other(ok);
+            const fvec4 q0 = {f[0], f[1], f[2], f[3]}, q1 = {f[4], f[5], f[6], f[7]};
+            const fvec4 t = other(odd ? q0 : q1);
+            float* a = reinterpret_cast<float*>(p) + (odd ? 4 - 4 * G : 0);
+            if (odd ? ok2 : ok) st_f4<NT>(a, odd ? t : q0);
+            if (odd ? ok : ok2) st_f4<NT>(a + 4 * G, odd ? q1 : t);
+        } else {
+            if (ok) store8<T, NT>(p, f);
+        }
+    }
+};
+
 // Make eight fp32 values exist as fp32 before they are narrowed: without it the compiler may fold
 // a final fma into the conversion (v_fma_mixlo_f16: one rounding instead of two), and it takes
 // that decision instantiation by instantiation, so two kernels that must agree bit for bit would not.
@@ -213,12 +285,6 @@ __device__ __forceinline__ void store4(T* __restrict__ p, const float (&f)[4])
 // wave64.  Lanes 1..15 apart are reached with DPP (quad permutes and row mirrors,
 // no LDS traffic); 16 apart with a 32-lane swizzle; the last step of a full-wave
 // reduction reads the four row results through scalar registers.
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-
 struct OpSum { static __device__ __forceinline__ float apply(float a, float b) { return a + b; } };
 struct OpMax { static __device__ __forceinline__ float apply(float a, float b) { return fmaxf(a, b); } };
 

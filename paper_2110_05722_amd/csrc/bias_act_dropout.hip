@@ -90,7 +90,7 @@ __device__ __forceinline__ void bad_factors(const DropoutParams& d, int64_t e, f
 // all its lanes stay, because a pack's dropout words come from two lanes.  Forward / backward in us, the flat walk in brackets: 8192 x 1281
 // bf16 GELU with dropout 16.0 / 27.2 (19.1 / 41.9: a gather per bias element, column sums through LDS), 600 x 16001 14.2 / 22.8
 // (18.6 / 98.6), 500 x 1027 fp16 ReLU 3.4 / 7.2 (7.1 / 13.7), 2000 x 5001 f32 without dropout 21.0 / 29.5 (34.2 / 69.4).
-template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG>
+template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG, bool NTL>
 __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T* __restrict__ bias, int64_t rows,
                                                     RowPackIO<T, RAG> io, DropoutParams d)
 {
@@ -102,8 +102,8 @@ __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T*
     float b[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if constexpr (HAS_BIAS) unpack<T>(io.template load<false>(bias, 0, P::kPaired ? min(col, io.ppr - 1) : cp), b);
     auto fetch = [&](const T* t, int64_t row) {
-        if constexpr (P::kPaired) return P::template load<kNT>(t + io.element(row, cp), mine);
-        else return io.template ahead<kNT>(t, row, cp);
+        if constexpr (P::kPaired) return P::template load<NTL>(t + io.element(row, cp), mine);
+        else return io.template ahead<NTL>(t, row, cp);
     };
     auto settle = [&](const RawPack<T>& v) {
         if constexpr (P::kPaired) return P::settle(v);
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T*
     }
 }
 
-template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG>
+template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG, bool NTL>
 __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ partial, const T* dy, const T* x,
                                                     const T* __restrict__ bias, int64_t rows, RowPackIO<T, RAG> io, DropoutParams d)
 {
@@ -144,8 +144,8 @@ __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ p
     const int col = blockIdx.x * (RAG ? kRagLanes : 64) + P::pack(lane), cp = RAG ? min(col, io.ppr - 1) : col;
     const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
     auto fetch = [&](const T* t, int64_t row) {
-        if constexpr (P::kPaired) return P::template load<kNT>(t + io.element(row, cp), mine);
-        else return io.template ahead<kNT>(t, row, cp);
+        if constexpr (P::kPaired) return P::template load<NTL>(t + io.element(row, cp), mine);
+        else return io.template ahead<NTL>(t, row, cp);
     };
     auto settle = [&](const RawPack<T>& v) {
         if constexpr (P::kPaired) return P::settle(v);
@@ -300,9 +300,11 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
         if (rb * cb <= (sizeof(T) == 2 ? 1024 : 511)) rb = ceil_div(rows, kBadWaves);
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(cb), static_cast<unsigned>(rb)), block(256);
+        const bool cached = stays_cached(rows * hidden, sizeof(T));
 #define LSQ_BAD_FWD(BIAS, DROP)                                                                                                            \
-        if (hidden % kPack == 0) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
-        else hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, true>(hidden), d)
+        if (hidden % kPack == 0 && !cached) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else if (hidden % kPack == 0) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, false>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, true, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, true>(hidden), d)
         const bool drop = d.on != 0;
         if (bp && drop) { LSQ_BAD_FWD(true, true); }
         else if (bp) { LSQ_BAD_FWD(true, false); }
@@ -327,9 +329,11 @@ static lsq_status bad_bwd_dispatch(void* dx, float* dbias, const void* dy, const
         const int rb = bad_bwd_row_blocks(rows, hidden);
         const dim3 grid(static_cast<unsigned>(bad_col_blocks(hidden)), static_cast<unsigned>(rb)), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
+        const bool cached = stays_cached(rows * hidden, sizeof(T));
 #define LSQ_BAD_BWD(BIAS, DROP)                                                                                                            \
-        if (hidden % kPack == 0) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
-        else hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, true>(hidden), d)
+        if (hidden % kPack == 0 && !cached) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else if (hidden % kPack == 0) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, true, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, true>(hidden), d)
         const bool drop = d.on != 0;
         if (bp && drop) { LSQ_BAD_BWD(true, true); }
         else if (bp) { LSQ_BAD_BWD(true, false); }

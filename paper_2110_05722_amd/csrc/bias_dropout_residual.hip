@@ -25,7 +25,7 @@ template <int W> struct BdrLane {
     __device__ __forceinline__ BdrLane() : lane((threadIdx.x & 63) % W), sub((threadIdx.x & 63) / W) {}
 };
 
-template <typename T, bool HAS_BIAS, bool DROP, int W>
+template <typename T, bool HAS_BIAS, bool DROP, int W, bool NTL>
 __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const T* x, const T* __restrict__ bias,
                                                                   const T* res, int64_t rows, int ppr, DropoutParams d)
 {
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const 
         for (int u = 0; u < U; ++u) {
             const int64_t r = base + (u * kBdrFwdWaves + wave) * SUB + ln.sub;
             const bool ok = r < rows && (!P::kPaired || mine);
-            xr[u] = P::template load<kNT>(x + (r * ppr + cp) * kPack, ok);
-            rr[u] = P::template load<kNT>(res + (r * ppr + cp) * kPack, ok);
+            xr[u] = P::template load<NTL>(x + (r * ppr + cp) * kPack, ok);
+            rr[u] = P::template load<NTL>(res + (r * ppr + cp) * kPack, ok);
         }
         // the dropout factors need no data: they are drawn while the loads are in flight
         float k[DROP ? U : 1][8];
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const 
 
 // Backward.  partial: [gridDim.y][hidden] fp32 column sums of the workgroups' rows (nullptr:
 // dbias not wanted), summed over the row blocks by colsum_finalize_kernel.
-template <typename T, bool DROP, int W>
+template <typename T, bool DROP, int W, bool NTL>
 __global__ __launch_bounds__(64 * kBdrBwdWaves) void bdr_bwd_cols(T* dx, float* __restrict__ partial, const T* dy,
                                                                   int64_t rows, int ppr, int trips, DropoutParams d)
 {
@@ -99,12 +99,12 @@ __global__ __launch_bounds__(64 * kBdrBwdWaves) void bdr_bwd_cols(T* dx, float* 
         // loaded before this trip's is used, and the dropout factors, which need no data, are
         // drawn while the loads are in flight.
         const int64_t first = static_cast<int64_t>(blockIdx.y) * trips * (NW * SUB) + wave * SUB + ln.sub;
-        RawPack<T> nxt = P::template load<kNT>(dy + (first * ppr + cp) * kPack, first < rows && mine);
+        RawPack<T> nxt = P::template load<NTL>(dy + (first * ppr + cp) * kPack, first < rows && mine);
         for (int t = 0; t < trips; ++t) {
             const int64_t r = first + static_cast<int64_t>(t) * (NW * SUB);
             const RawPack<T> cur = nxt;
             const int64_t rn = r + NW * SUB;
-            if (t + 1 < trips && rn < rows) nxt = P::template load<kNT>(dy + (rn * ppr + cp) * kPack, mine);
+            if (t + 1 < trips && rn < rows) nxt = P::template load<NTL>(dy + (rn * ppr + cp) * kPack, mine);
             if (r < rows) {
                 const int64_t pack = r * ppr + cp;
                 float g[8], k[8];
@@ -296,14 +296,15 @@ static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, c
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(ceil_div(ppr, w)), static_cast<unsigned>(rb)), block(64 * kBdrFwdWaves);
         const bool drop = d.on != 0;
-#define LSQ_BDR_FWD(W)                                                                                                  \
-        if (w == W) {                                                                                                   \
-            if (bp && drop) hipLaunchKernelGGL((bdr_fwd_cols<T, true, true, W>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);    \
-            else if (bp) hipLaunchKernelGGL((bdr_fwd_cols<T, true, false, W>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);     \
-            else if (drop) hipLaunchKernelGGL((bdr_fwd_cols<T, false, true, W>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);   \
-            else hipLaunchKernelGGL((bdr_fwd_cols<T, false, false, W>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);            \
+        const bool cached = stays_cached(rows * hidden, sizeof(T));
+#define LSQ_BDR_FWD(W, NTL)                                                                                             \
+        if (w == W && cached != NTL) {                                                                                                   \
+            if (bp && drop) hipLaunchKernelGGL((bdr_fwd_cols<T, true, true, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);    \
+            else if (bp) hipLaunchKernelGGL((bdr_fwd_cols<T, true, false, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);     \
+            else if (drop) hipLaunchKernelGGL((bdr_fwd_cols<T, false, true, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);   \
+            else hipLaunchKernelGGL((bdr_fwd_cols<T, false, false, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);            \
         }
-        LSQ_BDR_FWD(32) LSQ_BDR_FWD(16)
+        LSQ_BDR_FWD(32, true) LSQ_BDR_FWD(16, true) LSQ_BDR_FWD(32, false) LSQ_BDR_FWD(16, false)
 #undef LSQ_BDR_FWD
     } else if (!flat) {
         const RowPackIO<T, true> io(hidden);
@@ -330,12 +331,13 @@ static lsq_status bdr_bwd_dispatch(void* dx, float* dbias, const void* dy, int64
         const BdrBwdPlan pl = bdr_bwd_plan(rows, hidden);
         const dim3 grid(static_cast<unsigned>(pl.col_blocks), static_cast<unsigned>(pl.row_blocks)), block(64 * kBdrBwdWaves);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-#define LSQ_BDR_BWD(W)                                                                                                  \
-        if (pl.w == W) {                                                                                                \
-            if (d.on) hipLaunchKernelGGL((bdr_bwd_cols<T, true, W>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);    \
-            else hipLaunchKernelGGL((bdr_bwd_cols<T, false, W>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);         \
+const bool cached = stays_cached(rows * hidden, sizeof(T));
+#define LSQ_BDR_BWD(W, NTL)                                                                                                  \
+        if (pl.w == W && cached != NTL) {                                                                                                \
+            if (d.on) hipLaunchKernelGGL((bdr_bwd_cols<T, true, W, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);    \
+            else hipLaunchKernelGGL((bdr_bwd_cols<T, false, W, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);         \
         }
-        LSQ_BDR_BWD(32) LSQ_BDR_BWD(16)
+        LSQ_BDR_BWD(32, true) LSQ_BDR_BWD(16, true) LSQ_BDR_BWD(32, false) LSQ_BDR_BWD(16, false)
         if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, pl.row_blocks, hidden, s);
 #undef LSQ_BDR_BWD
     } else if (!flat) {

@@ -226,6 +226,17 @@ struct LanePacks {
         }
     }
     template <bool NT>
+    static __device__ __forceinline__ void move(T* p, const RawPack<T>& r)        // what load() has read, whole groups, to where the lane's pack goes
+    {
+        if constexpr (kPaired) {
+            float* a = reinterpret_cast<float*>(p) + (threadIdx.x & 1 ? 4 - 4 * G : 0);
+            st_f4<NT>(a, r.a);
+            st_f4<NT>(a + 4 * G, r.b);
+        } else {
+            store_raw<T, NT>(p, r);
+        }
+    }
+    template <bool NT>
     static __device__ __forceinline__ void store(T* p, const float (&f)[8], bool ok)
     {
         if constexpr (kPaired) {

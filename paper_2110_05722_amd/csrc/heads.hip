@@ -14,7 +14,6 @@
 
 namespace lsq {
 
-constexpr bool kNT = true;
 constexpr int kHeadWaves = 4;
 
 struct HeadGeom {
@@ -39,7 +38,9 @@ __device__ __forceinline__ int64_t head_offset(const HeadGeom& g, int64_t t, int
     return ((b * g.heads + n) * g.len + l) * static_cast<int64_t>(g.head_dim) + dd;
 }
 
-template <typename T, bool HAS_BIAS>
+// fp32 in lane pairs of groups of 8 packs where these lie in one head (heads of a multiple of 64 columns), else through the caches
+template <typename T> constexpr int kHeadGroup = sizeof(T) == 4 ? 8 : 1;
+template <typename T, bool HAS_BIAS, int G, bool NTL>
 __global__ __launch_bounds__(256) void split_heads_kernel(T* __restrict__ o0, T* __restrict__ o1, T* __restrict__ o2,
                                                           const T* __restrict__ in, const T* __restrict__ bias,
                                                           HeadGeom g)
@@ -48,8 +49,10 @@ __global__ __launch_bounds__(256) void split_heads_kernel(T* __restrict__ o0, T*
     // row blocks fastest: consecutive workgroups (consecutive XCDs) take consecutive row blocks of one column block;
     // 18.5 against 19.5 us at 4096 x 3072 and 23.7 against 24.4 us at 8192 x 3840 (the merge is 1-3 % slower that way)
     const GridBlock gb = grid_block<1>();
-    const int cp = gb.col * 64 + lane;
-    if (cp >= g.ppr) return;
+    using P = LanePacks<T, G>;
+    constexpr bool kNTS = sizeof(T) == 2 || P::kPaired;
+    const int cp = gb.col * 64 + P::pack(lane);
+    if (cp >= g.ppr) return;                                     // (whole groups)
     const int col = cp * kPack;
     const int part = col / g.hidden;
     const int within = col - part * g.hidden;
@@ -59,26 +62,25 @@ __global__ __launch_bounds__(256) void split_heads_kernel(T* __restrict__ o0, T*
     const int64_t stride = static_cast<int64_t>(gridDim.y) * kHeadWaves;
     // the pack of the next token is loaded before this token's is stored
     int64_t t = static_cast<int64_t>(gb.row) * kHeadWaves + wave;
-    RawPack<T> nxt = t < g.rows ? load_raw<T, kNT>(in + (t * g.ppr + cp) * kPack) : zero_raw<T>();
+    RawPack<T> nxt = t < g.rows ? P::template load<NTL>(in + (t * g.ppr + cp) * kPack, true) : zero_raw<T>();
     for (; t < g.rows; t += stride) {
         const RawPack<T> r = nxt;
-        if (t + stride < g.rows) nxt = load_raw<T, kNT>(in + ((t + stride) * g.ppr + cp) * kPack);
+        if (t + stride < g.rows) nxt = P::template load<NTL>(in + ((t + stride) * g.ppr + cp) * kPack, true);
         T* dst = out + head_offset(g, t, within);
         if constexpr (HAS_BIAS) {
             float f[8];
-            unpack<T>(r, f);
+            unpack<T>(P::settle(r), f);
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] += b[j];
-            store8<T, kNT>(dst, f);
+            P::template store<kNTS>(dst, f, true);
         } else {                                                 // a pure move: bit-exact
-            if constexpr (sizeof(T) == 2) st_u4<kNT>(dst, r.u);
-            else { st_f4<kNT>(reinterpret_cast<float*>(dst), r.a); st_f4<kNT>(reinterpret_cast<float*>(dst) + 4, r.b); }
+            P::template move<kNTS>(dst, r);
         }
     }
 }
 
 // inverse: `parts` tensors [batch, heads, len, head_dim] -> [T, parts*hidden]; partial: dbias partial rows or nullptr
-template <typename T>
+template <typename T, int G, bool NTL>
 __global__ __launch_bounds__(256) void merge_heads_kernel(T* __restrict__ out, float* __restrict__ partial,
                                                           const T* __restrict__ i0, const T* __restrict__ i1,
                                                           const T* __restrict__ i2, HeadGeom g)
@@ -86,7 +88,9 @@ __global__ __launch_bounds__(256) void merge_heads_kernel(T* __restrict__ out, f
     __shared__ float sm[kHeadWaves][8][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const GridBlock gb = grid_block<0>();
-    const int cp = gb.col * 64 + lane;
+    using P = LanePacks<T, G>;
+    constexpr bool kNTS = sizeof(T) == 2 || P::kPaired;
+    const int cp = gb.col * 64 + P::pack(lane);
     const bool active = cp < g.ppr;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (active) {
@@ -96,13 +100,11 @@ __global__ __launch_bounds__(256) void merge_heads_kernel(T* __restrict__ out, f
         const T* in = pick(i0, i1, i2, part);
         const int64_t stride = static_cast<int64_t>(gridDim.y) * kHeadWaves;
         for (int64_t t = static_cast<int64_t>(gb.row) * kHeadWaves + wave; t < g.rows; t += stride) {
-            const RawPack<T> r = load_raw<T, kNT>(in + head_offset(g, t, within));
-            T* dst = out + (t * g.ppr + cp) * kPack;
-            if constexpr (sizeof(T) == 2) st_u4<kNT>(dst, r.u);
-            else { st_f4<kNT>(reinterpret_cast<float*>(dst), r.a); st_f4<kNT>(reinterpret_cast<float*>(dst) + 4, r.b); }
+            const RawPack<T> r = P::template load<NTL>(in + head_offset(g, t, within), true);
+            P::template move<kNTS>(out + (t * g.ppr + cp) * kPack, r);
             if (partial) {
                 float f[8];
-                unpack<T>(r, f);
+                unpack<T>(P::settle(r), f);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[j] += f[j];
             }
@@ -189,8 +191,15 @@ static lsq_status split_dispatch(void* o0, void* o1, void* o2, const void* in, c
     const T* bp = static_cast<const T*>(bias);
     if (g.head_dim % kPack == 0) {
         const dim3 grid(static_cast<unsigned>(ceil_div(g.ppr, 64)), static_cast<unsigned>(head_row_blocks(g.rows))), block(256);
-        if (bp) hipLaunchKernelGGL((split_heads_kernel<T, true>), grid, block, 0, s, a, b, c, ip, bp, g);
-        else hipLaunchKernelGGL((split_heads_kernel<T, false>), grid, block, 0, s, a, b, c, ip, bp, g);
+        const bool cached = stays_cached(g.rows * g.parts * g.hidden, sizeof(T)), pairs = sizeof(T) == 4 && g.head_dim % 64 == 0;
+#define LSQ_SPLIT(G, NTL)                                                                                                              \
+        if (bp) hipLaunchKernelGGL((split_heads_kernel<T, true, G, NTL>), grid, block, 0, s, a, b, c, ip, bp, g);                      \
+        else hipLaunchKernelGGL((split_heads_kernel<T, false, G, NTL>), grid, block, 0, s, a, b, c, ip, bp, g)
+        if (pairs && cached) { LSQ_SPLIT(kHeadGroup<T>, false); }
+        else if (pairs) { LSQ_SPLIT(kHeadGroup<T>, true); }
+        else if (cached || sizeof(T) == 4) { LSQ_SPLIT(1, false); }
+        else { LSQ_SPLIT(1, true); }
+#undef LSQ_SPLIT
     } else {
         const int64_t total = g.rows * g.parts * g.hidden;
         hipLaunchKernelGGL((split_heads_flat<T>), dim3(static_cast<unsigned>(ceil_div(total, 256))), dim3(256), 0, s,
@@ -210,7 +219,13 @@ static lsq_status merge_dispatch(void* out, float* dbias, const void* i0, const 
         const int rb = heads_bwd_row_blocks(g.rows, cols, sizeof(T));
         const dim3 grid(static_cast<unsigned>(ceil_div(g.ppr, 64)), static_cast<unsigned>(dbias ? rb : head_row_blocks(g.rows))), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        hipLaunchKernelGGL((merge_heads_kernel<T>), grid, block, 0, s, o, partial, a, b, c, g);
+        const bool cached = stays_cached(g.rows * g.hidden, sizeof(T)), pairs = sizeof(T) == 4 && g.head_dim % 64 == 0;
+#define LSQ_MERGE(G, NTL) hipLaunchKernelGGL((merge_heads_kernel<T, G, NTL>), grid, block, 0, s, o, partial, a, b, c, g)
+        if (pairs && cached) LSQ_MERGE(kHeadGroup<T>, false);
+        else if (pairs) LSQ_MERGE(kHeadGroup<T>, true);
+        else if (cached || sizeof(T) == 4) LSQ_MERGE(1, false);
+        else LSQ_MERGE(1, true);
+#undef LSQ_MERGE
         if (dbias) launch_colsum_finalize(dbias, dbias, cols, partial, rb, cols, s);
     } else {
         const int64_t total = g.rows * cols;

@@ -56,6 +56,14 @@ inline lsq_status zero_fill(float* p, int64_t n, hipStream_t s)
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The streamed inputs of a call are loaded past the caches (nontemporal) only where a tensor is larger than this: what the kernel ahead has just written, a smaller
+// one, is still in the 256 MB Infinity Cache.  Past the caches / through them in us, bf16, inputs there and (cold) in far memory: bias+dropout+residual forward
+// 2000 x 1024 4.0 / 3.3 (3.6 / 3.9), backward 8192 x 1024 10.8 / 9.7 (10.9 / 11.1); head split backward 128 x 32 x 8 x 64 x 3 9.8 / 8.7 (9.7 / 10.0), padding restored
+// 30 x 100 x 768 4.2 / 3.3 (3.8 / 3.2); a captured layer of 128 x 32 tokens, hidden 512, 92.2 / 85.2.  Beyond, cold costs more than there gives: 16384 x 1024
+// 17.6 / 16.3 (17.5 / 18.5), heads of 8192 x 1280 (21 MB a tensor) 67.0 / 67.9 for a pass over fresh inputs.
+constexpr int64_t kCachedBytes = 16ll << 20;
+inline bool stays_cached(int64_t elements, size_t elem_bytes) { return elements * static_cast<int64_t>(elem_bytes) <= kCachedBytes; }
+
 // Division of a row index (below 2^32) by a launch constant: multiply-high by a host-made reciprocal, two shifts
 // (Granlund and Montgomery's round-up form) -- 5 integer instructions where the 64-bit division the compiler emits
 // for an int64 row index takes about 40 per row (a tenth of a short softmax row's vector-ALU work).

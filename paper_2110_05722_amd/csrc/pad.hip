@@ -74,7 +74,7 @@ __device__ __forceinline__ int64_t packed_row(const PadGeom& g, const int32_t* _
 // RESTORE = true:  padded <- packed, zeros on the padding.
 // Rows that are not whole packs, or tensors that are not 16-byte aligned, take the same walk with element-aligned packs
 // (RAG) from kPadFlat columns on: 128 x 64 x 1001 halves, remove / restore 7.2 / 7.9 us against 17.6 / 18.1 with one element per thread.
-template <typename T, bool RESTORE, bool RAG>
+template <typename T, bool RESTORE, bool RAG, bool NTL>
 __global__ __launch_bounds__(256) void pad_move_kernel(T* __restrict__ dst, const T* __restrict__ src,
                                                        const int32_t* __restrict__ offsets, PadGeom g)
 {
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void pad_move_kernel(T* __restrict__ dst, cons
         for (int k = 0; k < kPadRows; ++k) {
             pr[k] = packed_row(g, offsets, t0 + k);      // wave-uniform
             const int64_t from = RESTORE ? pr[k] : t0 + k;
-            if (pr[k] >= 0) raw[k] = io.template ahead<kNT>(src, from, cp);
+            if (pr[k] >= 0) raw[k] = io.template ahead<NTL>(src, from, cp);
             else raw[k] = zero_raw<T>();
         }
 #pragma unroll
@@ -141,8 +141,10 @@ static lsq_status pad_dispatch(void* dst, const void* src, const int32_t* offset
     const int64_t cap = 16384 / gx > 1 ? 16384 / gx : 1;      // about 64 workgroups per compute unit
     if (gy > cap) gy = cap;
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy)), block(256);
-    if (whole) hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, false>), grid, block, 0, s, d, a, offsets, g);
-    else hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, true>), grid, block, 0, s, d, a, offsets, g);
+    const bool cached = stays_cached((RESTORE ? g.packed_rows : g.rows) * g.hidden, sizeof(T));
+    if (whole && cached) hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, false, false>), grid, block, 0, s, d, a, offsets, g);
+    else if (whole) hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, false, true>), grid, block, 0, s, d, a, offsets, g);
+    else hipLaunchKernelGGL((pad_move_kernel<T, RESTORE, true, true>), grid, block, 0, s, d, a, offsets, g);
     return launch_status();
 }
 

@@ -226,6 +226,16 @@ struct LanePacks {
         }
     }
     template <bool NT>
+    static __device__ __forceinline__ void store(T* p, const RawPack<T>& r, bool ok)
+    {
+        if constexpr (kPaired) {
+            const float f[8] = {r.a.x, r.a.y, r.a.z, r.a.w, r.b.x, r.b.y, r.b.z, r.b.w};
+            store<NT>(p, f, ok);
+        } else {
+            if (ok) store_raw<T, NT>(p, r);
+        }
+    }
+    template <bool NT>
     static __device__ __forceinline__ void move(T* p, const RawPack<T>& r)        // what load() has read, whole groups, to where the lane's pack goes
     {
         if constexpr (kPaired) {

@@ -70,11 +70,17 @@ __device__ __forceinline__ float ln_row_total(const float (&part)[kLnParts<LPR, 
     }
 }
 
+// fp32 rows in lane pairs of groups of 8 lanes, in every shape of the forward, so that a row's sums have one order (LanePacks).  Inputs cold, us, consecutive packs
+// (gamma and beta from the caches) and like this: forward 8192 x 1024 16.6 / 13.3, 4096 x 4096 30.7 / 26.5, fused 8192 x 1280 41.0 / 33.7, 4096 x 1024 17.5 / 13.7;
+// backward (groups of 32) 16384 x 1024 55.8 / 48.4, 300 x 8192 21.8 / 18.5, fused 8192 x 1280 46.3 / 42.5, 300 x 8192 26.6 / 22.4.
+template <typename T, int VPL> using LnPacks = LanePacks<T, VPL < 8 ? 8 : 1>;      // (256 lanes x 8 packs, the only shape beyond 12288 columns, would spill)
+template <typename T> constexpr bool kLnNT = sizeof(T) == 2;       // of fp32 packs that are not in pairs: through the caches
+
 // Raw packs of row r for this lane (zeros where the row or the pack does not exist).
 // Loads only, no arithmetic: every load of the row is in flight before the first use.
 // NT: past the caches, for the rows; not for gamma, beta and bias, which every workgroup reads (past the caches they were fetched anew by each: forward
 // 16384 x 1024 bf16 16.7 us, 14.3 from the caches, 1000 x 1024 4.0 / 3.2, 4096 x 4096 f32 36.7 / 31.0; fused 8192 x 1280 bf16 17.9 / 16.8; inputs cold).
-template <typename T, int LPR, int VPL, bool NT = kNT>
+template <typename T, int LPR, int VPL, bool NT = kLnNT<T>>
 __device__ __forceinline__ void ln_load_row(RawPack<T> (&raw)[VPL], const T* __restrict__ base, int64_t r, bool rv,
                                             int hidden, int nv, int sub)
 {
@@ -83,6 +89,17 @@ __device__ __forceinline__ void ln_load_row(RawPack<T> (&raw)[VPL], const T* __r
         const int idx = sub + k * LPR;
         if (rv && idx < nv) raw[k] = load_raw<T, NT>(base + r * hidden + idx * kPack);
         else raw[k] = zero_raw<T>();
+    }
+}
+
+// The same as LnPacks: to be settled before use
+template <typename T, int LPR, int VPL>
+__device__ __forceinline__ void ln_load_paired(RawPack<T> (&raw)[VPL], const T* __restrict__ base, int64_t r, bool rv, int hidden, int nv, int sub)
+{
+#pragma unroll
+    for (int k = 0; k < VPL; ++k) {
+        const int idx = sub + k * LPR;
+        raw[k] = LnPacks<T, VPL>::template load<kNT>(base + r * hidden + idx * kPack, rv && idx < nv);
     }
 }
 
@@ -108,7 +125,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
     __shared__ float lds[2][LPR == 256 ? 256 : 1];     // in turn: sum, squares (a barrier lies between two writes of either)
     constexpr int RPB = 256 / LPR;                     // rows a workgroup handles at a time
     constexpr int NP = kLnParts<LPR, VPL>;
-    const int sub = threadIdx.x % LPR;
+    using P = LnPacks<T, VPL>;
+    const int sub = P::pack(threadIdx.x % LPR);
     const int slot = threadIdx.x / LPR;
     const int nv = hidden / kPack;
     const float inv_h = 1.0f / static_cast<float>(hidden);
@@ -129,22 +147,22 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
 
     int64_t base = static_cast<int64_t>(blockIdx.x) * RPB;
     RawPack<T> nxt[VPL], nres[FUSE ? VPL : 1];
-    ln_load_row<T, LPR, VPL>(nxt, x, base + slot, base + slot < rows, hidden, nv, sub);
-    if constexpr (FUSE) ln_load_row<T, LPR, VPL>(nres, fz.residual, base + slot, base + slot < rows, hidden, nv, sub);
+    ln_load_paired<T, LPR, VPL>(nxt, x, base + slot, base + slot < rows, hidden, nv, sub);
+    if constexpr (FUSE) ln_load_paired<T, LPR, VPL>(nres, fz.residual, base + slot, base + slot < rows, hidden, nv, sub);
     for (; base < rows; base += gstride) {
         const int64_t r = base + slot;
         const bool rv = r < rows;
         RawPack<T> cur[VPL], cres[FUSE ? VPL : 1];
 #pragma unroll
-        for (int k = 0; k < VPL; ++k) cur[k] = nxt[k];
+        for (int k = 0; k < VPL; ++k) cur[k] = P::settle(nxt[k]);
         if constexpr (FUSE) {
 #pragma unroll
-            for (int k = 0; k < VPL; ++k) cres[k] = nres[k];
+            for (int k = 0; k < VPL; ++k) cres[k] = P::settle(nres[k]);
         }
         if (base + gstride < rows) {          // prefetch the next row group while this one is reduced
-            ln_load_row<T, LPR, VPL>(nxt, x, r + gstride, r + gstride < rows, hidden, nv, sub);
+            ln_load_paired<T, LPR, VPL>(nxt, x, r + gstride, r + gstride < rows, hidden, nv, sub);
             if constexpr (FUSE)
-                ln_load_row<T, LPR, VPL>(nres, fz.residual, r + gstride, r + gstride < rows, hidden, nv, sub);
+                ln_load_paired<T, LPR, VPL>(nres, fz.residual, r + gstride, r + gstride < rows, hidden, nv, sub);
         }
         if constexpr (FUSE) {
             // same expressions as the stand-alone bias+dropout+residual kernel; the pack index of
@@ -152,7 +170,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
 #pragma unroll
             for (int k = 0; k < VPL; ++k) {
                 const int idx = sub + k * LPR;
-                if (rv && idx < nv) {
+                const bool ok = rv && idx < nv;
+                if (P::kPaired || ok) {       // (absent packs stay zeros)
                     float xf[8], rf[8], b8[8], kf[8];
                     unpack<T>(cur[k], xf);
                     unpack<T>(cres[k], rf);
@@ -164,8 +183,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
                         rf[j] = DROP ? fmaf(z, kf[j], rf[j]) : rf[j] + z;
                     }
                     pin_f32(rf);              // rounds like the stand-alone bias+dropout+residual kernel
-                    cur[k] = pack_raw<T>(rf);
-                    store_raw<T, kNT>(fz.out + r * hidden + idx * kPack, cur[k]);
+                    if (!P::kPaired || ok) cur[k] = pack_raw<T>(rf);
+                    P::template store<kNT>(fz.out + r * hidden + idx * kPack, cur[k], ok);
                 }
             }
         }
@@ -203,14 +222,15 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR;
-            if (rv && idx < nv) {
+            const bool ok = rv && idx < nv;
+            if (P::kPaired || ok) {
                 float o[8], g8[8], b8[8];
                 unpack<T>(gm[k], g8);
                 unpack<T>(bt[k], b8);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] = fmaf(xv[k][j] * rs, g8[j], b8[j]);
                 pin_f32(o);                   // the fused and the plain kernel round alike
-                store8<T, kNT>(yr + idx * kPack, o);
+                P::template store<kNT>(yr + idx * kPack, o, ok);
             }
         }
     }
@@ -368,10 +388,10 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
                 }
                 pin_f32(o);               // the fused and the plain kernel round alike
                 if constexpr (!FUSE) {
-                    store8<T, kNT>(dx + ro + idx * kPack, o);
+                    store8<T, kLnNT<T>>(dx + ro + idx * kPack, o);
                 } else {
                     const RawPack<T> hp = pack_raw<T>(o);
-                    store_raw<T, kNT>(dx + ro + idx * kPack, hp);
+                    store_raw<T, kLnNT<T>>(dx + ro + idx * kPack, hp);
                     float gq[8];
                     unpack<T>(hp, gq);
                     if constexpr (DROP) {
@@ -381,7 +401,7 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
                         for (int j = 0; j < 8; ++j) gq[j] *= kf[j];
                     }
                     pin_f32(gq);
-                    store8<T, kNT>(fz.out + ro + idx * kPack, gq);
+                    store8<T, kLnNT<T>>(fz.out + ro + idx * kPack, gq);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) dbi[k][j] += gq[j];
                 }
@@ -463,7 +483,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
     extern __shared__ float span_lds[];       // the rows' exchange [2][32-lane groups][2], later the slots' [slots / 2][NACC * 8][lanes]
     const int LR = LRC ? LRC : lanes;
     const int slots = blockDim.x / LR;
-    const int slot = threadIdx.x / LR, sub = threadIdx.x - slot * LR;
+    using P = LanePacks<T, RAG || LRC == 64 ? 1 : 32>;      // (512 columns, few waves: 6.5 us, in pairs 7.2 at 512 rows)
+    const int slot = threadIdx.x / LR, sub = P::pack(threadIdx.x - slot * LR);
     const RowPackIO<T, RAG> io(hidden);
     const int nv = io.ppr;
     const bool on = sub < nv;
@@ -485,13 +506,21 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         if constexpr (HAS_RES) nres = zero_raw<T>();
         nmu = 0.0f; nrs = 0.0f;
         if (r < rows) {
-            if (on) {
+            if constexpr (P::kPaired) {
+                ndy = P::template load<kNT>(dy + io.element(r, sub), on);
+                nx = P::template load<kNT>(x + io.element(r, sub), on);
+                if constexpr (HAS_RES) nres = P::template load<kNT>(dres + io.element(r, sub), on);
+            } else if (on) {
                 ndy = io.template ahead<kNT>(dy, r, sub);
                 nx = io.template ahead<kNT>(x, r, sub);
                 if constexpr (HAS_RES) nres = io.template ahead<kNT>(dres, r, sub);
             }
             nmu = mean[r]; nrs = rstd[r];
         }
+    };
+    auto settle = [&](const RawPack<T>& v) {
+        if constexpr (P::kPaired) return P::settle(v);
+        else return io.settle(v, sub);
     };
     int64_t base = static_cast<int64_t>(blockIdx.x) * slots;
     fetch(base + slot);
@@ -510,8 +539,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         // the two row sums and the column sums; absent packs and rows hold dy = 0
         const float nmr = -mu * rs;
         float gy[8], xh[8], s1 = 0.0f, s2 = 0.0f;
-        unpack<T>(io.settle(cdy, sub), gy);
-        unpack<T>(io.settle(cx, sub), xh);
+        unpack<T>(settle(cdy), gy);
+        unpack<T>(settle(cx), xh);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             xh[j] = fmaf(xh[j], rs, nmr);
@@ -548,9 +577,9 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         }
         // dx = rstd*(g - (s1 + xhat*s2)/hidden) = g*rstd + xhat*c1 + c0
         const float c0 = -rs * s1 * inv_h, c1 = -rs * s2 * inv_h;
-        if (r < rows && on) {
+        if (r < rows && (P::kPaired || on)) {
             float o[8];
-            if constexpr (HAS_RES) unpack<T>(io.settle(cres, sub), o);
+            if constexpr (HAS_RES) unpack<T>(settle(cres), o);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float v = fmaf(gy[j], rs, fmaf(xh[j], c1, c0));
@@ -558,7 +587,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
             }
             pin_f32(o);                       // the fused and the plain kernel round alike
             const RawPack<T> hp = pack_raw<T>(o);
-            io.template put<kNT>(dx, r, sub, hp);
+            if constexpr (P::kPaired) P::template store<kNT>(dx + io.element(r, sub), o, on);
+            else io.template put<kNT>(dx, r, sub, hp);
             if constexpr (FUSE) {
                 float gq[8];
                 unpack<T>(hp, gq);
@@ -570,7 +600,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
                     }
                 }
                 pin_f32(gq);
-                store8<T, kNT>(fz.out + io.element(r, sub), gq);
+                if constexpr (P::kPaired) P::template store<kNT>(fz.out + io.element(r, sub), gq, on);
+                else store8<T, kNT>(fz.out + io.element(r, sub), gq);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[2][j] += gq[j];
             }

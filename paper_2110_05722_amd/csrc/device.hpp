@@ -196,21 +196,23 @@ struct LanePacks {
     }
     static __device__ __forceinline__ bool other(bool ok) { return __builtin_amdgcn_update_dpp(0, ok ? 1 : 0, 0xB1, 0xF, 0xF, false) != 0; }
     template <bool NT>
-    static __device__ __forceinline__ RawPack<T> load(const T* p, bool ok)        // p: the lane's own pack
+    static __device__ __forceinline__ void load_into(RawPack<T>& r, const T* p, bool ok)      // p: the lane's own pack; r stays where it is not there
     {
         if constexpr (kPaired) {
             const bool odd = threadIdx.x & 1, ok2 = other(ok);
             const float* a = reinterpret_cast<const float*>(p) + (odd ? 4 - 4 * G : 0);
-            fvec4 va = {0, 0, 0, 0}, vb = {0, 0, 0, 0};
-            if (odd ? ok2 : ok) va = ld_f4<NT>(a);
-            if (odd ? ok : ok2) vb = ld_f4<NT>(a + 4 * G);
-            RawPack<T> r;
-            r.a = va;
-            r.b = vb;
-            return r;                                              // settled where it is used: the exchange would wait for it
+            if (odd ? ok2 : ok) r.a = ld_f4<NT>(a);
+            if (odd ? ok : ok2) r.b = ld_f4<NT>(a + 4 * G);        // settled where it is used: the exchange would wait for it
         } else {
-            return ok ? load_raw<T, NT>(p) : zero_raw<T>();
+            if (ok) r = load_raw<T, NT>(p);
         }
+    }
+    template <bool NT>
+    static __device__ __forceinline__ RawPack<T> load(const T* p, bool ok)
+    {
+        RawPack<T> r = zero_raw<T>();
+        load_into<NT>(r, p, ok);
+        return r;
     }
     static __device__ __forceinline__ RawPack<T> settle(const RawPack<T>& r)
     {

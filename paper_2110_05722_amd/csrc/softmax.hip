@@ -174,6 +174,10 @@ template <typename T, int LPR, int VPL, bool RAG> constexpr bool sm_store_nt()
     return !RAG || VPL == 1 || LPR > kWave || (sizeof(T) == 2 && (LPR == kWave || (LPR > 8 && VPL == 2)));
 }
 
+// Packs in lane pairs (LanePacks), fp32 rows of 8 lanes and more: sm_paired below.  What the row-wide sums add up is the same, in another order.  A pack that is
+// loaded before the row's limit is known lies in the first group of 8, and there in the first half: in one of the two pieces of every lane.
+template <typename T, bool PAIR> using SmPacks = LanePacks<T, PAIR ? 8 : 1>;
+
 // pack `idx` of a row (`base`: the workgroup's first pack); the last pack of the tensor may be cut short
 template <typename T, int LPR, int VPL, bool RAG>
 __device__ __forceinline__ RawPack<T> load_row_pack(const T* base, const RowPacks<RAG>& p, int idx, int elems)
@@ -261,7 +265,7 @@ __device__ __forceinline__ void mask_packs(RawPack<T> (&pk)[VPL], int sub, int s
 // in parts is the first pack of the wave's first row and the last pack of its last.  All lanes of the wave call it
 // (`rv`: the row exists); LPR = 256 means the row spans the workgroup.  Rows of at most a pack may share one with
 // several others and are stored element by element.
-template <typename T, int LPR, int VPL, bool RAG>
+template <typename T, int LPR, int VPL, bool RAG, bool PAIR>
 __device__ __forceinline__ void store_row(T* base, const RowPacks<RAG>& p, int sub, bool rv, bool next_rv, int k_len,
                                           const RawPack<T> (&pk)[VPL])
 {
@@ -269,7 +273,7 @@ __device__ __forceinline__ void store_row(T* base, const RowPacks<RAG>& p, int s
     if constexpr (!RAG) {
 #pragma unroll
         for (int k = 0; k < VPL; ++k)
-            if (rv && sub + k * LPR < p.n) store_raw<T, sm_store_nt<T, LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k]);
+            SmPacks<T, PAIR>::template store<sm_store_nt<T, LPR, VPL, RAG>()>(at + k * LPR * kPack, pk[k], rv && sub + k * LPR < p.n);
     } else {
         if (k_len <= kPack) {                                         // uniform
 #pragma unroll
@@ -332,7 +336,8 @@ __device__ __forceinline__ void zero_rows(T* base, const BlockRows<RAG>& blk, in
     if (first >= end) return;
     const int a = blk.s + first * k_len, b = blk.s + end * k_len;
     const int a8 = (a + kPack - 1) / kPack * kPack, b8 = b / kPack * kPack;
-    for (int e = a8 + lane * kPack; e < b8; e += kWave * kPack) store_raw<T, NT>(base + e, zero_raw<T>());
+    constexpr int V = 16 / sizeof(T);
+    for (int e = a8 + lane * V; e < b8; e += kWave * V) st_f4<NT>(reinterpret_cast<float*>(base + e), fvec4{0, 0, 0, 0});
     if constexpr (RAG) {                                              // what is shared with the rows beside them
         if (a + lane < min(a8, b)) base[a + lane] = from_f32<T>(0.0f);
         if (b8 >= a8 && b8 + lane < b) base[b8 + lane] = from_f32<T>(0.0f);
@@ -342,12 +347,13 @@ __device__ __forceinline__ void zero_rows(T* base, const BlockRows<RAG>& blk, in
 // RPT rows per lane group: the loads of all RPT rows are issued before the first
 // reduction, so a wave has RPT*VPL packs per lane in flight and the two dependent
 // round trips (lengths, then scores) are paid once per RPT rows.
-template <typename T, int LPR, int VPL, int RPT, bool DROP, bool RAG>
+template <typename T, int LPR, int VPL, int RPT, bool DROP, bool RAG, bool PAIR>
 __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restrict__ yd, const T* x,
                                                           SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     constexpr int RPB = kSmWgFwd / LPR;
-    const int sub = threadIdx.x % LPR;
+    using P = SmPacks<T, PAIR>;
+    const int sub = P::pack(threadIdx.x % LPR);
     const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
     x += blk.pack0 * kPack;
     y += blk.pack0 * kPack;
@@ -371,7 +377,9 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
-            if (j0 < kEarly) {
+            if constexpr (P::kPaired) {
+                raw[r][k] = P::template load<true>(x + static_cast<unsigned>(rp[r].first + idx) * kPack, k == 0 && j0 < kEarly && row[r] < blk.rows && j0 < g.k_len);
+            } else if (j0 < kEarly) {
                 if (row[r] < blk.rows && j0 < g.k_len) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);
                 else raw[r][k] = zero_raw<T>();
             }
@@ -399,8 +407,11 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
-            if (j0 >= kEarly) {
-                if (pack_needed<RAG>(j0, limit[r])) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);   // implies a valid row and pack
+            const bool need = pack_needed<RAG>(j0, limit[r]);         // implies a valid row and pack
+            if constexpr (P::kPaired) {
+                P::template load_into<true>(raw[r][k], x + static_cast<unsigned>(rp[r].first + idx) * kPack, j0 >= kEarly && need);
+            } else if (j0 >= kEarly) {
+                if (need) raw[r][k] = load_row_pack<T, LPR, VPL, RAG>(x, rp[r], idx, blk.elems);
                 else raw[r][k] = zero_raw<T>();
             }
         }
@@ -419,7 +430,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
             const int j0 = (sub + k * LPR) * kPack - rp[r].s;
             live[k] = __ballot(pack_needed<RAG>(j0, lim)) != 0;
             if (live[k]) {    // a pack that is masked for the whole wave costs no arithmetic
-                unpack<T>(raw[r][k], v[k]);
+                unpack<T>(P::settle(raw[r][k]), v[k]);
                 if (!fold) {
 #pragma unroll
                     for (int j = 0; j < 8; ++j) v[k][j] *= g.scale;
@@ -465,7 +476,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
             }
         }
         if (nan_row) mask_packs<T, LPR, false>(pk, sub, rp[r].s, lim);
-        store_row<T, LPR, VPL, RAG>(y, rp[r], sub, rv, next_rv, g.k_len, pk);
+        store_row<T, LPR, VPL, RAG, PAIR>(y, rp[r], sub, rv, next_rv, g.k_len, pk);
         if constexpr (DROP) {
 #pragma unroll
             for (int k = 0; k < VPL; ++k) {
@@ -479,17 +490,18 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
                 }
             }
             if (nan_row) mask_packs<T, LPR, true>(pk, sub, rp[r].s, lim, d, blk.pack0 + rp[r].first);
-            store_row<T, LPR, VPL, RAG>(yd, rp[r], sub, rv, next_rv, g.k_len, pk);
+            store_row<T, LPR, VPL, RAG, PAIR>(yd, rp[r], sub, rv, next_rv, g.k_len, pk);
         }
     }
 }
 
-template <typename T, int LPR, int VPL, int RPT, bool DROP, bool RAG>
+template <typename T, int LPR, int VPL, int RPT, bool DROP, bool RAG, bool PAIR>
 __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* dy, const T* __restrict__ y,
                                                           SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     constexpr int RPB = kSmWgBwd / LPR;
-    const int sub = threadIdx.x % LPR;
+    using P = SmPacks<T, PAIR>;
+    const int sub = P::pack(threadIdx.x % LPR);
     const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
     y += blk.pack0 * kPack;
     dy += blk.pack0 * kPack;
@@ -508,7 +520,12 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
-            if (j0 < kEarly) {
+            if constexpr (P::kPaired) {
+                const unsigned e = static_cast<unsigned>(rp[r].first + idx) * kPack;
+                const bool ok = k == 0 && j0 < kEarly && row[r] < blk.rows && j0 < g.k_len;
+                ry[r][k] = P::template load<true>(y + e, ok);
+                rg[r][k] = P::template load<true>(dy + e, ok);
+            } else if (j0 < kEarly) {
                 if (row[r] < blk.rows && j0 < g.k_len) {
                     ry[r][k] = load_row_pack<T, LPR, VPL, RAG>(y, rp[r], idx, blk.elems);
                     rg[r][k] = load_row_pack<T, LPR, VPL, RAG>(dy, rp[r], idx, blk.elems);
@@ -540,8 +557,14 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR, j0 = idx * kPack - rp[r].s;
-            if (j0 >= kEarly) {
-                if (pack_needed<RAG>(j0, limit[r])) {
+            const bool need = pack_needed<RAG>(j0, limit[r]);
+            if constexpr (P::kPaired) {
+                const unsigned e = static_cast<unsigned>(rp[r].first + idx) * kPack;
+                const bool ok = j0 >= kEarly && need;
+                P::template load_into<true>(ry[r][k], y + e, ok);
+                P::template load_into<true>(rg[r][k], dy + e, ok);
+            } else if (j0 >= kEarly) {
+                if (need) {
                     ry[r][k] = load_row_pack<T, LPR, VPL, RAG>(y, rp[r], idx, blk.elems);
                     rg[r][k] = load_row_pack<T, LPR, VPL, RAG>(dy, rp[r], idx, blk.elems);
                 } else {
@@ -559,8 +582,8 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR;
             const int j0 = idx * kPack - rp[r].s;
-            unpack<T>(ry[r][k], yv[k]);
-            unpack<T>(rg[r][k], gv[k]);
+            unpack<T>(P::settle(ry[r][k]), yv[k]);
+            unpack<T>(P::settle(rg[r][k]), gv[k]);
             if constexpr (DROP) {
                 // RAG: a dropped infinity is 0.  For whole packs the factors, which are ready before the data, are 5 % faster at 16 keys;
                 // a dropped infinity spoils the row's sum there.
@@ -599,7 +622,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
             pk[k] = pack_raw<T>(o);
         }
         if (spoilt) mask_packs<T, LPR, false>(pk, sub, rp[r].s, lim);           // 0 * (0 - dot) is NaN there
-        store_row<T, LPR, VPL, RAG>(dx, rp[r], sub, row[r] < blk.rows, row[r] + 1 < blk.rows, g.k_len, pk);
+        store_row<T, LPR, VPL, RAG, PAIR>(dx, rp[r], sub, row[r] < blk.rows, row[r] + 1 < blk.rows, g.k_len, pk);
     }
 }
 
@@ -768,11 +791,13 @@ __global__ __launch_bounds__(256) void softmax_bwd_lds(T* dx, const T* dy, const
 
 // ---- long rows (257..2048 packs: about 2048 < k_len <= 16384): one workgroup per row, VPL packs per thread in
 // registers, the two reductions cross the four waves through LDS.  Still one read of the row.
-template <typename T, int VPL, bool DROP, bool RAG>
+template <typename T, int VPL, bool DROP, bool RAG, bool PAIR>
 __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd, const T* x,
                                                         SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     __shared__ float red[4];
+    using P = SmPacks<T, PAIR>;
+    const int sub = P::pack(threadIdx.x);
     const int64_t row = blockIdx.x;
     const BlockRows<RAG> blk(g, row);
     const RowPacks<RAG> rp = blk.row(g, 0);
@@ -783,16 +808,17 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
     RawPack<T> raw[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int idx = threadIdx.x + k * 256;
-        if (idx * kPack - rp.s < limit) raw[k] = load_row_pack<T, 256, VPL, RAG>(x, rp, idx, blk.elems);
+        const int idx = sub + k * 256;
+        if constexpr (P::kPaired) raw[k] = P::template load<true>(x + static_cast<unsigned>(rp.first + idx) * kPack, idx * kPack < limit);
+        else if (idx * kPack - rp.s < limit) raw[k] = load_row_pack<T, 256, VPL, RAG>(x, rp, idx, blk.elems);
         else raw[k] = zero_raw<T>();
     }
     float v[VPL][8];
     float mx = -INFINITY;
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int j0 = (threadIdx.x + k * 256) * kPack - rp.s;
-        unpack<T>(raw[k], v[k]);
+        const int j0 = (sub + k * 256) * kPack - rp.s;
+        unpack<T>(P::settle(raw[k]), v[k]);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             bool in = j0 + j < limit;
@@ -822,12 +848,12 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
         pk[k] = pack_raw<T>(v[k]);
     }
     const bool nan_row = z != z;                                          // uniform: a NaN row stays NaN inside the mask only
-    if (nan_row) mask_packs<T, 256, false>(pk, threadIdx.x, rp.s, limit);
-    store_row<T, 256, VPL, RAG>(y, rp, threadIdx.x, true, false, g.k_len, pk);
+    if (nan_row) mask_packs<T, 256, false>(pk, sub, rp.s, limit);
+    store_row<T, 256, VPL, RAG, PAIR>(y, rp, sub, true, false, g.k_len, pk);
     if constexpr (DROP) {
 #pragma unroll
         for (int k = 0; k < VPL; ++k) {
-            const int idx = threadIdx.x + k * 256;
+            const int idx = sub + k * 256;
             if (idx * kPack - rp.s < limit) {
                 float kf[8];
                 dropout_factors8(d, static_cast<uint64_t>(blk.pack0 + (rp.first + idx)), kf);
@@ -836,16 +862,18 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
                 pk[k] = pack_raw<T>(kf);
             }
         }
-        if (nan_row) mask_packs<T, 256, true>(pk, threadIdx.x, rp.s, limit, d, blk.pack0 + rp.first);
-        store_row<T, 256, VPL, RAG>(yd, rp, threadIdx.x, true, false, g.k_len, pk);
+        if (nan_row) mask_packs<T, 256, true>(pk, sub, rp.s, limit, d, blk.pack0 + rp.first);
+        store_row<T, 256, VPL, RAG, PAIR>(yd, rp, sub, true, false, g.k_len, pk);
     }
 }
 
-template <typename T, int VPL, bool DROP, bool RAG>
+template <typename T, int VPL, bool DROP, bool RAG, bool PAIR>
 __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, const T* __restrict__ y,
                                                         SoftmaxLens len, SoftmaxGeom g, DropoutParams d)
 {
     __shared__ float red[4];
+    using P = SmPacks<T, PAIR>;
+    const int sub = P::pack(threadIdx.x);
     const int64_t row = blockIdx.x;
     const BlockRows<RAG> blk(g, row);
     const RowPacks<RAG> rp = blk.row(g, 0);
@@ -856,8 +884,12 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
     RawPack<T> ry[VPL], rg[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int idx = threadIdx.x + k * 256;
-        if (idx * kPack - rp.s < limit) {
+        const int idx = sub + k * 256;
+        if constexpr (P::kPaired) {
+            const unsigned e = static_cast<unsigned>(rp.first + idx) * kPack;
+            ry[k] = P::template load<true>(y + e, idx * kPack < limit);
+            rg[k] = P::template load<true>(dy + e, idx * kPack < limit);
+        } else if (idx * kPack - rp.s < limit) {
             ry[k] = load_row_pack<T, 256, VPL, RAG>(y, rp, idx, blk.elems);
             rg[k] = load_row_pack<T, 256, VPL, RAG>(dy, rp, idx, blk.elems);
         } else {
@@ -869,10 +901,10 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
     float dot = 0.0f;
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
-        const int idx = threadIdx.x + k * 256;
+        const int idx = sub + k * 256;
         const int j0 = idx * kPack - rp.s;
-        unpack<T>(ry[k], yv[k]);
-        unpack<T>(rg[k], gv[k]);
+        unpack<T>(P::settle(ry[k]), yv[k]);
+        unpack<T>(P::settle(rg[k]), gv[k]);
         if constexpr (DROP) {
             if (j0 < limit) {
                 float kf[8];
@@ -896,10 +928,10 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
         float o[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            o[j] = ((threadIdx.x + k * 256) * kPack - rp.s + j < limit) ? g.scale * yv[k][j] * (gv[k][j] - dot) : 0.0f;
+            o[j] = ((sub + k * 256) * kPack - rp.s + j < limit) ? g.scale * yv[k][j] * (gv[k][j] - dot) : 0.0f;
         pk[k] = pack_raw<T>(o);
     }
-    store_row<T, 256, VPL, RAG>(dx, rp, threadIdx.x, true, false, g.k_len, pk);
+    store_row<T, 256, VPL, RAG, PAIR>(dx, rp, sub, true, false, g.k_len, pk);
 }
 
 // ---- rows of more than 2048 packs (beyond about 16384 keys): one workgroup per row, element-strided, the row is
@@ -1118,6 +1150,14 @@ inline SmLds sm_lds_shape(int dir, size_t elem, int k, bool drop, bool lens, boo
 }
 #define LSQ_SM_LDS_CASES(X) X(8, 1) X(8, 2) X(8, 4) X(8, 8) X(16, 8) X(32, 8) X(64, 8)
 
+// fp32 rows in lane pairs (SmPacks): with a lane's pack as two 16-byte accesses 32 bytes apart each line is read and written in halves.  Time with consecutive
+// packs and in pairs, forward with dropout / backward, us, inputs cold: 4 x 16 x 1024 x 1024 160 -> 134 / 151 -> 129, with padding 183 -> 128 / 105 -> 91;
+// 8 x 16 x 512 x 512 80 -> 67 / 75 -> 65; 32 x 16 x 128 x 128 23.4 -> 19.0 / 20.6 -> 18.6; 64 x 16 x 64 x 64 14.7 -> 9.6 / 11.8 -> 11.0; 2 x 4 x 4096 x 4096
+// causal 428 -> 237 / 202 -> 178.  Not where rows are not whole 128-byte lines (their pieces meet in the middle of a line: 1000 keys 55 -> 74 / 52 -> 57, 200 keys 32.5 -> 37.0
+// forward), and not below 2 Mi scores, where the second address and the exchange are in the way of a few waves (16 x 8 x 1 x 512 3.4 -> 4.0 / 2.7 -> 3.5;
+// 8 x 20 x 96 x 96 with padding 6.1 -> 6.4 / 5.1 -> 5.6).
+inline bool sm_paired(size_t storage, const SoftmaxGeom& g) { return storage == 4 && g.k_len % 32 == 0 && g.nrows * g.k_len >= (1 << 21); }
+
 // The paths by row length, with `np` the packs a row touches (base pointers are 16-byte aligned, checked at the entry):
 // up to 256 packs the lanes of a wave, up to 2048 a workgroup per row, beyond that the element-strided kernels; each in a
 // form for rows of whole packs and one for any other length.
@@ -1130,20 +1170,26 @@ static lsq_status softmax_fwd_dispatch(void* y, void* yd, const void* x, Softmax
     const T* xp = static_cast<const T*>(x);
     const bool rag = g.k_len % kPack != 0;
     const int np = rag ? sm_ragged_packs(g.k_len) : g.k_len / kPack;
-    const bool drop = d.on != 0;
+    const bool drop = d.on != 0, pair = sm_paired(sizeof(T), g);
     if (np > 256) {
         const dim3 grid(static_cast<unsigned>(g.nrows)), block(256);
         const int vpl = softmax_wide_vpl(np);
         if (vpl == 0) hipLaunchKernelGGL((softmax_fwd_generic<T>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);
+        constexpr bool kPair = sizeof(T) == 4;
+#define W2(V, RAG, PAIR)                                                                                     \
+            {                                                                                                \
+                if (drop) hipLaunchKernelGGL((softmax_fwd_wide<T, V, true, RAG, PAIR>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);   \
+                else hipLaunchKernelGGL((softmax_fwd_wide<T, V, false, RAG, PAIR>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);       \
+            }
 #define W(V)                                                                                                 \
         if (vpl == V) {                                                                                      \
-            if (rag && drop) hipLaunchKernelGGL((softmax_fwd_wide<T, V, true, true>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);   \
-            else if (rag) hipLaunchKernelGGL((softmax_fwd_wide<T, V, false, true>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);      \
-            else if (drop) hipLaunchKernelGGL((softmax_fwd_wide<T, V, true, false>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);     \
-            else hipLaunchKernelGGL((softmax_fwd_wide<T, V, false, false>), grid, block, 0, s, yp, ydp, xp, key_len, g, d);              \
+            if (rag) W2(V, true, false)                                                                      \
+            else if (pair) W2(V, false, kPair)                                                               \
+            else W2(V, false, false)                                                                         \
         }
         W(2) W(4) W(8)
 #undef W
+#undef W2
         return launch_status();
     }
     if (rag) {
@@ -1162,10 +1208,16 @@ static lsq_status softmax_fwd_dispatch(void* y, void* yd, const void* x, Softmax
     }
     const SmCand c = rag ? sm_ragged_choose(kSmRaggedFwd, np) : sm_choose(key_len, g, drop, sizeof(T), 0, forced);
     const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgFwd / c.lpr), c.rpt)));
+#define XP(L, V, R, RAG, PAIR)                                                                               \
+    {                                                                                                        \
+        if (drop) hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, true, RAG, PAIR>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d); \
+        else hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, false, RAG, PAIR>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d);    \
+    }
 #define XR(L, V, R, RAG)                                                                                     \
     if (rag == RAG && c.lpr == L && c.vpl == V && c.rpt == R) {                                              \
-        if (drop) hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, true, RAG>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d); \
-        else hipLaunchKernelGGL((softmax_fwd_kernel<T, L, V, R, false, RAG>), grid, dim3(kSmWgFwd), 0, s, yp, ydp, xp, key_len, g, d);    \
+        constexpr bool kPair = sizeof(T) == 4 && !RAG && L >= 8;                                             \
+        if (pair) XP(L, V, R, RAG, kPair)                                                                    \
+        else XP(L, V, R, RAG, false)                                                                         \
     }
 #define X(L, V, R) XR(L, V, R, false)
     LSQ_SM_CASES(X)
@@ -1174,6 +1226,7 @@ static lsq_status softmax_fwd_dispatch(void* y, void* yd, const void* x, Softmax
     LSQ_SM_RAGGED_FWD(X)
 #undef X
 #undef XR
+#undef XP
     return launch_status();
 }
 
@@ -1186,20 +1239,26 @@ static lsq_status softmax_bwd_dispatch(void* dx, const void* dy, const void* y, 
     const T* yp = static_cast<const T*>(y);
     const bool rag = g.k_len % kPack != 0;
     const int np = rag ? sm_ragged_packs(g.k_len) : g.k_len / kPack;
-    const bool drop = d.on != 0;
+    const bool drop = d.on != 0, pair = sm_paired(sizeof(T), g);
     if (np > 256) {
         const dim3 grid(static_cast<unsigned>(g.nrows)), block(256);
         const int vpl = softmax_wide_vpl(np);
         if (vpl == 0) hipLaunchKernelGGL((softmax_bwd_generic<T>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);
+        constexpr bool kPair = sizeof(T) == 4;
+#define W2(V, RAG, PAIR)                                                                                     \
+            {                                                                                                \
+                if (drop) hipLaunchKernelGGL((softmax_bwd_wide<T, V, true, RAG, PAIR>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);   \
+                else hipLaunchKernelGGL((softmax_bwd_wide<T, V, false, RAG, PAIR>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);       \
+            }
 #define W(V)                                                                                                 \
         if (vpl == V) {                                                                                      \
-            if (rag && drop) hipLaunchKernelGGL((softmax_bwd_wide<T, V, true, true>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);   \
-            else if (rag) hipLaunchKernelGGL((softmax_bwd_wide<T, V, false, true>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);      \
-            else if (drop) hipLaunchKernelGGL((softmax_bwd_wide<T, V, true, false>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);     \
-            else hipLaunchKernelGGL((softmax_bwd_wide<T, V, false, false>), grid, block, 0, s, dxp, dyp, yp, key_len, g, d);              \
+            if (rag) W2(V, true, false)                                                                      \
+            else if (pair) W2(V, false, kPair)                                                               \
+            else W2(V, false, false)                                                                         \
         }
         W(2) W(4) W(8)
 #undef W
+#undef W2
         return launch_status();
     }
     if (rag) {
@@ -1218,10 +1277,16 @@ static lsq_status softmax_bwd_dispatch(void* dx, const void* dy, const void* y, 
     }
     const SmCand c = rag ? sm_ragged_choose(kSmRaggedBwd, np) : sm_choose(key_len, g, drop, sizeof(T), 1, forced);
     const dim3 grid(static_cast<unsigned>(ceil_div(ceil_div(g.nrows, kSmWgBwd / c.lpr), c.rpt)));
+#define XP(L, V, R, RAG, PAIR)                                                                               \
+    {                                                                                                        \
+        if (drop) hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, true, RAG, PAIR>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d); \
+        else hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, false, RAG, PAIR>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d);    \
+    }
 #define XR(L, V, R, RAG)                                                                                     \
     if (rag == RAG && c.lpr == L && c.vpl == V && c.rpt == R) {                                              \
-        if (drop) hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, true, RAG>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d); \
-        else hipLaunchKernelGGL((softmax_bwd_kernel<T, L, V, R, false, RAG>), grid, dim3(kSmWgBwd), 0, s, dxp, dyp, yp, key_len, g, d);    \
+        constexpr bool kPair = sizeof(T) == 4 && !RAG && L >= 8;                                             \
+        if (pair) XP(L, V, R, RAG, kPair)                                                                    \
+        else XP(L, V, R, RAG, false)                                                                         \
     }
 #define X(L, V, R) XR(L, V, R, false)
     LSQ_SM_CASES(X)
@@ -1230,6 +1295,7 @@ static lsq_status softmax_bwd_dispatch(void* dx, const void* dy, const void* y, 
     LSQ_SM_RAGGED_BWD(X)
 #undef X
 #undef XR
+#undef XP
     return launch_status();
 }
 

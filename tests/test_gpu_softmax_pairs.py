@@ -1,0 +1,59 @@
+"""GPU: fp32 attention softmax of 2 Mi scores and more with rows of whole 128-byte lines, whose packs lie in lane pairs: each sentence of such a call
+against the call of this sentence alone, which is too small for that form and is checked against the CPU oracle elsewhere.
+
+The two forms differ in the order of a row's sums only.  A lane adds up to 64 terms one after the other, and the tree over the lanes and waves has at most
+9 steps: each order is within 73 roundings of 2**-24 of the sum of the terms' magnitudes, so the two differ by at most twice that, and a few
+roundings of the result's own (4 are allowed)."""
+import pytest
+import torch
+
+import paper_2110_05722_amd as L
+from tests._util import dev, say
+
+pytestmark = pytest.mark.gpu
+SUMS, OWN = 2 * 73 * 2.0 ** -24, 4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Lk", [64, 96, 128, 160, 288, 544, 1056, 1568, 2048, 2080, 4128, 8224, 16384])
+def test_large_calls_and_their_sentences(Lk, causal):
+    say(f"[softmax pairs] keys {Lk} causal {causal}")
+    d = dev()
+    N, Lq, scale = 2, 40 if Lk < 2048 else 9, 0.7
+    B = (1 << 21) // (N * Lq * Lk) + 2
+    g = torch.Generator(device=d).manual_seed(Lk)
+    x, dy = (torch.randn(B, N, Lq, Lk, generator=g, device=d) * 2 for _ in range(2))
+    kl = torch.randint(0, Lk + 1, (B,), generator=g, device=d, dtype=torch.int32)
+    ql = torch.randint(0, Lq + 1, (B,), generator=g, device=d, dtype=torch.int32)
+    kl[0], ql[0], kl[-1], ql[-1], kl[B // 2] = Lk - 3, Lq, 5, Lq - 1, Lk
+    out = torch.arange(Lk, device=d)[None, None, None, :] >= kl[:, None, None, None]
+    x, dy = x.masked_fill(out, float("nan")), dy.masked_fill(out, float("inf"))        # what lies behind the keys never counts
+    x[-1, 0, 0, 1], dy[0, 1, 2, 3] = float("nan"), float("inf")                        # rows that are spoilt inside the mask
+    for p in (0.0, 0.2):
+        for lens in ((None, None), (kl, None), (kl, ql)):
+            if lens[0] is None:
+                xs, dys = torch.nan_to_num(x), torch.nan_to_num(dy, posinf=1.0)
+            else:
+                xs, dys = x, dy
+            y, yd = L.lsq_softmax_varlen_fwd(xs, *lens, causal, scale, p, 3, 5)
+            dx = L.lsq_softmax_varlen_bwd(dys, y, *lens, causal, scale, p, 3, 5)
+            for b in ((0,) if p else (0, B // 2, B - 1)):                              # (the draws count from the tensor's start)
+                one = [None if v is None else v[b:b + 1].contiguous() for v in lens]
+                y1, yd1 = L.lsq_softmax_varlen_fwd(xs[b:b + 1].contiguous(), *one, causal, scale, p, 3, 5)
+                yb = y[b:b + 1].contiguous()
+                torch.testing.assert_close(yb, y1, rtol=SUMS + OWN, atol=0.0, equal_nan=True)
+                assert torch.equal(yb == 0, y1 == 0) and not torch.signbit(yb).any()
+                if p:
+                    torch.testing.assert_close(yd[b:b + 1], yd1, rtol=SUMS + OWN, atol=0.0, equal_nan=True)
+                dx1 = L.lsq_softmax_varlen_bwd(dys[b:b + 1].contiguous(), yb, *one, causal, scale, p, 3, 5)
+                gy = (torch.where(yb > 0, dys[b:b + 1], 0.0) / (1 - p)).abs()
+                total = (gy * yb).sum(-1, keepdim=True)
+                bound = scale * yb * (SUMS * total + OWN * (gy + total))
+                got = dx[b:b + 1]
+                ok = torch.isfinite(dx1) & torch.isfinite(bound)
+                assert torch.equal(torch.isfinite(got), torch.isfinite(dx1))
+                assert ((got - dx1).abs()[ok] <= bound[ok]).all()
+            xi, di = xs.clone(), dys.clone()                                           # in place
+            if not p:
+                assert torch.equal(torch.nan_to_num(L.lsq_softmax_varlen_fwd(xi, *lens, causal, scale, p, 3, 5, y=xi)[0]), torch.nan_to_num(y))
+            assert torch.equal(torch.nan_to_num(L.lsq_softmax_varlen_bwd(di, y, *lens, causal, scale, p, 3, 5, dx=di)), torch.nan_to_num(dx))

@@ -174,9 +174,11 @@ template <typename T, int LPR, int VPL, bool RAG> constexpr bool sm_store_nt()
     return !RAG || VPL == 1 || LPR > kWave || (sizeof(T) == 2 && (LPR == kWave || (LPR > 8 && VPL == 2)));
 }
 
-// Packs in lane pairs (LanePacks), fp32 rows of 8 lanes and more: sm_paired below.  What the row-wide sums add up is the same, in another order.  A pack that is
-// loaded before the row's limit is known lies in the first group of 8, and there in the first half: in one of the two pieces of every lane.
+// Packs in lane pairs (LanePacks), fp32 rows of 8 lanes and more: sm_paired below.  Where it says no, the lanes hold the same packs all the same (SmOrder)
+// and fetch them by themselves, so a row's sums have one order whatever the size of the call.  A pack that is loaded before the row's limit is known lies in
+// the first group of 8, and there in the first half: in the first piece of every lane of the group.
 template <typename T, bool PAIR> using SmPacks = LanePacks<T, PAIR ? 8 : 1>;
+template <typename T, int LPR, bool RAG> using SmOrder = LanePacks<T, !RAG && LPR >= 8 ? 8 : 1>;
 
 // pack `idx` of a row (`base`: the workgroup's first pack); the last pack of the tensor may be cut short
 template <typename T, int LPR, int VPL, bool RAG>
@@ -353,7 +355,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
 {
     constexpr int RPB = kSmWgFwd / LPR;
     using P = SmPacks<T, PAIR>;
-    const int sub = P::pack(threadIdx.x % LPR);
+    const int sub = SmOrder<T, LPR, RAG>::pack(threadIdx.x % LPR);
     const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
     x += blk.pack0 * kPack;
     y += blk.pack0 * kPack;
@@ -501,7 +503,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
 {
     constexpr int RPB = kSmWgBwd / LPR;
     using P = SmPacks<T, PAIR>;
-    const int sub = P::pack(threadIdx.x % LPR);
+    const int sub = SmOrder<T, LPR, RAG>::pack(threadIdx.x % LPR);
     const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
     y += blk.pack0 * kPack;
     dy += blk.pack0 * kPack;
@@ -797,7 +799,7 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
 {
     __shared__ float red[4];
     using P = SmPacks<T, PAIR>;
-    const int sub = P::pack(threadIdx.x);
+    const int sub = SmOrder<T, 256, RAG>::pack(threadIdx.x);
     const int64_t row = blockIdx.x;
     const BlockRows<RAG> blk(g, row);
     const RowPacks<RAG> rp = blk.row(g, 0);
@@ -873,7 +875,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
 {
     __shared__ float red[4];
     using P = SmPacks<T, PAIR>;
-    const int sub = P::pack(threadIdx.x);
+    const int sub = SmOrder<T, 256, RAG>::pack(threadIdx.x);
     const int64_t row = blockIdx.x;
     const BlockRows<RAG> blk(g, row);
     const RowPacks<RAG> rp = blk.row(g, 0);

@@ -1,9 +1,6 @@
 """GPU: fp32 attention softmax of 2 Mi scores and more with rows of whole 128-byte lines, whose packs lie in lane pairs: each sentence of such a call
-against the call of this sentence alone, which is too small for that form and is checked against the CPU oracle elsewhere.
-
-The two forms differ in the order of a row's sums only.  A lane adds up to 64 terms one after the other, and the tree over the lanes and waves has at most
-9 steps: each order is within 73 roundings of 2**-24 of the sum of the terms' magnitudes, so the two differ by at most twice that, and a few
-roundings of the result's own (4 are allowed)."""
+against the call of this sentence alone, which is too small for that form and is checked against the CPU oracle elsewhere, bit for bit: the
+lanes hold the same packs and add in the same order."""
 import pytest
 import torch
 
@@ -11,7 +8,6 @@ import paper_2110_05722_amd as L
 from tests._util import dev, say
 
 pytestmark = pytest.mark.gpu
-SUMS, OWN = 2 * 73 * 2.0 ** -24, 4 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("causal", [False, True])
@@ -41,18 +37,11 @@ def test_large_calls_and_their_sentences(Lk, causal):
                 one = [None if v is None else v[b:b + 1].contiguous() for v in lens]
                 y1, yd1 = L.lsq_softmax_varlen_fwd(xs[b:b + 1].contiguous(), *one, causal, scale, p, 3, 5)
                 yb = y[b:b + 1].contiguous()
-                torch.testing.assert_close(yb, y1, rtol=SUMS + OWN, atol=0.0, equal_nan=True)
-                assert torch.equal(yb == 0, y1 == 0) and not torch.signbit(yb).any()
+                assert torch.equal(yb.view(torch.int32), y1.view(torch.int32))
                 if p:
-                    torch.testing.assert_close(yd[b:b + 1], yd1, rtol=SUMS + OWN, atol=0.0, equal_nan=True)
+                    assert torch.equal(yd[b:b + 1].contiguous().view(torch.int32), yd1.view(torch.int32))
                 dx1 = L.lsq_softmax_varlen_bwd(dys[b:b + 1].contiguous(), yb, *one, causal, scale, p, 3, 5)
-                gy = (torch.where(yb > 0, dys[b:b + 1], 0.0) / (1 - p)).abs()
-                total = (gy * yb).sum(-1, keepdim=True)
-                bound = scale * yb * (SUMS * total + OWN * (gy + total))
-                got = dx[b:b + 1]
-                ok = torch.isfinite(dx1) & torch.isfinite(bound)
-                assert torch.equal(torch.isfinite(got), torch.isfinite(dx1))
-                assert ((got - dx1).abs()[ok] <= bound[ok]).all()
+                assert torch.equal(dx[b:b + 1].contiguous().view(torch.int32), dx1.view(torch.int32))
             xi, di = xs.clone(), dys.clone()                                           # in place
             if not p:
                 assert torch.equal(torch.nan_to_num(L.lsq_softmax_varlen_fwd(xi, *lens, causal, scale, p, 3, 5, y=xi)[0]), torch.nan_to_num(y))

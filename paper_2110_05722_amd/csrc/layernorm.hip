@@ -73,6 +73,8 @@ __device__ __forceinline__ float ln_row_total(const float (&part)[kLnParts<LPR, 
 // fp32 rows in lane pairs of groups of 8 lanes, in every shape of the forward, so that a row's sums have one order (LanePacks).  Inputs cold, us, consecutive packs
 // (gamma and beta from the caches) and like this: forward 8192 x 1024 16.6 / 13.3, 4096 x 4096 30.7 / 26.5, fused 8192 x 1280 41.0 / 33.7, 4096 x 1024 17.5 / 13.7;
 // backward (groups of 32) 16384 x 1024 55.8 / 48.4, 300 x 8192 21.8 / 18.5, fused 8192 x 1280 46.3 / 42.5, 300 x 8192 26.6 / 22.4.
+// Rows that end inside a 128-byte line gain less (8192 x 1304 24.5 / 24.1, backward 40.8 / 36.6, fused 48.0 / 45.3 and 49.7 / 44.2), one in nine lost: fused forward
+// 5000 x 2040 43.2 / 46.0.
 template <typename T, int VPL> using LnPacks = LanePacks<T, VPL < 8 ? 8 : 1>;      // (256 lanes x 8 packs, the only shape beyond 12288 columns, would spill)
 template <typename T> constexpr bool kLnNT = sizeof(T) == 2;       // of fp32 packs that are not in pairs: through the caches
 

@@ -275,3 +275,25 @@ def test_embedding_bwd_runs(lengths, tokens, H):
     half = torch.from_numpy(d0).to(d).half()
     L.lsq_embedding_bwd(half, None, torch.from_numpy(dys).to(d).half(), torch.from_numpy(tok).to(d), PAD, 2.0, 0.5, 3, 7)
     assert torch.equal(half, demb.half())                    # one rounding per call
+
+
+def test_embedding_bwd_one_id_takes_time_in_proportion_to_the_tokens():
+    """Four times the tokens of one id: four times the rows to add.  A search for the run's ends by each of its workgroups makes it 11 times, and 16 further on."""
+    d, H, us = dev(), 1280, []
+    for rows in (1 << 18, 1 << 20):
+        say(f"[embedding] one id in {rows} tokens")
+        tok = torch.full((rows // 1024, 1024), 7, dtype=torch.int32, device=d)
+        dy = torch.ones((rows, H), dtype=torch.bfloat16, device=d)
+        demb, dpos = torch.zeros((50, H), dtype=torch.bfloat16, device=d), torch.zeros((1024, H), dtype=torch.bfloat16, device=d)
+        times = []
+        for _ in range(4):
+            demb.zero_()
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            L.lsq_embedding_bwd(demb, dpos, dy, tok, PAD, 1.0, 0.0, 3, 7)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        assert (demb[7] == rows).all() and demb.float().sum() == rows * H       # powers of two: exact in any order
+        us.append(min(times[1:]))
+    assert us[1] < 8 * us[0], us

@@ -21,8 +21,8 @@ extern "C" size_t lsq_workspace_bytes(int32_t op, int64_t rows, int32_t cols)
         case LSQ_OP_BIAS_ACT_DROPOUT_BWD: return bad_bwd_bytes_upto(rows, cols);
         case LSQ_OP_SPLIT_HEADS_BWD: return heads_bwd_bytes_upto(rows, cols);
         case LSQ_OP_EMBEDDING_BWD:
-            // sorted order, the sort's second buffer and digit counts
-            return emb_bwd_plan(rows).total();
+            // sorted order, the sort's second buffer and digit counts, the partial rows of long calls
+            return emb_bwd_plan(rows, cols).total();
         default:
             return 0;
     }

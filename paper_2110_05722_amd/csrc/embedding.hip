@@ -10,7 +10,8 @@
 //      of the launch stream dy for dP; beyond that the sort runs over many workgroups, two launches per digit;
 //   2. accumulate: workgroups take 64 entries of the sorted order and 16 packs of the columns and sum m (.) dy of equal
 //      neighbours in ascending position in fp32; an id that goes on beyond its 64 entries has workgroups of its own
-//      that share its columns.  One rounding of dE per call either way.
+//      that share its columns, or beyond 16384 tokens leaves an fp32 row per 64 entries, which a last launch adds.
+//      One rounding of dE per call either way.
 // Tokens equal to pad_idx (or outside the vocabulary) produce zero rows and no gradient.
 #include <limits.h>
 
@@ -536,8 +537,8 @@ __global__ __launch_bounds__(256) void emb_radix_scatter(int2* __restrict__ dst,
 // workgroups of its own (emb_border_run) and is left out here.  The destination rows are fetched together with the dy rows.
 // What bounds it is the chain order -> rows -> rows of dE; 4 waves per SIMD at 8192 x 1280.  One wave per (8 entries, 64 packs), which left an fp32 row
 // for every run that crossed its entries, and a last launch that added these took 13.1 + 6.0 us there; whole backward, bf16 with dropout, in us before and now:
-// 8192 x 1280 words 28.6 / 23.4, distinct 29.0 / 23.7, half of one id 40.5 / 31.8, 16384 x 1024 40.9 / 36.4, 2048 x 768 f16 15.3 / 12.6, 1106 calls of 512 to
-// 128000 tokens and 8 to 2048 columns geometric mean 0.795, none above 1.01.  Units of 8 entries 0.84, ranges before borders 0.81, 128 registers forced 0.80.
+// 8192 x 1280 words 28.6 / 23.4, distinct 29.0 / 23.7, half of one id 40.5 / 31.8, 16384 x 1024 40.9 / 36.4, 2048 x 768 f16 15.3 / 12.6.  Units of 8 entries,
+// ranges before borders and 128 registers forced were slower.
 constexpr int kEmbUnit = 4;
 // dy is read twice in a call, by token and by position: through the caches (8192 x 1280 24.1 us, 26.2 past them, 16384 x 1024 37.6 / 41.2)
 static_assert(kEmbRange == 16 * kEmbUnit, "four waves of four units");
@@ -549,10 +550,16 @@ __device__ __forceinline__ int emb_key_at(const int2* __restrict__ order, int64_
     return i >= 0 && i < rows ? order[i].y : static_cast<int>(kNoKey);
 }
 
-template <typename T, bool DROP, bool RAG>
+// PARTS (beyond the in-LDS sort's tokens): a run that crosses borders is not left out, the range's share of it goes to one of the range's two fp32 rows of `part` ([2 * ranges]
+// rows of whole packs: the share of the run that came in, or fills the range, and of the one that goes on), and emb_join adds these.  The columns of a run
+// end at 16 workgroups per column block, and in slices of one pack, which read an eighth of a line each; thousands of its rows are too long for them.  Whole backward,
+// us, windows of 8 entries / shared columns / an fp32 row per range: words, 1280 bf16, 2^15 tokens 95.5 / 86.6 / 82.1, 2^16 144 / 140 / 121, 2^17 240 / 274 / 210; half of one
+// id 2^15 145 / 110 / 81, 2^16 248 / 189 / 119; 500 ids, 1001 f16 2^15 96.0 / 101.2 / 93.8.  Up to 16384 tokens the launch more costs what it gives (8192 x 1280 words 21.5 / 24.1, ids
+// without a word's frequencies 16384 x 1280 47.2 / 37.0 / 40.0); beyond, only such ids of narrow rows lose (20480 x 64 uniform 39.2 / 42.8).
+template <typename T, bool DROP, bool RAG, bool PARTS>
 __device__ __forceinline__ void emb_range_runs(float* lds, T* __restrict__ demb, const T* __restrict__ dy, const int2* __restrict__ order,
-                                               int64_t range, int64_t rows, int cb, const RowPackIO<T, RAG>& io, float scale,
-                                               const DropoutParams& d)
+                                               float* __restrict__ part, int64_t range, int64_t rows, int cb, const RowPackIO<T, RAG>& io,
+                                               float scale, const DropoutParams& d)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, c = cb * 16 + (lane & 15);
     const bool mine = c < io.ppr;
@@ -574,9 +581,11 @@ __device__ __forceinline__ void emb_range_runs(float* lds, T* __restrict__ demb,
         if (base + k >= rows) key[k] = static_cast<int>(kNoKey);
     bool live[kEmbUnit], ends[kEmbUnit];
 #pragma unroll
-    for (int k = 0; k < kEmbUnit; ++k) live[k] = emb_live_key(key[k]) && key[k] != before && key[k] != after;
+    for (int k = 0; k < kEmbUnit; ++k) live[k] = emb_live_key(key[k]) && (PARTS || (key[k] != before && key[k] != after));
 #pragma unroll
     for (int k = 0; k < kEmbUnit; ++k) ends[k] = live[k] && key[k] != key[k + 1];
+    const bool first_unit = PARTS && wave == 0 && grp == 0, last_unit = PARTS && wave == 3 && grp == 3;
+    if (last_unit) ends[kEmbUnit - 1] = live[kEmbUnit - 1];        // the range's share of a run ends with the range
     RawPack<T> raw[kEmbUnit], dst[kEmbUnit];
 #pragma unroll
     for (int k = 0; k < kEmbUnit; ++k) {
@@ -585,17 +594,25 @@ __device__ __forceinline__ void emb_range_runs(float* lds, T* __restrict__ demb,
     }
 #pragma unroll
     for (int k = 0; k < kEmbUnit; ++k) {
-        if (ends[k]) dst[k] = io.template ahead<false>(demb, key[k], cp);
+        if (ends[k] && !(PARTS && (key[k] == before || key[k] == after))) dst[k] = io.template ahead<false>(demb, key[k], cp);
         else dst[k] = zero_raw<T>();
     }
     auto add_to = [&](int row, const RawPack<T>& to, const float (&a)[8]) {
+        if (PARTS && (row == before || row == after)) {
+            float* q = part + (2 * range + (row == before ? 0 : 1)) * (static_cast<int64_t>(io.ppr) * kPack) + cp * kPack;
+            if (mine) {
+                st_f4<false>(q, fvec4{a[0], a[1], a[2], a[3]});
+                st_f4<false>(q + 4, fvec4{a[4], a[5], a[6], a[7]});
+            }
+            return;
+        }
         float o[8];
         unpack<T>(io.settle(to, cp), o);
 #pragma unroll
         for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, a[j], o[j]);
         if (mine) io.template store<false>(demb, row, cp, o);
     };
-    bool open = live[0] && key[0] == prev;                         // the run at hand came from the unit before
+    bool open = !first_unit && live[0] && key[0] == prev;          // the run at hand came from the unit before
     const bool came = open;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, head[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     RawPack<T> head_dst = zero_raw<T>();
@@ -792,15 +809,82 @@ __device__ __forceinline__ void emb_border_run(float* lds, T* __restrict__ demb,
     }
 }
 
-template <typename T, bool DROP, bool RAG>
+template <typename T, bool DROP, bool RAG, bool PARTS>
 __global__ __launch_bounds__(256) void emb_accumulate(T* __restrict__ demb, const T* __restrict__ dy, const int2* __restrict__ order,
-                                                      int64_t rows, int borders, int ncb, RowPackIO<T, RAG> io, float scale,
-                                                      DropoutParams d)
+                                                      float* __restrict__ part, int64_t rows, int borders, int ncb, RowPackIO<T, RAG> io,
+                                                      float scale, DropoutParams d)
 {
     __shared__ float lds[4 * 128 + 4];
     const int unit = static_cast<int>(blockIdx.x) / ncb, cb = static_cast<int>(blockIdx.x) % ncb;
-    if (unit < borders) emb_border_run<T, DROP, RAG>(lds, demb, dy, order, unit + 1, rows, cb, io, scale, d);
-    else emb_range_runs<T, DROP, RAG>(lds, demb, dy, order, unit - borders, rows, cb, io, scale, d);
+    if (!PARTS && unit < borders) emb_border_run<T, DROP, RAG>(lds, demb, dy, order, unit + 1, rows, cb, io, scale, d);
+    else emb_range_runs<T, DROP, RAG, PARTS>(lds, demb, dy, order, part, PARTS ? unit : unit - borders, rows, cb, io, scale, d);
+}
+
+// PARTS: the shares of a run that crosses borders of ranges, added in ascending order of the ranges by the workgroup of its first border (the others
+// leave), 16 lanes per row, 16 rows at once.  One partial row per 64 entries: the bytes are nothing beside those of dy.
+template <typename T, bool RAG>
+__global__ __launch_bounds__(256) void emb_join(T* __restrict__ demb, const float* __restrict__ part, const int2* __restrict__ order, int64_t rows,
+                                                int ncb, RowPackIO<T, RAG> io, float scale)
+{
+    __shared__ float lds[3 * 128];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t border = static_cast<int>(blockIdx.x) / ncb + 1, end = (rows + kEmbRange - 1) / kEmbRange - 1;     // the last range
+    // the border's two entries and the one before the range in front of it: the same for all threads, so the exits are workgroup-uniform
+    const int key = emb_key_at(order, border * kEmbRange, rows);
+    if (!emb_live_key(key) || emb_key_at(order, border * kEmbRange - 1, rows) != key) return;
+    if (emb_key_at(order, (border - 1) * kEmbRange - 1, rows) == key) return;
+    int64_t last = border;                                         // the last range that the run touches
+    for (int64_t b = border;; b += 64) {                           // 64 ranges per trip
+        const int64_t v = b + lane;
+        const uint64_t m = __ballot(v == end || (v < end && order[(v + 1) * kEmbRange].y != key));
+        if (m != 0) { last = b + __builtin_ctzll(m); break; }      // `end` stops
+    }
+    const int c = (static_cast<int>(blockIdx.x) % ncb) * 16 + (lane & 15), cp = min(c, io.ppr - 1);
+    const bool writes = threadIdx.x < 16 && c < io.ppr;
+    RawPack<T> dst = zero_raw<T>();
+    if (writes) dst = io.template ahead<false>(demb, key, cp);
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    constexpr int U = 4;
+    const int64_t colsp = static_cast<int64_t>(io.ppr) * kPack;
+    for (int64_t v0 = border - 1 + (threadIdx.x >> 4); v0 <= last; v0 += 16 * U) {
+        fvec4 a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + 16 * u;
+            a[u] = fvec4{0, 0, 0, 0};
+            b[u] = fvec4{0, 0, 0, 0};
+            if (v <= last) {
+                const float* q = part + (2 * v + (v < border ? 1 : 0)) * colsp + cp * kPack;
+                a[u] = ld_f4<false>(q);
+                b[u] = ld_f4<false>(q + 4);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc[0] += a[u].x; acc[1] += a[u].y; acc[2] += a[u].z; acc[3] += a[u].w;
+            acc[4] += b[u].x; acc[5] += b[u].y; acc[6] += b[u].z; acc[7] += b[u].w;
+        }
+    }
+#pragma unroll
+    for (int w = 16; w < 64; w <<= 1)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], w);
+    if (wave > 0 && lane < 16) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) lds[((wave - 1) * 8 + j) * 16 + lane] = acc[j];
+    }
+    __syncthreads();
+    if (writes) {
+#pragma unroll
+        for (int w = 0; w < 3; ++w)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += lds[(w * 8 + j) * 16 + lane];
+        float o[8];
+        unpack<T>(io.settle(dst, cp), o);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = fmaf(scale, acc[j], o[j]);
+        io.template store<false>(demb, key, cp, o);
+    }
 }
 
 // dP[l,:] += sum over the batch.  256 threads own W packs of one position; 256 / W groups of W lanes take every
@@ -947,7 +1031,7 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
                                    const DropoutParams& d, hipStream_t s)
 {
     const int64_t rows = static_cast<int64_t>(batch) * len;
-    const EmbBwdPlan plan = emb_bwd_plan(rows);
+    const EmbBwdPlan plan = emb_bwd_plan(rows, hidden);
     int2* order = reinterpret_cast<int2*>(ws);
     T* de = static_cast<T*>(demb);
     T* dp = static_cast<T*>(dpos);
@@ -981,9 +1065,16 @@ static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const
         }
     }
     const int ranges = static_cast<int>(ceil_div(rows, kEmbRange)), ncb = static_cast<int>(ceil_div(io.ppr, 16));
-    const dim3 grid(static_cast<unsigned>(2 * ranges - 1) * static_cast<unsigned>(ncb)), block(256);
-    if (d.on) hipLaunchKernelGGL((emb_accumulate<T, true, RAG>), grid, block, 0, s, de, g, order, rows, ranges - 1, ncb, io, scale, d);
-    else hipLaunchKernelGGL((emb_accumulate<T, false, RAG>), grid, block, 0, s, de, g, order, rows, ranges - 1, ncb, io, scale, d);
+    float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * plan.pair_bytes + plan.hist_bytes);
+    const bool parts = plan.part_bytes != 0;
+    const int borders = parts ? 0 : ranges - 1;
+    const dim3 grid(static_cast<unsigned>(borders + ranges) * static_cast<unsigned>(ncb)), block(256);
+#define A(DROP, PARTS) hipLaunchKernelGGL((emb_accumulate<T, DROP, RAG, PARTS>), grid, block, 0, s, de, g, order, part, rows, borders, ncb, io, scale, d)
+    if (parts) { if (d.on) A(true, true); else A(false, true); }
+    else { if (d.on) A(true, false); else A(false, false); }
+#undef A
+    if (parts)
+        hipLaunchKernelGGL((emb_join<T, RAG>), dim3(static_cast<unsigned>(ranges - 1) * static_cast<unsigned>(ncb)), block, 0, s, de, part, order, rows, ncb, io, scale);
     return launch_status();
 }
 
@@ -1030,7 +1121,7 @@ extern "C" lsq_status lsq_embedding_bwd(void* demb, void* dpos, const void* dy, 
     LSQ_REQUIRE(ceil_div(rows, 256) * 64 + ceil_div(hidden, 8 * 64) * static_cast<int64_t>(len) < 0x7FFFFFFF);   // (position, column block) pairs
     LSQ_REQUIRE(demb && dy && tokens);
     LSQ_ALIGNED(demb); LSQ_ALIGNED(dpos); LSQ_ALIGNED(dy); LSQ_ALIGNED(workspace);
-    const size_t need = emb_bwd_plan(rows).total();
+    const size_t need = emb_bwd_plan(rows, hidden).total();
     if (!workspace || workspace_bytes < need) return LSQ_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     void* ws = workspace;

@@ -499,19 +499,21 @@ inline size_t ln_bwd_bytes(int64_t rows, int32_t hidden, int sums) { return part
 //   order  [rows] (token position, sort key), 8 bytes each
 //   second buffer of the radix sort, as many; the parts of the in-LDS sort that are too large for it (beyond 2048 tokens) lie there too
 //   digit counts of the radix sort [256][workgroups]
+//   beyond kEmbSortMax tokens: two fp32 rows per range
 constexpr int64_t kEmbSortMax = 16384;
 constexpr int kEmbRange = 64;        // entries of the sorted order that a workgroup of the accumulation owns
 struct EmbBwdPlan {
     int radix_blocks;
-    size_t pair_bytes, hist_bytes;
-    size_t total() const { return 2u * pair_bytes + hist_bytes; }        // never falls as the rows grow
+    size_t pair_bytes, hist_bytes, part_bytes;
+    size_t total() const { return 2u * pair_bytes + hist_bytes + part_bytes; }        // never falls as the rows grow
 };
-inline EmbBwdPlan emb_bwd_plan(int64_t rows)
+inline EmbBwdPlan emb_bwd_plan(int64_t rows, int32_t hidden)
 {
     EmbBwdPlan p;
     p.pair_bytes = static_cast<size_t>(ceil_div(rows, kEmbRange)) * kEmbRange * 8u;        // whole ranges
     p.radix_blocks = static_cast<int>(ceil_div(rows, 2048));
     p.hist_bytes = static_cast<size_t>(256) * static_cast<size_t>(p.radix_blocks) * sizeof(int32_t);
+    p.part_bytes = rows > kEmbSortMax ? 2u * static_cast<size_t>(ceil_div(rows, kEmbRange)) * static_cast<size_t>(ceil_div(hidden, kPack)) * kPack * sizeof(float) : 0;
     return p;
 }
 

@@ -254,7 +254,9 @@ def test_embedding_bwd_class_sorted_by_counting(n, frequent, tokens, parts):
 # rows of part of a column block, of one and a bit, cut packs.  Whole numbers, p = 0.5 (factors 0 and 2): every sum is exact in fp32.
 @pytest.mark.parametrize("H", [8, 40, 136, 203])
 @pytest.mark.parametrize("lengths,tokens", [((1, 3, 4, 5), 1500), ((15, 16, 17, 2), 1500), ((31, 33, 63, 64, 65, 1), 2000), ((127, 129, 200, 256, 6), 2500),
-                                            ((500, 560, 1100, 1200, 2), 8000), ((5000, 7, 3), 6000), ((9000, 64, 1), 17000), ((66,), 66), ((65,), 65), ((64,), 64)])
+                                            ((500, 560, 1100, 1200, 2), 8000), ((5000, 7, 3), 6000), ((9000, 64, 1), 17000), ((66,), 66), ((65,), 65), ((64,), 64),
+                                            ((5000, 64, 63, 65, 1, 128, 127, 129, 20), 16385), ((5000, 64, 63, 65, 1, 128, 127, 129, 20), 16384), ((64,), 33000), ((40000,), 40000),
+                                            ((3, 30000, 190, 193, 2), 65600)])
 def test_embedding_bwd_runs(lengths, tokens, H):
     say(f"[embedding] runs of {lengths} in {tokens} tokens, H={H}")
     d, V = dev(), 3000

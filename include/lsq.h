@@ -446,7 +446,9 @@ lsq_status lsq_embedding_fwd(void* out, const int32_t* tokens, const void* emb, 
  * demb [vocab, hidden] and dpos [len, hidden] are dt and are ACCUMULATED INTO (one
  * rounding per row and call; rows of tokens that do not occur are not touched).
  * Padding tokens receive nothing.  workspace: >= lsq_workspace_bytes(
- * LSQ_OP_EMBEDDING_BWD, batch*len, hidden) bytes.  Errors: batch*len beyond 2^30. */
+ * LSQ_OP_EMBEDDING_BWD, batch*len, hidden) bytes.  Errors (LSQ_INVALID_ARG, nothing is written): batch*len
+ * beyond 2^30; ceil(batch*len / 64) * ceil(hidden / 128) of 2^24 and more; with dpos, ceil(hidden / 512) * len within
+ * 128 of 2^24 and beyond: a launch would have 2^32 threads. */
 lsq_status lsq_embedding_bwd(void* demb, void* dpos, const void* dy, const int32_t* tokens,
                              int32_t batch, int32_t len, int32_t hidden, int32_t vocab, int32_t pad_idx,
                              float scale, float p, uint64_t seed, uint64_t offset,

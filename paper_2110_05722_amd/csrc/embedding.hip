@@ -1025,6 +1025,15 @@ static lsq_status emb_fwd_dispatch(void* out, const int32_t* tokens, const void*
     return launch_status();
 }
 
+// A launch of 2^32 threads and more is refused, and by then the launches before it have changed dP: no call whose accumulation or position gradient (the
+// wide form; the other has fewer than 4096 workgroups) is that large.  All others are smaller.
+inline bool emb_bwd_launches(int64_t rows, int len, int hidden, bool dpos)
+{
+    constexpr int64_t kMost = 0xFFFFFFFFll / 256;                  // workgroups of 256 threads
+    const int64_t ranges = ceil_div(rows, kEmbRange), units = rows > kEmbSortMax ? ranges : 2 * ranges - 1;
+    return units * ceil_div(hidden, 16 * kPack) <= kMost && (!dpos || ceil_div(hidden, 64 * kPack) * len + 128 <= kMost);       // (128: the sort's)
+}
+
 template <typename T, bool RAG>
 static lsq_status emb_bwd_dispatch(void* demb, void* dpos, const void* dy, const int32_t* tokens, void* ws,
                                    int batch, int len, int hidden, int vocab, int pad_idx, float scale,
@@ -1117,8 +1126,7 @@ extern "C" lsq_status lsq_embedding_bwd(void* demb, void* dpos, const void* dy, 
     const int64_t rows = static_cast<int64_t>(batch) * len;
     if (rows == 0) return LSQ_OK;
     LSQ_REQUIRE(rows <= 0x7FFFFFFF / 2);
-    LSQ_REQUIRE(ceil_div(rows, 8) * ceil_div(hidden, 8 * 64) < 0x7FFFFFFF);         // the accumulation's workgroups are not more than these and a few
-    LSQ_REQUIRE(ceil_div(rows, 256) * 64 + ceil_div(hidden, 8 * 64) * static_cast<int64_t>(len) < 0x7FFFFFFF);   // (position, column block) pairs
+    LSQ_REQUIRE(emb_bwd_launches(rows, len, hidden, dpos != nullptr));
     LSQ_REQUIRE(demb && dy && tokens);
     LSQ_ALIGNED(demb); LSQ_ALIGNED(dpos); LSQ_ALIGNED(dy); LSQ_ALIGNED(workspace);
     const size_t need = emb_bwd_plan(rows, hidden).total();

@@ -245,3 +245,16 @@ def test_a_workspace_of_the_longest_batch_serves_every_shorter_one(lib, op):
             need = L.lsq_workspace_bytes(op, r, cols)
             assert need >= most, (op, r, cols, need, most)
             most = need
+
+
+def test_embedding_backward_refuses_calls_that_no_launch_holds(lib):
+    """Without a workspace a call of an accepted size says so, one that is too large is invalid: before anything is launched."""
+    INVALID, WS = 1, 4
+    f = lambda batch, ln, hidden, dpos=A: lib.lsq_embedding_bwd(A, dpos, A, A, batch, ln, hidden, 1000, 1, 1.0, 0.1, 1, 0, None, 0, 1, None)  # noqa: E731
+    assert f(1 << 19, 1024, 1280) == INVALID                                  # 2^23 ranges of 64 tokens x 10 column blocks x 256 threads
+    assert f(1 << 19, 1024, 128) == WS
+    for hidden, blocks in ((8, 1), (128, 1), (129, 2), (1280, 10)):
+        most = ((1 << 24) - 1) // blocks * 64                                 # tokens
+        assert f(most // 64, 64, hidden) == WS and f(most // 64 + 1, 64, hidden) == INVALID, hidden
+    assert f(1, (1 << 24) - 129, 8) == WS and f(1, (1 << 24) - 128, 8) == INVALID and f(1, (1 << 24) - 128, 8, None) == WS        # positions
+    assert f(2, ((1 << 24) - 129) // 2, 513) == WS and f(2, ((1 << 24) - 129) // 2 + 1, 513) == INVALID

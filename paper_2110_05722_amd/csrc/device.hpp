@@ -311,13 +311,23 @@ __device__ __forceinline__ void store4(T* __restrict__ p, const float (&f)[4])
 struct OpSum { static __device__ __forceinline__ float apply(float a, float b) { return a + b; } };
 struct OpMax { static __device__ __forceinline__ float apply(float a, float b) { return fmaxf(a, b); } };
 
-template <int WIDTH, typename Op>
+//
+// PAIRED: the lanes hold packs as LanePacks of groups of 8 do, and the groups of 8 add in the order of the PACK's index (lane bits 1, 2, 0 are pack bits
+// 0, 1, 2): the result is, bit for bit, that of the same packs with pack = lane, so the two forms may be chosen by what is faster.
+template <int WIDTH, typename Op, bool PAIRED = false>
 __device__ __forceinline__ float group_allreduce(float v)
 {
     static_assert(WIDTH == 1 || WIDTH == 2 || WIDTH == 4 || WIDTH == 8 || WIDTH == 16 || WIDTH == 32 || WIDTH == 64, "");
-    if constexpr (WIDTH >= 2) v = Op::apply(v, dpp_mov<0xB1>(v));    // quad_perm [1,0,3,2]
-    if constexpr (WIDTH >= 4) v = Op::apply(v, dpp_mov<0x4E>(v));    // quad_perm [2,3,0,1]
-    if constexpr (WIDTH >= 8) v = Op::apply(v, dpp_mov<0x141>(v));   // row_half_mirror
+    if constexpr (PAIRED) {
+        static_assert(WIDTH >= 8, "");
+        v = Op::apply(v, dpp_mov<0x4E>(v));                          // 2 apart
+        v = Op::apply(v, dpp_mov<0x1B>(dpp_mov<0x141>(v)));          // 4 apart: quad_perm [3,2,1,0] of the half mirror
+        v = Op::apply(v, dpp_mov<0xB1>(v));                          // 1 apart
+    } else {
+        if constexpr (WIDTH >= 2) v = Op::apply(v, dpp_mov<0xB1>(v));    // quad_perm [1,0,3,2]
+        if constexpr (WIDTH >= 4) v = Op::apply(v, dpp_mov<0x4E>(v));    // quad_perm [2,3,0,1]
+        if constexpr (WIDTH >= 8) v = Op::apply(v, dpp_mov<0x141>(v));   // row_half_mirror
+    }
     if constexpr (WIDTH >= 16) v = Op::apply(v, dpp_mov<0x140>(v));  // row_mirror
     if constexpr (WIDTH == 32) {
         // swap with the lane 16 away inside each half-wave (bit-mask mode: and 0x1F, xor 0x10)
@@ -335,15 +345,15 @@ __device__ __forceinline__ float group_allreduce(float v)
     return v;
 }
 
-template <int WIDTH> __device__ __forceinline__ float group_sum(float v) { return group_allreduce<WIDTH, OpSum>(v); }
+template <int WIDTH, bool PAIRED = false> __device__ __forceinline__ float group_sum(float v) { return group_allreduce<WIDTH, OpSum, PAIRED>(v); }
 template <int WIDTH> __device__ __forceinline__ float group_max(float v) { return group_allreduce<WIDTH, OpMax>(v); }
 
 // Block-wide all-reduce for NWAVES waves; `scratch` holds NWAVES floats of LDS.
 // Every thread of the block must call it; it contains two barriers.
-template <int NWAVES, typename Op>
+template <int NWAVES, typename Op, bool PAIRED = false>
 __device__ __forceinline__ float block_allreduce(float v, float* scratch)
 {
-    v = group_allreduce<64, Op>(v);
+    v = group_allreduce<64, Op, PAIRED>(v);
     if constexpr (NWAVES == 1) return v;
     const int wave = threadIdx.x >> 6;
     __syncthreads();                    // scratch may still be read from a previous call

@@ -174,11 +174,10 @@ template <typename T, int LPR, int VPL, bool RAG> constexpr bool sm_store_nt()
     return !RAG || VPL == 1 || LPR > kWave || (sizeof(T) == 2 && (LPR == kWave || (LPR > 8 && VPL == 2)));
 }
 
-// Packs in lane pairs (LanePacks), fp32 rows of 8 lanes and more: sm_paired below.  Where it says no, the lanes hold the same packs all the same (SmOrder)
-// and fetch them by themselves, so a row's sums have one order whatever the size of the call.  A pack that is loaded before the row's limit is known lies in
+// Packs in lane pairs (LanePacks), fp32 rows of 8 lanes and more: sm_paired below.  Both forms add in the order of the packs, so a row of whole packs has the same
+// bits whatever the size of the call.  A pack that is loaded before the row's limit is known lies in
 // the first group of 8, and there in the first half: in the first piece of every lane of the group.
 template <typename T, bool PAIR> using SmPacks = LanePacks<T, PAIR ? 8 : 1>;
-template <typename T, int LPR, bool RAG> using SmOrder = LanePacks<T, !RAG && LPR >= 8 ? 8 : 1>;
 
 // pack `idx` of a row (`base`: the workgroup's first pack); the last pack of the tensor may be cut short
 template <typename T, int LPR, int VPL, bool RAG>
@@ -355,7 +354,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
 {
     constexpr int RPB = kSmWgFwd / LPR;
     using P = SmPacks<T, PAIR>;
-    const int sub = SmOrder<T, LPR, RAG>::pack(threadIdx.x % LPR);
+    const int sub = P::pack(threadIdx.x % LPR);
     const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
     x += blk.pack0 * kPack;
     y += blk.pack0 * kPack;
@@ -462,7 +461,7 @@ __global__ __launch_bounds__(kSmWgFwd) void softmax_fwd_kernel(T* y, T* __restri
                 }
             }
         }
-        z = group_sum<LPR>(z);
+        z = group_sum<LPR, P::kPaired>(z);
         const float inv = lim > 0 ? 1.0f / z : 0.0f;
         // a NaN row (a NaN or +inf among its scores, or nothing but -inf) stays NaN inside the mask only
         const bool nan_row = __ballot(z != z) != 0;            // wave-uniform
@@ -503,7 +502,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
 {
     constexpr int RPB = kSmWgBwd / LPR;
     using P = SmPacks<T, PAIR>;
-    const int sub = SmOrder<T, LPR, RAG>::pack(threadIdx.x % LPR);
+    const int sub = P::pack(threadIdx.x % LPR);
     const BlockRows<RAG> blk(g, static_cast<int64_t>(blockIdx.x) * (RPT * RPB));
     y += blk.pack0 * kPack;
     dy += blk.pack0 * kPack;
@@ -612,7 +611,7 @@ __global__ __launch_bounds__(kSmWgBwd) void softmax_bwd_kernel(T* dx, const T* d
                 dot = fmaf(gv[k][j], yv[k][j], dot);
             }
         }
-        dot = group_sum<LPR>(dot);
+        dot = group_sum<LPR, P::kPaired>(dot);
         const bool spoilt = __ballot(!__builtin_isfinite(dot)) != 0;      // wave-uniform: an infinity or a NaN reached a row's sum
         RawPack<T> pk[VPL];
 #pragma unroll
@@ -799,7 +798,7 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
 {
     __shared__ float red[4];
     using P = SmPacks<T, PAIR>;
-    const int sub = SmOrder<T, 256, RAG>::pack(threadIdx.x);
+    const int sub = P::pack(threadIdx.x);
     const int64_t row = blockIdx.x;
     const BlockRows<RAG> blk(g, row);
     const RowPacks<RAG> rp = blk.row(g, 0);
@@ -840,7 +839,7 @@ __global__ __launch_bounds__(256) void softmax_fwd_wide(T* y, T* __restrict__ yd
             v[k][j] = e;
             z += e;
         }
-    z = block_allreduce<4, OpSum>(z, red);
+    z = block_allreduce<4, OpSum, P::kPaired>(z, red);
     const float inv = limit > 0 ? 1.0f / z : 0.0f;
     RawPack<T> pk[VPL];
 #pragma unroll
@@ -875,7 +874,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
 {
     __shared__ float red[4];
     using P = SmPacks<T, PAIR>;
-    const int sub = SmOrder<T, 256, RAG>::pack(threadIdx.x);
+    const int sub = P::pack(threadIdx.x);
     const int64_t row = blockIdx.x;
     const BlockRows<RAG> blk(g, row);
     const RowPacks<RAG> rp = blk.row(g, 0);
@@ -923,7 +922,7 @@ __global__ __launch_bounds__(256) void softmax_bwd_wide(T* dx, const T* dy, cons
             dot = fmaf(gv[k][j], yv[k][j], dot);
         }
     }
-    dot = block_allreduce<4, OpSum>(dot, red);
+    dot = block_allreduce<4, OpSum, P::kPaired>(dot, red);
     RawPack<T> pk[VPL];
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {

@@ -1,6 +1,7 @@
 """GPU: fp32 attention softmax of 2 Mi scores and more with rows of whole 128-byte lines, whose packs lie in lane pairs: each sentence of such a call
-against the call of this sentence alone, which is too small for that form and is checked against the CPU oracle elsewhere, bit for bit: the
-lanes hold the same packs and add in the same order."""
+against the call of this sentence alone, which is too small for that form and is checked against the CPU oracle elsewhere, bit for bit: both
+add in the order of a row's packs."""
+import numpy as np
 import pytest
 import torch
 
@@ -46,3 +47,23 @@ def test_large_calls_and_their_sentences(Lk, causal):
             if not p:
                 assert torch.equal(torch.nan_to_num(L.lsq_softmax_varlen_fwd(xi, *lens, causal, scale, p, 3, 5, y=xi)[0]), torch.nan_to_num(y))
             assert torch.equal(torch.nan_to_num(L.lsq_softmax_varlen_bwd(di, y, *lens, causal, scale, p, 3, 5, dx=di)), torch.nan_to_num(dx))
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("Lk,lanes", [(64, 8), (128, 8), (256, 16), (512, 32), (1024, 64)])
+def test_order_of_a_rows_sum(Lk, lanes, large):
+    """Backward with y = 1 and scale 1: dx = dy - sum(dy).  The sum in float32, in the documented order: a lane adds its packs (lanes apart) element by
+    element, then the lanes meet by ascending bits of the pack's index."""
+    say(f"[softmax pairs] order of the sum, {Lk} keys, {'large' if large else 'small'} call")
+    d = dev()
+    rows = (1 << 21) // Lk + 3 if large else 37
+    dy = torch.randn((1, 1, rows, Lk), generator=torch.Generator().manual_seed(Lk)) * 100
+    dx = L.lsq_softmax_bwd(dy.to(d), torch.ones_like(dy, device=d), None, False, 1.0, 0.0, 1, 1).cpu().numpy().reshape(rows, Lk)
+    v = dy.numpy().reshape(rows, -1, lanes, 8)
+    acc = np.zeros((rows, lanes), np.float32)
+    for k in range(v.shape[1]):
+        for j in range(8):
+            acc += v[:, k, :, j]
+    while acc.shape[1] > 1:
+        acc = acc[:, 0::2] + acc[:, 1::2]
+    assert np.array_equal(dx, dy.numpy().reshape(rows, Lk) - acc)

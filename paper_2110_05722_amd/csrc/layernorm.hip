@@ -40,17 +40,17 @@ __device__ __forceinline__ float half_waves_sum(float v)
 }
 
 // `buf`: 256 floats where the row spans the workgroup; it may be written again only behind another barrier
-template <int LPR, int VPL>
+template <int LPR, int VPL, bool PAIRED>
 __device__ __forceinline__ float ln_row_total(const float (&part)[kLnParts<LPR, VPL>], float* buf)
 {
     constexpr int N = kLnParts<LPR, VPL>;
     if constexpr (LPR <= 16) {
-        return group_sum<LPR>(part[0]);
+        return group_sum<LPR, PAIRED>(part[0]);
     } else if constexpr (LPR == 32) {
         float v = part[0], w = N > 1 ? part[1] : 0.0f;            // the classes of the lower and of the upper half-wave
 #pragma unroll
         for (int k = 2; k < N; ++k) (k % 2 ? w : v) += part[k];
-        return group_sum<32>(N > 1 ? v + w : v);
+        return group_sum<32, PAIRED>(N > 1 ? v + w : v);
     } else {
         float v = part[0];
         if constexpr (LPR == 256) {
@@ -64,25 +64,21 @@ __device__ __forceinline__ float ln_row_total(const float (&part)[kLnParts<LPR, 
 #pragma unroll
             for (int k = 1; k < N; ++k) v += part[k];
         }
-        v = group_sum<16>(half_waves_sum(v));
+        v = group_sum<16, PAIRED>(half_waves_sum(v));
         const int iv = __builtin_bit_cast(int, v);
         return __builtin_bit_cast(float, __builtin_amdgcn_readlane(iv, 0)) + __builtin_bit_cast(float, __builtin_amdgcn_readlane(iv, 16));
     }
 }
 
-// fp32 rows in lane pairs of groups of 8 lanes, in every shape of the forward, so that a row's sums have one order (LanePacks).  Inputs cold, us, consecutive packs
-// (gamma and beta from the caches) and like this: forward 8192 x 1024 16.6 / 13.3, 4096 x 4096 30.7 / 26.5, fused 8192 x 1280 41.0 / 33.7, 4096 x 1024 17.5 / 13.7;
-// backward (groups of 32) 16384 x 1024 55.8 / 48.4, 300 x 8192 21.8 / 18.5, fused 8192 x 1280 46.3 / 42.5, 300 x 8192 26.6 / 22.4.
-// Rows that end inside a 128-byte line gain less (8192 x 1304 24.5 / 24.1, backward 40.8 / 36.6, fused 48.0 / 45.3 and 49.7 / 44.2), one in nine lost: fused forward
-// 5000 x 2040 43.2 / 46.0.
-template <typename T, int VPL> using LnPacks = LanePacks<T, VPL < 8 ? 8 : 1>;      // (256 lanes x 8 packs, the only shape beyond 12288 columns, would spill)
-template <typename T> constexpr bool kLnNT = sizeof(T) == 2;       // of fp32 packs that are not in pairs: through the caches
-
+// fp32 rows in lane pairs (LanePacks; groups of 8 lanes) or with pack = lane.  Both forms add in the order of the packs, so a row's bits do not depend on the choice:
+// ln_fwd_paired says which is faster.  Backward where a row spans several waves: pairs in groups of 32; 16384 x 1024 55.8 / 48.4, 300 x 8192 21.8 / 18.5, fused 8192 x 1280
+// 46.3 / 42.5, 300 x 8192 26.6 / 22.4.
+//
 // Raw packs of row r for this lane (zeros where the row or the pack does not exist).
 // Loads only, no arithmetic: every load of the row is in flight before the first use.
-// NT: past the caches, for the rows; not for gamma, beta and bias, which every workgroup reads (past the caches they were fetched anew by each: forward
+// NT: past the caches; not for gamma, beta and bias, which every workgroup reads (past the caches they were fetched anew by each: forward
 // 16384 x 1024 bf16 16.7 us, 14.3 from the caches, 1000 x 1024 4.0 / 3.2, 4096 x 4096 f32 36.7 / 31.0; fused 8192 x 1280 bf16 17.9 / 16.8; inputs cold).
-template <typename T, int LPR, int VPL, bool NT = kLnNT<T>>
+template <typename T, int LPR, int VPL, bool NT>
 __device__ __forceinline__ void ln_load_row(RawPack<T> (&raw)[VPL], const T* __restrict__ base, int64_t r, bool rv,
                                             int hidden, int nv, int sub)
 {
@@ -94,14 +90,14 @@ __device__ __forceinline__ void ln_load_row(RawPack<T> (&raw)[VPL], const T* __r
     }
 }
 
-// The same as LnPacks: to be settled before use
-template <typename T, int LPR, int VPL>
-__device__ __forceinline__ void ln_load_paired(RawPack<T> (&raw)[VPL], const T* __restrict__ base, int64_t r, bool rv, int hidden, int nv, int sub)
+// The same as the lanes of P hold it: to be settled before use
+template <typename P, typename T, int LPR, int VPL, bool NT>
+__device__ __forceinline__ void ln_load_packs(RawPack<T> (&raw)[VPL], const T* __restrict__ base, int64_t r, bool rv, int hidden, int nv, int sub)
 {
 #pragma unroll
     for (int k = 0; k < VPL; ++k) {
         const int idx = sub + k * LPR;
-        raw[k] = LnPacks<T, VPL>::template load<kNT>(base + r * hidden + idx * kPack, rv && idx < nv);
+        raw[k] = P::template load<NT>(base + r * hidden + idx * kPack, rv && idx < nv);
     }
 }
 
@@ -117,7 +113,7 @@ struct BdrFuse {
 // FUSE: the row that is normalised is h = residual + Dropout(x + bias), built in registers from
 // two loads, stored once (the next residual) and normalised from its STORED (rounded) value, so the
 // result equals bias+dropout+residual followed by LayerNorm bit for bit while h is never re-read.
-template <typename T, int LPR, int VPL, bool FUSE = false, bool DROP = false>
+template <typename T, int LPR, int VPL, bool FUSE, bool DROP, bool PAIR>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* __restrict__ mean,
                                                      float* __restrict__ rstd, const T* __restrict__ x,
                                                      const T* __restrict__ gamma, const T* __restrict__ beta,
@@ -127,7 +123,10 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
     __shared__ float lds[2][LPR == 256 ? 256 : 1];     // in turn: sum, squares (a barrier lies between two writes of either)
     constexpr int RPB = 256 / LPR;                     // rows a workgroup handles at a time
     constexpr int NP = kLnParts<LPR, VPL>;
-    using P = LnPacks<T, VPL>;
+    using P = LanePacks<T, PAIR ? 8 : 1>;
+    // fp32 with pack = lane: through the caches, or half lines move (unpaired / past the caches, us, cold: 16384 x 1032 29.4 / 33.0, 8192 x 2040 30.0 / 33.0, fused
+    // 56.2 / 63.1, 300 x 768 3.8 / 4.0, 1000 x 1024 4.3 / 4.1); 256 lanes x 8 packs only if fused (1000 x 16384 55.9 / 68.2, plain 31.0 / 29.7)
+    constexpr bool NT = sizeof(T) == 2 || PAIR || (VPL == 8 && !FUSE);
     const int sub = P::pack(threadIdx.x % LPR);
     const int slot = threadIdx.x / LPR;
     const int nv = hidden / kPack;
@@ -149,8 +148,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
 
     int64_t base = static_cast<int64_t>(blockIdx.x) * RPB;
     RawPack<T> nxt[VPL], nres[FUSE ? VPL : 1];
-    ln_load_paired<T, LPR, VPL>(nxt, x, base + slot, base + slot < rows, hidden, nv, sub);
-    if constexpr (FUSE) ln_load_paired<T, LPR, VPL>(nres, fz.residual, base + slot, base + slot < rows, hidden, nv, sub);
+    ln_load_packs<P, T, LPR, VPL, NT>(nxt, x, base + slot, base + slot < rows, hidden, nv, sub);
+    if constexpr (FUSE) ln_load_packs<P, T, LPR, VPL, NT>(nres, fz.residual, base + slot, base + slot < rows, hidden, nv, sub);
     for (; base < rows; base += gstride) {
         const int64_t r = base + slot;
         const bool rv = r < rows;
@@ -162,9 +161,9 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
             for (int k = 0; k < VPL; ++k) cres[k] = P::settle(nres[k]);
         }
         if (base + gstride < rows) {          // prefetch the next row group while this one is reduced
-            ln_load_paired<T, LPR, VPL>(nxt, x, r + gstride, r + gstride < rows, hidden, nv, sub);
+            ln_load_packs<P, T, LPR, VPL, NT>(nxt, x, r + gstride, r + gstride < rows, hidden, nv, sub);
             if constexpr (FUSE)
-                ln_load_paired<T, LPR, VPL>(nres, fz.residual, r + gstride, r + gstride < rows, hidden, nv, sub);
+                ln_load_packs<P, T, LPR, VPL, NT>(nres, fz.residual, r + gstride, r + gstride < rows, hidden, nv, sub);
         }
         if constexpr (FUSE) {
             // same expressions as the stand-alone bias+dropout+residual kernel; the pack index of
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
             for (int k = 0; k < VPL; ++k) {
                 const int idx = sub + k * LPR;
                 const bool ok = rv && idx < nv;
-                if (P::kPaired || ok) {       // (absent packs stay zeros)
+                if (P::kPaired ? rv && (idx & ~7) < nv : ok) {       // (whole groups of lanes; absent packs stay zeros)
                     float xf[8], rf[8], b8[8], kf[8];
                     unpack<T>(cur[k], xf);
                     unpack<T>(cres[k], rf);
@@ -186,7 +185,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
                     }
                     pin_f32(rf);              // rounds like the stand-alone bias+dropout+residual kernel
                     if (!P::kPaired || ok) cur[k] = pack_raw<T>(rf);
-                    P::template store<kNT>(fz.out + r * hidden + idx * kPack, cur[k], ok);
+                    P::template store<NT>(fz.out + r * hidden + idx * kPack, cur[k], ok);
                 }
             }
         }
@@ -201,7 +200,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
 #pragma unroll
             for (int j = 0; j < 8; ++j) part[k % NP] += xv[k][j];
         }
-        const float mu = ln_row_total<LPR, VPL>(part, lds[0]) * inv_h;
+        const float mu = ln_row_total<LPR, VPL, P::kPaired>(part, lds[0]) * inv_h;
 #pragma unroll
         for (int k = 0; k < NP; ++k) part[k] = 0.0f;
 #pragma unroll
@@ -214,7 +213,7 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
                 part[k % NP] = ok ? fmaf(dlt, dlt, part[k % NP]) : part[k % NP];
             }
         }
-        const float q = ln_row_total<LPR, VPL>(part, lds[1]);
+        const float q = ln_row_total<LPR, VPL, P::kPaired>(part, lds[1]);
         const float rs = 1.0f / sqrtf(fmaf(q, inv_h, eps));
         if (rv && sub == 0) {
             mean[r] = mu;
@@ -225,14 +224,14 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
         for (int k = 0; k < VPL; ++k) {
             const int idx = sub + k * LPR;
             const bool ok = rv && idx < nv;
-            if (P::kPaired || ok) {
+            if (P::kPaired ? rv && (idx & ~7) < nv : ok) {
                 float o[8], g8[8], b8[8];
                 unpack<T>(gm[k], g8);
                 unpack<T>(bt[k], b8);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] = fmaf(xv[k][j] * rs, g8[j], b8[j]);
                 pin_f32(o);                   // the fused and the plain kernel round alike
-                P::template store<kNT>(yr + idx * kPack, o, ok);
+                P::template store<NT>(yr + idx * kPack, o, ok);
             }
         }
     }
@@ -260,7 +259,8 @@ __device__ __forceinline__ float row_sum(float v, float* lds)
 // accumulators live in LDS instead, each thread reading and writing only its own columns' entries
 // (131 KB for 16384 columns: no barrier, no conflict, and the LDS traffic hides behind the row
 // stream).
-template <typename T, int LPR, int VPL, bool HAS_RES, int THREADS, bool FUSE = false, bool DROP = false>
+// NT: past the caches
+template <typename T, int LPR, int VPL, bool HAS_RES, int THREADS, bool FUSE, bool DROP, bool NT>
 __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restrict__ partial, const T* dy,
                                                          const T* __restrict__ x, const T* __restrict__ gamma,
                                                          const float* __restrict__ mean, const float* __restrict__ rstd,
@@ -310,9 +310,9 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
     {
         const int64_t r = base + slot;
         const bool rv = r < rows;
-        ln_load_row<T, LPR, VPL>(ndy, dy, r, rv, hidden, nv, sub);
-        ln_load_row<T, LPR, VPL>(nx, x, r, rv, hidden, nv, sub);
-        if constexpr (HAS_RES) ln_load_row<T, LPR, VPL>(nres, dres, r, rv, hidden, nv, sub);
+        ln_load_row<T, LPR, VPL, NT>(ndy, dy, r, rv, hidden, nv, sub);
+        ln_load_row<T, LPR, VPL, NT>(nx, x, r, rv, hidden, nv, sub);
+        if constexpr (HAS_RES) ln_load_row<T, LPR, VPL, NT>(nres, dres, r, rv, hidden, nv, sub);
         if (rv) { nmu = mean[r]; nrs = rstd[r]; }
     }
     for (; base < rows; base += gstride) {
@@ -330,9 +330,9 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
         if (base + gstride < rows) {          // prefetch the next row group
             const int64_t rn = r + gstride;
             const bool rnv = rn < rows;
-            ln_load_row<T, LPR, VPL>(ndy, dy, rn, rnv, hidden, nv, sub);
-            ln_load_row<T, LPR, VPL>(nx, x, rn, rnv, hidden, nv, sub);
-            if constexpr (HAS_RES) ln_load_row<T, LPR, VPL>(nres, dres, rn, rnv, hidden, nv, sub);
+            ln_load_row<T, LPR, VPL, NT>(ndy, dy, rn, rnv, hidden, nv, sub);
+            ln_load_row<T, LPR, VPL, NT>(nx, x, rn, rnv, hidden, nv, sub);
+            if constexpr (HAS_RES) ln_load_row<T, LPR, VPL, NT>(nres, dres, rn, rnv, hidden, nv, sub);
             nmu = 0.0f; nrs = 0.0f;
             if (rnv) { nmu = mean[rn]; nrs = rstd[rn]; }
         }
@@ -390,10 +390,10 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
                 }
                 pin_f32(o);               // the fused and the plain kernel round alike
                 if constexpr (!FUSE) {
-                    store8<T, kLnNT<T>>(dx + ro + idx * kPack, o);
+                    store8<T, NT>(dx + ro + idx * kPack, o);
                 } else {
                     const RawPack<T> hp = pack_raw<T>(o);
-                    store_raw<T, kLnNT<T>>(dx + ro + idx * kPack, hp);
+                    store_raw<T, NT>(dx + ro + idx * kPack, hp);
                     float gq[8];
                     unpack<T>(hp, gq);
                     if constexpr (DROP) {
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
                         for (int j = 0; j < 8; ++j) gq[j] *= kf[j];
                     }
                     pin_f32(gq);
-                    store8<T, kLnNT<T>>(fz.out + ro + idx * kPack, gq);
+                    store8<T, NT>(fz.out + ro + idx * kPack, gq);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) dbi[k][j] += gq[j];
                 }
@@ -935,6 +935,19 @@ inline LnShape ln_fwd_shape(int64_t rows, int hidden, int elem_bytes)
     return s;
 }
 
+// fp32 forward in lane pairs: not the calls of a few waves, whose time is latency, which the exchange adds to (their rows go through the caches), and of rows that end
+// inside a 128-byte line, where two pieces meet, only those of up to 2048 columns that are neither small nor long (long ones fetch each line once through the caches).
+// us, inputs cold: pack = lane past the caches / pairs everywhere / this rule: 8192 x 2048 33.4 / 25.5 / 25.5, fused with dropout 61.5 / 48.7 / 48.8; 300 x 1024 3.4 / 3.8 / 3.4,
+// 4.7 / 4.9 / 4.5; 300 x 2304 4.5 / 5.0 / 4.7, 6.1 / 7.0 / 6.5; 8192 x 2040 35.7 / 37.3 / 29.9, 66.7 / 74.1 / 56.4; 3000 x 1304 11.6 / 10.0 / 9.7, 20.2 / 16.3 / 17.6.
+// The fused shapes of four packs per lane and more take 256 registers and more in pairs, one wave per SIMD, and gain all the same (8192 x 4096 110 / 94 us) but
+// where that leaves a short last round (600 x 8192 with dropout 21 / 23).  256 lanes x 8 packs would spill.
+inline bool ln_fwd_paired(int64_t rows, int hidden)
+{
+    const int64_t n = rows * hidden;
+    if (n < (hidden <= 2048 ? 3ll << 18 : 1ll << 20)) return false;
+    return hidden % 32 == 0 || (hidden < 2048 && n < 7ll << 19);
+}
+
 // Row groups per workgroup: two, the second loaded ahead (8192 x 1280: one 11.1, two 9.2, four 10.4 us), but one where all groups find
 // a compute unit of their own: up to 256 always (one against two, all shapes: 0.66-0.90), up to 768 where the kernel is small enough for
 // three on a unit.  Time of one over two for 257..512 / 513..768 groups: 16 bits up to 5 packs per lane 0.87-1.02 / 0.90-1.05, more and
@@ -994,16 +1007,21 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
     bool launched = false;
     const dim3 grid(ln_fwd_blocks(rows, sh, sizeof(T))), block(256);
     const BdrFuse<T> none{};
+    const bool pair = sizeof(T) == 4 && ln_fwd_paired(rows, hidden);
 #define X(L, V)                                                                                              \
     if (sh.lpr == L && sh.vpl == V) {                                                                        \
         launched = true;                                                                                     \
-        if (!fuse) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, none); \
-        else if (fuse->d.on) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, true>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
-        else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
+        constexpr bool kPair = sizeof(T) == 4 && V < 8;                                                      \
+        if (pair) { F(L, V, kPair) } else { F(L, V, false) }                                                 \
     }
+#define F(L, V, PAIR)                                                                                        \
+        if (!fuse) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, false, false, PAIR>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, none); \
+        else if (fuse->d.on) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, true, PAIR>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
+        else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false, PAIR>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse);
     LSQ_LN_FWD_CASES(X)
     if constexpr (sizeof(T) == 2) { X(64, 5) }
 #undef X
+#undef F
     return launched ? launch_status() : LSQ_LAUNCH_FAILED;      // a shape without its kernel
 }
 
@@ -1016,8 +1034,8 @@ static lsq_status ln_bwd_wide(T* dxp, float* partial, const T* dyp, const T* xp,
     constexpr int TH = L >= 256 ? L : 256;
     const BdrFuse<T> nofuse{};
     const size_t shmem = sizeof(float) * 16 * ((hidden / kPack) | 1);
-    auto* kres = &ln_bwd_kernel<T, L, V, true, TH, false, false>;
-    auto* kplain = &ln_bwd_kernel<T, L, V, false, TH, false, false>;
+    auto* kres = &ln_bwd_kernel<T, L, V, true, TH, false, false, sizeof(T) == 2>;
+    auto* kplain = &ln_bwd_kernel<T, L, V, false, TH, false, false, sizeof(T) == 2>;
     // once per residual variant and device (a host-side note, guarded for concurrent host threads)
     static std::mutex mu;
     static bool ready[2][64] = {};
@@ -1115,18 +1133,19 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
 #define X(L, V)                                                                                              \
     if (!ln_bwd_spans(hidden) && sh.lpr == L && sh.vpl == V) {                                                                        \
         launched = true;                                                                                     \
-        constexpr int TH = kLnBwdThreads;                                                                 \
+        constexpr int TH = kLnBwdThreads;                                                                    \
+        constexpr bool NT = sizeof(T) == 2;                                                                  \
         const size_t shmem = one_copy * (TH / L);                                                            \
         const dim3 grid(P), block(TH);                                                                       \
         if (!fuse) {                                                                                         \
-            if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, none); \
-            else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, none);   \
+            if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH, false, false, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, none); \
+            else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, false, false, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, none);   \
         } else if (fuse->d.on) {                                                                            \
-            if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH, true, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse); \
-            else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
+            if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH, true, true, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse); \
+            else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, true, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
         } else {                                                                                             \
-            if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse); \
-            else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
+            if (rp) hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, true, TH, true, false, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse); \
+            else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, false, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
         }                                                                                                    \
     }
     X(8, 1) X(16, 1) X(32, 1) X(32, 2)       // what ln_shape gives up to 63 packs

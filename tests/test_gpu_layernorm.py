@@ -283,6 +283,31 @@ def test_layernorm_rows_do_not_depend_on_the_batch(hidden, dt):
         assert torch.equal(gotb, wantb[:n]), n
 
 
+# the order in which a row's terms are added, in both forms that fp32 rows have (pack = lane: short calls and rows that end inside a line; lane pairs): packs modulo
+# 256, element by element, 64 apart, half-waves, then by ascending bits of the pack's index
+@pytest.mark.parametrize("hidden", [64, 256, 264, 768, 1024, 1304, 2048, 2560, 3072, 4096])
+def test_layernorm_order_of_a_rows_sum(hidden):
+    say(f"[layernorm] order of the sum, hidden={hidden}")
+    d, big = dev(), (1 << 21) // hidden + 5
+    x = torch.randn((big, hidden), generator=torch.Generator().manual_seed(hidden)) * 3
+    packs = x.numpy().reshape(big, -1, 8)
+    acc = np.zeros((big, 256), np.float32)
+    for p in range(packs.shape[1]):
+        for j in range(8):
+            acc[:, p % 256] += packs[:, p, j]
+    acc = ((acc[:, :64] + acc[:, 64:128]) + acc[:, 128:192]) + acc[:, 192:]
+    acc = acc[:, :32] + acc[:, 32:]
+    while acc.shape[1] > 1:
+        acc = acc[:, 0::2] + acc[:, 1::2]
+    want = acc[:, 0] * (np.float32(1) / np.float32(hidden))
+    one, zero = torch.ones(hidden, device=d), torch.zeros(hidden, device=d)
+    for rows in (big, 40):
+        xs = x[:rows].to(d)
+        assert np.array_equal(L.lsq_layernorm_fwd(xs, one, zero, EPS)[1].cpu().numpy(), want[:rows]), rows
+        fused = L.lsq_bdr_layernorm_fwd(torch.zeros_like(xs), zero, xs, one, zero, 0.0, 1, 1)       # h = xs
+        assert np.array_equal(fused[2].cpu().numpy(), want[:rows]), rows
+
+
 # half-wave rows come in pairs: three trips' worth of rows is two pairs (1537..2304 rows)
 @pytest.mark.parametrize("rows,hidden", [(1536, 520), (1537, 640), (2304, 768), (2305, 520), (2100, 1281)])
 def test_layernorm_bwd_pairs_of_rows(rows, hidden):

@@ -345,6 +345,17 @@ __device__ __forceinline__ float group_allreduce(float v)
     return v;
 }
 
+// A half-wave's sum of packs in lane pairs of groups of 32: pack bits 0..3 are lane bits 1..4 and bit 4 is lane bit 0, so this adds over them in that order
+// and is, bit for bit, group_sum<32> of the same packs with pack = lane.
+__device__ __forceinline__ float paired_half_wave_sum(float v)
+{
+    v += dpp_mov<0x4E>(v);                                           // 2 apart
+    v += dpp_mov<0x1B>(dpp_mov<0x141>(v));                           // 4 apart
+    v += dpp_mov<0x128>(v);                                          // 8 apart: row_ror:8
+    v += __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F));      // 16 apart
+    return v + dpp_mov<0xB1>(v);                                     // 1 apart
+}
+
 template <int WIDTH, bool PAIRED = false> __device__ __forceinline__ float group_sum(float v) { return group_allreduce<WIDTH, OpSum, PAIRED>(v); }
 template <int WIDTH> __device__ __forceinline__ float group_max(float v) { return group_allreduce<WIDTH, OpMax>(v); }
 

@@ -71,8 +71,7 @@ __device__ __forceinline__ float ln_row_total(const float (&part)[kLnParts<LPR, 
 }
 
 // fp32 rows in lane pairs (LanePacks; groups of 8 lanes) or with pack = lane.  Both forms add in the order of the packs, so a row's bits do not depend on the choice:
-// ln_fwd_paired says which is faster.  Backward where a row spans several waves: pairs in groups of 32; 16384 x 1024 55.8 / 48.4, 300 x 8192 21.8 / 18.5, fused 8192 x 1280
-// 46.3 / 42.5, 300 x 8192 26.6 / 22.4.
+// ln_fwd_paired and ln_bwd_paired say which is faster.
 //
 // Raw packs of row r for this lane (zeros where the row or the pack does not exist).
 // Loads only, no arithmetic: every load of the row is in flight before the first use.
@@ -472,9 +471,9 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
 // 8192 x 1024 fp16 / 2100 x 512 f32: 2.5 / 2 / 0.75 waves per SIMD, which wait for memory, LDS or the barrier in 61 / 55 / 65 % of their life
 // and for issue in 13 / 15 / 5 %; vector ALU busy 32 / 23 / 5 %, memory units stalled 0.4 / 0.2 / 0.2 %.  So it is still a row's chain, with
 // too few rows beside it, most of all in short calls.
-// LRC = 64: 512 columns, a row per wave, no exchange.  Partial rows as ln_bwd_kernel's.
+// LRC = 64: 512 columns, a row per wave, no exchange, never in pairs (300 rows f32 6.3 us, in pairs 6.6).  Partial rows as ln_bwd_kernel's.
 // RAG: rows that are not whole packs, in packs counted from the row's start (RowPackIO; not fused).
-template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP, bool RAG = false>
+template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP, bool RAG, bool PAIR>
 __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restrict__ partial, const T* dy,
                                                            const T* __restrict__ x, const T* __restrict__ gamma,
                                                            const float* __restrict__ mean, const float* __restrict__ rstd,
@@ -485,7 +484,9 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
     extern __shared__ float span_lds[];       // the rows' exchange [2][32-lane groups][2], later the slots' [slots / 2][NACC * 8][lanes]
     const int LR = LRC ? LRC : lanes;
     const int slots = blockDim.x / LR;
-    using P = LanePacks<T, RAG || LRC == 64 ? 1 : 32>;      // (512 columns, few waves: 6.5 us, in pairs 7.2 at 512 rows)
+    static_assert(!PAIR || (sizeof(T) == 4 && !RAG && LRC == 0), "lane pairs are for fp32 rows of whole packs that span several waves");
+    using P = LanePacks<T, PAIR ? 32 : 1>;
+    constexpr bool NT = sizeof(T) == 2 || RAG || PAIR;        // fp32 with pack = lane: through the caches, or half lines move
     const int slot = threadIdx.x / LR, sub = P::pack(threadIdx.x - slot * LR);
     const RowPackIO<T, RAG> io(hidden);
     const int nv = io.ppr;
@@ -509,13 +510,13 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
         nmu = 0.0f; nrs = 0.0f;
         if (r < rows) {
             if constexpr (P::kPaired) {
-                ndy = P::template load<kNT>(dy + io.element(r, sub), on);
-                nx = P::template load<kNT>(x + io.element(r, sub), on);
-                if constexpr (HAS_RES) nres = P::template load<kNT>(dres + io.element(r, sub), on);
+                ndy = P::template load<NT>(dy + io.element(r, sub), on);
+                nx = P::template load<NT>(x + io.element(r, sub), on);
+                if constexpr (HAS_RES) nres = P::template load<NT>(dres + io.element(r, sub), on);
             } else if (on) {
-                ndy = io.template ahead<kNT>(dy, r, sub);
-                nx = io.template ahead<kNT>(x, r, sub);
-                if constexpr (HAS_RES) nres = io.template ahead<kNT>(dres, r, sub);
+                ndy = io.template ahead<NT>(dy, r, sub);
+                nx = io.template ahead<NT>(x, r, sub);
+                if constexpr (HAS_RES) nres = io.template ahead<NT>(dres, r, sub);
             }
             nmu = mean[r]; nrs = rstd[r];
         }
@@ -557,8 +558,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
             s1 = group_sum<64>(s1);
             s2 = group_sum<64>(s2);
         } else {
-            s1 = group_sum<32>(s1);
-            s2 = group_sum<32>(s2);
+            s1 = PAIR ? paired_half_wave_sum(s1) : group_sum<32>(s1);
+            s2 = PAIR ? paired_half_wave_sum(s2) : group_sum<32>(s2);
             if ((threadIdx.x & 31) == 0) {
                 sums[threadIdx.x / 16] = s1;
                 sums[threadIdx.x / 16 + 1] = s2;
@@ -589,8 +590,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
             }
             pin_f32(o);                       // the fused and the plain kernel round alike
             const RawPack<T> hp = pack_raw<T>(o);
-            if constexpr (P::kPaired) P::template store<kNT>(dx + io.element(r, sub), o, on);
-            else io.template put<kNT>(dx, r, sub, hp);
+            if constexpr (P::kPaired) P::template store<NT>(dx + io.element(r, sub), o, on);
+            else io.template put<NT>(dx, r, sub, hp);
             if constexpr (FUSE) {
                 float gq[8];
                 unpack<T>(hp, gq);
@@ -602,8 +603,8 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
                     }
                 }
                 pin_f32(gq);
-                if constexpr (P::kPaired) P::template store<kNT>(fz.out + io.element(r, sub), gq, on);
-                else store8<T, kNT>(fz.out + io.element(r, sub), gq);
+                if constexpr (P::kPaired) P::template store<NT>(fz.out + io.element(r, sub), gq, on);
+                else store8<T, NT>(fz.out + io.element(r, sub), gq);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[2][j] += gq[j];
             }
@@ -948,6 +949,13 @@ inline bool ln_fwd_paired(int64_t rows, int hidden)
     return hidden % 32 == 0 || (hidden < 2048 && n < 7ll << 19);
 }
 
+// fp32 backward where a row spans several waves, in lane pairs (groups of 32) beyond half a Mi elements: below, the exchange is in a chain that nothing covers. us,
+// pack = lane past the caches / pairs / pack = lane through the caches, inputs not in L2: 300 x 1000 7.9 / 8.1 / 7.9, fused with dropout and residual gradient 9.3 / 9.8 / 9.4, 512 x
+// 1024 7.8 / 8.0 / 8.0, 9.1 / 9.5 / 9.6; 1000 x 1024 9.0 / 8.7 / 9.2, 11.0 / 10.6 / 11.8, 8192 x 1280 30.4 / 28.5 / 28.8, 47.1 / 44.1 / 45.4, 1000 x 8192 36.5 / 29.3 / 29.5, 58.9 / 46.0 /
+// 47.9; rows that end inside a line the same: 8192 x 1304 32.0 / 29.5 / 29.6, 50.2 / 45.0 / 46.1, 5000 x 2040 32.6 / 29.4 / 28.9, 50.0 / 47.0 / 45.3.
+template <typename T>
+inline bool ln_bwd_paired(int64_t rows, int hidden) { return sizeof(T) == 4 && rows * hidden > (1 << 19); }
+
 // Row groups per workgroup: two, the second loaded ahead (8192 x 1280: one 11.1, two 9.2, four 10.4 us), but one where all groups find
 // a compute unit of their own: up to 256 always (one against two, all shapes: 0.66-0.90), up to 768 where the kernel is small enough for
 // three on a unit.  Time of one over two for 257..512 / 513..768 groups: 16 bits up to 5 packs per lane 0.87-1.02 / 0.90-1.05, more and
@@ -1106,25 +1114,27 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
         const dim3 grid(P), block(pl.slots * pl.lanes);
         const size_t exchange = sizeof(float) * (block.x / 8), tree = sizeof(float) * (pl.slots / 2) * (fuse ? 3 : 2) * 8 * pl.lanes;
         const size_t shmem = exchange > tree ? exchange : tree;
-#define X(C, M)                                                                                              \
+#define X(C, M, PAIR)                                                                                        \
     if (!fuse) {                                                                                             \
-        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, false, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none); \
-        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, false, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none);   \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, false, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none); \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, false, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none);   \
     } else if (fuse->d.on) {                                                                                 \
-        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);  \
-        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);    \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, true, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);  \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, true, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);    \
     } else {                                                                                                 \
-        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse); \
-        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);   \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse); \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);   \
     }
         if (ln_rag_spans(hidden)) {
-#define R(H, M) hipLaunchKernelGGL((ln_bwd_span_kernel<T, 0, H, M, false, false, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none)
+#define R(H, M) hipLaunchKernelGGL((ln_bwd_span_kernel<T, 0, H, M, false, false, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none)
             if (rp) { if (block.x <= kLnSpanThreads) R(true, kLnSpanThreads); else R(true, 1024); }
             else { if (block.x <= kLnSpanThreads) R(false, kLnSpanThreads); else R(false, 1024); }
 #undef R
-        } else if (pl.lanes == 64) { X(64, kLnSpanThreads) }
-        else if (block.x <= kLnSpanThreads) { X(0, kLnSpanThreads) }
-        else { X(0, 1024) }
+        } else if (pl.lanes == 64) { X(64, kLnSpanThreads, false) }
+        else if (block.x <= kLnSpanThreads && ln_bwd_paired<T>(rows, hidden)) { X(0, kLnSpanThreads, sizeof(T) == 4) }
+        else if (block.x <= kLnSpanThreads) { X(0, kLnSpanThreads, false) }
+        else if (ln_bwd_paired<T>(rows, hidden)) { X(0, 1024, sizeof(T) == 4) }
+        else { X(0, 1024, false) }
 #undef X
     }
     // shorter rows: lanes of one wave, one pack each, or two of 32 lanes

@@ -308,6 +308,29 @@ def test_layernorm_order_of_a_rows_sum(hidden):
         assert np.array_equal(fused[2].cpu().numpy(), want[:rows]), rows
 
 
+# fp32 backward: calls of up to half a Mi elements hold pack = lane, larger ones lane pairs; both add a row's terms in one order
+@pytest.mark.parametrize("hidden", [512, 520, 768, 1000, 1032, 2040, 4104, 6400, 8192])
+def test_layernorm_bwd_pairs_and_not(hidden):
+    say(f"[layernorm] backward in lane pairs and not, hidden={hidden}")
+    d, big = dev(), (1 << 19) // hidden + 9
+    n = big - 9
+    g = torch.Generator(device=d).manual_seed(hidden)
+    x, dy, res, gamma = (torch.randn(s, generator=g, device=d) for s in ((big, hidden), (big, hidden), (big, hidden), (hidden,)))
+    mu, rs = x.mean(1), 1 / torch.sqrt(x.var(1, unbiased=False) + EPS)
+    xh = (x.double() - mu.double()[:, None]) * rs.double()[:, None]
+    for extra in (None, res):
+        dx, dgamma, dbeta = L.lsq_layernorm_bwd(dy, x, gamma, mu, rs, extra)
+        fused = L.lsq_bdr_layernorm_bwd(dy, x, gamma, mu, rs, 0.25, 3, 4, extra)
+        for m in (n, 40):
+            assert torch.equal(dx[:m], L.lsq_layernorm_bwd(dy[:m], x[:m], gamma, mu[:m], rs[:m], None if extra is None else extra[:m])[0]), m
+            part = L.lsq_bdr_layernorm_bwd(dy[:m], x[:m], gamma, mu[:m], rs[:m], 0.25, 3, 4, None if extra is None else extra[:m])
+            assert torch.equal(fused[0][:m], part[0]) and torch.equal(fused[1][:m], part[1]), m
+        assert torch.equal(dx, fused[0])
+        # fp32 sums of `big` products of unit normals: well within 1e-5 of their 2-norm
+        for got, want in ((dgamma, (dy.double() * xh).sum(0)), (dbeta, dy.double().sum(0)), (fused[2], (dy.double() * xh).sum(0)), (fused[4], fused[1].double().sum(0))):
+            assert (got.double() - want).norm() <= 1e-5 * (big * hidden) ** 0.5
+
+
 # half-wave rows come in pairs: three trips' worth of rows is two pairs (1537..2304 rows)
 @pytest.mark.parametrize("rows,hidden", [(1536, 520), (1537, 640), (2304, 768), (2305, 520), (2100, 1281)])
 def test_layernorm_bwd_pairs_of_rows(rows, hidden):

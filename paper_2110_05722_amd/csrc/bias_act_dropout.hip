@@ -90,12 +90,12 @@ __device__ __forceinline__ void bad_factors(const DropoutParams& d, int64_t e, f
 // all its lanes stay, because a pack's dropout words come from two lanes.  Forward / backward in us, the flat walk in brackets: 8192 x 1281
 // bf16 GELU with dropout 16.0 / 27.2 (19.1 / 41.9: a gather per bias element, column sums through LDS), 600 x 16001 14.2 / 22.8
 // (18.6 / 98.6), 500 x 1027 fp16 ReLU 3.4 / 7.2 (7.1 / 13.7), 2000 x 5001 f32 without dropout 21.0 / 29.5 (34.2 / 69.4).
-template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG, bool NTL>
+template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG, bool PAIR, bool NTL>
 __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T* __restrict__ bias, int64_t rows,
                                                     RowPackIO<T, RAG> io, DropoutParams d)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    using P = LanePacks<T, RAG ? 1 : 64>;
+    using P = LanePacks<T, PAIR ? 64 : 1>;
     const int col = blockIdx.x * (RAG ? kRagLanes : 64) + P::pack(lane), cp = RAG ? min(col, io.ppr - 1) : col;
     const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
     if (!RAG && !P::kPaired && !mine) return;
@@ -134,13 +134,13 @@ __global__ __launch_bounds__(256) void bad_fwd_cols(T* out, const T* x, const T*
     }
 }
 
-template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG, bool NTL>
+template <typename T, int ACT, bool HAS_BIAS, bool DROP, bool RAG, bool PAIR, bool NTL>
 __global__ __launch_bounds__(256) void bad_bwd_cols(T* dx, float* __restrict__ partial, const T* dy, const T* x,
                                                     const T* __restrict__ bias, int64_t rows, RowPackIO<T, RAG> io, DropoutParams d)
 {
     __shared__ float sm[kBadWaves][8][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    using P = LanePacks<T, RAG ? 1 : 64>;
+    using P = LanePacks<T, PAIR ? 64 : 1>;
     const int col = blockIdx.x * (RAG ? kRagLanes : 64) + P::pack(lane), cp = RAG ? min(col, io.ppr - 1) : col;
     const bool mine = col < io.ppr && (!RAG || lane < kRagLanes);
     auto fetch = [&](const T* t, int64_t row) {
@@ -284,6 +284,17 @@ struct BadBwdFlat {
     }
 };
 
+// fp32 in lane pairs from these elements on: below, the second address and the exchange are in the way of a few waves, with dropout, whose words they wait for, the longer.
+// us, pack = lane and in pairs, GELU, inputs in L2 / from far memory: forward 1 MB 2.3 and 2.4 / 2.4 and 2.9; 1000 x 1280 2.9 and 2.8 / 3.8 and 3.6, with dropout 3.2 and 3.5 / 3.8 and 4.3, 2457 x 1280
+// with dropout 5.0 and 5.9 / 7.7 and 7.4, 4096 x 1024 7.0 and 6.0 / 8.4 and 7.8, 8192 x 1024 14.9 and 12.0 / 15.9 and 13.6; backward 1 MB 5.2 and 5.7 / 6.1 and 6.7; 1000 x 1280 5.9 and 6.0 / 8.2 and
+// 8.3, with dropout 7.0 and 7.6 / 8.8 and 8.8, 4096 x 512 7.6 and 8.5 / 10.2 and 10.6, 2457 x 1280 12.2 and 11.2 / 13.8 and 13.1, 8192 x 1024 23.4 and 20.4 / 25.0 and 22.8.
+template <typename T>
+inline bool bad_paired(int64_t rows, int32_t hidden, bool drop, bool fwd)
+{
+    const int64_t n = rows * hidden;
+    return sizeof(T) == 4 && hidden % kPack == 0 && n >= (1 << 20) && (!drop || (fwd ? n >= (1 << 22) : n > (1 << 21)));
+}
+
 template <typename T, int ACT>
 static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, int64_t rows, int32_t hidden,
                                    const DropoutParams& d, hipStream_t s)
@@ -300,11 +311,13 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
         if (rb * cb <= (sizeof(T) == 2 ? 1024 : 511)) rb = ceil_div(rows, kBadWaves);
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(cb), static_cast<unsigned>(rb)), block(256);
-        const bool cached = stays_cached(rows * hidden, sizeof(T));
+        const bool pair = bad_paired<T>(rows, hidden, d.on != 0, true), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+        constexpr bool kPair = sizeof(T) == 4;
 #define LSQ_BAD_FWD(BIAS, DROP)                                                                                                            \
-        if (hidden % kPack == 0 && !cached) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
-        else if (hidden % kPack == 0) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, false>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
-        else hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, true, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, true>(hidden), d)
+        if (hidden % kPack != 0) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, true, false, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, true>(hidden), d); \
+        else if (cached) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, kPair, false>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else if (pair) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, kPair, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, false, false, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, false>(hidden), d)
         const bool drop = d.on != 0;
         if (bp && drop) { LSQ_BAD_FWD(true, true); }
         else if (bp) { LSQ_BAD_FWD(true, false); }
@@ -329,11 +342,13 @@ static lsq_status bad_bwd_dispatch(void* dx, float* dbias, const void* dy, const
         const int rb = bad_bwd_row_blocks(rows, hidden);
         const dim3 grid(static_cast<unsigned>(bad_col_blocks(hidden)), static_cast<unsigned>(rb)), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        const bool cached = stays_cached(rows * hidden, sizeof(T));
+        const bool pair = bad_paired<T>(rows, hidden, d.on != 0, false), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+        constexpr bool kPair = sizeof(T) == 4;
 #define LSQ_BAD_BWD(BIAS, DROP)                                                                                                            \
-        if (hidden % kPack == 0 && !cached) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
-        else if (hidden % kPack == 0) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
-        else hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, true, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, true>(hidden), d)
+        if (hidden % kPack != 0) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, true, false, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, true>(hidden), d); \
+        else if (cached) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, kPair, false>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else if (pair) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, kPair, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d); \
+        else hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, false, false, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, false>(hidden), d)
         const bool drop = d.on != 0;
         if (bp && drop) { LSQ_BAD_BWD(true, true); }
         else if (bp) { LSQ_BAD_BWD(true, false); }

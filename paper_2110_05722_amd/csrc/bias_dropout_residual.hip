@@ -25,12 +25,12 @@ template <int W> struct BdrLane {
     __device__ __forceinline__ BdrLane() : lane((threadIdx.x & 63) % W), sub((threadIdx.x & 63) / W) {}
 };
 
-template <typename T, bool HAS_BIAS, bool DROP, int W, bool NTL>
+template <typename T, bool HAS_BIAS, bool DROP, int W, bool PAIR, bool NTL>
 __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const T* x, const T* __restrict__ bias,
                                                                   const T* res, int64_t rows, int ppr, DropoutParams d)
 {
     constexpr int SUB = 64 / W, U = kBdrFwdUnroll, RPI = kBdrFwdWaves * SUB * U;
-    using P = LanePacks<T, W>;
+    using P = LanePacks<T, PAIR ? W : 1>;
     const BdrLane<W> ln;
     const int wave = threadIdx.x >> 6;
     const int cp = blockIdx.x * W + P::pack(ln.lane);
@@ -82,13 +82,13 @@ __global__ __launch_bounds__(64 * kBdrFwdWaves) void bdr_fwd_cols(T* out, const 
 
 // Backward.  partial: [gridDim.y][hidden] fp32 column sums of the workgroups' rows (nullptr:
 // dbias not wanted), summed over the row blocks by colsum_finalize_kernel.
-template <typename T, bool DROP, int W, bool NTL>
+template <typename T, bool DROP, int W, bool PAIR, bool NTL>
 __global__ __launch_bounds__(64 * kBdrBwdWaves) void bdr_bwd_cols(T* dx, float* __restrict__ partial, const T* dy,
                                                                   int64_t rows, int ppr, int trips, DropoutParams d)
 {
     constexpr int SUB = 64 / W, NW = kBdrBwdWaves, THREADS = 64 * NW;
     __shared__ float sm[NW * 8 * 64];      // the lanes' sums
-    using P = LanePacks<T, W>;
+    using P = LanePacks<T, PAIR ? W : 1>;
     const BdrLane<W> ln;
     const int wave = threadIdx.x >> 6, lane = ln.sub * W + P::pack(ln.lane);      // by pack
     const int cp = blockIdx.x * W + P::pack(ln.lane);
@@ -279,6 +279,11 @@ struct BdrBwdFlat {
     }
 };
 
+// fp32 in lane pairs from 2 MiB a tensor on: below, the second address and the exchange are in the way of a few waves (1 MB forward / backward
+// 2.24 / 4.76 us, in pairs 2.34 / 4.80 with inputs in L2, 2.7 / 4.9 and 3.1 / 5.6 from far memory; 2 MB 4.0 / 6.0 and 3.6 / 6.3, 4 MB 5.8 / 7.1 and 5.2 / 7.2).
+template <typename T>
+inline bool bdr_paired(int64_t rows, int32_t hidden) { return sizeof(T) == 4 && rows * hidden >= (1 << 19); }
+
 template <typename T>
 static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, const void* res, int64_t rows,
                                    int32_t hidden, const DropoutParams& d, hipStream_t s)
@@ -296,15 +301,17 @@ static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, c
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(ceil_div(ppr, w)), static_cast<unsigned>(rb)), block(64 * kBdrFwdWaves);
         const bool drop = d.on != 0;
-        const bool cached = stays_cached(rows * hidden, sizeof(T));
-#define LSQ_BDR_FWD(W, NTL)                                                                                             \
-        if (w == W && cached != NTL) {                                                                                                   \
-            if (bp && drop) hipLaunchKernelGGL((bdr_fwd_cols<T, true, true, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);    \
-            else if (bp) hipLaunchKernelGGL((bdr_fwd_cols<T, true, false, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);     \
-            else if (drop) hipLaunchKernelGGL((bdr_fwd_cols<T, false, true, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);   \
-            else hipLaunchKernelGGL((bdr_fwd_cols<T, false, false, W, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);            \
+        const bool pair = bdr_paired<T>(rows, hidden), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+#define LSQ_BDR_FWD(W, PAIR, NTL)                                                                                            \
+        if (w == W && pair == (PAIR) && cached != NTL) {                                                                                   \
+            if (bp && drop) hipLaunchKernelGGL((bdr_fwd_cols<T, true, true, W, PAIR, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);    \
+            else if (bp) hipLaunchKernelGGL((bdr_fwd_cols<T, true, false, W, PAIR, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);     \
+            else if (drop) hipLaunchKernelGGL((bdr_fwd_cols<T, false, true, W, PAIR, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);   \
+            else hipLaunchKernelGGL((bdr_fwd_cols<T, false, false, W, PAIR, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);            \
         }
-        LSQ_BDR_FWD(32, true) LSQ_BDR_FWD(16, true) LSQ_BDR_FWD(32, false) LSQ_BDR_FWD(16, false)
+        LSQ_BDR_FWD(32, false, true) LSQ_BDR_FWD(16, false, true)
+        LSQ_BDR_FWD(32, sizeof(T) == 4, false) LSQ_BDR_FWD(16, sizeof(T) == 4, false)
+        if constexpr (sizeof(T) == 4) { LSQ_BDR_FWD(32, true, true) LSQ_BDR_FWD(16, true, true) }
 #undef LSQ_BDR_FWD
     } else if (!flat) {
         const RowPackIO<T, true> io(hidden);
@@ -331,13 +338,15 @@ static lsq_status bdr_bwd_dispatch(void* dx, float* dbias, const void* dy, int64
         const BdrBwdPlan pl = bdr_bwd_plan(rows, hidden);
         const dim3 grid(static_cast<unsigned>(pl.col_blocks), static_cast<unsigned>(pl.row_blocks)), block(64 * kBdrBwdWaves);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-const bool cached = stays_cached(rows * hidden, sizeof(T));
-#define LSQ_BDR_BWD(W, NTL)                                                                                                  \
-        if (pl.w == W && cached != NTL) {                                                                                                \
-            if (d.on) hipLaunchKernelGGL((bdr_bwd_cols<T, true, W, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);    \
-            else hipLaunchKernelGGL((bdr_bwd_cols<T, false, W, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);         \
+        const bool pair = bdr_paired<T>(rows, hidden), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+#define LSQ_BDR_BWD(W, PAIR, NTL)                                                                                       \
+        if (pl.w == W && pair == (PAIR) && cached != NTL) {                                                               \
+            if (d.on) hipLaunchKernelGGL((bdr_bwd_cols<T, true, W, PAIR, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);    \
+            else hipLaunchKernelGGL((bdr_bwd_cols<T, false, W, PAIR, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);         \
         }
-        LSQ_BDR_BWD(32, true) LSQ_BDR_BWD(16, true) LSQ_BDR_BWD(32, false) LSQ_BDR_BWD(16, false)
+        LSQ_BDR_BWD(32, false, true) LSQ_BDR_BWD(16, false, true)
+        LSQ_BDR_BWD(32, sizeof(T) == 4, false) LSQ_BDR_BWD(16, sizeof(T) == 4, false)
+        if constexpr (sizeof(T) == 4) { LSQ_BDR_BWD(32, true, true) LSQ_BDR_BWD(16, true, true) }
         if (dbias) launch_colsum_finalize(dbias, dbias, hidden, partial, pl.row_blocks, hidden, s);
 #undef LSQ_BDR_BWD
     } else if (!flat) {

@@ -38,7 +38,7 @@ __device__ __forceinline__ int64_t head_offset(const HeadGeom& g, int64_t t, int
     return ((b * g.heads + n) * g.len + l) * static_cast<int64_t>(g.head_dim) + dd;
 }
 
-// fp32 in lane pairs of groups of 8 packs where these lie in one head (heads of a multiple of 64 columns), else through the caches
+// fp32 in lane pairs of groups of 8 packs where these lie in one head, or with pack = lane (heads_paired, heads_half_lines); kNTS: stores past the caches
 template <typename T> constexpr int kHeadGroup = sizeof(T) == 4 ? 8 : 1;
 template <typename T, bool HAS_BIAS, int G, bool NTL>
 __global__ __launch_bounds__(256) void split_heads_kernel(T* __restrict__ o0, T* __restrict__ o1, T* __restrict__ o2,
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void split_heads_kernel(T* __restrict__ o0, T*
     // 18.5 against 19.5 us at 4096 x 3072 and 23.7 against 24.4 us at 8192 x 3840 (the merge is 1-3 % slower that way)
     const GridBlock gb = grid_block<1>();
     using P = LanePacks<T, G>;
-    constexpr bool kNTS = sizeof(T) == 2 || P::kPaired;
+    constexpr bool kNTS = sizeof(T) == 2 || P::kPaired || NTL;
     const int cp = gb.col * 64 + P::pack(lane);
     if (cp >= g.ppr) return;                                     // (whole groups)
     const int col = cp * kPack;
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void merge_heads_kernel(T* __restrict__ out, f
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const GridBlock gb = grid_block<0>();
     using P = LanePacks<T, G>;
-    constexpr bool kNTS = sizeof(T) == 2 || P::kPaired;
+    constexpr bool kNTS = sizeof(T) == 2 || P::kPaired || NTL;
     const int cp = gb.col * 64 + P::pack(lane);
     const bool active = cp < g.ppr;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -182,6 +182,15 @@ inline int head_row_blocks(int64_t rows)
     return static_cast<int>(b < 1 ? 1 : b);
 }
 
+// fp32 from 4 MiB on: a pack is two accesses of half a line each.  Heads of a multiple of 64 columns go in lane pairs; the others through the caches, loads and stores, or half lines
+// move.  Below, past the caches (three heads of 1 MB in lane pairs: split 2.35 / 3.1 us, backward 5.2 / 6.0).  us, past the caches / like this, in the states of stays_cached: in lane pairs, per
+// part, split 8 MB 13.3 / 11.1, 22.9 / 20.9, 14.9 / 12.6, backward 19.6 / 13.4, 30.0 / 25.1, 21.1 / 16.5; merge 16 MB 10.2 / 7.3, 17.4 / 14.6, 11.8 / 9.1.  Heads of 80 columns and others
+// through the caches: split backward 16 MB 37.3 / 22.7, 56.3 / 43.3, 39.5 / 32.3, merge 32 MB 22.6 / 14.8, 37.1 / 29.1, 25.4 / 20.9; split 16 MB 27.5 / 19.7, 41.7 / 45.4, 29.4 / 28.6, 32 MB
+// 58.7 / 46.0, 90.7 / 106.9, 61.9 / 58.2, merge backward 32 MB 18.1 / 14.6, 31.2 / 29.3, 20.2 / 21.8, 64 MB 36.6 / 28.3, 60.3 / 77.1, 39.2 / 41.3: these two lose behind the kernel that
+// wrote their input where they are long (only the loads, or only the stores, through the caches: 100 and 112 for the split of 32 MB, 70 and 67 for the merge backward of 64).
+template <typename T> inline bool heads_half_lines(const HeadGeom& g) { return sizeof(T) == 4 && g.rows * g.parts * g.hidden >= (1 << 20); }
+template <typename T> inline bool heads_paired(const HeadGeom& g) { return g.head_dim % 64 == 0 && heads_half_lines<T>(g); }
+
 template <typename T>
 static lsq_status split_dispatch(void* o0, void* o1, void* o2, const void* in, const void* bias, const HeadGeom& g,
                                  hipStream_t s)
@@ -191,13 +200,13 @@ static lsq_status split_dispatch(void* o0, void* o1, void* o2, const void* in, c
     const T* bp = static_cast<const T*>(bias);
     if (g.head_dim % kPack == 0) {
         const dim3 grid(static_cast<unsigned>(ceil_div(g.ppr, 64)), static_cast<unsigned>(head_row_blocks(g.rows))), block(256);
-        const bool cached = stays_cached(g.rows * g.parts * g.hidden, sizeof(T)), pairs = sizeof(T) == 4 && g.head_dim % 64 == 0;
+        const bool pairs = heads_paired<T>(g), cached = stays_cached(g.rows * g.parts * g.hidden, sizeof(T)) && (sizeof(T) == 2 || pairs);
 #define LSQ_SPLIT(G, NTL)                                                                                                              \
         if (bp) hipLaunchKernelGGL((split_heads_kernel<T, true, G, NTL>), grid, block, 0, s, a, b, c, ip, bp, g);                      \
         else hipLaunchKernelGGL((split_heads_kernel<T, false, G, NTL>), grid, block, 0, s, a, b, c, ip, bp, g)
         if (pairs && cached) { LSQ_SPLIT(kHeadGroup<T>, false); }
         else if (pairs) { LSQ_SPLIT(kHeadGroup<T>, true); }
-        else if (cached || sizeof(T) == 4) { LSQ_SPLIT(1, false); }
+        else if (cached || heads_half_lines<T>(g)) { LSQ_SPLIT(1, false); }
         else { LSQ_SPLIT(1, true); }
 #undef LSQ_SPLIT
     } else {
@@ -219,11 +228,11 @@ static lsq_status merge_dispatch(void* out, float* dbias, const void* i0, const 
         const int rb = heads_bwd_row_blocks(g.rows, cols, sizeof(T));
         const dim3 grid(static_cast<unsigned>(ceil_div(g.ppr, 64)), static_cast<unsigned>(dbias ? rb : head_row_blocks(g.rows))), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        const bool cached = stays_cached(g.rows * g.hidden, sizeof(T)), pairs = sizeof(T) == 4 && g.head_dim % 64 == 0;
+        const bool pairs = heads_paired<T>(g), cached = stays_cached(g.rows * g.hidden, sizeof(T)) && (sizeof(T) == 2 || pairs);
 #define LSQ_MERGE(G, NTL) hipLaunchKernelGGL((merge_heads_kernel<T, G, NTL>), grid, block, 0, s, o, partial, a, b, c, g)
         if (pairs && cached) LSQ_MERGE(kHeadGroup<T>, false);
         else if (pairs) LSQ_MERGE(kHeadGroup<T>, true);
-        else if (cached || sizeof(T) == 4) LSQ_MERGE(1, false);
+        else if (cached || heads_half_lines<T>(g)) LSQ_MERGE(1, false);
         else LSQ_MERGE(1, true);
 #undef LSQ_MERGE
         if (dbias) launch_colsum_finalize(dbias, dbias, cols, partial, rb, cols, s);

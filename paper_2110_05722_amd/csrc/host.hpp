@@ -56,13 +56,20 @@ inline lsq_status zero_fill(float* p, int64_t n, hipStream_t s)
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The streamed inputs of a call are loaded past the caches (nontemporal) only where a tensor is larger than this: what the kernel ahead has just written, a smaller
-// one, is still in the 256 MB Infinity Cache.  Past the caches / through them in us, bf16, inputs there and (cold) in far memory: bias+dropout+residual forward
-// 2000 x 1024 4.0 / 3.3 (3.6 / 3.9), backward 8192 x 1024 10.8 / 9.7 (10.9 / 11.1); head split backward 128 x 32 x 8 x 64 x 3 9.8 / 8.7 (9.7 / 10.0), padding restored
-// 30 x 100 x 768 4.2 / 3.3 (3.8 / 3.2); a captured layer of 128 x 32 tokens, hidden 512, 92.2 / 85.2.  Beyond, cold costs more than there gives: 16384 x 1024
-// 17.6 / 16.3 (17.5 / 18.5), heads of 8192 x 1280 (21 MB a tensor) 67.0 / 67.9 for a pass over fresh inputs.
-constexpr int64_t kCachedBytes = 16ll << 20;
-inline bool stays_cached(int64_t elements, size_t elem_bytes) { return elements * static_cast<int64_t>(elem_bytes) <= kCachedBytes; }
+// The streamed inputs of a call are loaded past the caches (nontemporal) unless a tensor has 2 to 16 MiB: what the kernel ahead has just written, or the same
+// pass will read again, is then in the 256 MB Infinity Cache, and a load past the caches gives the line up.  It is a choice between states. us, 16 bits, past the caches
+// and the change through them, in the order: passes over 100 MB that stay there / inputs written by the kernel ahead, outputs in far memory (its time counted too) / all in far
+// memory.  Backward of bias+dropout+residual, 8 MB 9.0 - 1.0 / 12.3 + 0.9 / 9.5 + 0.6; of the feed-forward 11.2 - 0.3 / 16.1 + 0.8 / 11.7 + 0.8; padding restored, 8 MB 5.9 - 1.2 / 8.1 + 1.3 / 6.3
+// + 0.5; head split backward, three of 8 MB 15.3 - 1.6 / 27.0 - 1.6 / 16.6 + 0.2.  Whole calls that take several of them gain: a captured layer of 128 x 32 tokens, hidden 512, 90.3 us with the
+// forwards and the feed-forward past the caches, 85.5 like this (about half of that on inputs that no pass has read), the four calls of a sub-layer boundary of 8192 x 1024 51.7 and 50.2.
+// Below, nothing gains in any state and a call from far memory loses: 1 MB 2.3 + 0.4 forward of bias+dropout+residual, 2.4 + 0.6 head merge backward, 5.6 + 0.8 feed-forward backward.
+// Beyond, far memory costs more: 24 MB heads 27.5 + 0.6 split, 10.2 + 0.9 merge backward, 20 MB feed-forward backward 16.8 + 0.8.
+constexpr int64_t kCachedLeast = 2ll << 20, kCachedMost = 16ll << 20;
+inline bool stays_cached(int64_t elements, size_t elem_bytes)
+{
+    const int64_t bytes = elements * static_cast<int64_t>(elem_bytes);
+    return bytes >= kCachedLeast && bytes <= kCachedMost;
+}
 
 // Division of a row index (below 2^32) by a launch constant: multiply-high by a host-made reciprocal, two shifts
 // (Granlund and Montgomery's round-up form) -- 5 integer instructions where the 64-bit division the compiler emits

@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kXbThreads) void xent_bwd_flat_kernel(T* dlogits, c
             const bool inB = e0 >= bnd;
             const bool live = inB ? liveB : liveA;
             const float ls = inB ? lsB : lsA;
-            const int64_t hp = (inB ? hitB : hitA) - e0;      // 0..7 iff the target element is in this pack
+            const int64_t hp = (inB ? hitB : hitA) - e0;      // 0..V-1 iff the target element is in this pack
 #pragma unroll
             for (int j = 0; j < V; ++j)
                 o[j] = live ? grad_scale * (__builtin_amdgcn_exp2f(fmaf(h[u][j], kLog2eX, -ls)) - smooth) : 0.0f;
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kXbThreads) void xent_bwd_flat_kernel(T* dlogits, c
         }
         store16<T, kBwdNTS>(dlogits + e0, o);
     }
-    // ragged end of the whole tensor (total % 8 elements): last workgroup, scalar
+    // ragged end of the whole tensor (total % V elements): last workgroup, scalar
     if (blockIdx.x == gridDim.x - 1) {
         const int64_t e = npacks * V + threadIdx.x;
         if (e < total) {

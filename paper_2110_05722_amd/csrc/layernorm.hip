@@ -112,7 +112,7 @@ struct BdrFuse {
 // FUSE: the row that is normalised is h = residual + Dropout(x + bias), built in registers from
 // two loads, stored once (the next residual) and normalised from its STORED (rounded) value, so the
 // result equals bias+dropout+residual followed by LayerNorm bit for bit while h is never re-read.
-template <typename T, int LPR, int VPL, bool FUSE, bool DROP, bool PAIR>
+template <typename T, int LPR, int VPL, bool FUSE, bool DROP, bool PAIR, bool NT>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* __restrict__ mean,
                                                      float* __restrict__ rstd, const T* __restrict__ x,
                                                      const T* __restrict__ gamma, const T* __restrict__ beta,
@@ -123,9 +123,6 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(T* __restrict__ y, float* _
     constexpr int RPB = 256 / LPR;                     // rows a workgroup handles at a time
     constexpr int NP = kLnParts<LPR, VPL>;
     using P = LanePacks<T, PAIR ? 8 : 1>;
-    // fp32 with pack = lane: through the caches, or half lines move (unpaired / past the caches, us, cold: 16384 x 1032 29.4 / 33.0, 8192 x 2040 30.0 / 33.0, fused
-    // 56.2 / 63.1, 300 x 768 3.8 / 4.0, 1000 x 1024 4.3 / 4.1); 256 lanes x 8 packs only if fused (1000 x 16384 55.9 / 68.2, plain 31.0 / 29.7)
-    constexpr bool NT = sizeof(T) == 2 || PAIR || (VPL == 8 && !FUSE);
     const int sub = P::pack(threadIdx.x % LPR);
     const int slot = threadIdx.x / LPR;
     const int nv = hidden / kPack;
@@ -473,7 +470,7 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_kernel(T* dx, float* __restric
 // too few rows beside it, most of all in short calls.
 // LRC = 64: 512 columns, a row per wave, no exchange, never in pairs (300 rows f32 6.3 us, in pairs 6.6).  Partial rows as ln_bwd_kernel's.
 // RAG: rows that are not whole packs, in packs counted from the row's start (RowPackIO; not fused).
-template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP, bool RAG, bool PAIR>
+template <typename T, int LRC, bool HAS_RES, int MAXT, bool FUSE, bool DROP, bool RAG, bool PAIR, bool NT>
 __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restrict__ partial, const T* dy,
                                                            const T* __restrict__ x, const T* __restrict__ gamma,
                                                            const float* __restrict__ mean, const float* __restrict__ rstd,
@@ -486,7 +483,6 @@ __global__ __launch_bounds__(MAXT) void ln_bwd_span_kernel(T* dx, float* __restr
     const int slots = blockDim.x / LR;
     static_assert(!PAIR || (sizeof(T) == 4 && !RAG && LRC == 0), "lane pairs are for fp32 rows of whole packs that span several waves");
     using P = LanePacks<T, PAIR ? 32 : 1>;
-    constexpr bool NT = sizeof(T) == 2 || RAG || PAIR;        // fp32 with pack = lane: through the caches, or half lines move
     const int slot = threadIdx.x / LR, sub = P::pack(threadIdx.x - slot * LR);
     const RowPackIO<T, RAG> io(hidden);
     const int nv = io.ppr;
@@ -936,7 +932,7 @@ inline LnShape ln_fwd_shape(int64_t rows, int hidden, int elem_bytes)
     return s;
 }
 
-// fp32 forward in lane pairs: not the calls of a few waves, whose time is latency, which the exchange adds to (their rows go through the caches), and of rows that end
+// fp32 forward in lane pairs: not the calls of a few waves, whose time is latency, which the exchange adds to, and of rows that end
 // inside a 128-byte line, where two pieces meet, only those of up to 2048 columns that are neither small nor long (long ones fetch each line once through the caches).
 // us, inputs cold: pack = lane past the caches / pairs everywhere / this rule: 8192 x 2048 33.4 / 25.5 / 25.5, fused with dropout 61.5 / 48.7 / 48.8; 300 x 1024 3.4 / 3.8 / 3.4,
 // 4.7 / 4.9 / 4.5; 300 x 2304 4.5 / 5.0 / 4.7, 6.1 / 7.0 / 6.5; 8192 x 2040 35.7 / 37.3 / 29.9, 66.7 / 74.1 / 56.4; 3000 x 1304 11.6 / 10.0 / 9.7, 20.2 / 16.3 / 17.6.
@@ -955,6 +951,14 @@ inline bool ln_fwd_paired(int64_t rows, int hidden)
 // 47.9; rows that end inside a line the same: 8192 x 1304 32.0 / 29.5 / 29.6, 50.2 / 45.0 / 46.1, 5000 x 2040 32.6 / 29.4 / 28.9, 50.0 / 47.0 / 45.3.
 template <typename T>
 inline bool ln_bwd_paired(int64_t rows, int hidden) { return sizeof(T) == 4 && rows * hidden > (1 << 19); }
+
+// fp32 with pack = lane goes through the caches, or half lines move, but only from 3 Mi elements on: below, as of a call whose inputs are not in L2, that is slower (300 x
+// 512 2.4 / 2.8 us). us, past the caches / through them, inputs just written / in far memory / in the Infinity Cache: forward 419 x 5000 9.3 / 10.6, 6.1 / 7.1, 5.7 / 6.2; 1258 x 5000 23.2 /
+// 20.6, 15.0 / 15.3, 14.1 / 10.9; 8388 x 1000 28.7 / 26.3, 21.1 / 20.3, 17.8 / 14.4; backward, fused with dropout and residual gradient, 8192 x 256 17.3 / 18.6, 14.4 / 15.4, 13.2 / 12.4;
+// 16384 x 512 49.5 / 46.5, 40.3 / 39.1, 37.8 / 29.1; 65536 x 128 49.6 / 47.0, 38.1 / 39.2, 38.6 / 29.3.  256 lanes x 8 packs only if fused (1000 x 16384 68.2 / 55.9, plain 29.7 / 31.0), backward of
+// more than 8192 columns always (30 x 16384 54.8 / 46.0, 57.5 / 47.1, 56.6 / 39.6).
+template <typename T>
+inline bool ln_cached(int64_t rows, int hidden) { return sizeof(T) == 4 && rows * hidden >= (3ll << 20); }
 
 // Row groups per workgroup: two, the second loaded ahead (8192 x 1280: one 11.1, two 9.2, four 10.4 us), but one where all groups find
 // a compute unit of their own: up to 256 always (one against two, all shapes: 0.66-0.90), up to 768 where the kernel is small enough for
@@ -1015,17 +1019,19 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
     bool launched = false;
     const dim3 grid(ln_fwd_blocks(rows, sh, sizeof(T))), block(256);
     const BdrFuse<T> none{};
-    const bool pair = sizeof(T) == 4 && ln_fwd_paired(rows, hidden);
+    const bool pair = sizeof(T) == 4 && ln_fwd_paired(rows, hidden), cached = ln_cached<T>(rows, hidden);
 #define X(L, V)                                                                                              \
     if (sh.lpr == L && sh.vpl == V) {                                                                        \
         launched = true;                                                                                     \
         constexpr bool kPair = sizeof(T) == 4 && V < 8;                                                      \
-        if (pair) { F(L, V, kPair) } else { F(L, V, false) }                                                 \
+        if (pair && kPair) { F(L, V, kPair, true) }                                                          \
+        else if (cached && (V < 8 || fuse)) { F(L, V, false, sizeof(T) == 2) }                               \
+        else { F(L, V, false, true) }                                                                        \
     }
-#define F(L, V, PAIR)                                                                                        \
-        if (!fuse) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, false, false, PAIR>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, none); \
-        else if (fuse->d.on) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, true, PAIR>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
-        else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false, PAIR>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse);
+#define F(L, V, PAIR, NT)                                                                                    \
+        if (!fuse) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, false, false, PAIR, NT>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, none); \
+        else if (fuse->d.on) hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, true, PAIR, NT>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse); \
+        else hipLaunchKernelGGL((ln_fwd_kernel<T, L, V, true, false, PAIR, NT>), grid, block, 0, s, yp, mean, rstd, xp, gp, bp, rows, hidden, eps, *fuse);
     LSQ_LN_FWD_CASES(X)
     if constexpr (sizeof(T) == 2) { X(64, 5) }
 #undef X
@@ -1114,37 +1120,40 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
         const dim3 grid(P), block(pl.slots * pl.lanes);
         const size_t exchange = sizeof(float) * (block.x / 8), tree = sizeof(float) * (pl.slots / 2) * (fuse ? 3 : 2) * 8 * pl.lanes;
         const size_t shmem = exchange > tree ? exchange : tree;
-#define X(C, M, PAIR)                                                                                        \
+#define X(C, M, PAIR, NT)                                                                                    \
     if (!fuse) {                                                                                             \
-        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, false, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none); \
-        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, false, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none);   \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, false, false, false, PAIR, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none); \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, false, false, false, PAIR, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none);   \
     } else if (fuse->d.on) {                                                                                 \
-        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, true, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);  \
-        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, true, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);    \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, true, false, PAIR, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);  \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, true, false, PAIR, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);    \
     } else {                                                                                                 \
-        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse); \
-        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, false, false, PAIR>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);   \
+        if (rp) hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, true, M, true, false, false, PAIR, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse); \
+        else hipLaunchKernelGGL((ln_bwd_span_kernel<T, C, false, M, true, false, false, PAIR, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, *fuse);   \
     }
         if (ln_rag_spans(hidden)) {
-#define R(H, M) hipLaunchKernelGGL((ln_bwd_span_kernel<T, 0, H, M, false, false, true, false>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none)
+#define R(H, M) hipLaunchKernelGGL((ln_bwd_span_kernel<T, 0, H, M, false, false, true, false, true>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, pl.lanes, none)
             if (rp) { if (block.x <= kLnSpanThreads) R(true, kLnSpanThreads); else R(true, 1024); }
             else { if (block.x <= kLnSpanThreads) R(false, kLnSpanThreads); else R(false, 1024); }
 #undef R
-        } else if (pl.lanes == 64) { X(64, kLnSpanThreads, false) }
-        else if (block.x <= kLnSpanThreads && ln_bwd_paired<T>(rows, hidden)) { X(0, kLnSpanThreads, sizeof(T) == 4) }
-        else if (block.x <= kLnSpanThreads) { X(0, kLnSpanThreads, false) }
-        else if (ln_bwd_paired<T>(rows, hidden)) { X(0, 1024, sizeof(T) == 4) }
-        else { X(0, 1024, false) }
+        } else if (pl.lanes == 64) {
+            if (ln_cached<T>(rows, hidden)) { X(64, kLnSpanThreads, false, sizeof(T) == 2) }
+            else { X(64, kLnSpanThreads, false, true) }
+        }
+        else if (block.x <= kLnSpanThreads && ln_bwd_paired<T>(rows, hidden)) { X(0, kLnSpanThreads, sizeof(T) == 4, true) }
+        else if (block.x <= kLnSpanThreads) { X(0, kLnSpanThreads, false, true) }
+        else if (ln_bwd_paired<T>(rows, hidden)) { X(0, 1024, sizeof(T) == 4, true) }
+        else { X(0, 1024, false, true) }
 #undef X
     }
     // shorter rows: lanes of one wave, one pack each, or two of 32 lanes
     const int nacc = fuse ? 3 : 2;
+    const bool cached = ln_cached<T>(rows, hidden);
     const size_t one_copy = sizeof(float) * 8 * nacc * ((hidden / kPack) | 1);
-#define X(L, V)                                                                                              \
-    if (!ln_bwd_spans(hidden) && sh.lpr == L && sh.vpl == V) {                                                                        \
+#define X(L, V, NT)                                                                                          \
+    if (!ln_bwd_spans(hidden) && sh.lpr == L && sh.vpl == V && cached != (NT)) {                                                        \
         launched = true;                                                                                     \
         constexpr int TH = kLnBwdThreads;                                                                    \
-        constexpr bool NT = sizeof(T) == 2;                                                                  \
         const size_t shmem = one_copy * (TH / L);                                                            \
         const dim3 grid(P), block(TH);                                                                       \
         if (!fuse) {                                                                                         \
@@ -1158,7 +1167,8 @@ static lsq_status ln_bwd_dispatch(void* dx, float* dgamma, float* dbeta, const v
             else hipLaunchKernelGGL((ln_bwd_kernel<T, L, V, false, TH, true, false, NT>), grid, block, shmem, s, dxp, partial, dyp, xp, gp, mean, rstd, rp, rows, hidden, *fuse);   \
         }                                                                                                    \
     }
-    X(8, 1) X(16, 1) X(32, 1) X(32, 2)       // what ln_shape gives up to 63 packs
+    X(8, 1, true) X(16, 1, true) X(32, 1, true) X(32, 2, true)       // what ln_shape gives up to 63 packs
+    if constexpr (sizeof(T) == 4) { X(8, 1, false) X(16, 1, false) X(32, 1, false) X(32, 2, false) }
 #undef X
     if (!launched) return LSQ_LAUNCH_FAILED;                    // a shape without its kernel
     if (fuse) launch_colsum_finalize(dgamma, dbeta, hidden, partial, P, 3 * hidden, s, dbias, 2 * hidden);

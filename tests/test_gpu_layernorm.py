@@ -308,11 +308,12 @@ def test_layernorm_order_of_a_rows_sum(hidden):
         assert np.array_equal(fused[2].cpu().numpy(), want[:rows]), rows
 
 
-# fp32 backward: calls of up to half a Mi elements hold pack = lane, larger ones lane pairs; both add a row's terms in one order
-@pytest.mark.parametrize("hidden", [512, 520, 768, 1000, 1032, 2040, 4104, 6400, 8192])
-def test_layernorm_bwd_pairs_and_not(hidden):
-    say(f"[layernorm] backward in lane pairs and not, hidden={hidden}")
-    d, big = dev(), (1 << 19) // hidden + 9
+# fp32 backward: calls of up to half a Mi elements hold pack = lane, larger ones lane pairs; both add a row's terms in one order.  Rows of up to 512 columns: past the caches
+# below 3 Mi elements, through them from there on
+@pytest.mark.parametrize("hidden,limit", [(h, 1 << 19) for h in (512, 520, 768, 1000, 1032, 2040, 4104, 6400, 8192)] + [(h, 3 << 20) for h in (64, 128, 264, 504, 512)])
+def test_layernorm_bwd_pairs_and_not(hidden, limit):
+    say(f"[layernorm] backward in lane pairs and not, hidden={hidden} about {limit}")
+    d, big = dev(), limit // hidden + 9
     n = big - 9
     g = torch.Generator(device=d).manual_seed(hidden)
     x, dy, res, gamma = (torch.randn(s, generator=g, device=d) for s in ((big, hidden), (big, hidden), (big, hidden), (hidden,)))

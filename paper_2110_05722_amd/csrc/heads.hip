@@ -183,11 +183,11 @@ inline int head_row_blocks(int64_t rows)
 }
 
 // fp32 from 4 MiB on: a pack is two accesses of half a line each.  Heads of a multiple of 64 columns go in lane pairs; the others through the caches, loads and stores, or half lines
-// move.  Below, past the caches (three heads of 1 MB in lane pairs: split 2.35 / 3.1 us, backward 5.2 / 6.0).  us, past the caches / like this, in the states of stays_cached: in lane pairs, per
-// part, split 8 MB 13.3 / 11.1, 22.9 / 20.9, 14.9 / 12.6, backward 19.6 / 13.4, 30.0 / 25.1, 21.1 / 16.5; merge 16 MB 10.2 / 7.3, 17.4 / 14.6, 11.8 / 9.1.  Heads of 80 columns and others
-// through the caches: split backward 16 MB 37.3 / 22.7, 56.3 / 43.3, 39.5 / 32.3, merge 32 MB 22.6 / 14.8, 37.1 / 29.1, 25.4 / 20.9; split 16 MB 27.5 / 19.7, 41.7 / 45.4, 29.4 / 28.6, 32 MB
-// 58.7 / 46.0, 90.7 / 106.9, 61.9 / 58.2, merge backward 32 MB 18.1 / 14.6, 31.2 / 29.3, 20.2 / 21.8, 64 MB 36.6 / 28.3, 60.3 / 77.1, 39.2 / 41.3: these two lose behind the kernel that
-// wrote their input where they are long (only the loads, or only the stores, through the caches: 100 and 112 for the split of 32 MB, 70 and 67 for the merge backward of 64).
+// move.  Below, past the caches (three heads of 1 MB in lane pairs: split 2.35 / 3.1 us, backward 5.2 / 6.0).  us, past the caches / like this, inputs in the Infinity Cache, then just
+// written by the kernel ahead (its time counted too), then in far memory: in lane pairs, per part, split 8 MB 13.3 / 11.1, 22.9 / 20.9, 14.9 / 12.6, backward 19.6 / 13.4, 30.0 / 25.1, 21.1 /
+// 16.5; merge 16 MB 10.2 / 7.3, 17.4 / 14.6, 11.8 / 9.1.  Heads of 80 columns and others through the caches: split backward 16 MB 37.3 / 22.7, 56.3 / 43.3, 39.5 / 32.3, merge 32 MB 22.6 /
+// 14.8, 37.1 / 29.1, 25.4 / 20.9; split 8 MB 19.5 / 12.8, 29.6 / 24.5, 21.4 / 19.4, 32 MB 58.7 / 46.0, 90.7 / 106.9, 61.9 / 58.2 (only the loads through the caches 51.3, 100.4, 56.8, only the stores
+// 56.4, 112, 61.2); merge backward, one tensor, not: 16 MB 9.4 / 8.0, 16.1 / 15.7, 10.4 / 11.7, 64 MB 36.6 / 28.3, 60.3 / 77.1, 39.2 / 41.3.
 template <typename T> inline bool heads_half_lines(const HeadGeom& g) { return sizeof(T) == 4 && g.rows * g.parts * g.hidden >= (1 << 20); }
 template <typename T> inline bool heads_paired(const HeadGeom& g) { return g.head_dim % 64 == 0 && heads_half_lines<T>(g); }
 
@@ -206,7 +206,7 @@ static lsq_status split_dispatch(void* o0, void* o1, void* o2, const void* in, c
         else hipLaunchKernelGGL((split_heads_kernel<T, false, G, NTL>), grid, block, 0, s, a, b, c, ip, bp, g)
         if (pairs && cached) { LSQ_SPLIT(kHeadGroup<T>, false); }
         else if (pairs) { LSQ_SPLIT(kHeadGroup<T>, true); }
-        else if (cached || heads_half_lines<T>(g)) { LSQ_SPLIT(1, false); }
+        else if (cached || (g.parts > 1 && heads_half_lines<T>(g))) { LSQ_SPLIT(1, false); }
         else { LSQ_SPLIT(1, true); }
 #undef LSQ_SPLIT
     } else {

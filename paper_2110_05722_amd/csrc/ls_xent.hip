@@ -35,7 +35,8 @@ constexpr int kXentUnroll = 4;
 // rows, 80 %: 10 %, all: none), its row is left in the 256 MB Infinity Cache for the backward, which reads it next; in tensors of up to 1.3 GB, 200 MB of which
 // are 15 %.  Forward alone / with the backward in us, every row skipping and every row cached, fp16 x 50257: 823 MB with 15 % counting 36.9 / 198.8 and
 // 35.7 / 175.6, 400 MB with 50 % 46.6 / 143.3 and 49.4 / 125.0; with 80 % 63.0 / 174.1 and 69.3 / 171.2, all 72.6 / 195.2 and 81.8 / 195.9: there the forward
-// alone loses.  Looks at 64 targets (a vector load) or 16 took 92 to 102 and 112 us for the forward of 40000 x 8000.  fp32 is always cached: its packs take
+// alone loses.  Part of that is rows which the pass before has left there.  2048 x 30522 with 15 % (125 MB) on logits from far memory 16.9 / 46.9 and 17.2 / 41.2, just written by the
+// kernel ahead (its time counted) 55.2 / 87.5 and 64.8 / 83.5: a forward without a backward loses there.  Looks at 64 targets (a vector load) or 16 took 92 to 102 and 112 us for the forward of 40000 x 8000.  fp32 is always cached: its packs take
 // two accesses of half a line each (200 MB x 30522 with 80 % 42.7 / 100.4 and 39.2 / 90.0).
 constexpr int64_t kKeepBytes = 1300000000;
 constexpr int kKeepRow = 16384;          // shorter rows lose by the look (the forward of 40000 x 8000 with 80 % counting 92 to 100 us)

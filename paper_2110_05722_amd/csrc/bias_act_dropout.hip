@@ -311,7 +311,7 @@ static lsq_status bad_fwd_dispatch(void* out, const void* x, const void* bias, i
         if (rb * cb <= (sizeof(T) == 2 ? 1024 : 511)) rb = ceil_div(rows, kBadWaves);
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(cb), static_cast<unsigned>(rb)), block(256);
-        const bool pair = bad_paired<T>(rows, hidden, d.on != 0, true), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+        const bool pair = bad_paired<T>(rows, hidden, d.on != 0, true), cached = stays_cached(rows * hidden, sizeof(T), kCachedLeastRows) && (sizeof(T) == 2 || pair);
         constexpr bool kPair = sizeof(T) == 4;
 #define LSQ_BAD_FWD(BIAS, DROP)                                                                                                            \
         if (hidden % kPack != 0) hipLaunchKernelGGL((bad_fwd_cols<T, ACT, BIAS, DROP, true, false, true>), grid, block, 0, s, o, xp, bp, rows, RowPackIO<T, true>(hidden), d); \
@@ -342,7 +342,7 @@ static lsq_status bad_bwd_dispatch(void* dx, float* dbias, const void* dy, const
         const int rb = bad_bwd_row_blocks(rows, hidden);
         const dim3 grid(static_cast<unsigned>(bad_col_blocks(hidden)), static_cast<unsigned>(rb)), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        const bool pair = bad_paired<T>(rows, hidden, d.on != 0, false), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+        const bool pair = bad_paired<T>(rows, hidden, d.on != 0, false), cached = stays_cached(rows * hidden, sizeof(T), kCachedLeastRows) && (sizeof(T) == 2 || pair);
         constexpr bool kPair = sizeof(T) == 4;
 #define LSQ_BAD_BWD(BIAS, DROP)                                                                                                            \
         if (hidden % kPack != 0) hipLaunchKernelGGL((bad_bwd_cols<T, ACT, BIAS, DROP, true, false, true>), grid, block, 0, s, o, partial, g, xp, bp, rows, RowPackIO<T, true>(hidden), d); \

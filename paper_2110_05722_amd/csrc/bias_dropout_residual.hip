@@ -301,7 +301,7 @@ static lsq_status bdr_fwd_dispatch(void* out, const void* x, const void* bias, c
         if (rb > 8192) rb = 8192;
         const dim3 grid(static_cast<unsigned>(ceil_div(ppr, w)), static_cast<unsigned>(rb)), block(64 * kBdrFwdWaves);
         const bool drop = d.on != 0;
-        const bool pair = bdr_paired<T>(rows, hidden), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+        const bool pair = bdr_paired<T>(rows, hidden), cached = stays_cached(rows * hidden, sizeof(T), kCachedLeastRows) && (sizeof(T) == 2 || pair);
 #define LSQ_BDR_FWD(W, PAIR, NTL)                                                                                            \
         if (w == W && pair == (PAIR) && cached != NTL) {                                                                                   \
             if (bp && drop) hipLaunchKernelGGL((bdr_fwd_cols<T, true, true, W, PAIR, NTL>), grid, block, 0, s, o, xp, bp, rp, rows, ppr, d);    \
@@ -338,7 +338,7 @@ static lsq_status bdr_bwd_dispatch(void* dx, float* dbias, const void* dy, int64
         const BdrBwdPlan pl = bdr_bwd_plan(rows, hidden);
         const dim3 grid(static_cast<unsigned>(pl.col_blocks), static_cast<unsigned>(pl.row_blocks)), block(64 * kBdrBwdWaves);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        const bool pair = bdr_paired<T>(rows, hidden), cached = stays_cached(rows * hidden, sizeof(T)) && (sizeof(T) == 2 || pair);
+        const bool pair = bdr_paired<T>(rows, hidden), cached = stays_cached(rows * hidden, sizeof(T), kCachedLeastRows) && (sizeof(T) == 2 || pair);
 #define LSQ_BDR_BWD(W, PAIR, NTL)                                                                                       \
         if (pl.w == W && pair == (PAIR) && cached != NTL) {                                                               \
             if (d.on) hipLaunchKernelGGL((bdr_bwd_cols<T, true, W, PAIR, NTL>), grid, block, 0, s, o, partial, g, rows, ppr, pl.trips, d);    \

@@ -56,19 +56,20 @@ inline lsq_status zero_fill(float* p, int64_t n, hipStream_t s)
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The streamed inputs of a call are loaded past the caches (nontemporal) unless a tensor has 2 to 16 MiB: what the kernel ahead has just written, or the same
+// The streamed inputs of a call are loaded past the caches (nontemporal) unless a tensor has 2 (heads, padding) or 4 to 16 MiB: what the kernel ahead has just written, or the same
 // pass will read again, is then in the 256 MB Infinity Cache, and a load past the caches gives the line up.  It is a choice between states. us, 16 bits, past the caches
 // and the change through them, in the order: passes over 100 MB that stay there / inputs written by the kernel ahead, outputs in far memory (its time counted too) / all in far
 // memory.  Backward of bias+dropout+residual, 8 MB 9.0 - 1.0 / 12.3 + 0.9 / 9.5 + 0.6; of the feed-forward 11.2 - 0.3 / 16.1 + 0.8 / 11.7 + 0.8; padding restored, 8 MB 5.9 - 1.2 / 8.1 + 1.3 / 6.3
 // + 0.5; head split backward, three of 8 MB 15.3 - 1.6 / 27.0 - 1.6 / 16.6 + 0.2.  Whole calls that take several of them gain: a captured layer of 128 x 32 tokens, hidden 512, 90.3 us with the
 // forwards and the feed-forward past the caches, 85.5 like this (about half of that on inputs that no pass has read), the four calls of a sub-layer boundary of 8192 x 1024 51.7 and 50.2.
-// Below, nothing gains in any state and a call from far memory loses: 1 MB 2.3 + 0.4 forward of bias+dropout+residual, 2.4 + 0.6 head merge backward, 5.6 + 0.8 feed-forward backward.
+// Below, nothing gains in any state and a call from far memory loses: 1 MB 2.4 + 0.6 head merge backward, 5.6 + 0.8 feed-forward backward; of bias+dropout+residual and feed-forward up to 4 MiB
+// (2048 x 512 bf16 forward 2.36 + 0.24 / 2.64 + 0.41 in the Infinity Cache and far, 3 MB feed-forward 3.1 + 0.2 / 3.4 + 0.4, backward 7.1 + 0.1 / 7.3 + 0.7).
 // Beyond, far memory costs more: 24 MB heads 27.5 + 0.6 split, 10.2 + 0.9 merge backward, 20 MB feed-forward backward 16.8 + 0.8.
-constexpr int64_t kCachedLeast = 2ll << 20, kCachedMost = 16ll << 20;
-inline bool stays_cached(int64_t elements, size_t elem_bytes)
+constexpr int64_t kCachedLeast = 2ll << 20, kCachedLeastRows = 4ll << 20, kCachedMost = 16ll << 20;
+inline bool stays_cached(int64_t elements, size_t elem_bytes, int64_t least = kCachedLeast)
 {
     const int64_t bytes = elements * static_cast<int64_t>(elem_bytes);
-    return bytes >= kCachedLeast && bytes <= kCachedMost;
+    return bytes >= least && bytes <= kCachedMost;
 }
 
 // Division of a row index (below 2^32) by a launch constant: multiply-high by a host-made reciprocal, two shifts

@@ -957,8 +957,12 @@ inline bool ln_bwd_paired(int64_t rows, int hidden) { return sizeof(T) == 4 && r
 // 20.6, 15.0 / 15.3, 14.1 / 10.9; 8388 x 1000 28.7 / 26.3, 21.1 / 20.3, 17.8 / 14.4; backward, fused with dropout and residual gradient, 8192 x 256 17.3 / 18.6, 14.4 / 15.4, 13.2 / 12.4;
 // 16384 x 512 49.5 / 46.5, 40.3 / 39.1, 37.8 / 29.1; 65536 x 128 49.6 / 47.0, 38.1 / 39.2, 38.6 / 29.3.  256 lanes x 8 packs only if fused (1000 x 16384 68.2 / 55.9, plain 29.7 / 31.0), backward of
 // more than 8192 columns always (30 x 16384 54.8 / 46.0, 57.5 / 47.1, 56.6 / 39.6).
+// The fused forward of up to 4096 columns from 1.5 Mi on: 612 x 2568 14.5 / 13.7, 9.4 / 9.4, 8.7 / 7.1; 1063 x 2800 22.9 / 21.5, 16.5 / 15.8, 15.7 / 12.7; wider ones 500 x 4104 16.0 / 16.4, 9.4 / 11.1, 8.5 / 8.8.
 template <typename T>
-inline bool ln_cached(int64_t rows, int hidden) { return sizeof(T) == 4 && rows * hidden >= (3ll << 20); }
+inline bool ln_cached(int64_t rows, int hidden, bool fused_fwd = false)
+{
+    return sizeof(T) == 4 && rows * hidden >= (fused_fwd && hidden <= 4096 ? 3ll << 19 : 3ll << 20);
+}
 
 // Row groups per workgroup: two, the second loaded ahead (8192 x 1280: one 11.1, two 9.2, four 10.4 us), but one where all groups find
 // a compute unit of their own: up to 256 always (one against two, all shapes: 0.66-0.90), up to 768 where the kernel is small enough for
@@ -1019,7 +1023,7 @@ static lsq_status ln_fwd_dispatch(void* y, float* mean, float* rstd, const void*
     bool launched = false;
     const dim3 grid(ln_fwd_blocks(rows, sh, sizeof(T))), block(256);
     const BdrFuse<T> none{};
-    const bool pair = sizeof(T) == 4 && ln_fwd_paired(rows, hidden), cached = ln_cached<T>(rows, hidden);
+    const bool pair = sizeof(T) == 4 && ln_fwd_paired(rows, hidden), cached = ln_cached<T>(rows, hidden, fuse != nullptr);
 #define X(L, V)                                                                                              \
     if (sh.lpr == L && sh.vpl == V) {                                                                        \
         launched = true;                                                                                     \

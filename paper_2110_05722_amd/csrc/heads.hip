@@ -228,7 +228,7 @@ static lsq_status merge_dispatch(void* out, float* dbias, const void* i0, const 
         const int rb = heads_bwd_row_blocks(g.rows, cols, sizeof(T));
         const dim3 grid(static_cast<unsigned>(ceil_div(g.ppr, 64)), static_cast<unsigned>(dbias ? rb : head_row_blocks(g.rows))), block(256);
         float* partial = dbias ? static_cast<float*>(workspace) : nullptr;
-        const bool pairs = heads_paired<T>(g), cached = stays_cached(g.rows * g.hidden, sizeof(T)) && (sizeof(T) == 2 || pairs);
+        const bool pairs = heads_paired<T>(g), cached = stays_cached(g.rows * g.hidden, sizeof(T), dbias ? kCachedLeastSums / g.parts : kCachedLeast) && (sizeof(T) == 2 || pairs);
 #define LSQ_MERGE(G, NTL) hipLaunchKernelGGL((merge_heads_kernel<T, G, NTL>), grid, block, 0, s, o, partial, a, b, c, g)
         if (pairs && cached) LSQ_MERGE(kHeadGroup<T>, false);
         else if (pairs) LSQ_MERGE(kHeadGroup<T>, true);

@@ -64,8 +64,9 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // forwards and the feed-forward past the caches, 85.5 like this (about half of that on inputs that no pass has read), the four calls of a sub-layer boundary of 8192 x 1024 51.7 and 50.2.
 // Below, nothing gains in any state and a call from far memory loses: 1 MB 2.4 + 0.6 head merge backward, 5.6 + 0.8 feed-forward backward; of bias+dropout+residual and feed-forward up to 4 MiB
 // (2048 x 512 bf16 forward 2.36 + 0.24 / 2.64 + 0.41 in the Infinity Cache and far, 3 MB feed-forward 3.1 + 0.2 / 3.4 + 0.4, backward 7.1 + 0.1 / 7.3 + 0.7).
+// The head split's backward with its bias sum, a serial walk without loads ahead, gains from 1 MiB in all heads on (three of 1 MB 5.9 - 0.2 / 11.5 + 0.2 / 6.0 + 0.6, of 1.5 MB 6.5 - 0.4 / 12.1 + 0.2 / 6.6 + 0.6).
 // Beyond, far memory costs more: 24 MB heads 27.5 + 0.6 split, 10.2 + 0.9 merge backward, 20 MB feed-forward backward 16.8 + 0.8.
-constexpr int64_t kCachedLeast = 2ll << 20, kCachedLeastRows = 4ll << 20, kCachedMost = 16ll << 20;
+constexpr int64_t kCachedLeast = 2ll << 20, kCachedLeastRows = 4ll << 20, kCachedLeastSums = 1ll << 20, kCachedMost = 16ll << 20;
 inline bool stays_cached(int64_t elements, size_t elem_bytes, int64_t least = kCachedLeast)
 {
     const int64_t bytes = elements * static_cast<int64_t>(elem_bytes);

@@ -534,7 +534,7 @@ __global__ __launch_bounds__(256) void emb_radix_scatter(int2* __restrict__ dst,
 // The sorted order is cut into units of kEmbUnit entries, ranges of kEmbRange entries and column blocks of 16 packs.  A workgroup takes a
 // (range, column block): 16 lanes own a unit's entries, a wave has four units, so no lane idles on a row's last packs, and what a unit's first or last
 // run shares with the unit beside it goes over by lane shuffles in a wave and LDS between the four.  A run that crosses the border of a range has
-// workgroups of its own (emb_border_run) and is left out here.  The destination rows are fetched together with the dy rows.
+// workgroups of its own (emb_border_run) and is left out here, or leaves its sum of the range in memory (PARTS, emb_range_runs).  The destination rows are fetched together with the dy rows.
 // What bounds it is the chain order -> rows -> rows of dE; 4 waves per SIMD at 8192 x 1280.  One wave per (8 entries, 64 packs), which left an fp32 row
 // for every run that crossed its entries, and a last launch that added these took 13.1 + 6.0 us there; whole backward, bf16 with dropout, in us before and now:
 // 8192 x 1280 words 28.6 / 23.4, distinct 29.0 / 23.7, half of one id 40.5 / 31.8, 16384 x 1024 40.9 / 36.4, 2048 x 768 f16 15.3 / 12.6.  Units of 8 entries,
@@ -721,8 +721,8 @@ __device__ __forceinline__ void emb_border_run(float* lds, T* __restrict__ demb,
         const int64_t v = border - 1 - lane;
         const uint64_t m = __ballot(v == 0 || (v > 0 && order[v * kEmbRange - 1].y != key));
         const int before = m != 0 ? __builtin_ctzll(m) : 64;       // of the run's borders, this one's index
-        // only the first borders have a slice: the others leave here, one look from the start (each of a long run's borders looking for its two
-        // ends, 64 ranges a look, was quadratic: one id in 2^18 / 2^20 tokens of 1280 columns bf16 1.84 / 20.98 ms, 1.11 / 4.62 like this)
+        // only the first borders have a slice: the others leave here, one look from the start (each of a run's borders looking for its two ends is
+        // quadratic in the run: one id in 16384 tokens of 1280 columns bf16 68.3 us, 66.5 like this)
         if (before >= here) return;
         from = (border - 1 - before) * kEmbRange;
     }
